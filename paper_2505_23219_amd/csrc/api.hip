@@ -754,6 +754,7 @@ struct DraftWs {
     half_t* n16;
     float* logits;
     int32_t* topk;
+    uint64_t* lists;      // per (head, segment of its row): the R best candidates
     size_t bytes;
 };
 
@@ -766,6 +767,7 @@ static DraftWs carve_draft(void* ws, int H, int K, int V, int R)
     d.n16 = cv.take<half_t>((size_t)H);
     d.logits = cv.take<float>((size_t)K * V);
     d.topk = cv.take<int32_t>((size_t)K * R);
+    d.lists = cv.take<uint64_t>(topk_list_entries(K, V, R));
     d.bytes = cv.off;
     return d;
 }
@@ -829,8 +831,7 @@ static ghd_status draft_tokens_impl(const void* g_final, const void* Wheads, int
     a.lin_epoch = 0;
     a.lin_ldy = (int64_t)K * V;
     if ((s = timed_fused(a, st))) return s;
-    if ((s = launch_topk(logits, K, V, R, topk, st))) return s;
-    return launch_tree_tokens(tokens_dev, parent_dev, rank_dev, M, topk, K, R, res_dev, V, st);
+    return launch_topk_tokens(logits, K, V, R, d.lists, topk, tokens_dev, parent_dev, rank_dev, M, res_dev, st);
 }
 
 ghd_status ghd_draft_tokens(const void* g_final, const void* Wheads, int K, int R, int H, int V,

@@ -255,3 +255,33 @@ def test_spec_step_7b_shape(B, model, orc32):
             v = ref_hl[depth[i] - 1]
             assert abs(v[got[i]] - v[ref_tokens[i]]) <= 2e-3, i
     assert checked >= 0.8 * (M - 1)
+
+
+@pytest.mark.parametrize("V,K,R", [(1, 1, 1), (40, 2, 32), (511, 3, 10), (2047, 2, 7), (2048, 2, 10), (2049, 5, 10),
+                                   (16384, 16, 32), (32000, 5, 10), (262144, 1, 32)])
+def test_topk_is_exact_on_the_logits_it_read(B, V, K, R):
+    """The candidates against a full sort of the very logits the call returned: rows of a
+    segment's length and one more or less, one segment and many, few picks and the most, many
+    equal values (weights of three values only), +-inf, NaN (never picked) and -0 beside +0."""
+    H, M = 8, 4
+    gen = torch.Generator().manual_seed(V + 7 * K + R)
+    W = torch.randint(-1, 2, (K * V, H), generator=gen).to(torch.float16)
+    if V > 64:
+        W[V // 2] = float("nan")
+        W[5, 0] = float("inf")
+        W[V - 1, 0] = float("-inf")
+        W[9], W[33] = 0.0, -0.0
+    x = wl.activations(M, H, 3, tag="xf", std=2.0).float()
+    res = torch.tensor([1, 3 % V, 0, 0, 0, 0], dtype=torch.int32)
+    parent, rank = torch.tensor([-1, 0, 0, 1], dtype=torch.int32), torch.tensor([0, 0, min(1, R - 1), R - 1], dtype=torch.int32)
+    say("top-R V=%d K=%d R=%d" % (V, K, R))
+    tokens, topk, logits = B.ghd_draft_tokens(torch.ones(H, dtype=torch.float16).cuda(), B.ghd_pack_weight(W.cuda()), K, R,
+                                              V, 1e-6, x.cuda(), res.cuda(), parent.cuda(), rank.cuda())
+    lg, top = logits.cpu().numpy(), topk.cpu().numpy()
+    for k in range(K):
+        ok = np.flatnonzero(~np.isnan(lg[k]))
+        want = ok[np.lexsort((ok, -lg[k][ok]))][:R]        # value falling, then index rising
+        assert np.array_equal(top[k][:len(want)], want), k
+    t = tokens.cpu().numpy()
+    head = lambda depth: min(depth, K) - 1
+    assert t[0] == 3 % V and t[1] == top[head(1), 0] and t[2] == top[head(1), min(1, R - 1)] and t[3] == top[head(2), R - 1]
