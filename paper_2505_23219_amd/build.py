@@ -12,12 +12,13 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libghd.so")
 PROBE = os.path.join(HERE, "ghd_stream_probe")       # measurement tool (bench.py --stream-probe), its own program
 PROBE_SOURCE = "stream_probe.hip"
-SOURCES = ["api.hip", "fused.hip", "linear.hip", "linear_mt1.hip", "linear_mt2.hip", "linear_mt4.hip",
-           "linear_mt8.hip", "qkv_attn_mt1.hip", "qkv_attn_mt2.hip", "qkv_attn_mt4.hip", "qkv_attn_mt8.hip",
-           "accept.hip", "draft.hip", "coo.hip"]
+SOURCES = ["api.hip", "fused.hip", "linear.hip", "accept.hip", "draft.hip", "coo.hip"] + \
+    ["linear_mt%d.hip" % n for n in (1, 2, 3, 4, 6, 8)] + ["qkv_attn_mt%d.hip" % n for n in (1, 2, 3, 4, 6, 8)]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          # keep the compiler from forming packed-fp32 instructions
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # the first twelve words of a kernel's arguments arrive in scalar registers (see LinHead)
+         "-mllvm", "-amdgpu-kernarg-preload-count=12",
          # per-kernel register and scratch use, checked below
          "-Rpass-analysis=kernel-resource-usage", "-fno-caret-diagnostics"]
 # The persistent kernels must not use scratch memory: a launch of a kernel that has a private

@@ -70,16 +70,11 @@ static bool linear_shape_ok(int N, int K)
     return ((int64_t)lay.nitems * lay.nks / 8 + lay.nks) * (kMaxShares / 8) < (1ll << 31);
 }
 
-// Fills in how the launch is cut (see plan_linear); false if the shape needs more work shares
-// than the counters are laid out for.
-static bool fill_plan(FusedArgs& a, int M, int N, int K)
+// Is there a cut that admits the shape (see plan_linear)?
+static bool linear_admitted(int M, int N, int K)
 {
     LinPlan pl;
-    if (!plan_linear(M, N, K, grid_for_sizing(), &pl)) return false;
-    a.lin_slots = pl.slots;
-    a.lin_passes = pl.passes;
-    a.lin_whole = pl.whole;
-    return true;
+    return plan_linear(M, N, K, grid_for_sizing(), &pl);
 }
 
 // ---- workspace carving ---------------------------------------------------------
@@ -149,11 +144,8 @@ static ghd_status check_cfg(const ghd_model_cfg* c, int M, int kv_len)
         return GHD_ERR_SHAPE;
     {
         // every linear layer of the model must fit the work-share plan at this M
-        LinPlan pl;
-        const int G = grid_for_sizing();
-        if (!plan_linear(M, 3 * c->H, c->H, G, &pl) || !plan_linear(M, c->H, c->H, G, &pl) ||
-            !plan_linear(M, 2 * c->F, c->H, G, &pl) || !plan_linear(M, c->H, c->F, G, &pl) ||
-            !plan_linear(M, c->V, c->H, G, &pl))
+        if (!linear_admitted(M, 3 * c->H, c->H) || !linear_admitted(M, c->H, c->H) ||
+            !linear_admitted(M, 2 * c->F, c->H) || !linear_admitted(M, c->H, c->F) || !linear_admitted(M, c->V, c->H))
             return GHD_ERR_SHAPE;
     }
     if (!(c->rope_base > 0.f) || !(c->rms_eps >= 0.f)) return GHD_ERR_SHAPE;
@@ -234,7 +226,6 @@ static ghd_status fill_linear(FusedArgs& a, const ghd_model_cfg* c, const Ws& w,
     a.lin_N = lc.N;
     a.lin_K = lc.K;
     a.lin_epi = lc.epi;
-    if (!fill_plan(a, M, lc.N, lc.K)) return GHD_ERR_SHAPE;
     a.lin_x = lc.in16;
     a.lin_rscale = lc.rscale;
     a.lin_gnext = lc.gnext;
@@ -285,7 +276,7 @@ static ghd_status step_qkv_attention(const ghd_model_cfg* c, const Ws& w, const 
     FusedArgs a = {};
     ghd_status s = fill_linear(a, c, w, x, M, kv_len, qkv);
     if (s) return s;
-    if (!g_split_qkv_attn && qkv_attn_available(M, a.lin_slots, a.lin_passes, c->d, c->nh)) {
+    if (!g_split_qkv_attn && qkv_attn_available(M, c->d, c->nh)) {
         a.mode = MODE_QKV_ATTN;
         fill_attention(a, w, kv, layer);
         return timed_fused(a, st);
@@ -398,12 +389,14 @@ ghd_status ghd_linear_skinny(void* y, const void* x, const void* Wp, int M, int 
     hipStream_t st = (hipStream_t)stream;
     Ws w = carve(ws, 1, M, 0, 0, 0, K);
     FusedArgs a = {};
-    if (!fill_plan(a, M, N, K)) return GHD_ERR_SHAPE;
-    ghd_status s = launch_fused_setup(w.sync, nullptr, M, mpad_of(M), 0, 0, 1.f, nullptr, nullptr,
-                                      nullptr, nullptr, 0, nullptr, nullptr, nullptr, st);
-    if (s) return s;
-    // the kernel reads x as MFMA operand blocks
-    if ((s = launch_pack_x(w.xpk, (const half_t*)x, M, mpad_of(M), K, ldx, st))) return s;
+    if (!linear_admitted(M, N, K)) return GHD_ERR_SHAPE;
+    const LinCut cut = choose_cut(M, N, K, grid_for_sizing(), true);
+    // Whole tiles with few rows of x: one launch reads x as it lies and needs nothing prepared.
+    // Otherwise the kernel reads x as MFMA operand blocks, and the counters have to be zero.
+    if (!cut.rows) {
+        ghd_status s = launch_pack_x(w.sync, w.xpk, (const half_t*)x, M, mpad_of(M), K, ldx, st);
+        if (s) return s;
+    }
     a.mode = MODE_LINEAR;
     a.M = M;
     a.Mpad = mpad_of(M);
@@ -411,7 +404,10 @@ ghd_status ghd_linear_skinny(void* y, const void* x, const void* Wp, int M, int 
     a.sync = w.sync;
     a.part = w.part;
     a.lin_W = (const half8*)Wp;
-    a.lin_x = w.xpk;
+    a.lin_x = cut.rows ? (const half_t*)x : w.xpk;
+    a.lin_ldx = ldx;
+    a.lin_row_major = 1;
+    a.lin_solo = cut.rows;
     a.lin_y = y;
     a.lin_N = N;
     a.lin_K = K;
@@ -812,9 +808,9 @@ static ghd_status draft_tokens_impl(const void* g_final, const void* Wheads, int
                                 nullptr, 0, nullptr, nullptr, nullptr, st)))
         return s;
     if ((s = launch_pick_norm(x_final, res_dev, M, H, g_final, rms_eps, d.n16, st))) return s;
-    if ((s = launch_pack_x(d.lin.xpk, d.n16, 1, mpad_of(1), H, H, st))) return s;
+    if ((s = launch_pack_x(nullptr, d.lin.xpk, d.n16, 1, mpad_of(1), H, H, st))) return s;
     FusedArgs a = {};
-    if (!fill_plan(a, 1, K * V, H)) return GHD_ERR_SHAPE;
+    if (!linear_admitted(1, K * V, H)) return GHD_ERR_SHAPE;
     a.mode = MODE_LINEAR;
     a.M = 1;
     a.Mpad = mpad_of(1);
@@ -918,8 +914,8 @@ void ghd_debug_share(int items, int per_item, int j, int G, int item, int* out5)
 }
 
 /* out3 = {row tiles a share handles at once, shares per workgroup, whole tiles (1) or k ranges of
- * four-tile row blocks (0)} for a linear layer [N, K] at M rows on G workgroups; returns 0, or -1
- * if the shape needs more shares than the library is laid out for. */
+ * four-tile row blocks (0)} of the general cut by which a linear layer [N, K] at M rows is admitted
+ * on G workgroups; returns 0, or -1 if the shape needs more shares than the library is laid out for. */
 int ghd_debug_plan(int M, int N, int K, int G, int* out3)
 {
     LinPlan pl;
@@ -928,6 +924,20 @@ int ghd_debug_plan(int M, int N, int K, int G, int* out3)
     out3[1] = pl.passes;
     out3[2] = pl.whole;
     return 0;
+}
+
+/* The tiles of workgroup i of a whole-tile launch with gx workgroups per XCD: out2 = {c0, c1}. */
+void ghd_debug_tile_range(int ntiles, int gx, int i, int* out2) { tile_range_on_host(ntiles, gx, i, out2); }
+
+/* out5 = {whole tiles, tiles per share, parts, workgroups, x read row-major} of a launch. */
+void ghd_debug_cut(int M, int N, int K, int G, int solo, int* out5)
+{
+    const LinCut c = choose_cut(M, N, K, G, solo != 0);
+    out5[0] = c.whole;
+    out5[1] = c.tiles;
+    out5[2] = c.parts;
+    out5[3] = c.grid;
+    out5[4] = c.rows;
 }
 
 void ghd_debug_attn_share(int nh, int ntile, int j, int G, int head, int* out6)

@@ -108,23 +108,24 @@ __host__ __device__ inline size_t xpk_halves(int K, int mtp) { return (size_t)((
 
 // The sync block (uint32 words), zeroed by the set-up kernel.  Every counter has a
 // 128-byte line of its own (kCntStride words apart): the workgroups of one item poll and
-// bump it without disturbing the others.  A linear layer's shared row block is counted on
-// the line of the first work share that has a part of it (one line per share is enough);
-// each kind of linear layer has an array of its own, reused layer after layer by epoch.
+// bump it without disturbing the others.  A linear layer's block is counted on the line of
+// its first part; each kind of linear layer has an array of its own, reused layer after layer
+// by epoch.
 constexpr int kSyncStatus = 1;    // 0 = ok, else the code of the wait that gave up (this set-up's calls)
 constexpr int kSyncSticky = 2;    // the first non-zero status an earlier set-up found in kSyncStatus
 constexpr int kSyncMagic = 3;     // kSyncMagicValue once a set-up kernel has run on this workspace
 constexpr uint32_t kSyncMagicValue = 0x67686453u;
 constexpr int kCntStride = 32;
-constexpr int kMaxShares = 2048;  // work shares of one linear launch (workgroups x passes)
+constexpr int kMaxShares = 2048;  // work shares of one linear launch
+constexpr int kCntLines = kRangeWgs;                  // per kind of linear layer: a line per workgroup is enough
 constexpr int kSyncCnt = 32;                          // first counter line
 constexpr int kCntQkv = kSyncCnt;
-constexpr int kCntWo = kCntQkv + kMaxShares * kCntStride;
-constexpr int kCntGu = kCntWo + kMaxShares * kCntStride;
-constexpr int kCntDown = kCntGu + kMaxShares * kCntStride;
-constexpr int kCntLm = kCntDown + kMaxShares * kCntStride;   // LM head and stand-alone linear calls
-constexpr int kCntDraft = kCntLm + kMaxShares * kCntStride;  // drafting heads inside a whole decoding step
-constexpr int kCntAttn = kCntDraft + kMaxShares * kCntStride;   // up to 256 heads
+constexpr int kCntWo = kCntQkv + kCntLines * kCntStride;
+constexpr int kCntGu = kCntWo + kCntLines * kCntStride;
+constexpr int kCntDown = kCntGu + kCntLines * kCntStride;
+constexpr int kCntLm = kCntDown + kCntLines * kCntStride;   // LM head and stand-alone linear calls
+constexpr int kCntDraft = kCntLm + kCntLines * kCntStride;  // drafting heads inside a whole decoding step
+constexpr int kCntAttn = kCntDraft + kCntLines * kCntStride;    // up to 256 heads
 constexpr int kCntXcd = kCntAttn + 256 * kCntStride;            // one line per XCD: QKV done, attention may start
 constexpr int kCntGo = kCntXcd + 8 * kCntStride;                // one line per workgroup: its XCD has met
 constexpr int kSyncWords = kCntGo + kRangeWgs * kCntStride;
@@ -159,12 +160,9 @@ struct FusedArgs {
     const uint64_t* mask;  // ancestor masks [M][2]
     // linear-layer launch
     const half8* lin_W;
-    const half_t* lin_x;   // input, packed activation layout
+    const half_t* lin_x;   // input, packed activation layout (or row-major, see lin_row_major)
     void* lin_y;
     int lin_N, lin_K, lin_epi;
-    int lin_slots;         // wide matrices: row tiles a work share handles at once (template choice)
-    int lin_passes;        // work shares per workgroup
-    int lin_whole;         // whole tiles are dealt out (always for wide matrices), else k ranges of row blocks
     int lin_rscale;        // the input is xg16: scale output row m by the RMSNorm factor of x[m]
     const half_t* lin_gnext;   // EPI_RESID: gain of the norm that follows (xg16 is rewritten)
     half_t *lin_kc, *lin_vc;   // EPI_QKV: the layer's cache
@@ -178,25 +176,39 @@ struct FusedArgs {
     const half_t *att_q, *att_k, *att_v;
     half_t* att_out;
     int att_out_packed;    // output in the packed activation layout (else row-major [M, nh, d])
-    // Filled in at launch (see with_launch_facts): the matrix' layout, and every workgroup's
-    // work share when there is one share per workgroup - what the kernel would otherwise
-    // work out with a dozen integer divisions before it can request its first weights.
-    int lin_ntiles, lin_nitems, lin_nks, lin_blk_shift;
-    int lin_range_ok;                      // lin_range is filled in
-    uint32_t lin_range[2 * kRangeWgs];     // workgroup j (logical index): units c0 .. c1 - 1 of its share
+    int64_t lin_ldx;       // lin_row_major: elements from row to row of lin_x
+    int lin_row_major;     // lin_x is the caller's row-major array (a call of its own), else packed
+    int lin_solo;          // a whole-tile call of its own: there was no set-up launch
 };
 
 ghd_status launch_fused(const FusedArgs& a, hipStream_t st);
+// How a launch of a linear layer is cut (see choose_cut): whole tiles, up to `tiles` per
+// workgroup, on a grid of any multiple of 8; or blocks of `tiles` tiles in `parts` parts each,
+// all workgroups resident.
+struct LinCut {
+    int whole, tiles, parts, grid;
+    int rows;              // x is read row-major as it lies
+};
+// the most tiles a part has
+constexpr int parts_max_tiles(int MT) { return 32 / MT < 8 ? 32 / MT : 8; }     // (eight wavefronts)
+constexpr int kRowsMaxMT = 4;     // row tiles of x up to which it is read row-major
+// row tiles of x that the kernels are built for: M rounded up to 1, 2, 3, 4, 6 or 8 tiles
+__host__ __device__ constexpr int row_tiles(int M)
+{
+    return M <= 64 ? (M + 15) / 16 : M <= 96 ? 6 : 8;
+}
+LinCut choose_cut(int M, int N, int K, int G, bool solo);
+
 ghd_status launch_linear(const FusedArgs& a, hipStream_t st);
 ghd_status launch_qkv_attn(const FusedArgs& a, hipStream_t st);
-bool qkv_attn_available(int M, int slots, int passes, int d, int nh);
-ghd_status launch_resident_checked(const void* kernel, int key, size_t lds, int* grid);
+bool qkv_attn_available(int M, int d, int nh);
+ghd_status launch_resident_checked(const void* kernel, int threads, size_t lds, int* grid = nullptr);
 int fused_grid_size();
 void share_on_host(int items, int per_item, int j, int G, int item, int* out);
+void tile_range_on_host(int ntiles, int gx, int i, int* out);
 void attn_share_on_host(int nh, int ntile, int j, int G, int head, int* out);
 
-// How a linear layer is cut for G workgroups and row tiles of M: passes (work shares per
-// workgroup) and, for wide matrices, the most row tiles one share touches.  Host only.
+// The general cut by which a shape is admitted (see plan_linear).  Host only.
 struct LinPlan { int slots, passes, whole; };
 bool plan_linear(int M, int N, int K, int G, LinPlan* out);
 size_t linear_part_floats(int M, int G);
@@ -207,8 +219,9 @@ ghd_status launch_fused_setup(uint32_t* sync, const int32_t* parent, int M, int 
                               float rope_base, uint64_t* mask, float2* rope, float* x,
                               const half_t* x_in16, int H, float* ss, const half_t* gain,
                               half_t* xg16, hipStream_t st);
-// row-major fp16 [M, ldx] -> packed activation layout (columns K.. of the last k-step zero)
-ghd_status launch_pack_x(half_t* dst, const half_t* src, int M, int Mpad, int K, int64_t ldx, hipStream_t st);
+// row-major fp16 [M, ldx] -> packed activation layout (columns K.. of the last k-step zero);
+// with sync, the same launch also zeroes the sync block
+ghd_status launch_pack_x(uint32_t* sync, half_t* dst, const half_t* src, int M, int Mpad, int K, int64_t ldx, hipStream_t st);
 
 // the drafted tokens' own attention block from the nonzeros of the mask only (coo.hip)
 ghd_status launch_tree_part_coo(void* out, const void* q, const void* kc, const void* vc, const uint64_t* mask,

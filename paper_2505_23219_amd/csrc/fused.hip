@@ -9,7 +9,6 @@ template <int MT, int D>
 __global__ __launch_bounds__(kFT) void k_attention(const FusedArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    touch_kernel_arguments();
     Ctx cx = make_ctx(a, lds);
     attn_phase<MT, D>(a, cx, a.att_q, a.att_k, a.att_v, a.att_out, a.att_epoch);
 }
@@ -22,7 +21,7 @@ static ghd_status launch_attention_t(const FusedArgs& a, hipStream_t st)
 {
     int G = 0;
     const size_t lds = sizeof(AttnLds<MT, D>);
-    ghd_status s = launch_resident_checked((const void*)k_attention<MT, D>, 0, lds, &G);
+    ghd_status s = launch_resident_checked((const void*)k_attention<MT, D>, kFT, lds, &G);
     if (s) return s;
     hipLaunchKernelGGL((k_attention<MT, D>), dim3(G), dim3(kFT), lds, st, a);
     return check_launch();
@@ -71,7 +70,7 @@ void attn_share_on_host(int nh, int ntile, int j, int G, int head, int* out)
 // blocks zero the sync block.  Further blocks: one per 16-column tile of the residual stream,
 // writing x = widen(x_in), the tile's sums of squares and the gain-scaled fp16 image.
 constexpr int kTreeBlocks = 8;
-constexpr int kZeroBlocks = 128;
+constexpr int kZeroBlocks = 64;
 
 __global__ __launch_bounds__(256) void k_fused_setup(uint32_t* __restrict__ sync,
                                                      const int32_t* __restrict__ parent, int M,
@@ -138,19 +137,7 @@ __global__ __launch_bounds__(256) void k_fused_setup(uint32_t* __restrict__ sync
         return;
     }
     if (blockIdx.x < kTreeBlocks + kZeroBlocks) {
-        // the status word is cleared for the calls that follow; what it held is kept in the
-        // sticky word (first failure wins), so that a caller who reads the status only now
-        // and then still learns of a call that gave up.  A workspace seen for the first time
-        // (no magic word) holds nothing meaningful.
-        if (blockIdx.x == kTreeBlocks && tid == 0) {
-            const uint32_t st = sync[kSyncStatus], sticky = sync[kSyncSticky];
-            const bool known = sync[kSyncMagic] == kSyncMagicValue;
-            sync[kSyncSticky] = known ? (sticky ? sticky : st) : 0u;
-            sync[kSyncMagic] = kSyncMagicValue;
-            sync[kSyncStatus] = 0;
-        }
-        for (int i = (blockIdx.x - kTreeBlocks) * 256 + tid; i < kSyncWords; i += kZeroBlocks * 256)
-            if (i < kSyncStatus || i > kSyncMagic) sync[i] = 0;
+        zero_sync<kZeroBlocks>(sync, blockIdx.x - kTreeBlocks);
         return;
     }
     // residual stream tiles: thread -> (row m, column within the 16-wide tile)

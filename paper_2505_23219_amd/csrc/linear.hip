@@ -32,57 +32,48 @@ int fused_grid_size()
     return g_num_cu[dev];
 }
 
-// All workgroups of a persistent kernel must be resident at once (they wait for each
-// other): one per compute unit.  The first launch of a kernel on a device raises its
-// dynamic LDS limit and checks that a workgroup fits; *grid = workgroups to launch.
-ghd_status launch_resident_checked(const void* kernel, int key, size_t lds, int* grid)
+// Workgroups of a launch that wait for each other must all be resident: one per compute
+// unit.  The first launch of a kernel on a device raises its dynamic LDS limit and checks
+// that a workgroup fits; *grid = compute units.
+ghd_status launch_resident_checked(const void* kernel, int threads, size_t lds, int* grid)
 {
-    (void)key;
     static std::mutex mu;
     static std::vector<const void*> checked[kMaxDevices];
     const int dev = current_device();
     const int G = fused_grid_size();
     // the hand-off of partial results is laid out for 8 XCDs of G / 8 compute units
-    // and for at most kRangeWgs workgroups (their work shares travel in the argument block)
-    if (dev < 0 || G <= 0 || G > kRangeWgs || (G % 8) != 0) return hip_fail(hipErrorInvalidDevice);
-    *grid = G;
+    // and for at most kRangeWgs workgroups (their counters in the sync block)
+    if (dev < 0 || G < 16 || G > kRangeWgs || (G % 8) != 0) return hip_fail(hipErrorInvalidDevice);
+    if (grid) *grid = G;
     std::lock_guard<std::mutex> lock(mu);
     for (const void* k : checked[dev])
         if (k == kernel) return GHD_OK;
     hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return hip_fail(e);
     int per_cu = 0;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kFT, lds);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds);
     if (e != hipSuccess) return hip_fail(e);
     if (per_cu < 1) return hip_fail(hipErrorLaunchOutOfResources);
     checked[dev].push_back(kernel);
     return GHD_OK;
 }
 
-// ---- how a linear layer is cut -------------------------------------------------------
-// Whole tiles: the 16-row tiles are dealt out, every share streams its tiles over the whole
-// k range and finishes them alone - nothing is exchanged between workgroups, at the price of
-// shares that differ by one tile and of x being read once per share.  That is how wide
-// matrices are cut at every M (measured against equal shares of k-steps with the boundary
-// tiles finished jointly: 5.7% of a 64-row step, 4.8% of a 1-row step), and narrow ones up to
-// 16 rows of x (where x is small) unless the one-tile difference between shares costs more
-// stream time than the exchange it saves (about 3 us a launch).  Otherwise narrow matrices
-// are cut into k ranges of four-tile row blocks: a share then reads a fraction of x, and the
-// blocks' partial sums are exchanged.  Every share streams all the row tiles it touches at
-// once, so their number is bounded by the accumulator registers (8 tiles up to 64 rows of x,
-// 4 above); more shares per workgroup (passes) make the shares smaller until that holds.
+// ---- which linear layers are taken ---------------------------------------------------
+// The cut that admits a shape: whole tiles in at most 8 passes of the bounded number of
+// tiles (8 up to 64 rows of x, 4 above) for wide matrices, whole tiles or row blocks of four
+// tiles for narrow ones.  A shape that has no such cut is refused; how a launch is cut in
+// the end is choose_cut's.
 constexpr double kStreamBytesPerUs = 6.4e6;    // what a launch streams at best (measured)
 constexpr double kExchangeUs = 3.0;            // what finishing shared row blocks jointly costs a launch
 
 static bool plan_whole(const WLayout& lay, int mt, int G, LinPlan* out)
 {
     const int cap = mt <= 4 ? 8 : 4;
+    const int nx = G % 8 == 0 ? 8 : 1;
     for (int P = 1; P <= kMaxShares / (G > 0 ? G : 1) && P <= 8; ++P) {
-        int most = 1;
-        for (int ls = 0; ls < G * P; ++ls) {
-            const Share sh = make_share(lay.ntiles, 1, ls, G * P);
-            most = sh.c1 - sh.c0 > most ? sh.c1 - sh.c0 : most;
-        }
+        // the largest share of make_share(ntiles, 1, ., G P): an XCD's tiles, equally dealt out
+        const int U = ceil_div(lay.ntiles, nx), Gx = G * P / nx;
+        const int most = U <= Gx ? 1 : ceil_div(U, Gx);
         if (most <= cap) {
             out->slots = most;
             out->passes = P;
@@ -109,41 +100,113 @@ bool plan_linear(int M, int N, int K, int G, LinPlan* out)
     return true;
 }
 
-// partial-sum slots of the row-block cut (one share per workgroup): two per share, each one
-// row block of fragments
+// partial-sum slots of the parts cut: one per workgroup, up to 8 tiles of fragments each
 size_t linear_part_floats(int M, int G)
 {
-    const size_t mt = (size_t)((M + 15) / 16 <= 1 ? 1 : (M + 15) / 16 <= 2 ? 2 : (M + 15) / 16 <= 4 ? 4 : 8);
-    return (size_t)G * 2 * kRbNarrow * mt * 256;
+    static_assert(parts_max_tiles(1) <= 8, "a slot holds a block's fragments");
+    return (size_t)G * 8 * layout_tiles(row_tiles(M)) * 256;
+}
+
+// ---- how a launch is cut ----------------------------------------------------------------
+// The estimate (microseconds) that chooses among the ways; its terms were fitted to launches
+// at 1 to 128 rows of 1280 x 1280 to 5120 x 13824 matrices, which it meets within 5 to 10%:
+//   weights: what HBM streams at best, or the longest share's at what one compute unit gets;
+//   x: comes on top, not beside it - a compute unit's vector memory path keeps some 16 KB on
+//   their way, in order, so x from the L2 waits its turn among weights from HBM.  [4096, 11008] at
+//   64 rows: 31 us whole-tile (1.4 MB of x per workgroup), 26 in parts of 2 tiles (0.7 MB), 22.6
+//   of 4 (0.34 MB), 23.3 of 8;
+//   parts: the exchange, its partial sums, and a little for every part.
+// Whole tiles read all of x in every workgroup, so they are for wide matrices, and for narrow
+// ones where x is small; parts divide x with the k range.  A call of its own pays one launch
+// more for parts (counters have to be zeroed, and x packed); with whole tiles it can read x
+// as it lies, which costs about twice the x time (64-byte pieces of 128-byte lines), where
+// that is less than the launch.
+constexpr double kCuStreamBytesPerUs = 40e3;
+constexpr double kCuReadBytesPerUs = 55e3;
+constexpr double kXBytesPerUs = 80e3;
+constexpr double kPartsUs = 1.6, kPartsFragmentUs = 0.1, kPartsPartUs = 0.25;
+constexpr double kPrepareUs = 2.5;
+
+LinCut choose_cut(int M, int N, int K, int G, bool solo)
+{
+    const WLayout lay = w_layout(N, K);
+    const int mt = row_tiles(M), Gx = G / 8;
+    const double hbm = 2.0 * N * K / kStreamBytesPerUs;
+    // a share of w tiles and x row tiles over ks k-steps
+    auto share_us = [&](double w, double x, double ks) {
+        const double wb = w * ks * 1024, xb = x * ks * 1024;
+        const double stream = wb / kCuStreamBytesPerUs;
+        const double a = (stream > hbm ? stream : hbm) + xb / kXBytesPerUs, b = (wb + xb) / kCuReadBytesPerUs;
+        return a > b ? a : b;
+    };
+    LinCut best = {};
+    const int U = ceil_div(lay.ntiles, 8);       // tiles of the fullest XCD
+    int P = 1;
+    while (U > 8 * Gx * P) ++P;
+    best.whole = 1;
+    best.tiles = U <= Gx * P ? 1 : ceil_div(U, Gx * P);
+    best.parts = 1;
+    best.grid = 8 * Gx * P;
+    best.rows = solo && mt <= kRowsMaxMT && mt * P * lay.nks * 1024.0 / kXBytesPerUs < kPrepareUs;
+    double best_us = share_us(best.tiles * P, mt * P * (best.rows ? 2 : 1), lay.nks) + (solo && !best.rows ? kPrepareUs : 0.0);
+    if (lay.rb == 1) return best;
+    for (int r = 1; r <= parts_max_tiles(mt); ++r) {
+        const int per_xcd = ceil_div(ceil_div(lay.ntiles, r), 8);
+        if (per_xcd > Gx) continue;
+        int S = Gx / per_xcd;
+        if (S > lay.nks / 8) S = lay.nks / 8;    // a k-step for each wavefront
+        if (S < 2) continue;
+        const double us = share_us(r, mt, ceil_div(lay.nks, S)) + kPartsUs + kPartsFragmentUs * r * mt + kPartsPartUs * S +
+                          (solo ? kPrepareUs : 0.0);
+        if (us < best_us) {
+            best_us = us;
+            best = LinCut{0, r, S, per_xcd * S * 8, 0};
+        }
+    }
+    return best;
 }
 
 ghd_status launch_linear(const FusedArgs& a, hipStream_t st)
 {
-    const int mt = (a.M + 15) / 16;
-    if (mt <= 1) return launch_linear_mt1(a, st);
-    if (mt <= 2) return launch_linear_mt2(a, st);
-    if (mt <= 4) return launch_linear_mt4(a, st);
-    return launch_linear_mt8(a, st);
+    const int G = fused_grid_size();
+    if (G <= 0) return hip_fail(hipErrorInvalidDevice);
+    const LinCut cut = choose_cut(a.M, a.lin_N, a.lin_K, G, a.lin_row_major != 0);
+    switch (row_tiles(a.M)) {
+    case 1: return launch_linear_mt1(a, cut, st);
+    case 2: return launch_linear_mt2(a, cut, st);
+    case 3: return launch_linear_mt3(a, cut, st);
+    case 4: return launch_linear_mt4(a, cut, st);
+    case 6: return launch_linear_mt6(a, cut, st);
+    default: return launch_linear_mt8(a, cut, st);
+    }
 }
 
 // The QKV layer and the attention share a launch when the packed QKV rows are grouped by
-// XCD, the matrix is a wide one that needs one share per workgroup, and a kernel was built
-// for the shape.
-bool qkv_attn_available(int M, int slots, int passes, int d, int nh)
+// XCD, the matrix is a wide one whose tiles fit one workgroup per compute unit, and a kernel
+// was built for the shape.
+bool qkv_attn_available(int M, int d, int nh)
 {
-    const int mt = (M + 15) / 16;
-    if (!qkv_grouped(nh) || d != 128 || passes != 1) return false;
-    if (w_layout(3 * nh * d, nh * d).rb != 1) return false;
-    return slots >= 3 && slots <= (mt <= 4 ? 6 : 4);
+    if (!qkv_grouped(nh) || d != 128) return false;
+    const WLayout lay = w_layout(3 * nh * d, nh * d);
+    const int G = fused_grid_size();
+    if (lay.rb != 1 || G < 8) return false;
+    const int slots = ceil_div(lay.ntiles, G);
+    return slots >= 3 && slots <= (row_tiles(M) <= 4 ? 6 : 4);
 }
 
 ghd_status launch_qkv_attn(const FusedArgs& a, hipStream_t st)
 {
-    const int mt = (a.M + 15) / 16;
-    if (mt <= 1) return launch_qkv_attn_mt1(a, st);
-    if (mt <= 2) return launch_qkv_attn_mt2(a, st);
-    if (mt <= 4) return launch_qkv_attn_mt4(a, st);
-    return launch_qkv_attn_mt8(a, st);
+    const int G = fused_grid_size();
+    if (G <= 0) return hip_fail(hipErrorInvalidDevice);
+    const LinCut cut = choose_cut(a.M, a.lin_N, a.lin_K, G, false);
+    switch (row_tiles(a.M)) {
+    case 1: return launch_qkv_attn_mt1(a, cut, st);
+    case 2: return launch_qkv_attn_mt2(a, cut, st);
+    case 3: return launch_qkv_attn_mt3(a, cut, st);
+    case 4: return launch_qkv_attn_mt4(a, cut, st);
+    case 6: return launch_qkv_attn_mt6(a, cut, st);
+    default: return launch_qkv_attn_mt8(a, cut, st);
+    }
 }
 
 // The work-share arithmetic evaluated on the host (for tests of its invariants): the unit
@@ -161,6 +224,11 @@ void share_on_host(int items, int per_item, int j, int G, int item, int* out)
         out[3] = sh.last_of(item);
         out[4] = sh.begins_in(j, item) ? 1 : 0;
     }
+}
+
+void tile_range_on_host(int ntiles, int gx, int i, int* out)
+{
+    tile_range(ntiles, gx, (uint32_t)(0x100000000ull / (uint64_t)gx + 1), i, out, out + 1);
 }
 
 // ---- weight packing ------------------------------------------------------------
@@ -222,11 +290,22 @@ ghd_status launch_pack2(void* dst, const void* src, int N, int K, int kind, int 
 
 // ---- activation packing -----------------------------------------------------------
 // One thread per 16-byte piece of the packed image: row-major [M, ldx] -> B-operand blocks.
-// Rows from M on and columns from K on are written as zeros.
-__global__ void k_pack_x(half8* __restrict__ dst, const half_t* __restrict__ src, int M, int mtp, int K,
-                         int64_t ldx)
+// Rows from M on and columns from K on are written as zeros.  With `sync`, the first
+// kPackZeroBlocks workgroups zero the sync block (the parts cut counts on it).
+constexpr int kPackZeroBlocks = 64;
+
+__global__ __launch_bounds__(256) void k_pack_x(uint32_t* __restrict__ sync, half8* __restrict__ dst,
+                                                const half_t* __restrict__ src, int M, int mtp, int K, int64_t ldx)
 {
-    size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    int block = blockIdx.x;
+    if (sync) {
+        if (block < kPackZeroBlocks) {
+            zero_sync<kPackZeroBlocks>(sync, block);
+            return;
+        }
+        block -= kPackZeroBlocks;
+    }
+    size_t id = (size_t)block * blockDim.x + threadIdx.x;
     size_t total = (size_t)((K + 31) / 32) * mtp * 64;
     if (id >= total) return;
     int lane = (int)(id & 63);
@@ -239,12 +318,12 @@ __global__ void k_pack_x(half8* __restrict__ dst, const half_t* __restrict__ src
     dst[id] = v;
 }
 
-ghd_status launch_pack_x(half_t* dst, const half_t* src, int M, int Mpad, int K, int64_t ldx, hipStream_t st)
+ghd_status launch_pack_x(uint32_t* sync, half_t* dst, const half_t* src, int M, int Mpad, int K, int64_t ldx, hipStream_t st)
 {
     const int mtp = Mpad / 16;
     size_t total = (size_t)((K + 31) / 32) * mtp * 64;
-    hipLaunchKernelGGL(k_pack_x, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, (half8*)dst, src, M,
-                       mtp, K, ldx);
+    hipLaunchKernelGGL(k_pack_x, dim3((unsigned)((total + 255) / 256) + (sync ? kPackZeroBlocks : 0)), dim3(256), 0, st,
+                       sync, (half8*)dst, src, M, mtp, K, ldx);
     return check_launch();
 }
 

@@ -1,25 +1,25 @@
-// The skinny linear layer: y[M, N] = x[M, K] W[N, K]^T with M <= 128 rows, one launch of one
-// 512-thread workgroup per compute unit.
+// The skinny linear layer: y[M, N] = x[M, K] W[N, K]^T with M <= 128 rows, one launch.
 //
 // The step re-reads every weight once per decoding step and is bound by that stream
-// (Ghidorah, sections 2.1 and 2.2.2), so the kernel is built around it.  A workgroup's share
-// is a group of R row tiles (16 output features each) and a k range.  Its eight wavefronts
-// split the k range between them; each wavefront streams its k-steps of ALL the group's
+// (Ghidorah, sections 2.1 and 2.2.2), so the kernel is built around it.  A workgroup has a
+// group of up to R row tiles (16 output features each) and a k range.  Its wavefronts
+// (eight) split the k range between them; each wavefront streams its k-steps of ALL the group's
 // tiles (W is the MFMA A operand, fetched with non-temporal 128-bit loads straight into
 // registers, a few k-steps ahead) together with the matching x fragments (the B operand,
-// read as it lies in the packed activation layout, from the L2), and keeps one fp32
-// accumulator fragment per (row tile, 16 rows of x).  There is no LDS staging and no barrier
-// inside the stream: the wavefronts run independently until their k ranges end.  Then the
-// eight partial fragments of every tile are added up through LDS, in wavefront order, and
-// the reducing wavefront runs the layer's element-wise epilogue (residual add + sums of
-// squares for the next RMSNorm, rotary embedding + KV append, SwiGLU).
+// from the L2), and keeps one fp32 accumulator fragment per (row tile, 16 rows of x).  There
+// is no LDS staging and no barrier inside the stream: the wavefronts run independently until
+// their k ranges end.  Then the partial fragments of every tile are added up through LDS,
+// in wavefront order, and the reducing wavefront runs the layer's element-wise epilogue
+// (residual add + sums of squares for the next RMSNorm, rotary embedding + KV append, SwiGLU).
+// Where the accumulators would leave one of eight wavefronts no registers for a load ring
+// (above 64 rows of x), the workgroup has four wavefronts of twice the registers.
 //
-// Two ways of dealing a matrix out (chosen on the host, see plan_linear).  Whole tiles: a
-// share is a run of consecutive tiles over the whole k range; nothing is exchanged between
-// workgroups, every workgroup reads all of x.  K ranges of four-tile row blocks (narrow
-// matrices at more than 16 rows of x): a share reads only its k range of x, stores the
-// block's partial sums, and the workgroups that share a block finish it jointly at the end
-// of the launch, parts added in index order, so results never depend on timing.
+// Two ways of dealing a matrix out (chosen on the host, see choose_cut).  Whole tiles: a
+// workgroup has a run of consecutive tiles over the whole k range; nothing is exchanged
+// between workgroups, every workgroup reads all of x.  Parts: a workgroup has 1/S of the k
+// range of a block of R tiles; it reads only that part of x, stores the block's partial sums,
+// and the S workgroups of a block, which run on one XCD, finish it jointly at the end of the
+// launch, parts added in index order, so results never depend on timing.
 #pragma once
 #include "persist.h"
 
@@ -27,59 +27,121 @@
 
 namespace ghd {
 
-struct GemmOp {
+// What a wavefront needs before it can request its first weights: twelve words that the
+// hardware puts into scalar registers at the start of the kernel (kernel argument preloading),
+// so the first loads go out some forty instructions after a wavefront starts instead of
+// waiting for the argument block (host memory: 0.6 us) and for index arithmetic.  Everything
+// else is in FusedArgs behind them and only read when those loads are on their way.
+struct LinHead {
     const half8* W;
-    int ntiles, nitems, nks, blk_shift;   // of the packed matrix (see WLayout)
-    int N, K;
-    int epi;
-    const half8* in;     // packed activation layout, Mpad rows
-    bool rscale;         // input is xg16: multiply output row m by rsqrt(mean x[m]^2 + eps) / kXgScale
-    const half_t* gnext; // RESID: gain of the next RMSNorm (xg16 is rewritten), or nullptr
-    void* out;           // STORE: y;  RESID: x;  SWIGLU: a16
-    int64_t ldo;
-    half_t *kc, *vc;     // QKV: this layer's cache
-    uint32_t* cnt;       // the operation's counters
-    uint32_t epoch;      // how many times these counters were used before (layer index)
-    int passes;          // shares per workgroup
+    const half_t* x;     // packed activation layout, or row-major (ROWS)
+    uint64_t aux;        // packed: the sums of squares (0: none); ROWS: elements from row to row
+    int nks, K, ntiles;
+    int cut;             // whole tiles: workgroups per XCD; parts: S
+    uint32_t magic;      // whole tiles: 2^32 / cut + 1; parts: 2^16 / cut + 1
+    uint32_t flags;      // see kHead*
 };
+constexpr int kHeadBlk = 0;      // bits 0-3: log2 of the tiles per storage block
+constexpr int kHeadMtp = 4;      // bits 4-7: row tiles of the packed activation layout (Mpad / 16)
+constexpr int kHeadM = 8;        // bits 8-15: rows of x
+constexpr int kHeadSolo = 16;    // bit 16: a call of its own, without a set-up kernel
+constexpr int kTailAt = 48;      // byte offset of FusedArgs in the kernel arguments
+static_assert(sizeof(LinHead) == kTailAt && alignof(FusedArgs) == 8, "kernel argument layout");
 
+// FusedArgs as it lies in the kernel arguments.  The (empty) asm makes the pointer opaque:
+// no read through it is moved ahead of this point.
+typedef const __attribute__((address_space(4))) FusedArgs* ArgPtr;
+__device__ __forceinline__ ArgPtr late_args()
+{
+    typedef const __attribute__((address_space(4))) char* kernarg_bytes;
+    kernarg_bytes p = (kernarg_bytes)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p)::"memory");
+    return (ArgPtr)(p + kTailAt);
+}
+
+// a pointer to device memory, as such (a pointer read from memory is otherwise taken to point
+// anywhere, and accessed with slower instructions)
+template <class T>
+__device__ __forceinline__ __attribute__((address_space(1))) T* gp(T* p)
+{
+    return (__attribute__((address_space(1))) T*)p;
+}
+
+// wavefronts of a workgroup
+__host__ __device__ constexpr int waves_of(int MT, int R) { return MT > 4 && R * MT > 32 ? 4 : 8; }
 
 #ifndef GHD_RING_REGS
 #define GHD_RING_REGS 80     // registers the load ring of a wavefront may take
 #endif
 #ifndef GHD_RING_KIB
-#define GHD_RING_KIB 4       // weight bytes a wavefront keeps in flight, in KiB (more was measured slower)
+#define GHD_RING_KIB 4       // weight bytes it keeps in flight, in KiB (more was measured slower)
 #endif
 // k-steps in flight per wavefront: limited by registers (accumulators + the ring) and by
 // what the stream needs (a few KiB per wavefront: loads return in issue order, and a long
 // queue only delays the x fragments behind it)
 __host__ __device__ constexpr int pd_of(int MT, int R)
 {
-    int by_regs = GHD_RING_REGS / ((R + MT) * 4);
-    int by_bytes = (GHD_RING_KIB + R - 1) / R;
+    const bool four = waves_of(MT, R) == 4;
+    const int regs = (four ? 304 : 200) - R * MT * 4;       // beside the accumulators
+    int by_regs = (four || regs < GHD_RING_REGS ? regs : GHD_RING_REGS) / ((R + MT) * 4);
+    int by_bytes = ((four ? 8 : GHD_RING_KIB) + R - 1) / R;
     int pd = by_regs < by_bytes ? by_regs : by_bytes;
     return pd < 1 ? 1 : (pd > 8 ? 8 : pd);
 }
 
-// share of a group's k range, in 32nds, that the first wavefront of every SIMD's pair takes
+// Accumulator sets that a wavefront's k-steps go to in turn, added up when its stream ends: the
+// rounding error of a sum grows with the length of its chain, and narrow matrices that are dealt
+// out in whole tiles (R <= 2) have long ones for what parts would do in short ones ([5003, 4104],
+// 33 rows: 1.6e-7 of the result in one chain per wavefront, 1.1e-7 in parts).  The registers are
+// there; the additions cost 0.1 to 0.5 us a launch, so the other cases do without.
+__host__ __device__ constexpr int acc_sets(int MT, int R)
+{
+    const int want = R > 2 || R * MT < 2 ? 1 : R * MT <= 4 ? 4 : R * MT <= 12 ? 2 : 1, pd = pd_of(MT, R);
+    return want < pd ? want : pd;
+}
+
+// Of eight wavefronts, w and w + 4 share a SIMD, and the first of the two gets its data sooner
+// throughout the stream: with equal ranges wavefronts 0-3 end 2.5-6 us before 4-7, which then
+// stream on alone, no faster.  So the first four split kFirstSet/32 of the k range between them
 // (measured on one box, alternating builds: 16 -> 3949 us per 64-row step, 17 -> 3896,
-// 18 -> 3871, 19 -> 3899)
+// 18 -> 3871, 19 -> 3899).
 constexpr int kFirstSet = 18;
+
+#define GLOBAL __attribute__((address_space(1)))
+
+// What the residual epilogue reads: four columns of a row of the residual stream and of the next
+// norm's gain.  The previous launch wrote the former, mostly on another XCD, so it comes from the
+// memory-side cache; requested behind the stream's first loads it is there when the stream
+// ends instead of adding its latency to the end of the launch.
+struct ResidOperands {
+    floatx4 x;
+    half4 g;
+};
+__device__ __forceinline__ ResidOperands resid_operands(ArgPtr a, int m, int n0)
+{
+    ResidOperands r = {{0.f, 0.f, 0.f, 0.f}, {0, 0, 0, 0}};
+    if (m < a->M && n0 < a->lin_N) {
+        r.x = *(GLOBAL const floatx4*)(gp((const float*)a->lin_y) + (size_t)m * a->lin_ldy + n0);
+        if (a->lin_gnext) r.g = *(GLOBAL const half4*)(gp(a->lin_gnext) + n0);
+    }
+    return r;
+}
 
 // ---------------------------------------------------------------------------
 // epilogue of one 16x16 output fragment: lane (c, g4) holds y[m][n0 .. n0+3]
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void epilogue(const FusedArgs& a, const GemmOp& op, floatx4 v, int m, int n0,
-                                         int lane, const float* s_rinv)
+__device__ __forceinline__ void epilogue(ArgPtr a, floatx4 v, int m, int n0, int lane, const float* s_rinv,
+                                         const ResidOperands& ro, bool have_ro)
 {
     // Everything below depends on the fragment's position: the (empty) asm keeps the compiler
     // from working parts of it out ahead of the weight stream, before the kernel's first loads.
     asm volatile("" : "+v"(m), "+v"(n0));
-    const bool mok = m < a.M;
-    const int mtp = a.Mpad >> 4;
-    if (op.rscale) v *= s_rinv[m];
-    if (op.epi == EPI_STORE_F32) {
-        if (a.lin_amax) {
+    const bool mok = m < a->M;
+    const int mtp = a->Mpad >> 4, N = a->lin_N, epi = a->lin_epi;
+    const int64_t ldo = a->lin_ldy;
+    if (a->lin_rscale) v *= s_rinv[m];
+    if (epi == EPI_STORE_F32) {
+        if (a->lin_amax) {
             // the row's best output among this tile's 16 columns: (largest value, lowest column).
             // Greedy acceptance (section 2.3) only needs the row argmax, so the finish of the
             // LM head leaves one candidate per tile and row instead of (or besides) the logits.
@@ -87,7 +149,7 @@ __device__ __forceinline__ void epilogue(const FusedArgs& a, const GemmOp& op, f
             int bi = 0x7fffffff;
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                if (n0 + r < op.N && v[r] > bv) {
+                if (n0 + r < N && v[r] > bv) {
                     bv = v[r];
                     bi = n0 + r;
                 }
@@ -100,79 +162,83 @@ __device__ __forceinline__ void epilogue(const FusedArgs& a, const GemmOp& op, f
                     bi = oi;
                 }
             }
-            if (lane < 16 && mok) a.lin_amax[(size_t)(n0 >> 4) * a.Mpad + m] = make_float2(bv, __int_as_float(bi));
+            if (lane < 16 && mok) {
+                const floatx2 best = {bv, __int_as_float(bi)};
+                *(GLOBAL floatx2*)(gp((float*)a->lin_amax) + ((size_t)(n0 >> 4) * a->Mpad + m) * 2) = best;
+            }
         }
-        if (!mok || !op.out) return;
-        float* o = (float*)op.out + (size_t)m * op.ldo + n0;
-        if (n0 + 3 < op.N && (op.ldo & 3) == 0) *(floatx4*)o = v;
+        if (!mok || !a->lin_y) return;
+        auto o = gp((float*)a->lin_y) + (size_t)m * ldo + n0;
+        if (n0 + 3 < N && (ldo & 3) == 0) *(GLOBAL floatx4*)o = v;
         else
             for (int r = 0; r < 4; ++r)
-                if (n0 + r < op.N) o[r] = v[r];
-    } else if (op.epi == EPI_STORE_F16) {
+                if (n0 + r < N) o[r] = v[r];
+    } else if (epi == EPI_STORE_F16) {
         if (!mok) return;
-        half_t* o = (half_t*)op.out + (size_t)m * op.ldo + n0;
+        auto o = gp((half_t*)a->lin_y) + (size_t)m * ldo + n0;
         for (int r = 0; r < 4; ++r)
-            if (n0 + r < op.N) o[r] = (half_t)v[r];
-    } else if (op.epi == EPI_RESID) {
+            if (n0 + r < N) o[r] = (half_t)v[r];
+    } else if (epi == EPI_RESID) {
         // x += y; sums of squares of the new x over this tile's 16 columns, per row
         float s = 0.f;
-        if (mok && n0 < op.N) {
-            floatx4* xp = (floatx4*)((float*)op.out + (size_t)m * op.ldo + n0);
-            floatx4 xn = *xp + v;
-            *xp = xn;
+        if (mok && n0 < N) {
+            ResidOperands r = ro;
+            if (!have_ro) r = resid_operands(a, m, n0);
+            const floatx4 xn = r.x + v;
+            *(GLOBAL floatx4*)(gp((float*)a->lin_y) + (size_t)m * ldo + n0) = xn;
             s = xn[0] * xn[0] + xn[1] * xn[1] + xn[2] * xn[2] + xn[3] * xn[3];
-            if (op.gnext) {
-                half4 gv = *(const half4*)(op.gnext + n0), o;
+            if (a->lin_gnext) {
+                half4 o;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) o[r] = (half_t)(xn[r] * (float)gv[r] * kXgScale);
-                *(half4*)(a.xg16 + xpk_index(m, n0, mtp)) = o;
+                for (int q = 0; q < 4; ++q) o[q] = (half_t)(xn[q] * (float)r.g[q] * kXgScale);
+                *(GLOBAL half4*)(gp(a->xg16) + xpk_index(m, n0, mtp)) = o;
             }
         }
         s += __shfl_xor(s, 16);
         s += __shfl_xor(s, 32);
-        if (lane < 16 && n0 < op.N) a.ss[(size_t)(n0 >> 4) * a.Mpad + m] = s;
-    } else if (op.epi == EPI_SWIGLU) {
+        if (lane < 16 && n0 < N) gp(a->ss)[(size_t)(n0 >> 4) * a->Mpad + m] = s;
+    } else if (epi == EPI_SWIGLU) {
         // packed rows: (gate f, gate f+1, up f, up f+1)
         if (!mok) return;
         int f = (n0 >> 4) * 8 + ((n0 & 15) >> 2) * 2;
-        if (f >= a.F) return;
+        if (f >= a->F) return;
         // silu with the hardware's exp2 and reciprocal: a few ulp, far below the fp16 rounding
         // of the result (and 0.3 us per launch on the critical path)
         float a0 = __fdividef(v[0], 1.0f + __expf(-v[0])) * v[2];
         float a1 = __fdividef(v[1], 1.0f + __expf(-v[1])) * v[3];
         half2_ h = {(half_t)a0, (half_t)a1};
-        *(half2_*)((half_t*)op.out + xpk_index(m, f, mtp)) = h;
+        *(GLOBAL half2_*)(gp((half_t*)a->lin_y) + xpk_index(m, f, mtp)) = h;
     } else {   // EPI_QKV: packed rows of a head: (j, j+1, j+d/2, j+1+d/2)
-        if (!mok || n0 >= op.N) return;
-        int nh = a.nh, d = a.d;
-        asm volatile("" : "+s"(nh), "+s"(d));     // (the divisions by these stay here, too)
+        if (!mok || n0 >= N) return;
+        const int nh = a->nh, d = a->d;
         const int H = nh * d, hd = d >> 1;
         const QkvRow qr = qkv_row(n0, nh, d);
         const int part = qr.part, head = qr.head, ph = qr.ph;
         int jj = (ph >> 2) * 2;
         float o0 = v[0], o1 = v[1], o2 = v[2], o3 = v[3];
         if (part < 2) {
-            float2 cs0 = a.rope[(size_t)m * hd + jj], cs1 = a.rope[(size_t)m * hd + jj + 1];
-            o0 = v[0] * cs0.x - v[2] * cs0.y;
-            o2 = v[2] * cs0.x + v[0] * cs0.y;
-            o1 = v[1] * cs1.x - v[3] * cs1.y;
-            o3 = v[3] * cs1.x + v[1] * cs1.y;
+            // (cos, sin) of channels jj and jj + 1 (jj is even: 16 bytes, aligned)
+            const floatx4 cs = *(GLOBAL const floatx4*)(gp((const float*)a->rope) + ((size_t)m * hd + jj) * 2);
+            o0 = v[0] * cs[0] - v[2] * cs[1];
+            o2 = v[2] * cs[0] + v[0] * cs[1];
+            o1 = v[1] * cs[2] - v[3] * cs[3];
+            o3 = v[3] * cs[2] + v[1] * cs[3];
         }
         if (part == 2) {
             // V is kept channel-major: row kv_len + m of channels jj, jj+1, jj+d/2, jj+1+d/2
-            half_t* col = op.vc + (size_t)head * a.v_stride_head + (size_t)(a.kv_len + m);
-            col[(size_t)jj * a.v_stride_ch] = (half_t)o0;
-            col[(size_t)(jj + 1) * a.v_stride_ch] = (half_t)o1;
-            col[(size_t)(jj + hd) * a.v_stride_ch] = (half_t)o2;
-            col[(size_t)(jj + 1 + hd) * a.v_stride_ch] = (half_t)o3;
+            auto col = gp(a->lin_vc) + (size_t)head * a->v_stride_head + (size_t)(a->kv_len + m);
+            col[(size_t)jj * a->v_stride_ch] = (half_t)o0;
+            col[(size_t)(jj + 1) * a->v_stride_ch] = (half_t)o1;
+            col[(size_t)(jj + hd) * a->v_stride_ch] = (half_t)o2;
+            col[(size_t)(jj + 1 + hd) * a->v_stride_ch] = (half_t)o3;
             return;
         }
-        half_t* dst = (part == 0)
-                          ? a.q16 + (size_t)m * H + head * d + jj
-                          : op.kc + (size_t)head * a.stride_head + (size_t)(a.kv_len + m) * a.stride_tok + jj;
+        auto dst = (part == 0)
+                       ? gp(a->q16) + (size_t)m * H + head * d + jj
+                       : gp(a->lin_kc) + (size_t)head * a->stride_head + (size_t)(a->kv_len + m) * a->stride_tok + jj;
         half2_ lo = {(half_t)o0, (half_t)o1}, hi = {(half_t)o2, (half_t)o3};
-        *(half2_*)dst = lo;
-        *(half2_*)(dst + hd) = hi;
+        *(GLOBAL half2_*)dst = lo;
+        *(GLOBAL half2_*)(dst + hd) = hi;
     }
 }
 
@@ -184,396 +250,414 @@ __device__ __forceinline__ void pin_order()
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// MT = 16-row tiles of x (Mpad / 16).  R = weight tiles streamed together.  RB = how the
-// matrix is dealt out.  RB == 1: whole tiles - a share is up to R consecutive tiles over the
-// whole k range, in either storage layout, and finishes them alone.  RB == 4 (== R): k ranges
-// of the four-tile row blocks of a narrow matrix - a share streams the blocks its range touches
-// one after the other, and a block whose k range is cut between shares is finished jointly.
-// Returns false if a wait for another share's partial sums gave up.
-template <int MT, int R, int RB>
-__device__ __forceinline__ bool gemm_phase(const FusedArgs& a, const GemmOp& op, Ctx& cx)
+// row tiles of the packed activation layout for MT row tiles of x
+__host__ __device__ constexpr int layout_tiles(int MT) { return MT <= 2 ? MT : MT <= 4 ? 4 : 8; }
+
+template <int MT, int R>
+struct LinShape {
+    static constexpr int NW = waves_of(MT, R), THREADS = NW * 64;
+    static constexpr int NF = R * MT;                        // accumulator fragments of a wavefront
+    static constexpr int CAP = 128 / NW;                     // ... reduced per round through LDS, at most
+    static constexpr int ROUNDS = (NF + CAP - 1) / CAP;
+    static constexpr int FR = (NF + ROUNDS - 1) / ROUNDS;    // ... and per round
+    static constexpr size_t lds_bytes = (size_t)NW * FR * 1024 + (128 + 1024 + 4) * sizeof(float);
+};
+
+// One workgroup's share: the tiles first .. first + count - 1 (count <= R; the other slots
+// re-read the first tile, and what they accumulate is never looked at) over the k-steps
+// k0 .. k1 - 1.  `finish(f, v, m, n0, operands, have)` is called by one wavefront for every
+// fragment f = slot * MT + row tile with the workgroup's sum v; `early()` runs between the
+// stream's first loads and its first wait.
+//
+// ROWS: x is row-major and read as it lies (16 rows x 64 bytes per load), which saves a
+// separate packing launch; columns from K on are not read.
+template <int MT, int R, bool ROWS, class Early, class Finish>
+__device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int first, int count, int k0, int k1,
+                                           Early early, Finish finish)
 {
-    static_assert(RB == 1 || R == RB, "narrow matrices: the slots are the tiles of one row block");
-    constexpr int NF = R * MT;                     // accumulator fragments per wavefront
-    constexpr int FR = NF < 16 ? NF : 16;          // fragments reduced per round through LDS
+    using S = LinShape<MT, R>;
+    constexpr int NW = S::NW, NF = S::NF, FR = S::FR;
     constexpr int PD = pd_of(MT, R);
-    constexpr int NFI = RB * MT;                   // fragments of one row block
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, g4 = lane >> 4;
-    const size_t lane16 = (size_t)(uint32_t)(lane * 16);   // this lane's 16 bytes of a 1 KiB block
-    floatx4* red = (floatx4*)cx.lds;                       // [8][FR][64]
-    float* s_rinv = (float*)(cx.lds + 8 * FR * 1024);      // 128 floats
+    const uint32_t lane16 = lane * 16;                     // this lane's 16 bytes of a 1 KiB block
+    floatx4* red = (floatx4*)lds;                          // [NW][FR][64]
+    float* s_rinv = (float*)(lds + NW * FR * 1024);        // 128 floats
     float* s_tmp = s_rinv + 128;                           // 1024 floats
-    int* s_wait_ok = (int*)(s_tmp + 1024);                 // thread 0's verdict on a bounded wait
-    const int nks = op.nks;
-    const int blk_sh = op.blk_shift;        // tiles per storage block: 8 or 4
-    const int L = cx.G * op.passes;
     const half8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
 
-    // ---- RMSNorm factor per row from the per-tile sums of squares ss[tile][Mpad], in two
-    //      steps.  Early, behind the stream's first loads (it has to wait for those anyway):
-    //      thread (rq, part) adds 4 rows of every P-th tile and the lanes of a wavefront that
-    //      share rq are combined by shuffles - no barrier, so that no wavefront waits for
-    //      another before it starts streaming.
-    //      Late, when the stream is over and the workgroup meets anyway: the 8 wavefronts'
-    //      sums are added through LDS.  Fixed order throughout.
-    bool rinv_loaded = !op.rscale, rinv_ready = !op.rscale;
-    floatx4 rs4 = {0.f, 0.f, 0.f, 0.f}, sst[8];
-    constexpr int RQ = MT * 4, P = kFT / RQ;      // Mpad = 16 MT rows, four per thread
-    const int n_ss = op.K >> 4, rq = tid % RQ, part = tid / RQ;
-    auto rinv_request = [&](int t0) {
+    // this wavefront's k-steps
+    const int n = k1 - k0;
+    int ws, we;
+    if constexpr (NW == 8) {
+        const int n_a = n * kFirstSet / 32, w4 = wave & 3;
+        ws = wave < 4 ? k0 + n_a * w4 / 4 : k0 + n_a + (n - n_a) * w4 / 4;
+        we = wave < 4 ? k0 + n_a * (w4 + 1) / 4 : k0 + n_a + (n - n_a) * (w4 + 1) / 4;
+    } else {
+        ws = k0 + n * wave / NW;
+        we = k0 + n * (wave + 1) / NW;
+    }
+    const int s_hi = max(we - 1, k0);       // loads never go past the wavefront's last k-step
+    const int blk_sh = (h.flags >> kHeadBlk) & 15;
+    const int mtp = ROWS ? 0 : (h.flags >> kHeadMtp) & 15;
+
+    const char* wbase[R];                   // the slot's block of k-step 0
 #pragma unroll
-        for (int q = 0; q < 8; ++q)
-            sst[q] = *(const floatx4*)(a.ss + (size_t)min(t0 + q * P, n_ss - 1) * a.Mpad + rq * 4);
-    };
-    auto rinv_add = [&](int t0) {
+    for (int t = 0; t < R; ++t) {
+        const int tile = first + (t < count ? t : 0);
+        const int blk = (tile >> blk_sh) * (h.nks << blk_sh) + (tile & ((1 << blk_sh) - 1));
+        wbase[t] = (const char*)h.W + ((size_t)(uint32_t)blk << 10);
+    }
+    const half_t* xrow[MT];                 // ROWS: this lane's rows of x
+    if constexpr (ROWS) {
+        const int M = (h.flags >> kHeadM) & 255;
 #pragma unroll
-        for (int q = 0; q < 8; ++q)
-            if (t0 + q * P < n_ss) rs4 += sst[q];
+        for (int b = 0; b < MT; ++b) xrow[b] = h.x + (int64_t)min(b * 16 + c, M - 1) * (int64_t)h.aux;
+    }
+
+    half8 wr[PD][R], xr[PD][MT];
+    constexpr int NA = acc_sets(MT, R);
+    floatx4 accs[NA][R][MT];
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int t = 0; t < R; ++t)
+#pragma unroll
+            for (int b = 0; b < MT; ++b) accs[i][t][b] = (floatx4){0.f, 0.f, 0.f, 0.f};
+    auto& acc = accs[0];
+
+    auto load = [&](auto slot, int s) {
+        constexpr int p = decltype(slot)::value;
+        if constexpr (ROWS) {
+            const int col = min(s * 32 + g4 * 8, h.K - 8);
+#pragma unroll
+            for (int b = 0; b < MT; ++b) xr[p][b] = *(const half8*)(xrow[b] + col);
+        } else {
+            const char* xq = (const char*)h.x + ((size_t)(uint32_t)(s * mtp) << 10);
+#pragma unroll
+            for (int b = 0; b < MT; ++b) xr[p][b] = *(const half8*)(xq + (b << 10) + lane16);
+        }
+#pragma unroll
+        for (int t = 0; t < R; ++t) {
+            const char* wq = wbase[t] + ((size_t)(uint32_t)(s << blk_sh) << 10);
+            wr[p][t] = __builtin_nontemporal_load((const half8*)(wq + lane16));
+        }
     };
-    auto rinv_sum = [&]() {
-        for (int t0 = part; t0 < n_ss; t0 += 8 * P) {
-            rinv_request(t0);
-            rinv_add(t0);
+    // MASKED: columns from K on count as zeros (the x fragments are zeroed: one select for all slots)
+    auto compute = [&](auto masked, auto slot, int s) {
+        constexpr int p = decltype(slot)::value;
+        constexpr bool MASKED = decltype(masked)::value;
+        half8 xf[MT];
+        if constexpr (MASKED) {
+            const bool use = s * 32 + g4 * 8 < h.K;
+#pragma unroll
+            for (int b = 0; b < MT; ++b) xf[b] = use ? xr[p][b] : zero8;
+        } else {
+#pragma unroll
+            for (int b = 0; b < MT; ++b) xf[b] = xr[p][b];
+        }
+#pragma unroll
+        for (int t = 0; t < R; ++t)
+#pragma unroll
+            for (int b = 0; b < MT; ++b)
+                accs[p % NA][t][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wr[p][t], xf[b], accs[p % NA][t][b], 0, 0, 0);
+    };
+    auto prologue = [&](auto self, auto slot) {
+        constexpr int p = decltype(slot)::value;
+        if constexpr (p < PD) {
+            load(slot, min(ws + p, s_hi));
+            pin_order();
+            self(self, std::integral_constant<int, p + 1>{});
+        }
+    };
+    auto ring = [&](auto self, auto slot, int s) {
+        constexpr int p = decltype(slot)::value;
+        if constexpr (p < PD) {
+            compute(std::false_type{}, slot, s + p);
+            pin_order();
+            load(slot, s + p + PD);
+            pin_order();
+            self(self, std::integral_constant<int, p + 1>{}, s);
+        }
+    };
+    // the last steps, PD of which are in the ring already: nothing is requested past the range
+    auto drain = [&](auto self, auto slot, int s) {
+        constexpr int p = decltype(slot)::value;
+        if constexpr (p < 2 * PD - 1) {
+            auto step = [&]() {
+                compute(std::true_type{}, std::integral_constant<int, p % PD>{}, s + p);
+                pin_order();
+                if constexpr (p < PD - 1) {
+                    if (s + p + PD < we) load(std::integral_constant<int, p % PD>{}, s + p + PD);
+                    pin_order();
+                }
+            };
+            // (nested conditions leave the loop sooner; four wavefronts' accumulators would be
+            // copied at every exit)
+            if constexpr (NW == 8) {
+                if (s + p < we) {
+                    step();
+                    self(self, std::integral_constant<int, p + 1>{}, s);
+                }
+            } else {
+                if (s + p < we) step();
+                self(self, std::integral_constant<int, p + 1>{}, s);
+            }
+        }
+    };
+
+    prologue(prologue, std::integral_constant<int, 0>{});
+    early();
+    const ArgPtr a = late_args();
+
+    // The residual epilogue's operands for the first fragment that this wavefront finishes.
+    ResidOperands ro = {{0.f, 0.f, 0.f, 0.f}, {0, 0, 0, 0}};
+    const bool resid = a->lin_epi == EPI_RESID;
+    if (resid && wave < FR && wave / MT < count)
+        ro = resid_operands(a, (wave % MT) * 16 + c, (first + wave / MT) * 16 + g4 * 4);
+
+    // RMSNorm factor per row from the per-tile sums of squares ss[tile][Mpad], in two steps.
+    // Early, here, where the stream's first loads are waited for anyway: thread (rq, part) adds 4
+    // rows of every P-th tile and the lanes of a wavefront that share rq are combined by
+    // shuffles.  Late, when the stream is over and the workgroup meets anyway: the wavefronts'
+    // sums are added through LDS.  Fixed order throughout.
+    constexpr int MTP = layout_tiles(MT), RQ = MTP * 4, P = S::THREADS / RQ;
+    floatx4 rs4 = {0.f, 0.f, 0.f, 0.f};
+    const bool rscale = !ROWS && h.aux != 0;
+    if (rscale) {
+        const auto ss = gp((const float*)h.aux);
+        const int n_ss = h.K >> 4, rq = tid % RQ;
+        for (int t0 = tid / RQ; t0 < n_ss; t0 += 8 * P) {
+            floatx4 sst[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                sst[q] = *(GLOBAL const floatx4*)(ss + (size_t)min(t0 + q * P, n_ss - 1) * (MTP * 16) + rq * 4);
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (t0 + q * P < n_ss) rs4 += sst[q];
         }
         for (int off = RQ; off < 64; off <<= 1) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) rs4[r] += __shfl_xor(rs4[r], off);
         }
-        rinv_loaded = true;
-    };
-    // (the barrier that makes s_rinv visible is the first one of the reduction that follows)
-    auto rinv_finish = [&]() {
-        if (lane < RQ) *(floatx4*)(s_tmp + (wave * RQ + lane) * 4) = rs4;
-        __syncthreads();
-        if (tid < MT * 16) {
-            float tot = 0.f;
-            for (int w = 0; w < 8; ++w) tot += s_tmp[(w * RQ + (tid >> 2)) * 4 + (tid & 3)];
-            s_rinv[tid] = (1.0f / kXgScale) / sqrtf(tot / (float)op.K + a.eps);
-        }
-        rinv_ready = true;
-    };
+    }
 
-    // Share ls of the launch.  RB == 1: the tiles are dealt out, c0 .. c1 are tile indices and
-    // every share covers the whole k range of its tiles - nothing is shared between shares.
-    // RB == 4: the k-steps of the four-tile row blocks are dealt out, c0 .. c1 are indices into
-    // the sequence [block][k-step]; a block whose k range is cut is finished jointly.
-    auto share_of = [&](int ls) {
-        return RB == 1 ? make_share(op.ntiles, 1, ls, L) : make_share(op.nitems, nks, ls, L);
-    };
-    auto is_shared = [&](const Share& sh, int block) { return RB != 1 && sh.first_of(block) != sh.last_of(block); };
-    // Slot 0 of a share holds the partial sums of the row block its range begins in, slot 1
-    // those of the block it ends in (when that is another one); blocks in between are whole.
-    auto slot_of = [&](const Share& sh, int ls, int block) -> float* {
-        return a.part + ((size_t)ls * 2 + (sh.begins_in(ls, block) ? 0 : 1)) * (size_t)(NFI * 256);
-    };
-    // A shared block is counted on the line of its first part (a share is the first part of
-    // at most one shared block: the one its range ends in).
-    auto counter_of = [&](int first) { return op.cnt + first * kCntStride; };
-
-    // ---- one group of R tile slots streamed together over the k-steps k0 .. k1 - 1.
-    //      RB == 1: the tiles first .. first + count - 1 (count <= R; the other slots re-read
-    //      slot 0's blocks, and what they accumulate is never looked at).
-    //      RB == 4: the four tiles of row block `first`.
-    auto run_group = [&](int ls, int first, int count, int k0, int k1) {
-        int s_blk[R];       // index of the 1 KiB block of the slot's k-step 0
+    if (ws < we) {
+        int s = ws;
+        for (; s + 2 * PD <= we; s += PD) ring(ring, std::integral_constant<int, 0>{}, s);
+        drain(drain, std::integral_constant<int, 0>{}, s);
+    }
 #pragma unroll
-        for (int t = 0; t < R; ++t) {
-            const int tile = first + (t < count ? t : 0);
-            s_blk[t] = RB == 1 ? (tile >> blk_sh) * (nks << blk_sh) + (tile & ((1 << blk_sh) - 1)) : first * nks * RB + t;
-        }
-        // This wavefront's k-steps.  Wavefronts w and w + 4 share a SIMD, and the first of the
-        // two gets its data sooner throughout the stream (measured: with equal ranges
-        // wavefronts 0-3 end 2.5-6 us before 4-7, which then stream on alone, no faster).
-        // So the first four split kFirstSet/32 of the range between them, the other four the rest.
-        const int n = k1 - k0, n_a = n * kFirstSet / 32, w4 = wave & 3;
-        const int ws = wave < 4 ? k0 + n_a * w4 / 4 : k0 + n_a + (n - n_a) * w4 / 4;
-        const int we = wave < 4 ? k0 + n_a * (w4 + 1) / 4 : k0 + n_a + (n - n_a) * (w4 + 1) / 4;
-        const int s_hi = max(we - 1, k0);       // loads never go past the wavefront's last k-step
-
-        half8 wr[PD][R], xr[PD][MT];
-        floatx4 acc[R][MT];
+    for (int i = 1; i < NA; ++i)
 #pragma unroll
         for (int t = 0; t < R; ++t)
 #pragma unroll
-            for (int b = 0; b < MT; ++b) acc[t][b] = (floatx4){0.f, 0.f, 0.f, 0.f};
+            for (int b = 0; b < MT; ++b) acc[t][b] += accs[i][t][b];
 
-        // All loads are unconditional (clamped addresses): the compiler's wait counts then
-        // stay exact and the queue is never drained inside the loop.  K-steps past the
-        // wavefront's range are re-reads of its last one; they are zeroed before use.
-        auto load = [&](auto slot, int s) {
-            constexpr int p = decltype(slot)::value;
-            const int sl = min(s, s_hi);
-            const char* xq = (const char*)op.in + ((size_t)(sl * MT) << 10);
-#pragma unroll
-            for (int b = 0; b < MT; ++b) xr[p][b] = *(const half8*)(xq + (b << 10) + lane16);
-#pragma unroll
-            for (int t = 0; t < R; ++t) {
-                const char* wq = (const char*)op.W + ((size_t)(s_blk[t] + (RB == 1 ? sl << blk_sh : sl * RB)) << 10);
-                wr[p][t] = __builtin_nontemporal_load((const half8*)(wq + lane16));
-            }
-        };
-        // MASKED: k-steps past the wavefront's range, and columns past K in the last k-step,
-        // count as zeros (the x fragments are zeroed: one select for all the slots).
-        auto compute = [&](auto masked, auto slot, int s) {
-            constexpr int p = decltype(slot)::value;
-            constexpr bool MASKED = decltype(masked)::value;
-            half8 xf[MT];
-            if constexpr (MASKED) {
-                const bool use = s < we && s * 32 + g4 * 8 < op.K;
-#pragma unroll
-                for (int b = 0; b < MT; ++b) xf[b] = use ? xr[p][b] : zero8;
-            } else {
-#pragma unroll
-                for (int b = 0; b < MT; ++b) xf[b] = xr[p][b];
-            }
-#pragma unroll
-            for (int t = 0; t < R; ++t)
-#pragma unroll
-                for (int b = 0; b < MT; ++b)
-                    acc[t][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wr[p][t], xf[b], acc[t][b], 0, 0, 0);
-        };
-        auto ring = [&](auto self, auto masked, auto slot, int s) {
-            constexpr int p = decltype(slot)::value;
-            if constexpr (p < PD) {
-                compute(masked, slot, s + p);
-                pin_order();
-                load(slot, s + p + PD);
-                pin_order();
-                self(self, masked, std::integral_constant<int, p + 1>{}, s);
-            }
-        };
-        auto prologue = [&](auto self, auto slot) {
-            constexpr int p = decltype(slot)::value;
-            if constexpr (p < PD) {
-                load(slot, ws + p);
-                pin_order();
-                self(self, std::integral_constant<int, p + 1>{});
-            }
-        };
-        // The norm factors are only needed by the epilogues, but their loads are cheapest here.
-        prologue(prologue, std::integral_constant<int, 0>{});
-        if (!rinv_loaded) rinv_sum();
-        // (the share's place among its neighbours is only needed for the finish: worked out
-        // here, while the first weights are on their way)
-        bool shared = false;
-        int first_part = 0;
-        float* my_slot = nullptr;
-        if constexpr (RB != 1) {
-            const Share sh = share_of(ls);
-            first_part = sh.first_of(first);
-            shared = first_part != sh.last_of(first);
-            my_slot = slot_of(sh, ls, first);
+    // ---- the wavefronts' k slices are added up through LDS, FR fragments of every wavefront
+    //      per round, in wavefront order; wavefront w has sums w, w + NW, ... of the round
+    if (rscale) {
+        if (lane < RQ) *(floatx4*)(s_tmp + (wave * RQ + lane) * 4) = rs4;
+        __syncthreads();
+        if (tid < MTP * 16) {
+            float tot = 0.f;
+            for (int w = 0; w < NW; ++w) tot += s_tmp[(w * RQ + (tid >> 2)) * 4 + (tid & 3)];
+            s_rinv[tid] = (1.0f / kXgScale) / sqrtf(tot / (float)h.K + a->eps);
         }
-        {
-            // whole rings of k-steps that need no masking first, then the rest
-            const bool plain = (op.K & 31) == 0 || we < nks;
-            int s = ws;
-            if (plain)
-                for (; s + PD <= we; s += PD) ring(ring, std::false_type{}, std::integral_constant<int, 0>{}, s);
-            for (; s < we; s += PD) ring(ring, std::true_type{}, std::integral_constant<int, 0>{}, s);
-        }
-
-        // ---- the eight k slices are added up through LDS, FR fragments per round; wavefront
-        //      w reduces fragments w, w + 8 of the round (in wavefront order) and finishes them:
-        //      the layer's epilogue, or - for a row block that other shares have parts of -
-        //      a store of the partial sums, which are signalled once all of them are stored.
-        if (!rinv_ready) rinv_finish();
-        constexpr int kLastRound = (NF - 1) / FR;
+        // (the first barrier of the reduction makes s_rinv visible)
+    }
 #pragma unroll
-        for (int r0 = 0; r0 < NF; r0 += FR) {
+    for (int r0 = 0; r0 < NF; r0 += FR) {
+        if (r0) __syncthreads();
 #pragma unroll
-            for (int ff = 0; ff < FR; ++ff)
-                if (r0 + ff < NF) red[(wave * FR + ff) * 64 + lane] = acc[(r0 + ff) / MT][(r0 + ff) % MT];
-            __syncthreads();
-            for (int ff = wave; ff < FR && r0 + ff < NF; ff += 8) {
-                floatx4 v = red[ff * 64 + lane];
+        for (int ff = 0; ff < FR; ++ff)
+            if (r0 + ff < NF) red[(wave * FR + ff) * 64 + lane] = acc[(r0 + ff) / MT][(r0 + ff) % MT];
+        __syncthreads();
+        for (int ff = wave; ff < FR && r0 + ff < NF; ff += NW) {
+            floatx4 v = red[ff * 64 + lane];
 #pragma unroll
-                for (int w = 1; w < 8; ++w) v += red[(w * FR + ff) * 64 + lane];
-                const int f = r0 + ff, t = f / MT, b = f % MT;
-                if (RB == 1 && t >= count) continue;
-                const int tile = RB == 1 ? first + t : first * RB + t;
-                if (!shared)
-                    epilogue(a, op, v, b * 16 + c, tile * 16 + g4 * 4, lane, s_rinv);
-                else
-                    *(floatx4*)(my_slot + ((size_t)(t * MT + b) * 64 + lane) * 4) = v;
-            }
-            if (shared && r0 / FR == kLastRound) wait_own_stores();   // the partials are in the L2
-            __syncthreads();
-            if (shared && r0 / FR == kLastRound && tid == 0) atomicAdd(counter_of(first_part), 1u);
-        }
-        return shared;
-    };
-
-    // ---- the shares of this workgroup, one after the other.  With one share per workgroup
-    //      its range comes from the table in the argument block.
-    bool shared_any = false;
-    for (int p = 0; p < op.passes; ++p) {
-        const int ls = cx.j * op.passes + p;
-        int c0, c1;
-        if (RB != 1 || a.lin_range_ok) {       // (the row-block cut always has one share per workgroup)
-            c0 = (int)a.lin_range[2 * cx.j];   // a scalar load from the argument block
-            c1 = (int)a.lin_range[2 * cx.j + 1];
-        } else {
-            const Share sh = share_of(ls);
-            c0 = sh.c0;
-            c1 = sh.c1;
-        }
-        if (c0 >= c1) continue;
-        if constexpr (RB == 1) {
-            run_group(ls, c0, c1 - c0, 0, nks);      // (the launch was planned for c1 - c0 <= R)
-        } else {
-            const int it0 = c0 / nks, it1 = (c1 - 1) / nks;
-            for (int it = it0; it <= it1; ++it)
-                shared_any = run_group(ls, it, RB, max(c0 - it * nks, 0), min(c1 - it * nks, nks)) || shared_any;
+            for (int w = 1; w < NW; ++w) v += red[(w * FR + ff) * 64 + lane];
+            const int f = r0 + ff, t = f / MT, b = f % MT;
+            if (t >= count) continue;
+            finish(a, f, v, b * 16 + c, (first + t) * 16 + g4 * 4, s_rinv, ro, resid && r0 == 0 && ff == wave);
         }
     }
-    if (!shared_any) return true;
-
-    // ---- joint finish of the shared row blocks this workgroup has parts of.  All its partial
-    //      sums were stored and signalled before it waits for anybody else's.
-    for (int p = 0; p < op.passes; ++p) {
-        const int ls = cx.j * op.passes + p;
-        const Share sh = share_of(ls);
-        if (sh.c0 >= sh.c1) continue;
-        const int it0 = sh.c0 / nks, it1 = (sh.c1 - 1) / nks;
-        for (int k = 0; k < 2; ++k) {
-            const int block = k ? it1 : it0;
-            if (k && it1 == it0) break;
-            if (!is_shared(sh, block)) continue;
-            const int first = sh.first_of(block), last = sh.last_of(block);
-            const int np = last - first + 1, me = ls - first;
-            if (tid == 0)
-                *s_wait_ok = bounded_wait(a.sync, counter_of(first), (uint32_t)np * (op.epoch + 1), 1000u + op.epi);
-            __syncthreads();
-            if (!*s_wait_ok) return false;    // the other parts never arrived: nothing sensible to write
-            const int f0 = NFI * me / np, f1 = NFI * (me + 1) / np;
-            for (int f = f0 + wave; f < f1; f += 8) {
-                // Sum the parts in index order (fixed order: the result does not depend on
-                // timing), eight loads in flight at a time.
-                const size_t foff = ((size_t)f * 64 + lane) * 4;
-                floatx4 v = *(const floatx4*)(slot_of(sh, first, block) + foff);
-                for (int p0 = 1; p0 < np; p0 += 8) {
-                    floatx4 t[8];
-#pragma unroll
-                    for (int q = 0; q < 8; ++q)
-                        if (p0 + q < np) t[q] = *(const floatx4*)(slot_of(sh, first + p0 + q, block) + foff);
-#pragma unroll
-                    for (int q = 0; q < 8; ++q)
-                        if (p0 + q < np) v += t[q];
-                }
-                const int tile = block * RB + f / MT, b = f % MT;
-                epilogue(a, op, v, b * 16 + c, tile * 16 + g4 * 4, lane, s_rinv);
-            }
-        }
-    }
-    return true;
 }
 
-__device__ __forceinline__ GemmOp linear_op_of(const FusedArgs& a)
+// The tiles [c0, c1) of workgroup i (i % 8 = its XCD) when `ntiles` tiles are dealt to the 8
+// XCDs in contiguous blocks and an XCD's tiles to its gx workgroups in equal contiguous runs:
+// make_share(ntiles, 1, (i % 8) * gx + i / 8, 8 * gx) without a division (magic = 2^32 / gx + 1, gx > 1;
+// exact while the tiles of an XCD times gx stay below 2^32 / gx).
+__host__ __device__ __forceinline__ void tile_range(int ntiles, int gx, uint32_t magic, int i, int* c0, int* c1)
 {
-    GemmOp op;
-    op.W = a.lin_W;
-    op.N = a.lin_N;
-    op.K = a.lin_K;
-    op.ntiles = a.lin_ntiles;
-    op.nitems = a.lin_nitems;
-    op.nks = a.lin_nks;
-    op.blk_shift = a.lin_blk_shift;
-    op.epi = a.lin_epi;
-    op.in = (const half8*)a.lin_x;
-    op.rscale = a.lin_rscale != 0;
-    op.gnext = a.lin_gnext;
-    op.out = a.lin_y;
-    op.ldo = a.lin_ldy;
-    op.kc = a.lin_kc;
-    op.vc = a.lin_vc;
-    op.cnt = a.sync + a.lin_cnt;
-    op.epoch = a.lin_epoch;
-    op.passes = a.lin_passes;
-    return op;
+    const int x = i & 7, w = i >> 3;
+    const int i0 = (int)((unsigned)ntiles * (unsigned)x >> 3), U = (int)((unsigned)ntiles * (unsigned)(x + 1) >> 3) - i0;
+    if (U < gx) {
+        *c0 = i0 + (w < U ? w : U);
+        *c1 = i0 + (w + 1 < U ? w + 1 : U);
+    } else {
+        *c0 = i0 + (int)(((uint64_t)((unsigned)U * (unsigned)w) * magic) >> 32);
+        *c1 = i0 + (int)(((uint64_t)((unsigned)U * (unsigned)(w + 1)) * magic) >> 32);
+    }
 }
 
-template <int MT, int R, int RB>
-__global__ __launch_bounds__(kFT) void k_linear(const FusedArgs a)
+// ---- whole tiles ----------------------------------------------------------------------
+template <int MT, int R, bool ROWS>
+__global__ __launch_bounds__((LinShape<MT, R>::THREADS)) void k_linear(const half8* W, const half_t* x, uint64_t aux, int nks, int K,
+                                                    int ntiles, int cut, uint32_t magic, uint32_t flags,
+                                                    const FusedArgs)
 {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    touch_kernel_arguments();
-    Ctx cx = make_ctx(a, lds);
-    const GemmOp op = linear_op_of(a);
-    gemm_phase<MT, R, RB>(a, op, cx);
+    const LinHead h = {W, x, aux, nks, K, ntiles, cut, magic, flags};
+    int c0, c1;
+    tile_range(ntiles, cut, magic, blockIdx.x, &c0, &c1);
+    // A call of its own that is dealt out in whole tiles needs nothing that a set-up kernel
+    // prepares; the workspace's status words are brought up to date here (nothing else in
+    // the launch touches them).
+    auto solo = [&]() {
+        if (((flags >> kHeadSolo) & 1) && blockIdx.x == 0 && threadIdx.x == 0) carry_status(late_args()->sync);
+    };
+    if (c0 >= c1) {
+        solo();
+        return;
+    }
+    const int lane = threadIdx.x & 63;
+    gemm_group<MT, R, ROWS>(
+        h, lds, c0, c1 - c0, 0, nks, solo,
+        [&](ArgPtr a, int, floatx4 v, int m, int n0, const float* s_rinv, const ResidOperands& ro, bool have) {
+            epilogue(a, v, m, n0, lane, s_rinv, ro, have);
+        });
 }
 
-// The launch's argument block with the facts the host can work out for the kernel: the packed
-// matrix' layout and, when there is one share per workgroup and the grid fits the table, every
-// workgroup's work share (the same make_share the kernel would evaluate).
-static inline FusedArgs with_launch_facts(const FusedArgs& a, int G)
-{
-    FusedArgs b = a;
-    const WLayout lay = w_layout(a.lin_N, a.lin_K);
-    const bool whole = lay.rb == 1 || a.lin_whole;
-    b.lin_ntiles = lay.ntiles;
-    b.lin_nitems = lay.nitems;
-    b.lin_nks = lay.nks;
-    b.lin_blk_shift = lay.blk == kWideBlock ? 3 : 2;
-    static_assert(kWideBlock == 8 && kRbNarrow == 4, "storage blocks of 8 or 4 tiles");
-    b.lin_range_ok = a.lin_passes == 1;     // (launches have at most kRangeWgs workgroups)
-    if (b.lin_range_ok)
-        for (int j = 0; j < G; ++j) {
-            const Share sh = whole ? make_share(lay.ntiles, 1, j, G) : make_share(lay.nitems, lay.nks, j, G);
-            b.lin_range[2 * j] = (uint32_t)sh.c0;
-            b.lin_range[2 * j + 1] = (uint32_t)sh.c1;
-        }
-    return b;
-}
-
+// ---- parts --------------------------------------------------------------------------
+// Workgroup i runs on XCD i % 8 (checked, see check_xcd); inside an XCD, S consecutive
+// workgroups are the parts of one block of R tiles, and the blocks are dealt to the XCDs in turn.
 template <int MT, int R>
-constexpr size_t linear_lds_bytes()
+__global__ __launch_bounds__((LinShape<MT, R>::THREADS)) void k_linear_parts(const half8* W, const half_t* x, uint64_t aux, int nks, int K,
+                                                      int ntiles, int cut, uint32_t magic, uint32_t flags,
+                                                      const FusedArgs)
 {
-    return 8 * (size_t)(R * MT < 16 ? R * MT : 16) * 1024 + (128 + 1024 + 4) * sizeof(float);
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const LinHead h = {W, x, aux, nks, K, ntiles, cut, magic, flags};
+    const int S = cut, xcd = blockIdx.x & 7, w = blockIdx.x >> 3;
+    const int bx = (int)(((uint32_t)w * magic) >> 16), part = w - bx * S;
+    const int first = (bx * 8 + xcd) * R;
+    if (first >= ntiles) return;
+    const int count = min(R, ntiles - first);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int k0 = nks * part / S, k1 = nks * (part + 1) / S;
+    constexpr int NF = R * MT;
+    const int f0 = count * MT * part / S, f1 = count * MT * (part + 1) / S;     // what this part finishes
+
+    // partial sums: one slot of NF fragments per workgroup; the block's parts are eight
+    // workgroups apart
+    const int slot0 = bx * S * 8 + xcd;
+    gemm_group<MT, R, false>(
+        h, lds, first, count, k0, k1, [&]() { check_xcd(late_args()->sync, xcd); },
+        [&](ArgPtr a, int f, floatx4 v, int, int, const float*, const ResidOperands&, bool) {
+            *(GLOBAL floatx4*)(gp(a->part) + ((size_t)(slot0 + part * 8) * NF + f) * 256 + lane * 4) = v;
+        });
+    const ArgPtr a = late_args();
+    const float* s_rinv = (const float*)(lds + LinShape<MT, R>::NW * LinShape<MT, R>::FR * 1024);
+    int* s_wait_ok = (int*)(s_rinv + 128 + 1024);
+    const int c = lane & 15, g4 = lane >> 4;
+    const auto position = [&](int f, int* m, int* n0) {
+        *m = (f % MT) * 16 + c;
+        *n0 = (first + f / MT) * 16 + g4 * 4;
+    };
+    // the epilogue's own operands are requested before the wait
+    ResidOperands ro = {{0.f, 0.f, 0.f, 0.f}, {0, 0, 0, 0}};
+    const bool resid = a->lin_epi == EPI_RESID;
+    if (resid && f0 + wave < f1) {
+        int m, n0;
+        position(f0 + wave, &m, &n0);
+        ro = resid_operands(a, m, n0);
+    }
+    wait_own_stores();                       // the partials are in the L2
+    __syncthreads();
+    uint32_t* const cnt = a->sync + a->lin_cnt + slot0 * kCntStride;
+    if (tid == 0) {
+        atomicAdd(cnt, 1u);
+        *s_wait_ok = bounded_wait(a->sync, cnt, (uint32_t)S * (a->lin_epoch + 1), 1000u + a->lin_epi);
+    }
+    __syncthreads();
+    if (!*s_wait_ok) return;                 // the other parts never arrived: nothing sensible to write
+    for (int f = f0 + wave; f < f1; f += LinShape<MT, R>::NW) {
+        // the parts in index order (fixed order: the result does not depend on timing), eight
+        // loads in flight at a time
+        const auto src = gp((const float*)a->part) + ((size_t)slot0 * NF + f) * 256 + lane * 4;
+        floatx4 v = {0.f, 0.f, 0.f, 0.f};
+        for (int p0 = 0; p0 < S; p0 += 8) {
+            floatx4 t[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (p0 + q < S) t[q] = *(GLOBAL const floatx4*)(src + (size_t)(p0 + q) * (8 * NF * 256));
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (p0 + q < S) v += t[q];
+        }
+        int m, n0;
+        position(f, &m, &n0);
+        epilogue(a, v, m, n0, lane, s_rinv, ro, resid && f == f0 + wave);
+    }
 }
 
-template <int MT, int R, int RB>
-static ghd_status launch_linear_t(const FusedArgs& a, hipStream_t st)
+// ---- launches -----------------------------------------------------------------------
+static inline LinHead head_of(const FusedArgs& a, const LinCut& cut)
 {
-    int G = 0;
-    const size_t lds = linear_lds_bytes<MT, R>();
-    ghd_status s = launch_resident_checked((const void*)k_linear<MT, R, RB>, (MT * 16 + R) * 8 + RB, lds, &G);
+    const WLayout lay = w_layout(a.lin_N, a.lin_K);
+    LinHead h;
+    h.W = a.lin_W;
+    h.x = a.lin_x;
+    h.aux = cut.rows ? (uint64_t)a.lin_ldx : a.lin_rscale ? (uint64_t)(uintptr_t)a.ss : 0;
+    h.nks = lay.nks;
+    h.K = a.lin_K;
+    h.ntiles = lay.ntiles;
+    h.cut = cut.whole ? cut.grid / 8 : cut.parts;
+    h.magic = (uint32_t)((cut.whole ? 0x100000000ull : 0x10000ull) / (uint64_t)h.cut + 1);
+    h.flags = (uint32_t)(lay.blk == kWideBlock ? 3 : 2) << kHeadBlk | (uint32_t)(a.Mpad / 16) << kHeadMtp |
+              (uint32_t)a.M << kHeadM | (uint32_t)(a.lin_solo != 0) << kHeadSolo;
+    static_assert(kWideBlock == 8 && kRbNarrow == 4, "storage blocks of 8 or 4 tiles");
+    return h;
+}
+
+template <class Kernel>
+static ghd_status launch_linear_kernel(Kernel kernel, const FusedArgs& a, const LinCut& cut, int threads, size_t lds,
+                                       hipStream_t st)
+{
+    ghd_status s = launch_resident_checked((const void*)kernel, threads, lds);
     if (s) return s;
-    hipLaunchKernelGGL((k_linear<MT, R, RB>), dim3(G), dim3(kFT), lds, st, with_launch_facts(a, G));
+    const LinHead h = head_of(a, cut);
+    hipLaunchKernelGGL(kernel, dim3(cut.grid), dim3(threads), lds, st, h.W, h.x, h.aux, h.nks, h.K, h.ntiles, h.cut,
+                       h.magic, h.flags, a);
     return check_launch();
 }
 
-// the instantiations of one M range; slots = row tiles a share handles at once
-template <int MT>
-ghd_status launch_linear_mt(const FusedArgs& a, hipStream_t st)
+// the instantiations for one number of row tiles of x
+template <int MT, int R>
+ghd_status launch_linear_r(const FusedArgs& a, const LinCut& cut, hipStream_t st)
 {
-    const WLayout lay = w_layout(a.lin_N, a.lin_K);
-    if (lay.rb != 1 && !a.lin_whole) return launch_linear_t<MT, kRbNarrow, kRbNarrow>(a, st);
-    constexpr int CAP = MT <= 4 ? 8 : 4;
-    switch (a.lin_slots) {
-    case 1: return launch_linear_t<MT, 1, 1>(a, st);
-    case 2: return launch_linear_t<MT, 2, 1>(a, st);
-    case 3: return launch_linear_t<MT, 3, 1>(a, st);
-    case 4: return launch_linear_t<MT, 4, 1>(a, st);
-    default: break;
-    }
-    if constexpr (CAP >= 8) {
-        switch (a.lin_slots) {
-        case 5: return launch_linear_t<MT, 5, 1>(a, st);
-        case 6: return launch_linear_t<MT, 6, 1>(a, st);
-        case 7: return launch_linear_t<MT, 7, 1>(a, st);
-        case 8: return launch_linear_t<MT, 8, 1>(a, st);
-        default: break;
+    using S = LinShape<MT, R>;
+    if (cut.whole) {
+        if (cut.tiles == R) {
+            if constexpr (MT <= kRowsMaxMT)
+                if (cut.rows) return launch_linear_kernel(k_linear<MT, R, true>, a, cut, S::THREADS, S::lds_bytes, st);
+            if (cut.rows) return GHD_ERR_SHAPE;
+            return launch_linear_kernel(k_linear<MT, R, false>, a, cut, S::THREADS, S::lds_bytes, st);
         }
+    } else if constexpr (R <= parts_max_tiles(MT)) {
+        if (cut.tiles == R) return launch_linear_kernel(k_linear_parts<MT, R>, a, cut, S::THREADS, S::lds_bytes, st);
     }
+    if constexpr (R < 8) return launch_linear_r<MT, R + 1>(a, cut, st);
     return GHD_ERR_SHAPE;
 }
 
-ghd_status launch_linear_mt1(const FusedArgs& a, hipStream_t st);
-ghd_status launch_linear_mt2(const FusedArgs& a, hipStream_t st);
-ghd_status launch_linear_mt4(const FusedArgs& a, hipStream_t st);
-ghd_status launch_linear_mt8(const FusedArgs& a, hipStream_t st);
+ghd_status launch_linear_mt1(const FusedArgs& a, const LinCut& cut, hipStream_t st);
+ghd_status launch_linear_mt2(const FusedArgs& a, const LinCut& cut, hipStream_t st);
+ghd_status launch_linear_mt3(const FusedArgs& a, const LinCut& cut, hipStream_t st);
+ghd_status launch_linear_mt4(const FusedArgs& a, const LinCut& cut, hipStream_t st);
+ghd_status launch_linear_mt6(const FusedArgs& a, const LinCut& cut, hipStream_t st);
+ghd_status launch_linear_mt8(const FusedArgs& a, const LinCut& cut, hipStream_t st);
 
 }  // namespace ghd

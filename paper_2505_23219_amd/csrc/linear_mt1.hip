@@ -1,8 +1,11 @@
-// Instantiations of the skinny linear kernel for up to 16 rows of x.
+// Instantiations of the skinny linear kernels for up to 16 rows of x.
 #include "linear_impl.h"
 
 namespace ghd {
 
-ghd_status launch_linear_mt1(const FusedArgs& a, hipStream_t st) { return launch_linear_mt<1>(a, st); }
+ghd_status launch_linear_mt1(const FusedArgs& a, const LinCut& cut, hipStream_t st)
+{
+    return launch_linear_r<1, 1>(a, cut, st);
+}
 
 }  // namespace ghd

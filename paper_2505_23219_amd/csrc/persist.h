@@ -3,8 +3,6 @@
 #pragma once
 #include "fused.h"
 
-#include <cstddef>
-
 namespace ghd {
 
 constexpr long long kWaitTicks = 2000000;   // bounded waits give up after 20 ms (100 MHz clock)
@@ -20,7 +18,8 @@ __device__ __forceinline__ uint32_t ld_relaxed(const uint32_t* p)
 }
 
 // Work shares.  An operation has `items` (row blocks, or heads) of `per_item` units
-// (k-steps, or key tiles) each.  Items are dealt to the 8 XCDs in contiguous blocks, and
+// (k-steps, or key tiles) each.  (The linear kernels use the case of one unit per item, in
+// closed form: tile_range.)  Items are dealt to the 8 XCDs in contiguous blocks, and
 // the units of an XCD's items to its shares in equal contiguous ranges.  Workgroup i runs
 // on XCD i % 8 (checked at kernel start), so the logical index j = (i % 8) * G/8 + i / 8
 // puts the G/8 workgroups of an XCD side by side.  An item that is split over several
@@ -105,35 +104,46 @@ __device__ __forceinline__ bool bounded_wait(uint32_t* sync, uint32_t* p, uint32
     return true;
 }
 
-// The argument block is a few 64-byte lines of kernel-argument memory, which the compiler
-// reads field by field as the code needs them, one memory round trip after the other.  One
-// word of every line is requested here, back to back at the start of the kernel, so that
-// the lines arrive together and the later reads find them in the scalar cache.  (Written as
-// one block of scalar loads with its own wait: left to the compiler, the five results are
-// parked one by one, with a wait after each load.)
-__device__ __forceinline__ void touch_kernel_arguments()
+// The exchange between workgroups relies on workgroup i running on XCD i % 8.
+__device__ __forceinline__ void check_xcd(uint32_t* sync, int xcd)
 {
-    static_assert(offsetof(FusedArgs, lin_range) > 320 && offsetof(FusedArgs, lin_range) <= 384,
-                  "six 64-byte lines before the table of work shares");
-    typedef const __attribute__((address_space(4))) uint32_t* kernarg_words;
-    kernarg_words kp = (kernarg_words)__builtin_amdgcn_kernarg_segment_ptr();
-    uint32_t t0, t1, t2, t3, t4, t5;
-    asm volatile(
-        "s_load_dword %0, %6, 0x0\n\t"
-        "s_load_dword %1, %6, 0x40\n\t"
-        "s_load_dword %2, %6, 0x80\n\t"
-        "s_load_dword %3, %6, 0xc0\n\t"
-        "s_load_dword %4, %6, 0x100\n\t"
-        "s_load_dword %5, %6, 0x140\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&s"(t0), "=&s"(t1), "=&s"(t2), "=&s"(t3), "=&s"(t4), "=&s"(t5)
-        : "s"(kp)
-        : "memory");
+    if (threadIdx.x == 0) {
+        const unsigned xcc = __builtin_amdgcn_s_getreg(20 | (31 << 11)) & 15u;   // HW_REG_XCC_ID
+        if (xcc != (unsigned)xcd) atomicCAS(sync + kSyncStatus, 0u, 3u);
+    }
+}
+
+// The status word is cleared for the calls that follow; what it held is kept in the sticky
+// word (first failure wins), so that a caller who reads the status only now and then still
+// learns of a call that gave up.  A workspace seen for the first time (no magic word) holds
+// nothing meaningful.  One thread of a call's first launch.
+__device__ __forceinline__ void carry_status(uint32_t* sync)
+{
+    const uint32_t st = sync[kSyncStatus], sticky = sync[kSyncSticky];
+    const bool known = sync[kSyncMagic] == kSyncMagicValue;
+    sync[kSyncSticky] = known ? (sticky ? sticky : st) : 0u;
+    sync[kSyncMagic] = kSyncMagicValue;
+    sync[kSyncStatus] = 0;
+}
+
+// Zeroes the sync block with BLOCKS workgroups of 256 threads, of which this is number `block`.
+// (The sizes are constants: reading them from the dispatch packet delays the first store.)
+template <int BLOCKS>
+__device__ __forceinline__ void zero_sync(uint32_t* sync, int block)
+{
+    static_assert(kSyncMagic == 3 && kSyncWords % 4 == 0, "the status words are the first 16 bytes");
+    typedef uint32_t word4 __attribute__((ext_vector_type(4)));
+    constexpr int n = kSyncWords / 4;
+#pragma unroll
+    for (int i0 = 0; i0 < n; i0 += BLOCKS * 256) {
+        const int i = i0 + block * 256 + (int)threadIdx.x;
+        if (i > 0 && i < n) ((word4*)sync)[i] = (word4){0u, 0u, 0u, 0u};
+    }
+    if (block == 0 && threadIdx.x == 0) carry_status(sync);
 }
 
 // Workgroups are dealt round-robin to the 8 XCDs; neighbours in the work sequence (which
-// share row blocks, or heads, and exchange partial results) get the same XCD.  The
-// exchange relies on workgroup i running on XCD i % 8, which is checked here.
+// share heads and exchange partial results) get the same XCD.
 __device__ __forceinline__ Ctx make_ctx(const FusedArgs& a, char* lds)
 {
     Ctx cx;
@@ -141,10 +151,7 @@ __device__ __forceinline__ Ctx make_ctx(const FusedArgs& a, char* lds)
     cx.G = G;
     cx.j = (G % 8 == 0) ? (i % 8) * (G / 8) + i / 8 : i;
     cx.lds = lds;
-    if (G % 8 == 0 && threadIdx.x == 0) {
-        unsigned xcc = __builtin_amdgcn_s_getreg(20 | (31 << 11)) & 15u;   // HW_REG_XCC_ID
-        if (xcc != (unsigned)(i % 8)) atomicCAS(a.sync + kSyncStatus, 0u, 3u);
-    }
+    if (G % 8 == 0) check_xcd(a.sync, i % 8);
     return cx;
 }
 

@@ -14,13 +14,25 @@
 namespace ghd {
 
 template <int MT, int R, int D>
-__global__ __launch_bounds__(kFT) void k_qkv_attn(const FusedArgs a)
+__global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* x, uint64_t aux, int nks, int K,
+                                                  int ntiles, int cut, uint32_t magic, uint32_t flags,
+                                                  const FusedArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    touch_kernel_arguments();
-    Ctx cx = make_ctx(a, lds);
-    const GemmOp op = linear_op_of(a);
-    const bool ok = gemm_phase<MT, R, 1>(a, op, cx);
+    const LinHead h = {W, x, aux, nks, K, ntiles, cut, magic, flags};
+    int c0, c1;
+    tile_range(ntiles, cut, magic, blockIdx.x, &c0, &c1);
+    const int lane = threadIdx.x & 63, xcd = blockIdx.x & 7, Gx = cut;
+    if (c0 < c1)
+        gemm_group<MT, R, false>(
+            h, lds, c0, c1 - c0, 0, nks, [&]() { check_xcd(late_args()->sync, xcd); },
+            [&](ArgPtr la, int, floatx4 v, int m, int n0, const float* s_rinv, const ResidOperands& ro, bool have) {
+                epilogue(la, v, m, n0, lane, s_rinv, ro, have);
+            });
+    Ctx cx;
+    cx.G = 8 * Gx;
+    cx.j = xcd * Gx + (blockIdx.x >> 3);
+    cx.lds = lds;
     // ---- the XCD's workgroups meet.  Every one of them counts itself in once its part of
     //      q16 and of the cache rows is acknowledged by the L2 they share (the wait below
     //      covers loads too, so it comes before the attention requests anything) ...
@@ -28,7 +40,6 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const FusedArgs a)
     //      behind each other (a poll then takes microseconds), so the counter is only
     //      incremented: the workgroup that arrives last tells the others, each on a line of
     //      its own.
-    const int Gx = cx.G / 8, xcd = cx.j / Gx;
     uint32_t* const cnt = a.sync + kCntXcd + xcd * kCntStride;
     uint32_t* const go = a.sync + kCntGo;
     const uint32_t round = a.att_epoch + 1;
@@ -46,9 +57,9 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const FusedArgs a)
     //     only after that set-up was measured slower: it is the stores that make a workgroup
     //     late, and everybody waits for the last.)
     auto gate = [&]() -> bool {
-        int* s_ok = &reinterpret_cast<AttnLds<MT, D>*>(cx.lds)->wait_ok;
+        int* s_ok = &reinterpret_cast<AttnLds<layout_tiles(MT), D>*>(cx.lds)->wait_ok;
         if (threadIdx.x == 0)
-            *s_ok = ok && (last || bounded_wait(a.sync, go + cx.j * kCntStride, round, 3000u));
+            *s_ok = last || bounded_wait(a.sync, go + cx.j * kCntStride, round, 3000u);
         __syncthreads();
         if (!*s_ok) return false;
         // Nothing of q16 or of the tree's cache rows should be in this compute unit's L1 (it
@@ -58,45 +69,29 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const FusedArgs a)
         invalidate_l1();
         return true;
     };
-    attn_phase<MT, D, true>(a, cx, a.att_q, a.att_k, a.att_v, a.att_out, a.att_epoch, gate);
+    attn_phase<layout_tiles(MT), D, true>(a, cx, a.att_q, a.att_k, a.att_v, a.att_out, a.att_epoch, gate);
 }
 
-template <int MT, int R, int D>
-static ghd_status launch_qkv_attn_t(const FusedArgs& a, hipStream_t st)
+// the instantiations for one number of row tiles of x: head dim 128, wide QKV matrices of 3
+// to 6 row tiles per workgroup (7B- to 70B-shaped layers)
+template <int MT, int R>
+ghd_status launch_qkv_attn_r(const FusedArgs& a, const LinCut& cut, hipStream_t st)
 {
-    int G = 0;
-    const size_t l1 = linear_lds_bytes<MT, R>(), l2 = sizeof(AttnLds<MT, D>);
-    const size_t lds = l1 > l2 ? l1 : l2;
-    ghd_status s = launch_resident_checked((const void*)k_qkv_attn<MT, R, D>, 0, lds, &G);
-    if (s) return s;
-    hipLaunchKernelGGL((k_qkv_attn<MT, R, D>), dim3(G), dim3(kFT), lds, st, with_launch_facts(a, G));
-    return check_launch();
-}
-
-// the instantiations of one M range: head dim 128, wide QKV matrices of 3 to 6 row tiles per
-// workgroup (7B- to 70B-shaped layers)
-template <int MT>
-ghd_status launch_qkv_attn_mt(const FusedArgs& a, hipStream_t st)
-{
-    if (a.d != 128) return GHD_ERR_SHAPE;
-    switch (a.lin_slots) {
-    case 3: return launch_qkv_attn_t<MT, 3, 128>(a, st);
-    case 4: return launch_qkv_attn_t<MT, 4, 128>(a, st);
-    default: break;
+    if (a.d != 128 || !cut.whole) return GHD_ERR_SHAPE;
+    if (cut.tiles == R) {
+        static_assert(LinShape<MT, R>::THREADS == kFT, "the attention works with eight wavefronts");
+        constexpr size_t l1 = LinShape<MT, R>::lds_bytes, l2 = sizeof(AttnLds<layout_tiles(MT), 128>);
+        return launch_linear_kernel(k_qkv_attn<MT, R, 128>, a, cut, kFT, l1 > l2 ? l1 : l2, st);
     }
-    if constexpr (MT <= 4) {
-        switch (a.lin_slots) {
-        case 5: return launch_qkv_attn_t<MT, 5, 128>(a, st);
-        case 6: return launch_qkv_attn_t<MT, 6, 128>(a, st);
-        default: break;
-        }
-    }
+    if constexpr (R < (MT <= 4 ? 6 : 4)) return launch_qkv_attn_r<MT, R + 1>(a, cut, st);
     return GHD_ERR_SHAPE;
 }
 
-ghd_status launch_qkv_attn_mt1(const FusedArgs& a, hipStream_t st);
-ghd_status launch_qkv_attn_mt2(const FusedArgs& a, hipStream_t st);
-ghd_status launch_qkv_attn_mt4(const FusedArgs& a, hipStream_t st);
-ghd_status launch_qkv_attn_mt8(const FusedArgs& a, hipStream_t st);
+ghd_status launch_qkv_attn_mt1(const FusedArgs& a, const LinCut& cut, hipStream_t st);
+ghd_status launch_qkv_attn_mt2(const FusedArgs& a, const LinCut& cut, hipStream_t st);
+ghd_status launch_qkv_attn_mt3(const FusedArgs& a, const LinCut& cut, hipStream_t st);
+ghd_status launch_qkv_attn_mt4(const FusedArgs& a, const LinCut& cut, hipStream_t st);
+ghd_status launch_qkv_attn_mt6(const FusedArgs& a, const LinCut& cut, hipStream_t st);
+ghd_status launch_qkv_attn_mt8(const FusedArgs& a, const LinCut& cut, hipStream_t st);
 
 }  // namespace ghd

@@ -1,8 +1,11 @@
-// Instantiations of the fused QKV + attention kernel for up to 32 rows of x.
+// Instantiations of the QKV + attention kernel for up to 32 rows of x.
 #include "qkv_attn_impl.h"
 
 namespace ghd {
 
-ghd_status launch_qkv_attn_mt2(const FusedArgs& a, hipStream_t st) { return launch_qkv_attn_mt<2>(a, st); }
+ghd_status launch_qkv_attn_mt2(const FusedArgs& a, const LinCut& cut, hipStream_t st)
+{
+    return launch_qkv_attn_r<2, 3>(a, cut, st);
+}
 
 }  // namespace ghd

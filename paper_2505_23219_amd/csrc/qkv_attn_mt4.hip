@@ -1,8 +1,11 @@
-// Instantiations of the fused QKV + attention kernel for up to 64 rows of x.
+// Instantiations of the QKV + attention kernel for up to 64 rows of x.
 #include "qkv_attn_impl.h"
 
 namespace ghd {
 
-ghd_status launch_qkv_attn_mt4(const FusedArgs& a, hipStream_t st) { return launch_qkv_attn_mt<4>(a, st); }
+ghd_status launch_qkv_attn_mt4(const FusedArgs& a, const LinCut& cut, hipStream_t st)
+{
+    return launch_qkv_attn_r<4, 3>(a, cut, st);
+}
 
 }  // namespace ghd

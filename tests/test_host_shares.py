@@ -173,3 +173,47 @@ def test_attention_share_invariants(nh, ntile, G):
         assert pos == ntile
         sizes = [parts[me][4] - parts[me][3] for me in range(np_)]
         assert max(sizes) - min(sizes) <= 1 and sizes[-1] == min(sizes)   # the last part gets a short range
+
+
+def tile_range(lib, ntiles, gx, i):
+    out = (C.c_int * 2)()
+    lib.ghd_debug_tile_range(ntiles, gx, i, out)
+    return list(out)
+
+
+@pytest.mark.parametrize("gx", [32, 2, 7, 64, 96, 256])
+def test_tile_range_is_the_general_share(gx):
+    """The division-free form that the kernels evaluate equals the general work share, for
+    every workgroup, from one tile to the most that a launch has."""
+    lib = B.lib()
+    for ntiles in list(range(1, 70)) + [255, 256, 257, 320, 1376, 2000, 8 * gx, 8 * gx + 1, 64 * gx, 64 * gx - 3, 16384]:
+        for i in range(0, 8 * gx, 1 if gx <= 32 else 37):
+            want = share(lib, ntiles, 1, (i % 8) * gx + i // 8, 8 * gx)[:2]
+            got = tile_range(lib, ntiles, gx, i)
+            assert got == want or (got[0] == got[1] and want[0] == want[1]), (ntiles, gx, i)
+
+
+@pytest.mark.parametrize("M", [1, 16, 17, 33, 48, 64, 65, 96, 97, 128])
+def test_linear_cut_covers_every_tile_and_fits(M):
+    """How a launch is cut: whole tiles, or parts whose workgroups are all resident (at most 32
+    on each XCD), with a k-step for each of eight wavefronts, of no more tiles than there are
+    accumulators for."""
+    lib = B.lib()
+    out = (C.c_int * 5)()
+    for N in (1, 16, 64, 130, 1000, 1280, 4096, 5003, 5120, 10224, 10240, 22016, 32000, 262144):
+        for K in (8, 40, 256, 688, 1280, 3416, 4096, 11008, 65536):
+            for solo in (0, 1):
+                lib.ghd_debug_cut(M, N, K, 256, solo, out)
+                whole, tiles, parts, grid, rows = list(out)
+                ntiles, nks = (N + 15) // 16, (K + 31) // 32
+                mt = (M + 15) // 16 if M <= 64 else 6 if M <= 96 else 8
+                assert 1 <= tiles <= 8 and grid % 8 == 0
+                if whole:
+                    assert parts == 1
+                    ranges = [tile_range(lib, ntiles, grid // 8, i) for i in range(grid)]
+                    assert max(b - a for a, b in ranges) <= tiles and sum(b - a for a, b in ranges) == ntiles
+                    assert not rows or (solo and mt <= 4)
+                else:
+                    assert not rows and tiles * mt <= 32 and 2 <= parts <= nks // 8 and ntiles < 640
+                    per_xcd = grid // 8 // parts
+                    assert grid == per_xcd * parts * 8 <= 256 and per_xcd * 8 * tiles >= ntiles
