@@ -457,7 +457,7 @@ __device__ __forceinline__ bool attn_phase(const FusedArgs& a, Ctx& cx, const ha
         }
         wait_own_stores();
         __syncthreads();   // partial state acknowledged by the L2; hand-over buffers free again
-        if (tid == 0) atomicAdd(sync + kCntAttn + head * kCntStride, 1u);
+        if (tid == 0) arrive(sync + kCntAttn + head * kCntStride);
 
         // ---- merge: every workgroup of the head combines its share of the rows
         if (tid == 0) sm.wait_ok = bounded_wait(sync, sync + kCntAttn + head * kCntStride, (uint32_t)np * (epoch + 1), 2000u);

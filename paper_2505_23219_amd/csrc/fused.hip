@@ -9,7 +9,7 @@ template <int MT, int D>
 __global__ __launch_bounds__(kFT) void k_attention(const FusedArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    Ctx cx = make_ctx(a, lds);
+    Ctx cx = make_ctx(lds);
     attn_phase<MT, D>(a, cx, a.att_q, a.att_k, a.att_v, a.att_out, a.att_epoch);
 }
 

@@ -485,7 +485,7 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
     }
 }
 
-// The tiles [c0, c1) of workgroup i (i % 8 = its XCD) when `ntiles` tiles are dealt to the 8
+// The tiles [c0, c1) of workgroup i (i % 8 stands for its XCD) when `ntiles` tiles are dealt to the 8
 // XCDs in contiguous blocks and an XCD's tiles to its gx workgroups in equal contiguous runs:
 // make_share(ntiles, 1, (i % 8) * gx + i / 8, 8 * gx) without a division (magic = 2^32 / gx + 1, gx > 1;
 // exact while the tiles of an XCD times gx stay below 2^32 / gx).
@@ -531,8 +531,8 @@ __global__ __launch_bounds__((LinShape<MT, R>::THREADS)) void k_linear(const hal
 }
 
 // ---- parts --------------------------------------------------------------------------
-// Workgroup i runs on XCD i % 8 (checked, see check_xcd); inside an XCD, S consecutive
-// workgroups are the parts of one block of R tiles, and the blocks are dealt to the XCDs in turn.
+// Workgroups i with the same i % 8 run on one XCD (checked, see arrive); of those, S consecutive
+// ones are the parts of one block of R tiles, and the blocks are dealt to the XCDs in turn.
 template <int MT, int R>
 __global__ __launch_bounds__((LinShape<MT, R>::THREADS)) void k_linear_parts(const half8* W, const half_t* x, uint64_t aux, int nks, int K,
                                                       int ntiles, int cut, uint32_t magic, uint32_t flags,
@@ -554,7 +554,7 @@ __global__ __launch_bounds__((LinShape<MT, R>::THREADS)) void k_linear_parts(con
     // workgroups apart
     const int slot0 = bx * S * 8 + xcd;
     gemm_group<MT, R, false>(
-        h, lds, first, count, k0, k1, [&]() { check_xcd(late_args()->sync, xcd); },
+        h, lds, first, count, k0, k1, []() {},
         [&](ArgPtr a, int f, floatx4 v, int, int, const float*, const ResidOperands&, bool) {
             *(GLOBAL floatx4*)(gp(a->part) + ((size_t)(slot0 + part * 8) * NF + f) * 256 + lane * 4) = v;
         });
@@ -578,7 +578,7 @@ __global__ __launch_bounds__((LinShape<MT, R>::THREADS)) void k_linear_parts(con
     __syncthreads();
     uint32_t* const cnt = a->sync + a->lin_cnt + slot0 * kCntStride;
     if (tid == 0) {
-        atomicAdd(cnt, 1u);
+        arrive(cnt);
         *s_wait_ok = bounded_wait(a->sync, cnt, (uint32_t)S * (a->lin_epoch + 1), 1000u + a->lin_epi);
     }
     __syncthreads();

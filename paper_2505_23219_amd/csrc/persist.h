@@ -21,7 +21,7 @@ __device__ __forceinline__ uint32_t ld_relaxed(const uint32_t* p)
 // (k-steps, or key tiles) each.  (The linear kernels use the case of one unit per item, in
 // closed form: tile_range.)  Items are dealt to the 8 XCDs in contiguous blocks, and
 // the units of an XCD's items to its shares in equal contiguous ranges.  Workgroup i runs
-// on XCD i % 8 (checked at kernel start), so the logical index j = (i % 8) * G/8 + i / 8
+// on the XCD of i % 8 (see arrive), so the logical index j = (i % 8) * G/8 + i / 8
 // puts the G/8 workgroups of an XCD side by side.  An item that is split over several
 // shares is therefore always finished inside one XCD, and its partial results are
 // exchanged through that XCD's L2 with plain stores and loads: every wavefront waits for
@@ -85,32 +85,46 @@ __device__ __forceinline__ uint32_t poll(uint32_t* p)
     return atomicOr(p, 0u);
 }
 
-// Waits until *p >= target.  Gives up (and raises the status word to `code`) after
-// kWaitTicks of wall-clock time, or as soon as another workgroup has given up, so that a
-// launch that is not fully resident ends with an error instead of hanging.  One thread calls.
-// Returns false if it gave up: what was waited for is then not there.
+// The workgroups that exchange something count themselves in on a line: arrivals in the low
+// half of the word, the sum of the arrivals' XCD numbers in the high half.  Which XCD a
+// dispatch begins with depends on the hardware queue (it goes round from there: workgroup i
+// runs on XCD (i + offset) % 8), so nothing is assumed about it; what the exchange relies on is
+// that the workgroups of one item share an XCD, and each of them sees that from the sum.
+__device__ __forceinline__ uint32_t my_xcd() { return __builtin_amdgcn_s_getreg(20 | (31 << 11)) & 15u; }   // HW_REG_XCC_ID
+__device__ __forceinline__ uint32_t arrive(uint32_t* p)      // returns the word with this arrival in it
+{
+    const uint32_t mine = 1u + (my_xcd() << 16);
+    return atomicAdd(p, mine) + mine;
+}
+static_assert(kMaxLayers * 64 * 7 < 0x10000, "64 parts at most, counted once per layer");
+
+// Did all the arrivals counted in `word` come from this workgroup's XCD?  If not, status 3.
+__device__ __forceinline__ bool same_xcd(uint32_t* sync, uint32_t word)
+{
+    if ((word >> 16) == my_xcd() * (word & 0xffffu)) return true;
+    atomicCAS(sync + kSyncStatus, 0u, 3u);
+    return false;
+}
+
+// Waits until the line p has counted `target` arrivals.  Gives up (and raises the status word
+// to `code`) after kWaitTicks of wall-clock time, or as soon as another workgroup has given up,
+// so that a launch that is not fully resident ends with an error instead of hanging.  One
+// thread calls.  Returns false if what was waited for is not there, or not visible here.
 __device__ __forceinline__ bool bounded_wait(uint32_t* sync, uint32_t* p, uint32_t target,
                                              uint32_t code)
 {
-    if (poll(p) >= target) return true;
-    const long long t0 = wall_clock64();
-    while (poll(p) < target) {
-        if (wall_clock64() - t0 > kWaitTicks || ld_relaxed(sync + kSyncStatus) != 0) {
-            atomicCAS(sync + kSyncStatus, 0u, code);
-            return false;
+    uint32_t v = poll(p);
+    if ((v & 0xffffu) < target) {
+        const long long t0 = wall_clock64();
+        while (((v = poll(p)) & 0xffffu) < target) {
+            if (wall_clock64() - t0 > kWaitTicks || ld_relaxed(sync + kSyncStatus) != 0) {
+                atomicCAS(sync + kSyncStatus, 0u, code);
+                return false;
+            }
+            __builtin_amdgcn_s_sleep(8);
         }
-        __builtin_amdgcn_s_sleep(8);
     }
-    return true;
-}
-
-// The exchange between workgroups relies on workgroup i running on XCD i % 8.
-__device__ __forceinline__ void check_xcd(uint32_t* sync, int xcd)
-{
-    if (threadIdx.x == 0) {
-        const unsigned xcc = __builtin_amdgcn_s_getreg(20 | (31 << 11)) & 15u;   // HW_REG_XCC_ID
-        if (xcc != (unsigned)xcd) atomicCAS(sync + kSyncStatus, 0u, 3u);
-    }
+    return same_xcd(sync, v);
 }
 
 // The status word is cleared for the calls that follow; what it held is kept in the sticky
@@ -144,14 +158,13 @@ __device__ __forceinline__ void zero_sync(uint32_t* sync, int block)
 
 // Workgroups are dealt round-robin to the 8 XCDs; neighbours in the work sequence (which
 // share heads and exchange partial results) get the same XCD.
-__device__ __forceinline__ Ctx make_ctx(const FusedArgs& a, char* lds)
+__device__ __forceinline__ Ctx make_ctx(char* lds)
 {
     Ctx cx;
     const int G = gridDim.x, i = blockIdx.x;
     cx.G = G;
     cx.j = (G % 8 == 0) ? (i % 8) * (G / 8) + i / 8 : i;
     cx.lds = lds;
-    if (G % 8 == 0) check_xcd(a.sync, i % 8);
     return cx;
 }
 

@@ -25,7 +25,7 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
     const int lane = threadIdx.x & 63, xcd = blockIdx.x & 7, Gx = cut;
     if (c0 < c1)
         gemm_group<MT, R, false>(
-            h, lds, c0, c1 - c0, 0, nks, [&]() { check_xcd(late_args()->sync, xcd); },
+            h, lds, c0, c1 - c0, 0, nks, []() {},
             [&](ArgPtr la, int, floatx4 v, int m, int n0, const float* s_rinv, const ResidOperands& ro, bool have) {
                 epilogue(la, v, m, n0, lane, s_rinv, ro, have);
             });
@@ -38,7 +38,7 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
     //      covers loads too, so it comes before the attention requests anything) ...
     //      Thirty-two workgroups polling one counter line with read-modify-writes queue up
     //      behind each other (a poll then takes microseconds), so the counter is only
-    //      incremented: the workgroup that arrives last tells the others, each on a line of
+    //      incremented: the workgroup that arrives last passes its word on to the others, each on a line of
     //      its own.
     uint32_t* const cnt = a.sync + kCntXcd + xcd * kCntStride;
     uint32_t* const go = a.sync + kCntGo;
@@ -46,11 +46,13 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
     wait_own_stores();
     __syncthreads();       // also: the linear phase's use of the LDS is over
     bool last = false;
+    uint32_t word = 0;
     if (threadIdx.x == 0) {
-        last = atomicAdd(cnt, 1u) + 1u == (uint32_t)Gx * round;
+        word = arrive(cnt);
+        last = (word & 0xffffu) == (uint32_t)Gx * round;
         if (last)
             for (int w = 0; w < Gx; ++w)
-                __hip_atomic_store(go + (xcd * Gx + w) * kCntStride, round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(go + (xcd * Gx + w) * kCntStride, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     // ... and waits for the others at the attention's gate, after it has set up its indices
     //     and requested the cache rows of earlier steps that it starts with.  (Counting in
@@ -59,7 +61,7 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
     auto gate = [&]() -> bool {
         int* s_ok = &reinterpret_cast<AttnLds<layout_tiles(MT), D>*>(cx.lds)->wait_ok;
         if (threadIdx.x == 0)
-            *s_ok = last || bounded_wait(a.sync, go + cx.j * kCntStride, round, 3000u);
+            *s_ok = last ? same_xcd(a.sync, word) : bounded_wait(a.sync, go + cx.j * kCntStride, (uint32_t)Gx * round, 3000u);
         __syncthreads();
         if (!*s_ok) return false;
         // Nothing of q16 or of the tree's cache rows should be in this compute unit's L1 (it

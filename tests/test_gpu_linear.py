@@ -34,3 +34,33 @@ def test_linear_kernels_at_their_edges(B, M):
         B.lib().ghd_debug_cut(M, N, K, 256, 1, out)
         kinds.add((out[0], out[1], out[4]))
     assert len(kinds) >= 5, kinds
+
+
+def test_every_stream_gives_the_same_result(B):
+    """The XCD that a dispatch begins with depends on the hardware queue it goes through.
+    Several streams in turn (more than there are queues), each with a small launch of its own in
+    between: the same layer, attention and split linear give the same bits and status 0 on all."""
+    from paper_2505_23219_amd import model, workloads as wl
+    say("streams")
+    s = wl.ModelShape("streams", H=1024, nh=8, d=128, F=2752, V=500, L=1)
+    M, kv = 40, 300
+    w = model.upload_layer(wl.layer_weights(s, 3, 0), s.d)
+    kc, vc = model.upload_cache(*wl.kv_cache(s, 384, kv, 3, 0))
+    x0 = wl.activations(M, s.H, 3).float().cuda()
+    parent = torch.from_numpy(wl.tree_random(M, 5, 3)).cuda()
+    W = B.ghd_pack_weight(wl.activations(1000, 4096, 4, tag="w", std=0.02).cuda())
+    xl = wl.activations(33, 4096, 5).cuda()
+    cfg = B.make_cfg(s, 384)
+    torch.cuda.synchronize()
+    want = None
+    for i in range(8):
+        with torch.cuda.stream(torch.cuda.Stream() if i else torch.cuda.default_stream()):
+            torch.zeros(64 * i + 1, device="cuda").add_(1)
+            ws, lws = B.workspace(B.ghd_workspace_bytes(cfg, M, kv)), B.workspace(B.lib().ghd_linear_workspace_bytes(33, 1000, 4096))
+            x = x0.clone()
+            B.ghd_verify_layer(cfg, w, kc, vc, x, parent, kv, ws=ws)
+            y = B.ghd_linear_skinny(xl, W, 1000, ws=lws)
+            assert (B.ghd_step_status(ws), B.ghd_step_status(lws)) == (0, 0), i
+            torch.cuda.synchronize()
+            want = want or (x, y)
+            assert torch.equal(x, want[0]) and torch.equal(y, want[1]), i
