@@ -940,9 +940,15 @@ void ghd_debug_cut(int M, int N, int K, int G, int solo, int* out5)
     out5[4] = c.rows;
 }
 
+/* The attention's shares; tmin: the fewest 64-key tiles that a part is made for. */
+void ghd_debug_attn_share_min(int nh, int ntile, int tmin, int j, int G, int head, int* out6)
+{
+    attn_share_on_host(nh, ntile, tmin, j, G, head, out6);
+}
+
 void ghd_debug_attn_share(int nh, int ntile, int j, int G, int head, int* out6)
 {
-    attn_share_on_host(nh, ntile, j, G, head, out6);
+    attn_share_on_host(nh, ntile, 1, j, G, head, out6);
 }
 
 void ghd_debug_split_qkv_attn(int on) { g_split_qkv_attn = on != 0; }

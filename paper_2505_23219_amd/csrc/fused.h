@@ -197,6 +197,8 @@ __host__ __device__ constexpr int row_tiles(int M)
 {
     return M <= 64 ? (M + 15) / 16 : M <= 96 ? 6 : 8;
 }
+// row tiles of the packed activation layout (and of all that is laid out by Mpad) for MT row tiles
+__host__ __device__ constexpr int layout_tiles(int MT) { return MT <= 2 ? MT : MT <= 4 ? 4 : 8; }
 LinCut choose_cut(int M, int N, int K, int G, bool solo);
 
 ghd_status launch_linear(const FusedArgs& a, hipStream_t st);
@@ -206,7 +208,7 @@ ghd_status launch_resident_checked(const void* kernel, int threads, size_t lds, 
 int fused_grid_size();
 void share_on_host(int items, int per_item, int j, int G, int item, int* out);
 void tile_range_on_host(int ntiles, int gx, int i, int* out);
-void attn_share_on_host(int nh, int ntile, int j, int G, int head, int* out);
+void attn_share_on_host(int nh, int ntile, int tmin, int j, int G, int head, int* out);
 
 // The general cut by which a shape is admitted (see plan_linear).  Host only.
 struct LinPlan { int slots, passes, whole; };

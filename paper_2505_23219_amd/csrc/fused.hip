@@ -20,7 +20,7 @@ template <int MT, int D>
 static ghd_status launch_attention_t(const FusedArgs& a, hipStream_t st)
 {
     int G = 0;
-    const size_t lds = sizeof(AttnLds<MT, D>);
+    const size_t lds = sizeof(typename AttnOf<MT, D>::Lds);
     ghd_status s = launch_resident_checked((const void*)k_attention<MT, D>, kFT, lds, &G);
     if (s) return s;
     hipLaunchKernelGGL((k_attention<MT, D>), dim3(G), dim3(kFT), lds, st, a);
@@ -30,16 +30,20 @@ static ghd_status launch_attention_t(const FusedArgs& a, hipStream_t st)
 template <int D>
 static ghd_status launch_attention_d(const FusedArgs& a, int mt, hipStream_t st)
 {
-    if (mt <= 1) return launch_attention_t<1, D>(a, st);
-    if (mt <= 2) return launch_attention_t<2, D>(a, st);
-    if (mt <= 4) return launch_attention_t<4, D>(a, st);
-    return launch_attention_t<8, D>(a, st);
+    switch (mt) {
+    case 1: return launch_attention_t<1, D>(a, st);
+    case 2: return launch_attention_t<2, D>(a, st);
+    case 3: return launch_attention_t<3, D>(a, st);
+    case 4: return launch_attention_t<4, D>(a, st);
+    case 6: return launch_attention_t<6, D>(a, st);
+    default: return launch_attention_t<8, D>(a, st);
+    }
 }
 
 // a.mode selects the kernel; the row-tile count of M selects the instantiation
 ghd_status launch_fused(const FusedArgs& a, hipStream_t st)
 {
-    const int mt = (a.M + 15) / 16;
+    const int mt = row_tiles(a.M);
     if (a.mode == MODE_LINEAR) return launch_linear(a, st);
     if (a.mode == MODE_QKV_ATTN) return launch_qkv_attn(a, st);
     return a.d == 64 ? launch_attention_d<64>(a, mt, st) : launch_attention_d<128>(a, mt, st);
@@ -48,14 +52,14 @@ ghd_status launch_fused(const FusedArgs& a, hipStream_t st)
 // The attention's work shares on the host: for workgroup j and head `head`,
 // out[0..5] = first part, number of parts, this part's index, t0, t1, and whether `head` is
 // one of j's heads at all (otherwise the first five are -1).
-void attn_share_on_host(int nh, int ntile, int j, int G, int head, int* out)
+void attn_share_on_host(int nh, int ntile, int tmin, int j, int G, int head, int* out)
 {
     const AttnHeads hs = attn_heads(nh, j, G);
     for (int i = 0; i < 6; ++i) out[i] = -1;
     out[5] = 0;
     const int hl = head - hs.hx0;
     if (hl < hs.h_lo || hl >= hs.h_hi) return;
-    const AttnTiles ts = attn_tiles(hs, hl, ntile);
+    const AttnTiles ts = attn_tiles(hs, hl, ntile, tmin);
     out[0] = ts.first;
     out[1] = ts.np;
     out[2] = ts.me;

@@ -59,14 +59,6 @@ __device__ __forceinline__ ArgPtr late_args()
     return (ArgPtr)(p + kTailAt);
 }
 
-// a pointer to device memory, as such (a pointer read from memory is otherwise taken to point
-// anywhere, and accessed with slower instructions)
-template <class T>
-__device__ __forceinline__ __attribute__((address_space(1))) T* gp(T* p)
-{
-    return (__attribute__((address_space(1))) T*)p;
-}
-
 // wavefronts of a workgroup
 __host__ __device__ constexpr int waves_of(int MT, int R) { return MT > 4 && R * MT > 32 ? 4 : 8; }
 
@@ -106,8 +98,6 @@ __host__ __device__ constexpr int acc_sets(int MT, int R)
 // (measured on one box, alternating builds: 16 -> 3949 us per 64-row step, 17 -> 3896,
 // 18 -> 3871, 19 -> 3899).
 constexpr int kFirstSet = 18;
-
-#define GLOBAL __attribute__((address_space(1)))
 
 // What the residual epilogue reads: four columns of a row of the residual stream and of the next
 // norm's gain.  The previous launch wrote the former, mostly on another XCD, so it comes from the
@@ -241,17 +231,6 @@ __device__ __forceinline__ void epilogue(ArgPtr a, floatx4 v, int m, int n0, int
         *(GLOBAL half2_*)(dst + hd) = hi;
     }
 }
-
-// keeps the compiler from moving memory operations, MFMAs or anything else across this point
-// (a load ring only works if its loads are issued where they are written)
-__device__ __forceinline__ void pin_order()
-{
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-}
-
-// row tiles of the packed activation layout for MT row tiles of x
-__host__ __device__ constexpr int layout_tiles(int MT) { return MT <= 2 ? MT : MT <= 4 ? 4 : 8; }
 
 template <int MT, int R>
 struct LinShape {

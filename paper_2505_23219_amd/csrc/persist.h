@@ -7,6 +7,24 @@ namespace ghd {
 
 constexpr long long kWaitTicks = 2000000;   // bounded waits give up after 20 ms (100 MHz clock)
 
+#define GLOBAL __attribute__((address_space(1)))
+
+// a pointer to device memory, as such (a pointer read from memory is otherwise taken to point
+// anywhere, and accessed with slower instructions)
+template <class T>
+__device__ __forceinline__ __attribute__((address_space(1))) T* gp(T* p)
+{
+    return (__attribute__((address_space(1))) T*)p;
+}
+
+// keeps the compiler from moving memory operations, MFMAs or anything else across this point
+// (a load ring only works if its loads are issued where they are written)
+__device__ __forceinline__ void pin_order()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 struct Ctx {
     int j, G;            // logical workgroup index, number of workgroups
     char* lds;           // dynamic LDS

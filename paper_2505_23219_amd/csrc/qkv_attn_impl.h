@@ -59,7 +59,7 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
     //     only after that set-up was measured slower: it is the stores that make a workgroup
     //     late, and everybody waits for the last.)
     auto gate = [&]() -> bool {
-        int* s_ok = &reinterpret_cast<AttnLds<layout_tiles(MT), D>*>(cx.lds)->wait_ok;
+        int* s_ok = &reinterpret_cast<typename AttnOf<MT, D>::Lds*>(cx.lds)->wait_ok;
         if (threadIdx.x == 0)
             *s_ok = last ? same_xcd(a.sync, word) : bounded_wait(a.sync, go + cx.j * kCntStride, (uint32_t)Gx * round, 3000u);
         __syncthreads();
@@ -71,7 +71,7 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
         invalidate_l1();
         return true;
     };
-    attn_phase<layout_tiles(MT), D, true>(a, cx, a.att_q, a.att_k, a.att_v, a.att_out, a.att_epoch, gate);
+    attn_phase<MT, D, true>(a, cx, a.att_q, a.att_k, a.att_v, a.att_out, a.att_epoch, gate);
 }
 
 // the instantiations for one number of row tiles of x: head dim 128, wide QKV matrices of 3
@@ -82,7 +82,7 @@ ghd_status launch_qkv_attn_r(const FusedArgs& a, const LinCut& cut, hipStream_t 
     if (a.d != 128 || !cut.whole) return GHD_ERR_SHAPE;
     if (cut.tiles == R) {
         static_assert(LinShape<MT, R>::THREADS == kFT, "the attention works with eight wavefronts");
-        constexpr size_t l1 = LinShape<MT, R>::lds_bytes, l2 = sizeof(AttnLds<layout_tiles(MT), 128>);
+        constexpr size_t l1 = LinShape<MT, R>::lds_bytes, l2 = sizeof(typename AttnOf<MT, 128>::Lds);
         return launch_linear_kernel(k_qkv_attn<MT, R, 128>, a, cut, kFT, l1 > l2 ? l1 : l2, st);
     }
     if constexpr (R < (MT <= 4 ? 6 : 4)) return launch_qkv_attn_r<MT, R + 1>(a, cut, st);

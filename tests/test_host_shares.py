@@ -217,3 +217,27 @@ def test_linear_cut_covers_every_tile_and_fits(M):
                     assert not rows and tiles * mt <= 32 and 2 <= parts <= nks // 8 and ntiles < 640
                     per_xcd = grid // 8 // parts
                     assert grid == per_xcd * parts * 8 <= 256 and per_xcd * 8 * tiles >= ntiles
+
+
+@pytest.mark.parametrize("tmin", [1, 2, 4])
+@pytest.mark.parametrize("nh,ntile", [(32, 33), (40, 129), (32, 1), (4, 3), (256, 2), (7, 9), (1, 40), (100, 17)])
+def test_attention_parts_are_not_made_too_small(nh, ntile, tmin):
+    """With at least tmin tiles wanted per part: still every tile once, in order, no empty part,
+    and no more parts than give each tmin tiles (the last may have fewer)."""
+    lib = B.lib()
+    out = (C.c_int * 6)()
+    for head in range(nh):
+        parts = {}
+        for j in range(256):
+            lib.ghd_debug_attn_share_min(nh, ntile, tmin, j, 256, head, out)
+            first, np_, me, t0, t1, mine = list(out)
+            if mine and me < np_:
+                parts[me] = (j, first, np_, t0, t1)
+        np_ = parts[0][2]
+        assert sorted(parts) == list(range(np_)) and np_ <= -(-ntile // tmin)
+        pos = 0
+        for me in range(np_):
+            j, first, n, t0, t1 = parts[me]
+            assert (j, n, t0) == (first + me, np_, pos) and t1 > t0
+            pos = t1
+        assert pos == ntile
