@@ -37,15 +37,25 @@ __global__ __launch_bounds__(256) void k_row_argmax(const float* __restrict__ lo
     int tid = threadIdx.x;
     float bv = -INFINITY;
     int bi = 0x7fffffff;
-    // four independent loads in flight per thread
-    for (int idx = lo + tid; idx < hi; idx += 1024) {
-        float v[4];
+    // The entries before the segment's first 16-byte boundary and after its last one by the
+    // first threads; between them 16 bytes at a time, four loads in flight (rows of an odd V, or a
+    // caller's array, start at any 4 bytes).
+    const int head = min((int)(((16 - ((uintptr_t)(row + lo) & 15)) & 15) >> 2), hi - lo);
+    const int v0 = lo + head, nv = (hi - v0) >> 2, t0 = v0 + nv * 4;
+    float edge = -INFINITY;
+    const int at = tid < head ? lo + tid : t0 + tid - head;
+    if (at < hi && (tid < head || tid < head + 3)) edge = row[at];
+    for (int q = tid; q < nv; q += 1024) {
+        floatx4 v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = (idx + 256 * u < hi) ? row[idx + 256 * u] : -INFINITY;
+        for (int u = 0; u < 4; ++u) v[u] = *(const floatx4*)(row + v0 + 4 * min(q + 256 * u, nv - 1));
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            if (idx + 256 * u < hi) argmax_merge(bv, bi, v[u], idx + 256 * u);
+            if (q + 256 * u < nv)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) argmax_merge(bv, bi, v[u][e], v0 + 4 * (q + 256 * u) + e);
     }
+    if (at < hi && tid < head + 3) argmax_merge(bv, bi, edge, at);
     for (int off = 32; off > 0; off >>= 1) {
         float ov = __shfl_xor(bv, off);
         int oi = __shfl_xor(bi, off);
@@ -106,53 +116,88 @@ __global__ __launch_bounds__(128) void k_accept(const float* __restrict__ seg_v,
                                                 int32_t* __restrict__ res,
                                                 int32_t* __restrict__ amax_out)
 {
-    __shared__ int32_t s_par[GHD_MAX_M], s_tok[GHD_MAX_M], s_amax[GHD_MAX_M];
+    __shared__ int32_t s_amax[GHD_MAX_M], s_up[GHD_MAX_M], s_depth[GHD_MAX_M];
+    __shared__ uint64_t s_lo[GHD_MAX_M], s_hi[GHD_MAX_M];
     __shared__ int s_key[2];
-    int i = threadIdx.x;
+    const int i = threadIdx.x;
+    int par = -1, tok = 0, bi = 0x7fffffff;
     if (i < M) {
-        s_par[i] = parent[i];
-        s_tok[i] = tokens[i];
-        float bv = -INFINITY;
-        int bi = 0x7fffffff;
+        par = parent[i];
+        tok = tokens[i];
         if (amax_in) bi = amax_in[i];
-        else
-            for (int sg = 0; sg < kArgSeg; ++sg) argmax_merge(bv, bi, seg_v[i * kArgSeg + sg], seg_i[i * kArgSeg + sg]);
+        else {
+            float bv = -INFINITY;
+            float sv[kArgSeg];
+            int si[kArgSeg];
+#pragma unroll
+            for (int sg = 0; sg < kArgSeg; ++sg) {
+                sv[sg] = seg_v[i * kArgSeg + sg];
+                si[sg] = seg_i[i * kArgSeg + sg];
+            }
+#pragma unroll
+            for (int sg = 0; sg < kArgSeg; ++sg) argmax_merge(bv, bi, sv[sg], si[sg]);
+        }
         s_amax[i] = bi;
-        if (amax_out) amax_out[i] = s_amax[i];
+        if (amax_out) amax_out[i] = bi;
     }
     __syncthreads();
-    // key orders candidates by depth first, then by lower node index
-    int key = -1;
+    // Root paths by pointer doubling: after a round a node knows, of twice as many edges up as
+    // before, whether all of them are valid, how many there are, which nodes they pass, and
+    // the node above them.  As many rounds as the deepest node needs; a parent that is not an
+    // earlier node is taken as "no parent".
+    int up = -1, depth = 0;
+    bool ok = true;
+    uint64_t lo = 0, hi = 0;
     if (i < M) {
-        bool ok = true;
-        int depth = 0, j = i;
-        for (int step = 0; step < M; ++step) {
-            int p = s_par[j];
-            if (p < 0 || p >= j) break;
-            ok = ok && (s_tok[j] == s_amax[p]);
-            j = p;
-            ++depth;
+        if (par >= 0 && par < i) {
+            up = par;
+            depth = 1;
+            ok = tok == s_amax[par];
         }
-        if (ok) key = depth * 256 + (255 - i);
+        if (i < 64) lo = 1ull << i;
+        else hi = 1ull << (i - 64);
     }
+    while (__syncthreads_or(up >= 0)) {
+        s_up[i] = up;
+        s_depth[i] = ok ? depth : -1 - depth;
+        s_lo[i] = lo;
+        s_hi[i] = hi;
+        __syncthreads();
+        if (up >= 0) {
+            const int d = s_depth[up], a = up;
+            ok = ok && d >= 0;
+            depth += d >= 0 ? d : -1 - d;
+            lo |= s_lo[a];
+            hi |= s_hi[a];
+            up = s_up[a];
+        }
+    }
+    // key orders candidates by depth first, then by lower node index
+    int key = i < M && ok ? depth * 256 + (255 - i) : -1;
     for (int off = 32; off > 0; off >>= 1) key = max(key, __shfl_xor(key, off));
     if ((i & 63) == 0) s_key[i >> 6] = key;
+    s_depth[i] = depth;
+    s_lo[i] = lo;
+    s_hi[i] = hi;
     __syncthreads();
+    const int best = max(s_key[0], s_key[1]), node = 255 - (best & 255);
     if (i == 0) {
-        int best = max(s_key[0], s_key[1]);
-        int depth = best >> 8, node = 255 - (best & 255);
-        res[0] = depth + 1;
+        res[0] = (best >> 8) + 1;
         res[1] = s_amax[node];
-        for (int pos = depth, j = node; pos >= 0 && j >= 0; --pos, j = s_par[j]) res[2 + pos] = j;
     }
+    if (i < M && (((i < 64 ? s_lo[node] >> i : s_hi[node] >> (i - 64)) & 1ull) != 0)) res[2 + depth] = i;
 }
 
 // ---- commit of the accepted path ---------------------------------------------
 // One workgroup per (layer, head).  The K rows (and the V columns: V is channel-major) of
-// the accepted nodes are gathered into LDS, and only after a barrier written to rows
-// kv_len + j, so no source can have been overwritten before it is read.  The path comes
-// from the device result of the acceptance kernel; its entries are clamped, so that
-// whatever that buffer holds no access leaves the tree rows.
+// the accepted nodes are read, and only after a barrier written to rows kv_len + j, so no
+// source can have been overwritten before it is read.  Rows that are where they belong are left
+// alone: the root always is, and with it as much of the path as follows the node order.  What
+// has to move usually fits the registers, K and V at once; longer paths go through LDS.  The path
+// comes from the device result of the acceptance kernel; its entries are clamped, so that
+// whatever that buffer holds no access leaves the tree rows.  (Bound by latency, a few rows per
+// workgroup: 8.5 us for 32 layers x 32 heads in four dependent steps with K and V one after the
+// other, 7.3 us in two.)
 struct CommitArgs {
     half_t* k[kCommitMaxLayers];
     half_t* v[kCommitMaxLayers];
@@ -164,31 +209,70 @@ __global__ __launch_bounds__(256) void k_commit_path(const CommitArgs a)
 {
     __shared__ __attribute__((aligned(16))) half_t s_rows[GHD_MAX_M * 128];
     __shared__ int32_t s_path[GHD_MAX_M];
+    __shared__ int s_moved;
     const int tid = threadIdx.x, layer = blockIdx.x / a.nh, head = blockIdx.x % a.nh;
     const int d = a.d, len = min(max(a.res[0], 0), a.M);
-    for (int j = tid; j < len; j += 256) s_path[j] = min(max(a.res[2 + j], 0), a.M - 1);
+    if (tid == 0) s_moved = a.M;
+    int at = 0;
+    if (tid < a.M) at = min(max(a.res[2 + tid], 0), a.M - 1);      // (M <= 128 entries follow the first two)
     __syncthreads();
-    half_t* kh = a.k[layer] + (size_t)head * a.cap * d;
-    const int cpr = d / 8;
-    for (int idx = tid; idx < len * cpr; idx += 256) {
-        int j = idx / cpr, c = idx % cpr;
-        *(half8*)(s_rows + idx * 8) = *(const half8*)(kh + (size_t)(a.kv_len + s_path[j]) * d + c * 8);
+    if (tid < len) {
+        s_path[tid] = at;
+        if (at != tid) atomicMin(&s_moved, tid);
     }
     __syncthreads();
-    for (int idx = tid; idx < len * cpr; idx += 256) {
-        int j = idx / cpr, c = idx % cpr;
-        *(half8*)(kh + (size_t)(a.kv_len + j) * d + c * 8) = *(const half8*)(s_rows + idx * 8);
-    }
-    __syncthreads();
+    const int j0 = s_moved, n = len - j0;                          // rows j0 .. len - 1 move
+    if (n <= 0) return;
+    const int32_t* path = s_path + j0;
+    half_t* kh = a.k[layer] + (size_t)head * a.cap * d + (size_t)a.kv_len * d;
     half_t* vh = a.v[layer] + (size_t)head * d * a.cap + a.kv_len;
-    for (int idx = tid; idx < d * len; idx += 256) {
-        int ch = idx / len, j = idx % len;
-        s_rows[idx] = vh[(size_t)ch * a.cap + s_path[j]];
+    const int cpr = d / 8;
+    constexpr int kMove = 16;                                      // rows that fit the registers
+    if (n <= kMove) {
+        constexpr int NK = kMove * 16 / 256, NV = kMove * 128 / 256;
+        half8 kr[NK];
+        half_t vr[NV];
+#pragma unroll
+        for (int i = 0; i < NK; ++i) {
+            const int idx = tid + 256 * i;
+            if (idx < n * cpr) kr[i] = *(const half8*)(kh + (size_t)path[idx / cpr] * d + idx % cpr * 8);
+        }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int idx = tid + 256 * i;
+            if (idx < d * n) vr[i] = vh[(size_t)(idx / n) * a.cap + path[idx % n]];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NK; ++i) {
+            const int idx = tid + 256 * i;
+            if (idx < n * cpr) *(half8*)(kh + (size_t)(j0 + idx / cpr) * d + idx % cpr * 8) = kr[i];
+        }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int idx = tid + 256 * i;
+            if (idx < d * n) vh[(size_t)(idx / n) * a.cap + j0 + idx % n] = vr[i];
+        }
+        return;
+    }
+    for (int idx = tid; idx < n * cpr; idx += 256) {
+        int j = idx / cpr, c = idx % cpr;
+        *(half8*)(s_rows + idx * 8) = *(const half8*)(kh + (size_t)path[j] * d + c * 8);
     }
     __syncthreads();
-    for (int idx = tid; idx < d * len; idx += 256) {
-        int ch = idx / len, j = idx % len;
-        vh[(size_t)ch * a.cap + j] = s_rows[idx];
+    for (int idx = tid; idx < n * cpr; idx += 256) {
+        int j = idx / cpr, c = idx % cpr;
+        *(half8*)(kh + (size_t)(j0 + j) * d + c * 8) = *(const half8*)(s_rows + idx * 8);
+    }
+    __syncthreads();
+    for (int idx = tid; idx < d * n; idx += 256) {
+        int ch = idx / n, j = idx % n;
+        s_rows[idx] = vh[(size_t)ch * a.cap + path[j]];
+    }
+    __syncthreads();
+    for (int idx = tid; idx < d * n; idx += 256) {
+        int ch = idx / n, j = idx % n;
+        vh[(size_t)ch * a.cap + j0 + j] = s_rows[idx];
     }
 }
 
