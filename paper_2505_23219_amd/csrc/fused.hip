@@ -70,10 +70,12 @@ void attn_share_on_host(int nh, int ntile, int tmin, int j, int G, int head, int
 
 // ---- setup kernel ------------------------------------------------------------
 // Blocks 0..kTreeBlocks-1: tree tables (every block walks the parents itself; block 0
-// writes the ancestor masks, each block a slice of the rotary table).  The next kZeroBlocks
+// writes the ancestor masks, each thread one element of the rotary table: the double-precision
+// sine and cosine are the longest chain of the launch).  The next kZeroBlocks
 // blocks zero the sync block.  Further blocks: one per 16-column tile of the residual stream,
 // writing x = widen(x_in), the tile's sums of squares and the gain-scaled fp16 image.
-constexpr int kTreeBlocks = 8;
+constexpr int kTreeBlocks = 32;      // a thread per element of the largest rotary table
+static_assert(kTreeBlocks * 256 >= GHD_MAX_M * 64, "128 rows of 64 pairs");
 constexpr int kZeroBlocks = 64;
 
 __global__ __launch_bounds__(256) void k_fused_setup(uint32_t* __restrict__ sync,
@@ -95,7 +97,13 @@ __global__ __launch_bounds__(256) void k_fused_setup(uint32_t* __restrict__ sync
         __shared__ int32_t s_up[GHD_MAX_M];
         __shared__ int32_t s_depth[GHD_MAX_M];
         __shared__ uint64_t s_lo[GHD_MAX_M], s_hi[GHD_MAX_M];
-        if (!parent) return;
+        if (!parent || (blockIdx.x > 0 && !rope)) return;
+        // This thread's element of the rotary table: its frequency base^(-2j/d), in double, while
+        // parent[] is on its way.
+        const int half = d / 2, e = blockIdx.x * 256 + tid;
+        const bool turn = rope && e < M * half;
+        if (blockIdx.x > 0 && blockIdx.x * 256 >= M * half) return;
+        const double freq = turn ? exp2(-2.0 / d * log2((double)rope_base) * (e % half)) : 0.0;
         int up = -1, dep = 0;
         uint64_t lo = 0, hi = 0;
         if (tid < M) {
@@ -128,15 +136,11 @@ __global__ __launch_bounds__(256) void k_fused_setup(uint32_t* __restrict__ sync
             }
         }
         __syncthreads();
-        if (rope) {
-            // angle = position * base^(-2j/d), evaluated in double
-            const int half = d / 2;
-            const double c = -2.0 / d * log2((double)rope_base);
-            for (int e = blockIdx.x * 256 + tid; e < M * half; e += kTreeBlocks * 256) {
-                int m = e / half, j = e % half;
-                double ang = (double)(kv_len + s_depth[m]) * exp2(c * j);
-                rope[e] = make_float2((float)cos(ang), (float)sin(ang));
-            }
+        if (turn) {
+            const double ang = (double)(kv_len + s_depth[e / half]) * freq;
+            double sn, cs;
+            sincos(ang, &sn, &cs);
+            rope[e] = make_float2((float)cs, (float)sn);
         }
         return;
     }
@@ -144,22 +148,35 @@ __global__ __launch_bounds__(256) void k_fused_setup(uint32_t* __restrict__ sync
         zero_sync<kZeroBlocks>(sync, blockIdx.x - kTreeBlocks);
         return;
     }
-    // residual stream tiles: thread -> (row m, column within the 16-wide tile)
-    int tile = blockIdx.x - kTreeBlocks - kZeroBlocks;
-    for (int e = tid; e < Mpad * 16; e += 256) {
-        int m = e >> 4, col = tile * 16 + (e & 15);
-        float v = 0.f;
+    // residual stream tiles: thread -> (row m, four columns of the 16-wide tile)
+    const int col = (blockIdx.x - kTreeBlocks - kZeroBlocks) * 16 + (tid & 3) * 4;
+    half4 g = {0, 0, 0, 0};
+    if (xg16) g = *(const half4*)(gain + col);
+#pragma unroll
+    for (int i = 0; i < GHD_MAX_M / 64; ++i) {
+        const int m = i * 64 + (tid >> 2);
+        if (m >= Mpad) break;
+        floatx4 v = {0.f, 0.f, 0.f, 0.f};
         if (m < M) {
-            v = x_in16 ? (float)x_in16[(size_t)m * H + col] : x[(size_t)m * H + col];
-            if (x_in16) x[(size_t)m * H + col] = v;
-            if (xg16) xg16[xpk_index(m, col, Mpad >> 4)] = (half_t)(v * (float)gain[col] * kXgScale);
+            if (x_in16) {
+                const half4 h = *(const half4*)(x_in16 + (size_t)m * H + col);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = (float)h[r];
+                *(floatx4*)(x + (size_t)m * H + col) = v;
+            } else {
+                v = *(const floatx4*)(x + (size_t)m * H + col);
+            }
+            if (xg16) {
+                half4 o;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o[r] = (half_t)(v[r] * (float)g[r] * kXgScale);
+                *(half4*)(xg16 + xpk_index(m, col, Mpad >> 4)) = o;
+            }
         }
-        float s = v * v;
+        float s = (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
         s += __shfl_xor(s, 1);
         s += __shfl_xor(s, 2);
-        s += __shfl_xor(s, 4);
-        s += __shfl_xor(s, 8);
-        if ((e & 15) == 0) ss[(size_t)tile * Mpad + m] = s;
+        if ((tid & 3) == 0) ss[(size_t)(col >> 4) * Mpad + m] = s;
     }
 }
 
