@@ -802,15 +802,15 @@ static ghd_status draft_tokens_impl(const void* g_final, const void* Wheads, int
     DraftWs d = carve_draft(ws, H, K, V, R);
     float* logits = head_logits ? head_logits : d.logits;
     int32_t* topk = topk_dev ? topk_dev : d.topk;
-    ghd_status s = GHD_OK;
-    if (!step_sync &&
-        (s = launch_fused_setup(d.lin.sync, nullptr, 1, mpad_of(1), 0, 0, 1.f, nullptr, nullptr, nullptr,
-                                nullptr, 0, nullptr, nullptr, nullptr, st)))
-        return s;
-    if ((s = launch_pick_norm(x_final, res_dev, M, H, g_final, rms_eps, d.n16, st))) return s;
-    if ((s = launch_pack_x(nullptr, d.lin.xpk, d.n16, 1, mpad_of(1), H, H, st))) return s;
-    FusedArgs a = {};
     if (!linear_admitted(1, K * V, H)) return GHD_ERR_SHAPE;
+    // Whole tiles: the heads read the normalised row as it lies and need nothing prepared.
+    // Otherwise it is packed, and the counters have to be zero.
+    const LinCut cut = choose_cut(1, K * V, H, grid_for_sizing(), true);
+    ghd_status s = launch_pick_norm(x_final, res_dev, M, H, g_final, rms_eps, d.n16, st);
+    if (s) return s;
+    if (!cut.rows && (s = launch_pack_x(step_sync ? nullptr : d.lin.sync, d.lin.xpk, d.n16, 1, mpad_of(1), H, H, st)))
+        return s;
+    FusedArgs a = {};
     a.mode = MODE_LINEAR;
     a.M = 1;
     a.Mpad = mpad_of(1);
@@ -818,7 +818,10 @@ static ghd_status draft_tokens_impl(const void* g_final, const void* Wheads, int
     a.sync = step_sync ? step_sync : d.lin.sync;
     a.part = d.lin.part;
     a.lin_W = (const half8*)Wheads;
-    a.lin_x = d.lin.xpk;
+    a.lin_x = cut.rows ? d.n16 : d.lin.xpk;
+    a.lin_ldx = H;
+    a.lin_row_major = 1;
+    a.lin_solo = cut.rows && !step_sync;
     a.lin_y = logits;
     a.lin_N = K * V;
     a.lin_K = H;

@@ -147,8 +147,10 @@ LinCut choose_cut(int M, int N, int K, int G, bool solo)
     best.tiles = U <= Gx * P ? 1 : ceil_div(U, Gx * P);
     best.parts = 1;
     best.grid = 8 * Gx * P;
-    best.rows = solo && mt <= kRowsMaxMT && mt * P * lay.nks * 1024.0 / kXBytesPerUs < kPrepareUs;
-    double best_us = share_us(best.tiles * P, mt * P * (best.rows ? 2 : 1), lay.nks) + (solo && !best.rows ? kPrepareUs : 0.0);
+    // (up to 16 rows only the rows that there are get read)
+    const double row_cost = mt == 1 ? M / 8.0 : 2.0;
+    best.rows = solo && mt <= kRowsMaxMT && (row_cost - 1.0) * mt * P * lay.nks * 1024.0 / kXBytesPerUs < kPrepareUs;
+    double best_us = share_us(best.tiles * P, mt * P * (best.rows ? row_cost : 1.0), lay.nks) + (solo && !best.rows ? kPrepareUs : 0.0);
     if (lay.rb == 1) return best;
     for (int r = 1; r <= parts_max_tiles(mt); ++r) {
         const int per_xcd = ceil_div(ceil_div(lay.ntiles, r), 8);
