@@ -260,7 +260,7 @@ def linear_roofline(torch, B, stack, x_in, parent, kv_len, ws, logits, stream, w
     per_launch_bytes = lin_bytes / per_step
     avg_ms = tot_ms / launches
     achieved = per_launch_bytes / (avg_ms * 1e-3) / 1e9
-    out = {"bound": "hbm", "kernel": "k_linear<MT, R, RB>", "achieved": round(achieved, 1),
+    out = {"bound": "hbm", "kernel": "k_linear<MT, R, ROWS>, k_linear_parts<MT, R>", "achieved": round(achieved, 1),
            "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4),
            "traffic": recorded_traffic(w.name), "launches_per_step": per_step,
            "avg_launch_us": round(avg_ms * 1e3, 2),

@@ -195,13 +195,12 @@ static ghd_status check_layer(const ghd_layer_weights* w, const ghd_kv* kv)
 
 
 // ---- the step as a sequence of single-phase launches ------------------------------
-// Every linear layer is one launch of the persistent GEMM kernel (all compute units,
-// equal contiguous shares of the packed weight stream).  The layer's element-wise work
-// rides on those launches: RMSNorm is applied while the fp32 residual stream is staged as
-// the GEMM's x operand (from per-tile sums of squares left by the producer), and the
-// finishing workgroups rotate q/k and append K/V (QKV), apply SwiGLU (gate|up), or add
-// into the residual stream and leave the new sums of squares (output and down linears).
-// A layer is five launches: QKV, attention, output, gate|up, down.
+// Every linear layer is one launch (linear_impl.h).  The layer's element-wise work rides on
+// those launches: RMSNorm is split between the producer of the residual stream, which leaves the
+// gain-scaled fp16 image and per-tile sums of squares, and the consumer's epilogue; the finishing
+// wavefronts rotate q/k and append K/V (QKV), apply SwiGLU (gate|up), or add into the
+// residual stream (output and down).  A layer is four launches: QKV with the attention, output,
+// gate|up, down; five where QKV and attention cannot share one.
 struct LinearCall {
     const void* Wp;
     int N, K, epi;

@@ -19,15 +19,15 @@ enum { PACK_PLAIN = 0, PACK_QKV = 1, PACK_GATE_UP = 2 };
 // streams together at one k-step lie side by side.  Wide matrices (many tiles per compute
 // unit) are stored in blocks of 8 tiles and always dealt out in whole tiles - a workgroup
 // streams several consecutive tiles over the whole K range.  Narrow ones are stored in
-// blocks of rb = 4 tiles, which are also the items of their other cut: a workgroup streams a
-// k range of one block, so that the x operand it reads is shared by 64 output features
-// (see plan_linear for which cut a launch takes).
+// blocks of rb = 4 tiles; their other cut has workgroups stream a k range of a few tiles, so
+// that the x operand they read is shared by as many output features (see choose_cut for
+// which cut a launch takes).
 constexpr int kRbNarrow = 4;
 constexpr int kWideBlock = 8;
 constexpr int kWideTiles = 640;   // from this many tiles on a matrix is wide
 
 struct WLayout {
-    int rb;        // 1: wide matrix; 4: narrow one (tiles per row block of the k-range cut)
+    int rb;        // 1: wide matrix; 4: narrow one
     int blk;       // tiles per storage block
     int ntiles;    // 16-row tiles (last one zero padded)
     int nitems;    // row blocks (last one padded with zero tiles)
@@ -147,7 +147,7 @@ struct FusedArgs {
     float eps, scale_log2e;
     // scratch (device)
     uint32_t* sync;        // kSyncWords
-    float* part;           // linear layers: partial sums of shared row blocks, two slots per work share
+    float* part;           // linear layers in parts: partial sums, a slot per workgroup
     float* o_part;         // attention partial states, one per workgroup: [G][Mpad][d]
     float* ml_part;        // [G][Mpad][2]
     float* x;              // residual stream [M, H] fp32

@@ -22,8 +22,8 @@ import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CALIBRATION_BYTES = 1 << 30          # bench.py --pmc-calibrate copies 1 GiB
-LINEAR_KERNEL = re.compile(r"k_linear<4, \d+, \d+>")        # linear-only launches of the M = 64 step
-FUSED_KERNEL = re.compile(r"k_qkv_attn<4, \d+, \d+>")      # QKV layer + attention in one launch
+LINEAR_KERNEL = re.compile(r"k_linear(_parts)?(<4,|ILi4E)")     # linear-only launches of the M = 64 step
+FUSED_KERNEL = re.compile(r"k_qkv_attn(<4,|ILi4E)")            # QKV layer + attention in one launch
 COPY_KERNEL = re.compile(r"k_debug_copy")
 
 
@@ -51,9 +51,8 @@ def stats(path: str, out: str, command: str) -> None:
         f.write("# rocprofv3 kernel statistics: verification step, workload stack7b\n\n")
         f.write("Command (on an MI355X, from the repository root):\n\n    %s\n\n" % command)
         f.write("Kernels of this library only (model set-up and PyTorch fill kernels left out); "
-                "the run holds tree steps (M=64: `k_linear<4, R, RB>`, `k_qkv_attn<4, R, 128>`) and 1-token "
-                "decode steps (`k_linear<1, R, RB>`, `k_qkv_attn<1, R, 128>`); R = row tiles streamed together, "
-                "RB = tiles per row block (4: narrow matrices, split along K).\n\n")
+                "the run holds tree steps (M=64: `k_linear`, `k_linear_parts` and `k_qkv_attn` of 4 row tiles) and 1-token "
+                "decode steps (the same of 1); template arguments: row tiles of x, weight tiles streamed together.\n\n")
         f.write("| kernel | calls | avg us | min us | max us | total ms | share |\n|---|---|---|---|---|---|---|\n")
         for r in sorted(rows, key=lambda r: -int(r["TotalDurationNs"])):
             f.write("| `%s` | %s | %.2f | %.2f | %.2f | %.3f | %.1f%% |\n" % (
@@ -87,7 +86,7 @@ def traffic(fetch_csv: str, write_csv: str, out: str, command: str) -> None:
     w_scale = CALIBRATION_BYTES / w_copy
     fetched, written = f_lin * f_scale, w_lin * w_scale
     with open(out, "w") as f:
-        f.write("# HBM traffic of the linear-layer kernel `k_linear<4, R, RB>`, workload stack7b\n\n")
+        f.write("# HBM traffic of the linear-layer kernels `k_linear<4, R>` and `k_linear_parts<4, R>`, workload stack7b\n\n")
         f.write("Commands (on an MI355X, from the repository root; one counter per run):\n\n")
         f.write("    %s\n\n" % command.replace("COUNTER", "FETCH_SIZE"))
         f.write("    %s\n\n" % command.replace("COUNTER", "WRITE_SIZE"))
