@@ -100,9 +100,8 @@ __host__ __device__ constexpr int acc_sets(int MT, int R)
 constexpr int kFirstSet = 18;
 
 // What the residual epilogue reads: four columns of a row of the residual stream and of the next
-// norm's gain.  The previous launch wrote the former, mostly on another XCD, so it comes from the
-// memory-side cache; requested behind the stream's first loads it is there when the stream
-// ends instead of adding its latency to the end of the launch.
+// norm's gain.  (Requested behind the stream's first loads, or before the wait for the other
+// parts, they delay the weights behind them by more than they save: 0.9% of a 64-row step.)
 struct ResidOperands {
     floatx4 x;
     half4 g;
@@ -120,8 +119,7 @@ __device__ __forceinline__ ResidOperands resid_operands(ArgPtr a, int m, int n0)
 // ---------------------------------------------------------------------------
 // epilogue of one 16x16 output fragment: lane (c, g4) holds y[m][n0 .. n0+3]
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void epilogue(ArgPtr a, floatx4 v, int m, int n0, int lane, const float* s_rinv,
-                                         const ResidOperands& ro, bool have_ro)
+__device__ __forceinline__ void epilogue(ArgPtr a, floatx4 v, int m, int n0, int lane, const float* s_rinv)
 {
     // Everything below depends on the fragment's position: the (empty) asm keeps the compiler
     // from working parts of it out ahead of the weight stream, before the kernel's first loads.
@@ -172,8 +170,7 @@ __device__ __forceinline__ void epilogue(ArgPtr a, floatx4 v, int m, int n0, int
         // x += y; sums of squares of the new x over this tile's 16 columns, per row
         float s = 0.f;
         if (mok && n0 < N) {
-            ResidOperands r = ro;
-            if (!have_ro) r = resid_operands(a, m, n0);
+            const ResidOperands r = resid_operands(a, m, n0);
             const floatx4 xn = r.x + v;
             *(GLOBAL floatx4*)(gp((float*)a->lin_y) + (size_t)m * ldo + n0) = xn;
             s = xn[0] * xn[0] + xn[1] * xn[1] + xn[2] * xn[2] + xn[3] * xn[3];
@@ -244,7 +241,7 @@ struct LinShape {
 
 // One workgroup's share: the tiles first .. first + count - 1 (count <= R; the other slots
 // re-read the first tile, and what they accumulate is never looked at) over the k-steps
-// k0 .. k1 - 1.  `finish(f, v, m, n0, operands, have)` is called by one wavefront for every
+// k0 .. k1 - 1.  `finish(a, f, v, m, n0, s_rinv)` is called by one wavefront for every
 // fragment f = slot * MT + row tile with the workgroup's sum v; `early()` runs between the
 // stream's first loads and its first wait.
 //
@@ -390,12 +387,6 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
     early();
     const ArgPtr a = late_args();
 
-    // The residual epilogue's operands for the first fragment that this wavefront finishes.
-    ResidOperands ro = {{0.f, 0.f, 0.f, 0.f}, {0, 0, 0, 0}};
-    const bool resid = a->lin_epi == EPI_RESID;
-    if (resid && wave < FR && wave / MT < count)
-        ro = resid_operands(a, (wave % MT) * 16 + c, (first + wave / MT) * 16 + g4 * 4);
-
     // RMSNorm factor per row from the per-tile sums of squares ss[tile][Mpad], in two steps.
     // Early, here, where the stream's first loads are waited for anyway: thread (rq, part) adds 4
     // rows of every P-th tile and the lanes of a wavefront that share rq are combined by
@@ -459,7 +450,7 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
             for (int w = 1; w < NW; ++w) v += red[(w * FR + ff) * 64 + lane];
             const int f = r0 + ff, t = f / MT, b = f % MT;
             if (t >= count) continue;
-            finish(a, f, v, b * 16 + c, (first + t) * 16 + g4 * 4, s_rinv, ro, resid && r0 == 0 && ff == wave);
+            finish(a, f, v, b * 16 + c, (first + t) * 16 + g4 * 4, s_rinv);
         }
     }
 }
@@ -504,8 +495,8 @@ __global__ __launch_bounds__((LinShape<MT, R>::THREADS)) void k_linear(const hal
     const int lane = threadIdx.x & 63;
     gemm_group<MT, R, ROWS>(
         h, lds, c0, c1 - c0, 0, nks, solo,
-        [&](ArgPtr a, int, floatx4 v, int m, int n0, const float* s_rinv, const ResidOperands& ro, bool have) {
-            epilogue(a, v, m, n0, lane, s_rinv, ro, have);
+        [&](ArgPtr a, int, floatx4 v, int m, int n0, const float* s_rinv) {
+            epilogue(a, v, m, n0, lane, s_rinv);
         });
 }
 
@@ -534,7 +525,7 @@ __global__ __launch_bounds__((LinShape<MT, R>::THREADS)) void k_linear_parts(con
     const int slot0 = bx * S * 8 + xcd;
     gemm_group<MT, R, false>(
         h, lds, first, count, k0, k1, []() {},
-        [&](ArgPtr a, int f, floatx4 v, int, int, const float*, const ResidOperands&, bool) {
+        [&](ArgPtr a, int f, floatx4 v, int, int, const float*) {
             *(GLOBAL floatx4*)(gp(a->part) + ((size_t)(slot0 + part * 8) * NF + f) * 256 + lane * 4) = v;
         });
     const ArgPtr a = late_args();
@@ -545,14 +536,6 @@ __global__ __launch_bounds__((LinShape<MT, R>::THREADS)) void k_linear_parts(con
         *m = (f % MT) * 16 + c;
         *n0 = (first + f / MT) * 16 + g4 * 4;
     };
-    // the epilogue's own operands are requested before the wait
-    ResidOperands ro = {{0.f, 0.f, 0.f, 0.f}, {0, 0, 0, 0}};
-    const bool resid = a->lin_epi == EPI_RESID;
-    if (resid && f0 + wave < f1) {
-        int m, n0;
-        position(f0 + wave, &m, &n0);
-        ro = resid_operands(a, m, n0);
-    }
     wait_own_stores();                       // the partials are in the L2
     __syncthreads();
     uint32_t* const cnt = a->sync + a->lin_cnt + slot0 * kCntStride;
@@ -578,7 +561,7 @@ __global__ __launch_bounds__((LinShape<MT, R>::THREADS)) void k_linear_parts(con
         }
         int m, n0;
         position(f, &m, &n0);
-        epilogue(a, v, m, n0, lane, s_rinv, ro, resid && f == f0 + wave);
+        epilogue(a, v, m, n0, lane, s_rinv);
     }
 }
 

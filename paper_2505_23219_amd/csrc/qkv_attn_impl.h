@@ -26,8 +26,8 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
     if (c0 < c1)
         gemm_group<MT, R, false>(
             h, lds, c0, c1 - c0, 0, nks, []() {},
-            [&](ArgPtr la, int, floatx4 v, int m, int n0, const float* s_rinv, const ResidOperands& ro, bool have) {
-                epilogue(la, v, m, n0, lane, s_rinv, ro, have);
+            [&](ArgPtr la, int, floatx4 v, int m, int n0, const float* s_rinv) {
+                epilogue(la, v, m, n0, lane, s_rinv);
             });
     Ctx cx;
     cx.G = 8 * Gx;
