@@ -156,7 +156,8 @@ ghd_status ghd_pack_weight(void *dst, const void *src, int N, int K, int kind, i
  *   x   fp16 [M, ldx] (ldx >= K, ldx % 8 == 0), K % 8 == 0
  *   Wp  packed W
  *   y   float or fp16 (flags) [M, ldy], ldy >= N
- * fp16 products, fp32 accumulation.  1 <= M <= GHD_MAX_M. */
+ * fp16 products, fp32 accumulation.  1 <= M <= GHD_MAX_M.  y may meet x in memory: x
+ * counts as it was before the call (and is then copied into ws first). */
 ghd_status ghd_linear_skinny(void *y, const void *x, const void *Wp, int M, int N, int K,
                              int64_t ldx, int64_t ldy, uint32_t flags, void *ws, size_t ws_bytes,
                              void *stream);

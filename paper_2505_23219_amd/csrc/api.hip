@@ -77,6 +77,24 @@ static bool linear_admitted(int M, int N, int K)
     return plan_linear(M, N, K, grid_for_sizing(), &pl);
 }
 
+// A linear call of its own may read x as the caller's array only if nothing is written there
+// meanwhile: workgroups that are done store y while others still read x.  (The rows' extents are
+// compared, not the elements: two halves of one wide buffer count as meeting.)
+static bool extents_meet(const void* y, int64_t ldy, int N, size_t y_size, const void* x, int64_t ldx, int K, int M)
+{
+    const uintptr_t y0 = (uintptr_t)y, y1 = y0 + ((size_t)(M - 1) * (size_t)ldy + N) * y_size;
+    const uintptr_t x0 = (uintptr_t)x, x1 = x0 + ((size_t)(M - 1) * (size_t)ldx + K) * sizeof(half_t);
+    return y0 < x1 && x0 < y1;
+}
+
+// How a linear call of its own is cut.
+static LinCut linear_call_cut(const void* y, const void* x, int M, int N, int K, int64_t ldx, int64_t ldy, uint32_t flags,
+                              bool* as_it_lies)
+{
+    *as_it_lies = !extents_meet(y, ldy, N, flags == GHD_OUT_F16 ? 2 : 4, x, ldx, K, M);
+    return choose_cut(M, N, K, grid_for_sizing(), *as_it_lies);
+}
+
 // ---- workspace carving ---------------------------------------------------------
 struct Carver {
     char* base;
@@ -389,9 +407,11 @@ ghd_status ghd_linear_skinny(void* y, const void* x, const void* Wp, int M, int 
     Ws w = carve(ws, 1, M, 0, 0, 0, K);
     FusedArgs a = {};
     if (!linear_admitted(M, N, K)) return GHD_ERR_SHAPE;
-    const LinCut cut = choose_cut(M, N, K, grid_for_sizing(), true);
+    bool as_it_lies;
+    const LinCut cut = linear_call_cut(y, x, M, N, K, ldx, ldy, flags, &as_it_lies);
     // Whole tiles with few rows of x: one launch reads x as it lies and needs nothing prepared.
-    // Otherwise the kernel reads x as MFMA operand blocks, and the counters have to be zero.
+    // Otherwise (and where y meets x) the kernel reads x as MFMA operand blocks, and the counters have
+    // to be zero.
     if (!cut.rows) {
         ghd_status s = launch_pack_x(w.sync, w.xpk, (const half_t*)x, M, mpad_of(M), K, ldx, st);
         if (s) return s;
@@ -405,7 +425,7 @@ ghd_status ghd_linear_skinny(void* y, const void* x, const void* Wp, int M, int 
     a.lin_W = (const half8*)Wp;
     a.lin_x = cut.rows ? (const half_t*)x : w.xpk;
     a.lin_ldx = ldx;
-    a.lin_row_major = 1;
+    a.lin_row_major = as_it_lies;
     a.lin_solo = cut.rows;
     a.lin_y = y;
     a.lin_N = N;
@@ -940,6 +960,13 @@ void ghd_debug_cut(int M, int N, int K, int G, int solo, int* out5)
     out5[2] = c.parts;
     out5[3] = c.grid;
     out5[4] = c.rows;
+}
+
+/* Does a linear call with these arguments read x as the caller's array (1), or a copy (0)? */
+int ghd_debug_linear_reads_x(const void* y, const void* x, int M, int N, int K, int64_t ldx, int64_t ldy, uint32_t flags)
+{
+    bool as_it_lies;
+    return linear_call_cut(y, x, M, N, K, ldx, ldy, flags, &as_it_lies).rows;
 }
 
 /* The attention's shares; tmin: the fewest 64-key tiles that a part is made for. */

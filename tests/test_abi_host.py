@@ -369,3 +369,25 @@ def test_benchmark_loop_tree_is_pinned(lib, orc32):
     assert p0.tolist() == gold["parent"] and r0.tolist() == gold["rank"] and e0 == e
     # a tree over 5 heads never goes deeper than 5 drafted levels
     assert orc32.tree_depth(p0).max() <= gold["heads"]
+
+
+@pytest.mark.parametrize("M,N,K", [(16, 4096, 4096), (32, 1024, 1024), (64, 512, 512)])
+def test_linear_in_place_reads_a_copy_of_x(lib, M, N, K):
+    """A result that meets the input anywhere is written by workgroups that are done while others
+    still read, so such a call reads a packed copy of x; the same shape apart reads x as it lies."""
+    def reads_x(y, ldy=N, out16=True, ldx=K):
+        return lib.ghd_debug_linear_reads_x(C.c_void_p(y), C.c_void_p(FAKE), M, N, K, C.c_int64(ldx), C.c_int64(ldy),
+                                            C.c_uint32(B.GHD_OUT_F16 if out16 else B.GHD_OUT_F32))
+    x_bytes = ((M - 1) * K + K) * 2
+    assert reads_x(FAKE + x_bytes) == 1 and reads_x(FAKE + x_bytes, out16=False) == 1
+    assert reads_x(FAKE) == 0 and reads_x(FAKE, out16=False) == 0
+    assert reads_x(FAKE + x_bytes - 16) == 0                       # y begins inside x's last row
+    far = 1 << 30
+    for out16, size in ((True, 2), (False, 4)):
+        y_bytes = ((M - 1) * N + N) * size
+        base = far - y_bytes                                       # y ends where x could begin
+        assert lib.ghd_debug_linear_reads_x(C.c_void_p(base), C.c_void_p(far), M, N, K, C.c_int64(K), C.c_int64(N),
+                                            C.c_uint32(1 if out16 else 0)) == 1
+        assert lib.ghd_debug_linear_reads_x(C.c_void_p(base + 16), C.c_void_p(far), M, N, K, C.c_int64(K), C.c_int64(N),
+                                            C.c_uint32(1 if out16 else 0)) == 0
+    assert reads_x(FAKE + 2 * K, ldy=K + N, ldx=K + N) == 0        # side by side in one buffer

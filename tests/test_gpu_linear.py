@@ -64,3 +64,20 @@ def test_every_stream_gives_the_same_result(B):
             torch.cuda.synchronize()
             want = want or (x, y)
             assert torch.equal(x, want[0]) and torch.equal(y, want[1]), i
+
+
+@pytest.mark.parametrize("M,N,K", [(16, 4096, 4096), (32, 1024, 1024), (64, 512, 512), (33, 200, 1000), (1, 64, 64)])
+def test_linear_in_place(B, M, N, K):
+    """y == x with an fp16 result: x counts as it was before the call.  fp16 rounding of an fp32
+    sum: half an ulp (2^-11 of the value) plus the sum's own error, below 2e-6 of the row's scale."""
+    say("linear in place", M, N, K)
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    x = torch.randn((M, K), generator=g, device="cuda").to(torch.float16)
+    W = (torch.randn((N, K), generator=g, device="cuda") * 0.02).to(torch.float16)
+    ref = x.double() @ W.double().t()
+    y = x[:, :N]
+    ws = B.workspace(B.lib().ghd_linear_workspace_bytes(M, N, K))
+    B.ghd_linear_skinny(x, B.ghd_pack_weight(W), N, ws=ws, y=y)
+    assert B.ghd_step_status(ws) == 0
+    err = (y.double() - ref).abs()
+    assert bool((err <= 2.0 ** -11 * ref.abs() + 2e-6 * ref.std() + 2.0 ** -25).all()), float(err.max())
