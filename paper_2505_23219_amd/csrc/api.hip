@@ -951,6 +951,9 @@ int ghd_debug_plan(int M, int N, int K, int G, int* out3)
 /* The tiles of workgroup i of a whole-tile launch with gx workgroups per XCD: out2 = {c0, c1}. */
 void ghd_debug_tile_range(int ntiles, int gx, int i, int* out2) { tile_range_on_host(ntiles, gx, i, out2); }
 
+/* A counter line over the launches of a call; see exchange_on_host. */
+void ghd_debug_exchange(const int* xcd, int epochs, int n, int* ok) { exchange_on_host(xcd, epochs, n, ok); }
+
 /* out5 = {whole tiles, tiles per share, parts, workgroups, x read row-major} of a launch. */
 void ghd_debug_cut(int M, int N, int K, int G, int solo, int* out5)
 {

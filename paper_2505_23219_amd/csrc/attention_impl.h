@@ -383,8 +383,10 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const h
             uint32_t* const cnt = sync + kCntAttn + head * kCntStride;
             const int r0 = M * me / np, r1 = M * (me + 1) / np;        // the rows this part merges
             if (tid == 0) {
-                arrive(cnt);
-                if (r0 < r1) sm.wait_ok = bounded_wait(sync, cnt, (uint32_t)np * (epoch + 1), 2000u);
+                uint32_t* const word = epoch_word(cnt, epoch);
+                arrive(word);
+                if (me == 0) clear_next(cnt, epoch);
+                if (r0 < r1) sm.wait_ok = bounded_wait(sync, word, (uint32_t)np, (uint32_t)np, 2000u);
             }
             if (r0 < r1) {
                 __syncthreads();
@@ -799,10 +801,15 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const h
         }
         wait_own_stores();
         __syncthreads();   // partial state acknowledged by the L2; hand-over buffers free again
-        if (tid == 0) arrive(sync + kCntAttn + head * kCntStride);
 
         // ---- merge: every workgroup of the head combines its share of the rows
-        if (tid == 0) sm.wait_ok = bounded_wait(sync, sync + kCntAttn + head * kCntStride, (uint32_t)np * (epoch + 1), 2000u);
+        if (tid == 0) {
+            uint32_t* const cnt = sync + kCntAttn + head * kCntStride;
+            uint32_t* const word = epoch_word(cnt, epoch);
+            arrive(word);
+            if (me == 0) clear_next(cnt, epoch);
+            sm.wait_ok = bounded_wait(sync, word, (uint32_t)np, (uint32_t)np, 2000u);
+        }
         __syncthreads();
         if (!sm.wait_ok) return false;    // the other parts never arrived: nothing sensible to write
         int r0 = M * me / np, r1 = M * (me + 1) / np;

@@ -110,7 +110,7 @@ __host__ __device__ inline size_t xpk_halves(int K, int mtp) { return (size_t)((
 // 128-byte line of its own (kCntStride words apart): the workgroups of one item poll and
 // bump it without disturbing the others.  A linear layer's block is counted on the line of
 // its first part; each kind of linear layer has an array of its own, reused layer after layer
-// by epoch.
+// (see epoch_word).
 constexpr int kSyncStatus = 1;    // 0 = ok, else the code of the wait that gave up (this set-up's calls)
 constexpr int kSyncSticky = 2;    // the first non-zero status an earlier set-up found in kSyncStatus
 constexpr int kSyncMagic = 3;     // kSyncMagicValue once a set-up kernel has run on this workspace
@@ -167,7 +167,7 @@ struct FusedArgs {
     const half_t* lin_gnext;   // EPI_RESID: gain of the norm that follows (xg16 is rewritten)
     half_t *lin_kc, *lin_vc;   // EPI_QKV: the layer's cache
     int lin_cnt;           // which counter array of the sync block this call uses
-    uint32_t lin_epoch;    // how often that array was used since it was zeroed
+    uint32_t lin_epoch;    // how often that array was used since it was zeroed (the layer)
     uint32_t att_epoch;    // same for the attention head counters
     int64_t lin_ldy;
     float2* lin_amax;      // EPI_STORE_F32, optional: per (16-column tile, row) the largest output and,
@@ -207,6 +207,7 @@ bool qkv_attn_available(int M, int d, int nh);
 ghd_status launch_resident_checked(const void* kernel, int threads, size_t lds, int* grid = nullptr);
 int fused_grid_size();
 void share_on_host(int items, int per_item, int j, int G, int item, int* out);
+void exchange_on_host(const int* xcd, int epochs, int n, int* ok);
 void tile_range_on_host(int ntiles, int gx, int i, int* out);
 void attn_share_on_host(int nh, int ntile, int tmin, int j, int G, int head, int* out);
 

@@ -233,6 +233,21 @@ void tile_range_on_host(int ntiles, int gx, int i, int* out)
     tile_range(ntiles, gx, (uint32_t)(0x100000000ull / (uint64_t)gx + 1), i, out, out + 1);
 }
 
+// One line's counting over the launches of a call, with the very words that the kernels form:
+// workgroup i of epoch e runs on XCD xcd[e * n + i]; ok[e] = how many of the n take the exchange
+// to be whole and on their own XCD.
+void exchange_on_host(const int* xcd, int epochs, int n, int* ok)
+{
+    uint32_t line[2] = {0, 0};
+    for (int e = 0; e < epochs; ++e, xcd += n) {
+        uint32_t* const word = epoch_word(&line[0], (uint32_t)e);
+        for (int i = 0; i < n; ++i) *word += arrival_of((uint32_t)xcd[i]);
+        *epoch_word(&line[0], (uint32_t)e + 1) = 0;
+        ok[e] = 0;
+        for (int i = 0; i < n; ++i) ok[e] += (*word & 0xffffu) == (uint32_t)n && all_from(*word, (uint32_t)xcd[i], (uint32_t)n);
+    }
+}
+
 // ---- weight packing ------------------------------------------------------------
 // One thread per 16-byte piece of the packed image.  Packed row p of the matrix maps
 // to a source row through the permutation of its kind:

@@ -540,8 +540,10 @@ __global__ __launch_bounds__((LinShape<MT, R>::THREADS)) void k_linear_parts(con
     __syncthreads();
     uint32_t* const cnt = a->sync + a->lin_cnt + slot0 * kCntStride;
     if (tid == 0) {
-        arrive(cnt);
-        *s_wait_ok = bounded_wait(a->sync, cnt, (uint32_t)S * (a->lin_epoch + 1), 1000u + a->lin_epi);
+        uint32_t* const word = epoch_word(cnt, a->lin_epoch);
+        arrive(word);
+        if (part == 0) clear_next(cnt, a->lin_epoch);
+        *s_wait_ok = bounded_wait(a->sync, word, (uint32_t)S, (uint32_t)S, 1000u + a->lin_epi);
     }
     __syncthreads();
     if (!*s_wait_ok) return;                 // the other parts never arrived: nothing sensible to write

@@ -104,31 +104,45 @@ __device__ __forceinline__ uint32_t poll(uint32_t* p)
 }
 
 // The workgroups that exchange something count themselves in on a line: arrivals in the low
-// half of the word, the sum of the arrivals' XCD numbers in the high half.  Which XCD a
+// half of a word, the sum of the arrivals' XCD numbers in the high half.  Which XCD a
 // dispatch begins with depends on the hardware queue (it goes round from there: workgroup i
-// runs on XCD (i + offset) % 8), so nothing is assumed about it; what the exchange relies on is
-// that the workgroups of one item share an XCD, and each of them sees that from the sum.
+// runs on XCD (i + offset) % 8) and may change from one launch of a call to the next, so nothing
+// is assumed about it; what the exchange relies on is that the workgroups of one item share an XCD
+// within a launch, and each of them sees that from the sum.  A line is used once per layer: two of
+// its words take turns, and one workgroup of the launch that uses the one clears the other, which
+// no launch but the next looks at (the set-up clears both).
+__host__ __device__ constexpr uint32_t arrival_of(uint32_t xcd) { return 1u + (xcd << 16); }
+__host__ __device__ constexpr bool all_from(uint32_t word, uint32_t xcd, uint32_t n) { return (word >> 16) == xcd * n; }
+template <class Line>
+__host__ __device__ __forceinline__ Line epoch_word(Line line, uint32_t epoch) { return line + (epoch & 1); }
+static_assert(kRangeWgs / 8 * 7 < 0x10000, "at most an XCD's workgroups are summed up");
+
 __device__ __forceinline__ uint32_t my_xcd() { return __builtin_amdgcn_s_getreg(20 | (31 << 11)) & 15u; }   // HW_REG_XCC_ID
 __device__ __forceinline__ uint32_t arrive(uint32_t* p)      // returns the word with this arrival in it
 {
-    const uint32_t mine = 1u + (my_xcd() << 16);
+    const uint32_t mine = arrival_of(my_xcd());
     return atomicAdd(p, mine) + mine;
 }
-static_assert(kMaxLayers * 64 * 7 < 0x10000, "64 parts at most, counted once per layer");
-
-// Did all the arrivals counted in `word` come from this workgroup's XCD?  If not, status 3.
-__device__ __forceinline__ bool same_xcd(uint32_t* sync, uint32_t word)
+// by one workgroup of the line's item, in the launch of `epoch`
+__device__ __forceinline__ void clear_next(uint32_t* line, uint32_t epoch)
 {
-    if ((word >> 16) == my_xcd() * (word & 0xffffu)) return true;
+    __hip_atomic_store(epoch_word(line, epoch + 1), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Did all n arrivals summed up in `word` come from this workgroup's XCD?  If not, status 3.
+__device__ __forceinline__ bool same_xcd(uint32_t* sync, uint32_t word, uint32_t n)
+{
+    if (all_from(word, my_xcd(), n)) return true;
     atomicCAS(sync + kSyncStatus, 0u, 3u);
     return false;
 }
 
-// Waits until the line p has counted `target` arrivals.  Gives up (and raises the status word
-// to `code`) after kWaitTicks of wall-clock time, or as soon as another workgroup has given up,
-// so that a launch that is not fully resident ends with an error instead of hanging.  One
-// thread calls.  Returns false if what was waited for is not there, or not visible here.
-__device__ __forceinline__ bool bounded_wait(uint32_t* sync, uint32_t* p, uint32_t target,
+// Waits until the low half of p has come to `target`, then looks at the XCDs of the n arrivals
+// summed up in the high half.  Gives up (and raises the status word to `code`) after kWaitTicks of
+// wall-clock time, or as soon as another workgroup has given up, so that a launch that is not fully
+// resident ends with an error instead of hanging.  One thread calls.  Returns false if what was
+// waited for is not there, or not visible here.
+__device__ __forceinline__ bool bounded_wait(uint32_t* sync, uint32_t* p, uint32_t target, uint32_t n,
                                              uint32_t code)
 {
     uint32_t v = poll(p);
@@ -142,7 +156,7 @@ __device__ __forceinline__ bool bounded_wait(uint32_t* sync, uint32_t* p, uint32
             __builtin_amdgcn_s_sleep(8);
         }
     }
-    return same_xcd(sync, v);
+    return same_xcd(sync, v, n);
 }
 
 // The status word is cleared for the calls that follow; what it held is kept in the sticky

@@ -38,8 +38,8 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
     //      covers loads too, so it comes before the attention requests anything) ...
     //      Thirty-two workgroups polling one counter line with read-modify-writes queue up
     //      behind each other (a poll then takes microseconds), so the counter is only
-    //      incremented: the workgroup that arrives last passes its word on to the others, each on a line of
-    //      its own.
+    //      incremented: the workgroup that arrives last passes the sum of the XCD numbers on to
+    //      the others, each on a line of its own, with the number of the layer in place of the count.
     uint32_t* const cnt = a.sync + kCntXcd + xcd * kCntStride;
     uint32_t* const go = a.sync + kCntGo;
     const uint32_t round = a.att_epoch + 1;
@@ -48,11 +48,14 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
     bool last = false;
     uint32_t word = 0;
     if (threadIdx.x == 0) {
-        word = arrive(cnt);
-        last = (word & 0xffffu) == (uint32_t)Gx * round;
-        if (last)
+        word = arrive(epoch_word(cnt, a.att_epoch));
+        last = (word & 0xffffu) == (uint32_t)Gx;
+        if (last) {
             for (int w = 0; w < Gx; ++w)
-                __hip_atomic_store(go + (xcd * Gx + w) * kCntStride, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(go + (xcd * Gx + w) * kCntStride, (word & 0xffff0000u) | round, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            clear_next(cnt, a.att_epoch);
+        }
     }
     // ... and waits for the others at the attention's gate, after it has set up its indices
     //     and requested the cache rows of earlier steps that it starts with.  (Counting in
@@ -61,7 +64,8 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
     auto gate = [&]() -> bool {
         int* s_ok = &reinterpret_cast<typename AttnOf<MT, D>::Lds*>(cx.lds)->wait_ok;
         if (threadIdx.x == 0)
-            *s_ok = last ? same_xcd(a.sync, word) : bounded_wait(a.sync, go + cx.j * kCntStride, (uint32_t)Gx * round, 3000u);
+            *s_ok = last ? same_xcd(a.sync, word, (uint32_t)Gx)
+                        : bounded_wait(a.sync, go + cx.j * kCntStride, round, (uint32_t)Gx, 3000u);
         __syncthreads();
         if (!*s_ok) return false;
         // Nothing of q16 or of the tree's cache rows should be in this compute unit's L1 (it

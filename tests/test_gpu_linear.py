@@ -81,3 +81,30 @@ def test_linear_in_place(B, M, N, K):
     assert B.ghd_step_status(ws) == 0
     err = (y.double() - ref).abs()
     assert bool((err <= 2.0 ** -11 * ref.abs() + 2e-6 * ref.std() + 2.0 ** -25).all()), float(err.max())
+
+
+@pytest.mark.parametrize("M", [16, 40])
+def test_every_stream_gives_the_same_stack(B, M):
+    """The same over three layers that share a QKV + attention launch each: every counter line is
+    used again and again, the XCDs meet between the two halves of the launch, and a head's cached
+    rows are split over several workgroups on both ways through the attention."""
+    from paper_2505_23219_amd import model, workloads as wl
+    say("streams, stack", M)
+    s = wl.ModelShape("streams", H=4096, nh=32, d=128, F=1376, V=500, L=3)
+    kv = 700
+    layer = model.upload_layer(wl.layer_weights(s, 3, 0), s.d)
+    caches = [model.upload_cache(*wl.kv_cache(s, 768, kv, 3, l)) for l in range(s.L)]
+    stack = model.build_stack(s, 768, [layer] * s.L, caches, model.upload_head(wl.head_weights(s, 3)))
+    x16 = wl.activations(M, s.H, 3).cuda()
+    parent = torch.from_numpy(wl.tree_random(M, 5, 3)).cuda()
+    torch.cuda.synchronize()
+    want = None
+    for i in range(8):
+        with torch.cuda.stream(torch.cuda.Stream() if i else torch.cuda.default_stream()):
+            torch.zeros(64 * i + 1, device="cuda").add_(1)
+            ws = B.workspace(B.ghd_workspace_bytes(stack.cfg, M, kv))
+            logits = B.ghd_verify_stack(stack, x16, parent, kv, ws=ws)
+            assert B.ghd_step_status(ws) == 0, i
+            torch.cuda.synchronize()
+            want = logits if want is None else want
+            assert torch.equal(logits, want) and bool(torch.isfinite(logits).all()), i

@@ -241,3 +241,22 @@ def test_attention_parts_are_not_made_too_small(nh, ntile, tmin):
             assert (j, n, t0) == (first + me, np_, pos) and t1 > t0
             pos = t1
         assert pos == ntile
+
+
+@pytest.mark.parametrize("n", [2, 7, 32])
+def test_exchange_counts_each_launch_by_itself(n):
+    """The workgroups that exchange partial results count themselves in with their XCD numbers, on a
+    line that every layer of a call uses again.  Whichever XCD each launch begins with, workgroups that
+    share one pass, over as many layers as a model may have; one workgroup elsewhere fails that
+    launch for the others, and only that."""
+    lib = B.lib()
+    epochs = 48
+    start = [(5 * e * e + 3 * e) % 8 for e in range(epochs)]          # another XCD from launch to launch
+    xcd = [s for s in start for _ in range(n)]
+    ok = (C.c_int * epochs)()
+    lib.ghd_debug_exchange((C.c_int * len(xcd))(*xcd), epochs, n, ok)
+    assert list(ok) == [n] * epochs
+    stray = 20
+    xcd[stray * n] = (xcd[stray * n] + 1) % 8
+    lib.ghd_debug_exchange((C.c_int * len(xcd))(*xcd), epochs, n, ok)
+    assert ok[stray] < n and [o for e, o in enumerate(ok) if e != stray] == [n] * (epochs - 1)
