@@ -385,8 +385,8 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const h
             if (tid == 0) {
                 uint32_t* const word = epoch_word(cnt, epoch);
                 arrive(word);
-                if (me == 0) clear_next(cnt, epoch);
                 if (r0 < r1) sm.wait_ok = bounded_wait(sync, word, (uint32_t)np, (uint32_t)np, 2000u);
+                if (me == 0) clear_next(cnt, epoch);
             }
             if (r0 < r1) {
                 __syncthreads();
@@ -807,8 +807,8 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const h
             uint32_t* const cnt = sync + kCntAttn + head * kCntStride;
             uint32_t* const word = epoch_word(cnt, epoch);
             arrive(word);
-            if (me == 0) clear_next(cnt, epoch);
             sm.wait_ok = bounded_wait(sync, word, (uint32_t)np, (uint32_t)np, 2000u);
+            if (me == 0) clear_next(cnt, epoch);
         }
         __syncthreads();
         if (!sm.wait_ok) return false;    // the other parts never arrived: nothing sensible to write

@@ -542,8 +542,8 @@ __global__ __launch_bounds__((LinShape<MT, R>::THREADS)) void k_linear_parts(con
     if (tid == 0) {
         uint32_t* const word = epoch_word(cnt, a->lin_epoch);
         arrive(word);
-        if (part == 0) clear_next(cnt, a->lin_epoch);
         *s_wait_ok = bounded_wait(a->sync, word, (uint32_t)S, (uint32_t)S, 1000u + a->lin_epi);
+        if (part == 0) clear_next(cnt, a->lin_epoch);
     }
     __syncthreads();
     if (!*s_wait_ok) return;                 // the other parts never arrived: nothing sensible to write
