@@ -310,7 +310,7 @@ ghd_status ghd_accept_greedy_static(const float *logits, const int32_t *tokens_d
  * kv_len + j, j = 0 .. len-1; the caller then counts kv_len + len committed rows.
  * res_dev is the device result of ghd_accept_greedy for the same tree (len =
  * res_dev[0], path = res_dev[2..]), read on the device: no host round trip
- * between acceptance and commit.  Entries are clamped to the tree, so a corrupt
+ * between acceptance and commit; words after the path are not read.  Entries are clamped to the tree, so a corrupt
  * result cannot reach other rows.  kv_host: host array of cfg->L caches (device
  * pointers).  One launch. */
 ghd_status ghd_commit_path(const ghd_model_cfg *cfg, const ghd_kv *kv_host, const int32_t *res_dev,

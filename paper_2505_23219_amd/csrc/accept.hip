@@ -213,8 +213,9 @@ __global__ __launch_bounds__(256) void k_commit_path(const CommitArgs a)
     const int tid = threadIdx.x, layer = blockIdx.x / a.nh, head = blockIdx.x % a.nh;
     const int d = a.d, len = min(max(a.res[0], 0), a.M);
     if (tid == 0) s_moved = a.M;
+    // (the path's entries only: a result that ends with them is as good as one of 2 + M words)
     int at = 0;
-    if (tid < a.M) at = min(max(a.res[2 + tid], 0), a.M - 1);      // (M <= 128 entries follow the first two)
+    if (tid < len) at = min(max(a.res[2 + tid], 0), a.M - 1);
     __syncthreads();
     if (tid < len) {
         s_path[tid] = at;

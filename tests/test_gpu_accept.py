@@ -66,3 +66,24 @@ def test_commit_moves_exactly_the_path(B, d, path):
     res = torch.tensor([len(path), 4] + path + [0] * (M - len(path)), dtype=torch.int32).cuda()
     B.ghd_commit_path(stack, res, M, kv)
     assert torch.equal(kd.cpu(), want_k) and torch.equal(vd.cpu(), want_v)
+
+
+@pytest.mark.parametrize("path", [[0], [0, 3, 4, 9]])
+def test_commit_reads_no_more_of_the_result_than_the_path(B, path):
+    """A result that ends with its path, in an allocation of just that size."""
+    from paper_2505_23219_amd.workloads import ModelShape
+    say("commit, short result", len(path))
+    L, nh, d, M, kv, cap = 2, 2, 64, 128, 5, 136
+    k, v = torch.randn(L, nh, cap, d).half(), torch.randn(L, nh, d, cap).half()
+    want_k, want_v = k.clone(), v.clone()
+    at = torch.tensor(path) + kv
+    want_k[:, :, kv:kv + len(path)] = k[:, :, at]
+    want_v[:, :, :, kv:kv + len(path)] = v[:, :, :, at]
+    kd, vd = k.cuda(), v.cuda()
+    g = torch.ones(8, dtype=torch.float16, device="cuda")
+    none = {n: g for n in ("g_attn", "Wqkv", "Wo", "g_ffn", "Wgu", "Wdown")}
+    shape = ModelShape("c", H=nh * d, nh=nh, d=d, F=8, V=16, L=L)
+    stack = B.Stack(B.make_cfg(shape, cap), [none] * L, [(kd[l], vd[l]) for l in range(L)], {"g_final": g, "Wlm": g})
+    res = torch.tensor([len(path), 4] + path, dtype=torch.int32).cuda()
+    B.ghd_commit_path(stack, res, M, kv)
+    assert torch.equal(kd.cpu(), want_k) and torch.equal(vd.cpu(), want_v)
