@@ -9,7 +9,7 @@
 // from the L2), and keeps one fp32 accumulator fragment per (row tile, 16 rows of x).  There
 // is no LDS staging and no barrier inside the stream: the wavefronts run independently until
 // their k ranges end.  Then the partial fragments of every tile are added up through LDS,
-// in wavefront order, and the reducing wavefront runs the layer's element-wise epilogue
+// in pairs of pairs of wavefronts, and the reducing wavefront runs the layer's element-wise epilogue
 // (residual add + sums of squares for the next RMSNorm, rotary embedding + KV append, SwiGLU).
 // Where the accumulators would leave one of eight wavefronts no registers for a load ring
 // (above 64 rows of x), the workgroup has four wavefronts of twice the registers.
@@ -45,6 +45,7 @@ constexpr int kHeadBlk = 0;      // bits 0-3: log2 of the tiles per storage bloc
 constexpr int kHeadMtp = 4;      // bits 4-7: row tiles of the packed activation layout (Mpad / 16)
 constexpr int kHeadM = 8;        // bits 8-15: rows of x
 constexpr int kHeadSolo = 16;    // bit 16: a call of its own, without a set-up kernel
+constexpr int kHeadLong = 17;    // bit 17: chains of sums are cut short (see folded)
 constexpr int kTailAt = 48;      // byte offset of FusedArgs in the kernel arguments
 static_assert(sizeof(LinHead) == kTailAt && alignof(FusedArgs) == 8, "kernel argument layout");
 
@@ -71,9 +72,9 @@ __host__ __device__ constexpr int waves_of(int MT, int R) { return MT > 4 && R *
 // k-steps in flight per wavefront: limited by registers (accumulators + the ring) and by
 // what the stream needs (a few KiB per wavefront: loads return in issue order, and a long
 // queue only delays the x fragments behind it)
-__host__ __device__ constexpr int pd_of(int MT, int R)
+__host__ __device__ constexpr int pd_of(int MT, int R, int NW)
 {
-    const bool four = waves_of(MT, R) == 4;
+    const bool four = NW == 4;
     const int regs = (four ? 304 : 200) - R * MT * 4;       // beside the accumulators
     int by_regs = (four || regs < GHD_RING_REGS ? regs : GHD_RING_REGS) / ((R + MT) * 4);
     int by_bytes = ((four ? 8 : GHD_RING_KIB) + R - 1) / R;
@@ -81,16 +82,26 @@ __host__ __device__ constexpr int pd_of(int MT, int R)
     return pd < 1 ? 1 : (pd > 8 ? 8 : pd);
 }
 
-// Accumulator sets that a wavefront's k-steps go to in turn, added up when its stream ends: the
-// rounding error of a sum grows with the length of its chain, and narrow matrices that are dealt
-// out in whole tiles (R <= 2) have long ones for what parts would do in short ones ([5003, 4104],
-// 33 rows: 1.6e-7 of the result in one chain per wavefront, 1.1e-7 in parts).  The registers are
-// there; the additions cost 0.1 to 0.5 us a launch, so the other cases do without.
-__host__ __device__ constexpr int acc_sets(int MT, int R)
+// How sums are kept short.  The rounding error of a chain of MFMAs grows with its length (measured:
+// squared relative error 4.4e-15 + 1.3e-15 per k-step of a wavefront's chain), so a cut whose
+// chains come out long must not leave them in one piece (see long_chains).  Two ways:
+//   FOLDED: a second set of accumulators; after every two to four k-steps the first is added to
+//   it and begins anew (an addition rounds a quarter as badly as an MFMA);
+//   STRETCHES, where there are no registers for that: a wavefront's range is taken in halves, and the
+//   sums of the first are set aside, in the LDS that the reduction uses later and in what registers
+//   are left; the last fragments of the largest groups are added up step by step instead.
+// [2048, 13824] at 1 row: 2.8e-7 of the result in one chain, 1.2e-7 folded (12.6 and 12.9 us);
+// [22016, 4096] at 128 rows, four wavefronts: 2.1e-7 in one chain, 1.5e-7 in halves (47.4 and 49.3 us).
+constexpr int kFoldSteps = 2;
+__host__ __device__ constexpr bool folded(int MT, int R) { return R * MT <= (R <= 3 ? 18 : 16); }
+// Stretches that a range is taken in: two halves, or three where the chains of an even deal are less
+// than half as long.  (Of more than three whole tiles on eight wavefronts only wide matrices are dealt
+// out, whose chains are never long.)
+__host__ __device__ constexpr int stretches_whole(int MT, int R)
 {
-    const int want = R > 2 || R * MT < 2 ? 1 : R * MT <= 4 ? 4 : R * MT <= 12 ? 2 : 1, pd = pd_of(MT, R);
-    return want < pd ? want : pd;
+    return folded(MT, R) ? 1 : waves_of(MT, R) == 4 ? 2 : R <= 3 ? 3 : 1;
 }
+__host__ __device__ constexpr int stretches_parts(int MT, int R) { return folded(MT, R) ? 1 : 2; }
 
 // Of eight wavefronts, w and w + 4 share a SIMD, and the first of the two gets its data sooner
 // throughout the stream: with equal ranges wavefronts 0-3 end 2.5-6 us before 4-7, which then
@@ -229,14 +240,22 @@ __device__ __forceinline__ void epilogue(ArgPtr a, floatx4 v, int m, int n0, int
     }
 }
 
-template <int MT, int R>
+template <int MT, int R, int NW>
 struct LinShape {
-    static constexpr int NW = waves_of(MT, R), THREADS = NW * 64;
+    static constexpr int THREADS = NW * 64;
     static constexpr int NF = R * MT;                        // accumulator fragments of a wavefront
     static constexpr int CAP = 128 / NW;                     // ... reduced per round through LDS, at most
     static constexpr int ROUNDS = (NF + CAP - 1) / CAP;
     static constexpr int FR = (NF + ROUNDS - 1) / ROUNDS;    // ... and per round
-    static constexpr size_t lds_bytes = (size_t)NW * FR * 1024 + (128 + 1024 + 4) * sizeof(float);
+    static constexpr size_t small_bytes = (128 + 1024 + 4) * sizeof(float);
+    // HALVED: fragments of the first half that a wavefront keeps in the LDS; the rest stay in registers
+    static constexpr int ROOM = (160 * 1024 - (int)small_bytes) / (NW * 1024);
+    static constexpr int ASIDE = NF < ROOM ? NF : ROOM;
+    // LDS of a launch, and where the small arrays begin
+    template <bool HALVED>
+    static constexpr size_t red_bytes = (size_t)NW * (HALVED && ASIDE > FR ? ASIDE : FR) * 1024;
+    template <bool HALVED>
+    static constexpr size_t lds_bytes = red_bytes<HALVED> + small_bytes;
 };
 
 // One workgroup's share: the tiles first .. first + count - 1 (count <= R; the other slots
@@ -246,20 +265,20 @@ struct LinShape {
 // stream's first loads and its first wait.
 //
 // ROWS: x is row-major and read as it lies (16 rows x 64 bytes per load), which saves a
-// separate packing launch; columns from K on are not read.
-template <int MT, int R, bool ROWS, class Early, class Finish>
+// separate packing launch; columns from K on are not read.  STRETCHES: see folded().
+template <int MT, int R, int NW, bool ROWS, int STRETCHES, class Early, class Finish>
 __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int first, int count, int k0, int k1,
                                            Early early, Finish finish)
 {
-    using S = LinShape<MT, R>;
-    constexpr int NW = S::NW, NF = S::NF, FR = S::FR;
-    constexpr int PD = pd_of(MT, R);
+    using S = LinShape<MT, R, NW>;
+    constexpr int NF = S::NF, FR = S::FR;
+    constexpr int PD = pd_of(MT, R, NW);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, g4 = lane >> 4;
     const uint32_t lane16 = lane * 16;                     // this lane's 16 bytes of a 1 KiB block
     floatx4* red = (floatx4*)lds;                          // [NW][FR][64]
-    float* s_rinv = (float*)(lds + NW * FR * 1024);        // 128 floats
+    float* s_rinv = (float*)(lds + S::template red_bytes<(STRETCHES > 1)>);    // 128 floats
     float* s_tmp = s_rinv + 128;                           // 1024 floats
     const half8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
 
@@ -293,15 +312,40 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
     }
 
     half8 wr[PD][R], xr[PD][MT];
-    constexpr int NA = acc_sets(MT, R);
-    floatx4 accs[NA][R][MT];
+    constexpr bool FOLDED = folded(MT, R), HALVED = STRETCHES > 1;
+    static_assert(!(FOLDED && HALVED), "one way or the other");
+    // What came before: FOLDED: the sums of earlier k-steps; HALVED: those of the first half that
+    // stay in registers, as many as there are registers for.  The last NSTEP fragments are not set
+    // aside but added up step by step (all of them that way: 78 us for [32000, 4096] at 128 rows, 66).
+    constexpr int NSTEP = HALVED && NF - S::ASIDE > 13 ? NF - S::ASIDE - (NF > 60 ? 4 : 12) : 0;
+    constexpr int NB = FOLDED ? NF : HALVED ? NF - S::ASIDE - NSTEP : 0;
+    floatx4 acc[R][MT], before[NB > 0 ? NB : 1];
+    const floatx4 zero4 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < NA; ++i)
+    for (int f = 0; f < NF; ++f) acc[f / MT][f % MT] = zero4;
 #pragma unroll
-        for (int t = 0; t < R; ++t)
+    for (int f = 0; f < NB; ++f) before[f] = zero4;
+    const bool long_chains = (h.flags >> kHeadLong) & 1;
+    auto fold = [&]() {
+        if (!long_chains) return;              // (uniform)
 #pragma unroll
-            for (int b = 0; b < MT; ++b) accs[i][t][b] = (floatx4){0.f, 0.f, 0.f, 0.f};
-    auto& acc = accs[0];
+        for (int f = 0; f < NB; ++f) {
+            before[f] += acc[f / MT][f % MT];
+            acc[f / MT][f % MT] = zero4;
+        }
+    };
+    floatx4* const aside = red + (size_t)wave * S::ASIDE * 64 + lane;      // HALVED; this lane's alone
+    auto set_aside = [&](bool again) {
+#pragma unroll
+        for (int f = 0; f < NF - NSTEP; ++f) {
+            const bool more = STRETCHES > 2 && again;
+            if (f < S::ASIDE) aside[f * 64] = more ? aside[f * 64] + acc[f / MT][f % MT] : acc[f / MT][f % MT];
+            else if (STRETCHES > 2) before[f - S::ASIDE] += acc[f / MT][f % MT];
+            else before[f - S::ASIDE] = acc[f / MT][f % MT];
+            acc[f / MT][f % MT] = zero4;
+            if (f % 8 == 7) pin_order();       // (few registers at a time)
+        }
+    };
 
     auto load = [&](auto slot, int s) {
         constexpr int p = decltype(slot)::value;
@@ -334,10 +378,14 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
             for (int b = 0; b < MT; ++b) xf[b] = xr[p][b];
         }
 #pragma unroll
-        for (int t = 0; t < R; ++t)
+        for (int tt = 0; tt < R; ++tt)
 #pragma unroll
-            for (int b = 0; b < MT; ++b)
-                accs[p % NA][t][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wr[p][t], xf[b], accs[p % NA][t][b], 0, 0, 0);
+            for (int bb = 0; bb < MT; ++bb) {
+                // (those that are added up step by step first: the additions wait for the products)
+                const int t = NSTEP ? R - 1 - tt : tt, b = NSTEP ? MT - 1 - bb : bb;
+                if (t * MT + b >= NF - NSTEP) acc[t][b] += __builtin_amdgcn_mfma_f32_16x16x32_f16(wr[p][t], xf[b], zero4, 0, 0, 0);
+                else acc[t][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wr[p][t], xf[b], acc[t][b], 0, 0, 0);
+            }
     };
     auto prologue = [&](auto self, auto slot) {
         constexpr int p = decltype(slot)::value;
@@ -364,6 +412,7 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
             auto step = [&]() {
                 compute(std::true_type{}, std::integral_constant<int, p % PD>{}, s + p);
                 pin_order();
+                if constexpr (FOLDED && p % kFoldSteps == kFoldSteps - 1) fold();
                 if constexpr (p < PD - 1) {
                     if (s + p + PD < we) load(std::integral_constant<int, p % PD>{}, s + p + PD);
                     pin_order();
@@ -415,18 +464,62 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
 
     if (ws < we) {
         int s = ws;
-        for (; s + 2 * PD <= we; s += PD) ring(ring, std::integral_constant<int, 0>{}, s);
+        if constexpr (FOLDED) {
+            constexpr int ROUNDS = (kFoldSteps + PD - 1) / PD;
+            for (; s + (ROUNDS + 1) * PD <= we; s += ROUNDS * PD) {
+#pragma unroll
+                for (int r = 0; r < ROUNDS; ++r) ring(ring, std::integral_constant<int, 0>{}, s + r * PD);
+                fold();
+            }
+            if constexpr (ROUNDS > 1) {
+                for (; s + 2 * PD <= we; s += PD) ring(ring, std::integral_constant<int, 0>{}, s);
+                fold();
+            }
+        } else {
+            auto stream = [&](int end) {
+                for (; s + 2 * PD <= we && s < end; s += PD) ring(ring, std::integral_constant<int, 0>{}, s);
+            };
+            if constexpr (STRETCHES == 2 && NW == 8) {
+                // (written out twice, what is set aside needs no registers in the first stretch)
+                if (long_chains) {
+                    stream(ws + (we - ws) / 2);
+                    set_aside(false);
+                }
+                stream(we);
+            } else {
+                // (once: the code is fetched while it runs)
+                const int stretches = long_chains ? STRETCHES : 1;
+                for (int i = 1;; ++i) {
+                    stream(i == stretches ? we : ws + (we - ws) * i / STRETCHES);
+                    if (i == stretches) break;
+                    set_aside(i > 1);
+                }
+            }
+        }
         drain(drain, std::integral_constant<int, 0>{}, s);
     }
+    if constexpr (FOLDED) {
+        if (long_chains) {
 #pragma unroll
-    for (int i = 1; i < NA; ++i)
+            for (int f = 0; f < NB; ++f) acc[f / MT][f % MT] += before[f];
+        }
+    }
+    if constexpr (HALVED) {
+        if (long_chains) {
+            if (ws < we) {
 #pragma unroll
-        for (int t = 0; t < R; ++t)
-#pragma unroll
-            for (int b = 0; b < MT; ++b) acc[t][b] += accs[i][t][b];
+                for (int f = 0; f < NF - NSTEP; ++f) {
+                    if (f < S::ASIDE) acc[f / MT][f % MT] += aside[f * 64];
+                    else acc[f / MT][f % MT] += before[f - S::ASIDE];
+                    if (f % 8 == 7) pin_order();
+                }
+            }
+            __syncthreads();       // (the reduction lays the same LDS out in another way)
+        }
+    }
 
     // ---- the wavefronts' k slices are added up through LDS, FR fragments of every wavefront
-    //      per round, in wavefront order; wavefront w has sums w, w + NW, ... of the round
+    //      per round, in a fixed order; wavefront w has sums w, w + NW, ... of the round
     if (rscale) {
         if (lane < RQ) *(floatx4*)(s_tmp + (wave * RQ + lane) * 4) = rs4;
         __syncthreads();
@@ -445,9 +538,15 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
             if (r0 + ff < NF) red[(wave * FR + ff) * 64 + lane] = acc[(r0 + ff) / MT][(r0 + ff) % MT];
         __syncthreads();
         for (int ff = wave; ff < FR && r0 + ff < NF; ff += NW) {
-            floatx4 v = red[ff * 64 + lane];
+            // (pairs of pairs: half the roundings of one sum after the other)
+            floatx4 part[NW];
 #pragma unroll
-            for (int w = 1; w < NW; ++w) v += red[(w * FR + ff) * 64 + lane];
+            for (int w = 0; w < NW; ++w) part[w] = red[(w * FR + ff) * 64 + lane];
+#pragma unroll
+            for (int d = 1; d < NW; d *= 2)
+#pragma unroll
+                for (int w = 0; w < NW; w += 2 * d) part[w] += part[w + d];
+            const floatx4 v = part[0];
             const int f = r0 + ff, t = f / MT, b = f % MT;
             if (t >= count) continue;
             finish(a, f, v, b * 16 + c, (first + t) * 16 + g4 * 4, s_rinv);
@@ -474,7 +573,7 @@ __host__ __device__ __forceinline__ void tile_range(int ntiles, int gx, uint32_t
 
 // ---- whole tiles ----------------------------------------------------------------------
 template <int MT, int R, bool ROWS>
-__global__ __launch_bounds__((LinShape<MT, R>::THREADS)) void k_linear(const half8* W, const half_t* x, uint64_t aux, int nks, int K,
+__global__ __launch_bounds__(waves_of(MT, R) * 64) void k_linear(const half8* W, const half_t* x, uint64_t aux, int nks, int K,
                                                     int ntiles, int cut, uint32_t magic, uint32_t flags,
                                                     const FusedArgs)
 {
@@ -493,7 +592,7 @@ __global__ __launch_bounds__((LinShape<MT, R>::THREADS)) void k_linear(const hal
         return;
     }
     const int lane = threadIdx.x & 63;
-    gemm_group<MT, R, ROWS>(
+    gemm_group<MT, R, waves_of(MT, R), ROWS, stretches_whole(MT, R)>(
         h, lds, c0, c1 - c0, 0, nks, solo,
         [&](ArgPtr a, int, floatx4 v, int m, int n0, const float* s_rinv) {
             epilogue(a, v, m, n0, lane, s_rinv);
@@ -504,7 +603,7 @@ __global__ __launch_bounds__((LinShape<MT, R>::THREADS)) void k_linear(const hal
 // Workgroups i with the same i % 8 run on one XCD (checked, see arrive); of those, S consecutive
 // ones are the parts of one block of R tiles, and the blocks are dealt to the XCDs in turn.
 template <int MT, int R>
-__global__ __launch_bounds__((LinShape<MT, R>::THREADS)) void k_linear_parts(const half8* W, const half_t* x, uint64_t aux, int nks, int K,
+__global__ __launch_bounds__(512) void k_linear_parts(const half8* W, const half_t* x, uint64_t aux, int nks, int K,
                                                       int ntiles, int cut, uint32_t magic, uint32_t flags,
                                                       const FusedArgs)
 {
@@ -523,13 +622,13 @@ __global__ __launch_bounds__((LinShape<MT, R>::THREADS)) void k_linear_parts(con
     // partial sums: one slot of NF fragments per workgroup; the block's parts are eight
     // workgroups apart
     const int slot0 = bx * S * 8 + xcd;
-    gemm_group<MT, R, false>(
+    gemm_group<MT, R, 8, false, stretches_parts(MT, R)>(
         h, lds, first, count, k0, k1, []() {},
         [&](ArgPtr a, int f, floatx4 v, int, int, const float*) {
             *(GLOBAL floatx4*)(gp(a->part) + ((size_t)(slot0 + part * 8) * NF + f) * 256 + lane * 4) = v;
         });
     const ArgPtr a = late_args();
-    const float* s_rinv = (const float*)(lds + LinShape<MT, R>::NW * LinShape<MT, R>::FR * 1024);
+    const float* s_rinv = (const float*)(lds + LinShape<MT, R, 8>::template red_bytes<(stretches_parts(MT, R) > 1)>);
     int* s_wait_ok = (int*)(s_rinv + 128 + 1024);
     const int c = lane & 15, g4 = lane >> 4;
     const auto position = [&](int f, int* m, int* n0) {
@@ -547,7 +646,7 @@ __global__ __launch_bounds__((LinShape<MT, R>::THREADS)) void k_linear_parts(con
     }
     __syncthreads();
     if (!*s_wait_ok) return;                 // the other parts never arrived: nothing sensible to write
-    for (int f = f0 + wave; f < f1; f += LinShape<MT, R>::NW) {
+    for (int f = f0 + wave; f < f1; f += 8) {
         // the parts in index order (fixed order: the result does not depend on timing), eight
         // loads in flight at a time
         const auto src = gp((const float*)a->part) + ((size_t)slot0 * NF + f) * 256 + lane * 4;
@@ -586,13 +685,31 @@ static inline LinHead head_of(const FusedArgs& a, const LinCut& cut)
     return h;
 }
 
+// Are a cut's chains (k-steps of a wavefront) longer than an even deal over all compute units, eight
+// wavefronts each, would make them: of whole tiles for wide matrices, of the k-steps of four-tile
+// blocks for narrow ones?  Pairwise sums of the wavefronts make up for half a k-step, with four of
+// them for a whole one.
+static inline bool long_chains(const WLayout& lay, const LinCut& cut, int waves)
+{
+    const double chain = (double)ceil_div(lay.nks, cut.parts) / waves;
+    double even = lay.nks / 8.0;
+    if (lay.rb != 1) {
+        const double share = (double)lay.nitems / kRangeWgs;
+        even *= share;
+        // (a run of k-steps that goes over a block's end is two chains)
+        if (kRangeWgs % lay.nitems != 0) even *= 1.0 - share / 3.0;
+    }
+    return chain >= 2.0 && chain > even + (waves == 8 ? 0.5 : 1.0);
+}
+
 template <class Kernel>
 static ghd_status launch_linear_kernel(Kernel kernel, const FusedArgs& a, const LinCut& cut, int threads, size_t lds,
                                        hipStream_t st)
 {
     ghd_status s = launch_resident_checked((const void*)kernel, threads, lds);
     if (s) return s;
-    const LinHead h = head_of(a, cut);
+    LinHead h = head_of(a, cut);
+    if (long_chains(w_layout(a.lin_N, a.lin_K), cut, threads / 64)) h.flags |= 1u << kHeadLong;
     hipLaunchKernelGGL(kernel, dim3(cut.grid), dim3(threads), lds, st, h.W, h.x, h.aux, h.nks, h.K, h.ntiles, h.cut,
                        h.magic, h.flags, a);
     return check_launch();
@@ -602,17 +719,17 @@ static ghd_status launch_linear_kernel(Kernel kernel, const FusedArgs& a, const 
 template <int MT, int R>
 ghd_status launch_linear_r(const FusedArgs& a, const LinCut& cut, hipStream_t st)
 {
-    using S = LinShape<MT, R>;
-    if (cut.whole) {
-        if (cut.tiles == R) {
-            if constexpr (MT <= kRowsMaxMT)
-                if (cut.rows) return launch_linear_kernel(k_linear<MT, R, true>, a, cut, S::THREADS, S::lds_bytes, st);
-            if (cut.rows) return GHD_ERR_SHAPE;
-            return launch_linear_kernel(k_linear<MT, R, false>, a, cut, S::THREADS, S::lds_bytes, st);
-        }
-    } else if constexpr (R <= parts_max_tiles(MT)) {
-        if (cut.tiles == R) return launch_linear_kernel(k_linear_parts<MT, R>, a, cut, S::THREADS, S::lds_bytes, st);
+    if (cut.tiles == R && cut.whole) {
+        constexpr int threads = waves_of(MT, R) * 64;
+        constexpr size_t lds = LinShape<MT, R, waves_of(MT, R)>::template lds_bytes<(stretches_whole(MT, R) > 1)>;
+        if constexpr (MT <= kRowsMaxMT)
+            if (cut.rows) return launch_linear_kernel(k_linear<MT, R, true>, a, cut, threads, lds, st);
+        if (cut.rows) return GHD_ERR_SHAPE;
+        return launch_linear_kernel(k_linear<MT, R, false>, a, cut, threads, lds, st);
     }
+    if constexpr (R <= parts_max_tiles(MT))
+        if (cut.tiles == R)
+            return launch_linear_kernel(k_linear_parts<MT, R>, a, cut, 512, LinShape<MT, R, 8>::template lds_bytes<(stretches_parts(MT, R) > 1)>, st);
     if constexpr (R < 8) return launch_linear_r<MT, R + 1>(a, cut, st);
     return GHD_ERR_SHAPE;
 }

@@ -24,7 +24,7 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
     tile_range(ntiles, cut, magic, blockIdx.x, &c0, &c1);
     const int lane = threadIdx.x & 63, xcd = blockIdx.x & 7, Gx = cut;
     if (c0 < c1)
-        gemm_group<MT, R, false>(
+        gemm_group<MT, R, 8, false, stretches_whole(MT, R)>(
             h, lds, c0, c1 - c0, 0, nks, []() {},
             [&](ArgPtr la, int, floatx4 v, int m, int n0, const float* s_rinv) {
                 epilogue(la, v, m, n0, lane, s_rinv);
@@ -85,8 +85,8 @@ ghd_status launch_qkv_attn_r(const FusedArgs& a, const LinCut& cut, hipStream_t 
 {
     if (a.d != 128 || !cut.whole) return GHD_ERR_SHAPE;
     if (cut.tiles == R) {
-        static_assert(LinShape<MT, R>::THREADS == kFT, "the attention works with eight wavefronts");
-        constexpr size_t l1 = LinShape<MT, R>::lds_bytes, l2 = sizeof(typename AttnOf<MT, 128>::Lds);
+        static_assert(waves_of(MT, R) * 64 == kFT, "the attention works with eight wavefronts");
+        constexpr size_t l1 = LinShape<MT, R, 8>::template lds_bytes<(stretches_whole(MT, R) > 1)>, l2 = sizeof(typename AttnOf<MT, 128>::Lds);
         return launch_linear_kernel(k_qkv_attn<MT, R, 128>, a, cut, kFT, l1 > l2 ? l1 : l2, st);
     }
     if constexpr (R < (MT <= 4 ? 6 : 4)) return launch_qkv_attn_r<MT, R + 1>(a, cut, st);

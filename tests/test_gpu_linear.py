@@ -108,3 +108,28 @@ def test_every_stream_gives_the_same_stack(B, M):
             torch.cuda.synchronize()
             want = logits if want is None else want
             assert torch.equal(logits, want) and bool(torch.isfinite(logits).all()), i
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 2048, 13824), (8, 2048, 5888), (16, 2048, 5888), (33, 9000, 5888), (64, 9000, 4096),
+                                   (80, 22016, 11008), (96, 32000, 4096), (100, 9000, 11008), (128, 22016, 4096),
+                                   (128, 27648, 2560), (128, 32000, 4096), (128, 5003, 13824)])
+def test_linear_sums_are_not_left_in_long_chains(B, M, N, K):
+    """The relative error (2-norm) of the fp32 sums, however a matrix is cut.  A chain of c MFMAs of 32
+    columns leaves a squared error of about 5.5e-15 + 1.4e-15 c (measured over 1 to 60 of them, the
+    sums over wavefronts and parts included); c is what an even deal of the matrix over 256 compute
+    units of eight wavefronts makes it, of whole tiles for 640 tiles or more, else of the k-steps of
+    four-tile blocks.  10% more for the spread between inputs and shapes."""
+    say("linear sums", M, N, K)
+    nks, tiles = (K + 31) // 32, (N + 15) // 16
+    chain = nks / 8 if tiles >= 640 else nks / 8 * ((tiles + 3) // 4) / 256
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    W = (torch.randn((N, K), generator=g, device="cuda") * 0.02).to(torch.float16)
+    Wp, W64 = B.ghd_pack_weight(W), W.double().t()
+    num = den = 0.0
+    for _ in range(1 + 20000 // (M * N)):
+        x = torch.randn((M, K), generator=g, device="cuda").to(torch.float16)
+        ref = x.double() @ W64
+        num += float(((B.ghd_linear_skinny(x, Wp, N).double() - ref) ** 2).sum())
+        den += float((ref ** 2).sum())
+    err = (num / den) ** 0.5
+    assert err < 1.1 * (5.5e-15 + 1.4e-15 * chain) ** 0.5, err
