@@ -64,7 +64,8 @@ __device__ __forceinline__ ArgPtr late_args()
 __host__ __device__ constexpr int waves_of(int MT, int R) { return MT > 4 && R * MT > 32 ? 4 : 8; }
 
 #ifndef GHD_RING_REGS
-#define GHD_RING_REGS 80     // registers the load ring of a wavefront may take
+#define GHD_RING_REGS 88     // registers the load ring of a wavefront may take: two k-steps of three tiles
+                             // by 128 rows of x (one, with 80: [9000, 13824] 91.7 us instead of 87.9)
 #endif
 #ifndef GHD_RING_KIB
 #define GHD_RING_KIB 4       // weight bytes it keeps in flight, in KiB (more was measured slower)
