@@ -61,21 +61,16 @@ static int mpad_of(int M)
     return (mt <= 1 ? 1 : mt <= 2 ? 2 : mt <= 4 ? 4 : 8) * 16;
 }
 
-// Is a linear layer of this shape within what the kernel's 32-bit share arithmetic covers?
+// Is a linear layer of this shape within what the 32-bit arithmetic of the cuts covers?
 static bool linear_shape_ok(int N, int K)
 {
     if (N < 1 || K < 8 || (K % 8) != 0) return false;
     const WLayout lay = w_layout(N, K);
-    // units of one XCD times shares of one XCD must fit 32 bits
-    return ((int64_t)lay.nitems * lay.nks / 8 + lay.nks) * (kMaxShares / 8) < (1ll << 31);
+    // an XCD's k-steps, of all its row blocks, times its workgroups in all passes
+    return ((int64_t)lay.nitems * lay.nks / 8 + lay.nks) * (kRangeWgs * kMaxPasses / 8) < (1ll << 31);
 }
 
-// Is there a cut that admits the shape (see plan_linear)?
-static bool linear_admitted(int M, int N, int K)
-{
-    LinPlan pl;
-    return plan_linear(M, N, K, grid_for_sizing(), &pl);
-}
+static bool linear_admitted(int M, int N, int K) { return linear_admitted(M, N, K, grid_for_sizing()); }
 
 // A linear call of its own may read x as the caller's array only if nothing is written there
 // meanwhile: workgroups that are done store y while others still read x.  (The rows' extents are
@@ -161,7 +156,7 @@ static ghd_status check_cfg(const ghd_model_cfg* c, int M, int kv_len)
         !linear_shape_ok(c->H, c->F) || !linear_shape_ok(c->V, c->H))
         return GHD_ERR_SHAPE;
     {
-        // every linear layer of the model must fit the work-share plan at this M
+        // every linear layer of the model must have a cut at this M
         if (!linear_admitted(M, 3 * c->H, c->H) || !linear_admitted(M, c->H, c->H) ||
             !linear_admitted(M, 2 * c->F, c->H) || !linear_admitted(M, c->H, c->F) || !linear_admitted(M, c->V, c->H))
             return GHD_ERR_SHAPE;
@@ -928,25 +923,9 @@ ghd_status ghd_spec_step(const ghd_spec_model* m, const int32_t* parent_dev, con
  * synchronising the stream, ghd_debug_profile_read returns the number of launches and
  * their summed duration in milliseconds.  ghd_debug_copy is a plain copy kernel of known
  * traffic (bytes read + bytes written) used to calibrate the profiler's byte counters. */
-/* Test support (not part of the documented ABI): the kernels' work-share arithmetic on the
- * host; see share_on_host. */
-void ghd_debug_share(int items, int per_item, int j, int G, int item, int* out5)
-{
-    share_on_host(items, per_item, j, G, item, out5);
-}
-
-/* out3 = {row tiles a share handles at once, shares per workgroup, whole tiles (1) or k ranges of
- * four-tile row blocks (0)} of the general cut by which a linear layer [N, K] at M rows is admitted
- * on G workgroups; returns 0, or -1 if the shape needs more shares than the library is laid out for. */
-int ghd_debug_plan(int M, int N, int K, int G, int* out3)
-{
-    LinPlan pl;
-    if (!plan_linear(M, N, K, G, &pl)) return -1;
-    out3[0] = pl.slots;
-    out3[1] = pl.passes;
-    out3[2] = pl.whole;
-    return 0;
-}
+/* Test support (not part of the documented ABI): the host's rules and the kernels' arithmetic. */
+/* Is a linear layer [N, K] taken at M rows on G compute units? */
+int ghd_debug_admitted(int M, int N, int K, int G) { return linear_admitted(M, N, K, G); }
 
 /* The tiles of workgroup i of a whole-tile launch with gx workgroups per XCD: out2 = {c0, c1}. */
 void ghd_debug_tile_range(int ntiles, int gx, int i, int* out2) { tile_range_on_host(ntiles, gx, i, out2); }

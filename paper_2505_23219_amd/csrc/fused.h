@@ -6,7 +6,7 @@ namespace ghd {
 
 constexpr int kFT = 512;        // threads per workgroup (8 wavefronts)
 constexpr int kMaxLayers = 48;  // the counter epochs (one per layer) are laid out for this many
-constexpr int kRangeWgs = 256;  // workgroups whose work shares fit the argument block
+constexpr int kRangeWgs = 256;  // workgroups that exchange partial results in a launch, at most
 
 enum { EPI_STORE_F32 = 0, EPI_STORE_F16 = 1, EPI_RESID = 2, EPI_SWIGLU = 3, EPI_QKV = 4 };
 enum { MODE_LINEAR = 0, MODE_ATTN = 1, MODE_QKV_ATTN = 2 };
@@ -116,7 +116,7 @@ constexpr int kSyncSticky = 2;    // the first non-zero status an earlier set-up
 constexpr int kSyncMagic = 3;     // kSyncMagicValue once a set-up kernel has run on this workspace
 constexpr uint32_t kSyncMagicValue = 0x67686453u;
 constexpr int kCntStride = 32;
-constexpr int kMaxShares = 2048;  // work shares of one linear launch
+constexpr int kMaxPasses = 8;     // workgroups per compute unit of a wide linear launch, at most
 constexpr int kCntLines = kRangeWgs;                  // per kind of linear layer: a line per workgroup is enough
 constexpr int kSyncCnt = 32;                          // first counter line
 constexpr int kCntQkv = kSyncCnt;
@@ -206,14 +206,11 @@ ghd_status launch_qkv_attn(const FusedArgs& a, hipStream_t st);
 bool qkv_attn_available(int M, int d, int nh);
 ghd_status launch_resident_checked(const void* kernel, int threads, size_t lds, int* grid = nullptr);
 int fused_grid_size();
-void share_on_host(int items, int per_item, int j, int G, int item, int* out);
 void exchange_on_host(const int* xcd, int epochs, int n, int* ok);
 void tile_range_on_host(int ntiles, int gx, int i, int* out);
 void attn_share_on_host(int nh, int ntile, int tmin, int j, int G, int head, int* out);
 
-// The general cut by which a shape is admitted (see plan_linear).  Host only.
-struct LinPlan { int slots, passes, whole; };
-bool plan_linear(int M, int N, int K, int G, LinPlan* out);
+bool linear_admitted(int M, int N, int K, int G);
 size_t linear_part_floats(int M, int G);
 
 // setup kernel: zero the sync block, tree tables, and (optionally) the residual stream

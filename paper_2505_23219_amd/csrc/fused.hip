@@ -28,14 +28,13 @@ static ghd_status launch_attention_t(const FusedArgs& a, hipStream_t st)
 }
 
 template <int D>
-static ghd_status launch_attention_d(const FusedArgs& a, int mt, hipStream_t st)
+static ghd_status launch_attention_d(const FusedArgs& a, hipStream_t st)
 {
-    switch (mt) {
+    // (above 32 rows the attention has wavefronts for 4 or 8 row tiles)
+    switch (layout_tiles(row_tiles(a.M))) {
     case 1: return launch_attention_t<1, D>(a, st);
     case 2: return launch_attention_t<2, D>(a, st);
-    case 3: return launch_attention_t<3, D>(a, st);
     case 4: return launch_attention_t<4, D>(a, st);
-    case 6: return launch_attention_t<6, D>(a, st);
     default: return launch_attention_t<8, D>(a, st);
     }
 }
@@ -43,10 +42,9 @@ static ghd_status launch_attention_d(const FusedArgs& a, int mt, hipStream_t st)
 // a.mode selects the kernel; the row-tile count of M selects the instantiation
 ghd_status launch_fused(const FusedArgs& a, hipStream_t st)
 {
-    const int mt = row_tiles(a.M);
     if (a.mode == MODE_LINEAR) return launch_linear(a, st);
     if (a.mode == MODE_QKV_ATTN) return launch_qkv_attn(a, st);
-    return a.d == 64 ? launch_attention_d<64>(a, mt, st) : launch_attention_d<128>(a, mt, st);
+    return a.d == 64 ? launch_attention_d<64>(a, st) : launch_attention_d<128>(a, st);
 }
 
 // The attention's work shares on the host: for workgroup j and head `head`,

@@ -59,45 +59,13 @@ ghd_status launch_resident_checked(const void* kernel, int threads, size_t lds, 
 }
 
 // ---- which linear layers are taken ---------------------------------------------------
-// The cut that admits a shape: whole tiles in at most 8 passes of the bounded number of
-// tiles (8 up to 64 rows of x, 4 above) for wide matrices, whole tiles or row blocks of four
-// tiles for narrow ones.  A shape that has no such cut is refused; how a launch is cut in
-// the end is choose_cut's.
-constexpr double kStreamBytesPerUs = 6.4e6;    // what a launch streams at best (measured)
-constexpr double kExchangeUs = 3.0;            // what finishing shared row blocks jointly costs a launch
-
-static bool plan_whole(const WLayout& lay, int mt, int G, LinPlan* out)
-{
-    const int cap = mt <= 4 ? 8 : 4;
-    const int nx = G % 8 == 0 ? 8 : 1;
-    for (int P = 1; P <= kMaxShares / (G > 0 ? G : 1) && P <= 8; ++P) {
-        // the largest share of make_share(ntiles, 1, ., G P): an XCD's tiles, equally dealt out
-        const int U = ceil_div(lay.ntiles, nx), Gx = G * P / nx;
-        const int most = U <= Gx ? 1 : ceil_div(U, Gx);
-        if (most <= cap) {
-            out->slots = most;
-            out->passes = P;
-            out->whole = 1;
-            return true;
-        }
-    }
-    return false;
-}
-
-bool plan_linear(int M, int N, int K, int G, LinPlan* out)
+// Any narrow matrix; a wide one that at most 8 passes over the compute units deal out in whole
+// tiles, 8 of them a workgroup at up to 64 rows of x, 4 above (the launch itself would take 8 there
+// too).  How a launch is cut is choose_cut's.
+bool linear_admitted(int M, int N, int K, int G)
 {
     const WLayout lay = w_layout(N, K);
-    const int mt = (M + 15) / 16;
-    if (lay.rb == 1) return plan_whole(lay, mt, G, out);
-    if (mt <= 1 && plan_whole(lay, mt, G, out)) {
-        // stream time lost to the shares with one tile more than the average
-        const double excess = (double)out->slots * out->passes * G / lay.ntiles - 1.0;
-        if (excess * (2.0 * N * K / kStreamBytesPerUs) < kExchangeUs) return true;
-    }
-    out->slots = kRbNarrow;
-    out->passes = 1;
-    out->whole = 0;
-    return true;
+    return lay.rb != 1 || ceil_div(lay.ntiles, 8) <= (M <= 64 ? 8 : 4) * (G / 8) * kMaxPasses;
 }
 
 // partial-sum slots of the parts cut: one per workgroup, up to 8 tiles of fragments each
@@ -121,6 +89,7 @@ size_t linear_part_floats(int M, int G)
 // more for parts (counters have to be zeroed, and x packed); with whole tiles it can read x
 // as it lies, which costs about twice the x time (64-byte pieces of 128-byte lines), where
 // that is less than the launch.
+constexpr double kStreamBytesPerUs = 6.4e6;    // what a launch streams from HBM at best (measured)
 constexpr double kCuStreamBytesPerUs = 40e3;
 constexpr double kCuReadBytesPerUs = 55e3;
 constexpr double kXBytesPerUs = 80e3;
@@ -211,23 +180,7 @@ ghd_status launch_qkv_attn(const FusedArgs& a, hipStream_t st)
     }
 }
 
-// The work-share arithmetic evaluated on the host (for tests of its invariants): the unit
-// range of share j, and for `item` its first and last part and whether j's range begins
-// in it.  out[0..4] = c0, c1, first_of(item), last_of(item), begins_in(j, item).
-void share_on_host(int items, int per_item, int j, int G, int item, int* out)
-{
-    const Share sh = make_share(items, per_item, j, G);
-    out[0] = sh.c0;
-    out[1] = sh.c1;
-    out[2] = out[3] = out[4] = -1;
-    // only items of j's XCD can be asked about
-    if (sh.U > 0 && item * per_item >= sh.base && item * per_item < sh.base + sh.U) {
-        out[2] = sh.first_of(item);
-        out[3] = sh.last_of(item);
-        out[4] = sh.begins_in(j, item) ? 1 : 0;
-    }
-}
-
+// The kernels' arithmetic evaluated on the host, for tests of its invariants.
 void tile_range_on_host(int ntiles, int gx, int i, int* out)
 {
     tile_range(ntiles, gx, (uint32_t)(0x100000000ull / (uint64_t)gx + 1), i, out, out + 1);

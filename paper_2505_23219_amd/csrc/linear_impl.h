@@ -556,9 +556,9 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
 }
 
 // The tiles [c0, c1) of workgroup i (i % 8 stands for its XCD) when `ntiles` tiles are dealt to the 8
-// XCDs in contiguous blocks and an XCD's tiles to its gx workgroups in equal contiguous runs:
-// make_share(ntiles, 1, (i % 8) * gx + i / 8, 8 * gx) without a division (magic = 2^32 / gx + 1, gx > 1;
-// exact while the tiles of an XCD times gx stay below 2^32 / gx).
+// XCDs in contiguous blocks, x * ntiles / 8 and on, and an XCD's U tiles to its gx workgroups in
+// contiguous runs, w * U / gx and on (single tiles to the first U if U < gx), without a division:
+// magic = 2^32 / gx + 1, gx > 1; exact while U times gx stays below 2^32 / gx.
 __host__ __device__ __forceinline__ void tile_range(int ntiles, int gx, uint32_t magic, int i, int* c0, int* c1)
 {
     const int x = i & 7, w = i >> 3;

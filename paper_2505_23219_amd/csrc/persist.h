@@ -35,56 +35,13 @@ __device__ __forceinline__ uint32_t ld_relaxed(const uint32_t* p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Work shares.  An operation has `items` (row blocks, or heads) of `per_item` units
-// (k-steps, or key tiles) each.  (The linear kernels use the case of one unit per item, in
-// closed form: tile_range.)  Items are dealt to the 8 XCDs in contiguous blocks, and
-// the units of an XCD's items to its shares in equal contiguous ranges.  Workgroup i runs
-// on the XCD of i % 8 (see arrive), so the logical index j = (i % 8) * G/8 + i / 8
-// puts the G/8 workgroups of an XCD side by side.  An item that is split over several
-// shares is therefore always finished inside one XCD, and its partial results are
-// exchanged through that XCD's L2 with plain stores and loads: every wavefront waits for
-// the acknowledgement of its own stores before the barrier after which thread 0 bumps the
-// item's counter, and a reader's first access to a slot line in a launch cannot hit in
-// its L1.  No device-scope fence (a write-back and invalidate of a whole L2, about
-// 4 us here) is needed anywhere inside a launch.
-struct Share {
-    int U;        // units of this XCD (fits 32 bits together with the factor Ge)
-    int base;     // global index of its first unit (the unit count of an operation fits 31 bits)
-    int Ge;       // shares of this XCD that get units
-    int wg0;      // index of its first share
-    int c0, c1;   // this share's range of global unit indices (empty if c0 == c1)
-    int per_item;
-    // local (within-XCD) unit index where share wg's range begins
-    __host__ __device__ int lbegin(int wg) const { return (int)((unsigned)U * (unsigned)(wg - wg0) / (unsigned)Ge); }
-    __host__ __device__ int owner_local(int lunit) const
-    {
-        return wg0 + (int)(((unsigned)(lunit + 1) * (unsigned)Ge - 1u) / (unsigned)U);
-    }
-    __host__ __device__ int litem0(int item) const { return item * per_item - base; }
-    __host__ __device__ int first_of(int item) const { return owner_local(litem0(item)); }
-    __host__ __device__ int last_of(int item) const { return owner_local(litem0(item) + per_item - 1); }
-    // does share wg's range begin inside `item` (and not in an earlier one)?
-    __host__ __device__ bool begins_in(int wg, int item) const { return lbegin(wg) >= litem0(item); }
-};
-
-__host__ __device__ __forceinline__ Share make_share(int items, int per_item, int j, int G)
-{
-    const int nx = (G % 8 == 0) ? 8 : 1;
-    const int Gx = G / nx, x = j / Gx;
-    const int i0 = items * x / nx, i1 = items * (x + 1) / nx;
-    Share sh;
-    sh.per_item = per_item;
-    sh.U = (i1 - i0) * per_item;
-    sh.base = i0 * per_item;
-    sh.wg0 = x * Gx;
-    sh.Ge = sh.U < Gx ? sh.U : Gx;
-    sh.c0 = sh.c1 = 0;
-    if (j - sh.wg0 < sh.Ge) {
-        sh.c0 = sh.base + sh.lbegin(j);
-        sh.c1 = sh.base + ((j + 1 - sh.wg0 < sh.Ge) ? sh.lbegin(j + 1) : sh.U);
-    }
-    return sh;
-}
+// Partial results stay inside an XCD.  Workgroup i runs on the XCD of i % 8 (see arrive); an item
+// - a block of a linear layer's tiles, a head - that several workgroups share is dealt to workgroups
+// of one XCD, and its partial results go through that XCD's L2 with plain stores and loads: every
+// wavefront waits for the acknowledgement of its own stores before the barrier after which thread 0
+// bumps the item's counter, and a reader's first access to a slot line in a launch cannot hit in its
+// L1.  No device-scope fence (a write-back and invalidate of a whole L2, about 4 us here) is needed
+// anywhere inside a launch.
 
 // Every wavefront calls this before the barrier that precedes a counter bump: it returns
 // once the wavefront's own stores have been acknowledged by the L2, i.e. are visible to
@@ -188,14 +145,15 @@ __device__ __forceinline__ void zero_sync(uint32_t* sync, int block)
     if (block == 0 && threadIdx.x == 0) carry_status(sync);
 }
 
-// Workgroups are dealt round-robin to the 8 XCDs; neighbours in the work sequence (which
-// share heads and exchange partial results) get the same XCD.
+// Workgroups are dealt round-robin to the 8 XCDs (of which the grid is a multiple, see
+// launch_resident_checked); neighbours in the work sequence, which share heads and exchange partial
+// results, get the same XCD.
 __device__ __forceinline__ Ctx make_ctx(char* lds)
 {
     Ctx cx;
     const int G = gridDim.x, i = blockIdx.x;
     cx.G = G;
-    cx.j = (G % 8 == 0) ? (i % 8) * (G / 8) + i / 8 : i;
+    cx.j = (i % 8) * (G / 8) + i / 8;
     cx.lds = lds;
     return cx;
 }

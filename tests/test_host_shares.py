@@ -1,12 +1,9 @@
-"""Invariants of the kernels' work-share arithmetic (which workgroup streams which units,
-which workgroups share an item), evaluated on the host through the library.
+"""Invariants of the kernels' work-share arithmetic (which workgroup works on which tiles, which
+workgroups share a block or a head), evaluated on the host through the library.
 
-The kernels rely on: every unit is streamed exactly once; a workgroup's range is contiguous
-and the ranges of an XCD's workgroups are balanced within one unit; an item (a row slice of a
-linear layer) is always finished inside one XCD; only the first and the last item of a
-workgroup's range can be shared with other workgroups (two partial-sum slots per workgroup);
-and a workgroup is the first part of at most one shared item (one counter line per
-workgroup)."""
+The kernels rely on: every tile is dealt out exactly once, in contiguous runs, those of an XCD's
+workgroups balanced within one tile; a share has no more tiles than there are accumulators for; what
+several workgroups finish together is shared inside one XCD."""
 import ctypes as C
 
 import pytest
@@ -14,125 +11,31 @@ import pytest
 from paper_2505_23219_amd import binding as B
 
 
-def share(lib, items, per_item, j, G, item=0):
+@pytest.mark.parametrize("M", [1, 16, 64, 65, 128])
+def test_which_linear_layers_are_taken(M):
+    """Narrow matrices always (up to 639 tiles of 16 rows); wide ones up to what eight passes over 256
+    compute units deal out in shares of 8 tiles, of 4 above 64 rows of x: 262144 and 131072 rows."""
+    lib = B.lib()
+    for N in (1, 16, 130, 4096, 10224, 10225, 12288, 22016, 32000, 131072, 131073, 152064, 262144, 262145, 400000):
+        for K in (8, 4096, 13824):
+            want = (N + 15) // 16 < 640 or N <= (262144 if M <= 64 else 131072)
+            assert lib.ghd_debug_admitted(M, N, K, 256) == want, (N, K)
+
+
+def test_cuts_of_known_shapes():
+    """(whole tiles, tiles per share, parts, workgroups) of 7B- and 13B-shaped layers inside a step: wide
+    matrices go whole-tile; output projections too up to some 30 rows of x, and in parts above; down
+    projections, with their long k range, always in parts."""
+    lib = B.lib()
     out = (C.c_int * 5)()
-    lib.ghd_debug_share(items, per_item, j, G, item, out)
-    return list(out)
-
-
-CASES = [
-    # items, units per item, workgroups
-    (48, 32, 256), (16, 32, 256), (86, 32, 256), (16, 86, 256), (125, 32, 256),   # the 7B layers (256-row groups)
-    (96, 16, 256), (172, 16, 256), (500, 8, 256),                                  # row-split variants
-    (3, 2, 256), (1, 1, 256), (7, 5, 256), (300, 1, 256), (9, 1000, 256),
-    (5, 3, 16), (40, 7, 24), (13, 9, 8), (11, 4, 7), (2, 50, 5),                   # small grids, also not a multiple of 8
-    # row blocks x k-steps of the packed 7B / 13B matrices (wide ones tile by tile, narrow ones in
-    # blocks of four tiles), one and two shares per workgroup
-    (768, 128, 256), (64, 128, 256), (1376, 128, 256), (64, 344, 256), (2000, 128, 512),
-    (960, 160, 256), (80, 160, 256), (1728, 160, 256), (80, 432, 256), (2000, 160, 512),
-]
-
-
-@pytest.mark.parametrize("items,per_item,G", CASES)
-def test_share_invariants(items, per_item, G):
-    lib = B.lib()
-    nx = 8 if G % 8 == 0 else 1
-    Gx = G // nx
-    total = items * per_item
-    ranges = [share(lib, items, per_item, j, G)[:2] for j in range(G)]
-    # every unit exactly once, ranges contiguous in workgroup order inside an XCD
-    covered = 0
-    for x in range(nx):
-        i0, i1 = items * x // nx, items * (x + 1) // nx
-        pos = i0 * per_item
-        sizes = []
-        for j in range(x * Gx, (x + 1) * Gx):
-            c0, c1 = ranges[j]
-            if c0 == c1:
-                continue
-            assert c0 == pos and c1 > c0
-            sizes.append(c1 - c0)
-            pos = c1
-        assert pos == i1 * per_item                       # the XCD's items, all of them
-        covered += pos - i0 * per_item
-        if sizes:
-            assert max(sizes) - min(sizes) <= 1
-            assert len(sizes) == min(Gx, (i1 - i0) * per_item)
-    assert covered == total
-    # per item: its parts are exactly the workgroups whose range meets it
-    first_count = {}
-    for item in range(items):
-        lo, hi = item * per_item, (item + 1) * per_item
-        parts = [j for j in range(G) if ranges[j][0] < hi and ranges[j][1] > lo]
-        assert parts == list(range(parts[0], parts[-1] + 1))
-        assert parts[0] // Gx == parts[-1] // Gx          # inside one XCD
-        for j in parts:
-            _, _, first, last, begins = share(lib, items, per_item, j, G, item)
-            assert (first, last) == (parts[0], parts[-1])
-            assert begins == (1 if ranges[j][0] >= lo else 0)
-        if len(parts) > 1:
-            first_count[parts[0]] = first_count.get(parts[0], 0) + 1
-    assert all(v == 1 for v in first_count.values())      # one counter line per workgroup is enough
-    # only the first and the last item of a range can be shared
-    for j in range(G):
-        c0, c1 = ranges[j]
-        if c0 == c1:
-            continue
-        for item in range(c0 // per_item + 1, (c1 - 1) // per_item):
-            assert item * per_item >= c0 and (item + 1) * per_item <= c1
-
-
-@pytest.mark.parametrize("M,N,K", [(64, 12288, 4096), (64, 4096, 4096), (64, 22016, 4096), (64, 4096, 11008),
-                                   (64, 32000, 4096), (1, 32000, 4096), (128, 22016, 4096), (128, 32000, 4096),
-                                   (64, 15360, 5120), (64, 27648, 5120), (16, 160000, 4096), (128, 16384 * 16, 64),
-                                   (1, 4096, 4096), (16, 4096, 11008), (17, 4096, 11008), (8, 5120, 13824), (3, 130, 688)])
-def test_linear_plan(M, N, K):
-    """The cut of a linear layer.  A wide matrix (640 tiles of 16 rows or more) is dealt out in
-    whole tiles, so that no share has more tiles than the kernel keeps accumulators for (8 up to
-    64 rows of x, 4 above), with as few shares per workgroup as that takes.  So is a narrow one at
-    up to 16 rows of x if its tiles spread evenly enough over the workgroups; otherwise a narrow
-    one streams a k range of one block of four tiles at a time, one share per workgroup."""
-    lib = B.lib()
-    G = 256
-    out = (C.c_int * 3)()
-    rc = lib.ghd_debug_plan(M, N, K, G, out)
-    ntiles = (N + 15) // 16
-    cap = 8 if M <= 64 else 4
-
-    def most(P):
-        worst = 0
-        for j in range(G * P):
-            c0, c1 = share(lib, ntiles, 1, j, G * P)[:2]
-            worst = max(worst, c1 - c0)
-        return worst
-
-    feasible = [P for P in range(1, 9) if most(P) <= cap]
-    whole = bool(feasible)
-    if ntiles < 640:
-        if M > 16:
-            whole = False
-        elif whole:
-            P = feasible[0]
-            excess = most(P) * P * G / ntiles - 1.0
-            whole = excess * (2.0 * N * K / 6.4e6) < 3.0
-        if not whole:
-            assert rc == 0 and list(out) == [4, 1, 0]
-            return
-    if not feasible:
-        assert rc == -1
-        return
-    assert rc == 0 and out[2] == 1 and out[1] == feasible[0] and out[0] == most(feasible[0]) and 1 <= out[0] <= cap
-
-
-def test_linear_plan_known_shapes():
-    """7B-shaped output and down projections (256 tiles on 256 workgroups) go whole-tile at one
-    row of x; the 13B-shaped ones (320 tiles: shares of one and two) do not."""
-    lib = B.lib()
-    out = (C.c_int * 3)()
-    for (M, N, K), want in [((1, 4096, 4096), [1, 1, 1]), ((16, 4096, 11008), [1, 1, 1]), ((17, 4096, 4096), [4, 1, 0]),
-                            ((1, 5120, 5120), [4, 1, 0]), ((1, 5120, 13824), [4, 1, 0]), ((64, 22016, 4096), [6, 1, 1]),
-                            ((64, 12288, 4096), [3, 1, 1]), ((128, 22016, 4096), [3, 2, 1])]:
-        assert lib.ghd_debug_plan(M, N, K, 256, out) == 0 and list(out) == want, (M, N, K, list(out))
+    for (M, N, K), want in [((1, 4096, 4096), [1, 1, 1, 256]), ((17, 4096, 4096), [1, 1, 1, 256]), ((64, 4096, 4096), [0, 4, 4, 256]),
+                            ((1, 4096, 11008), [0, 4, 4, 256]), ((64, 4096, 11008), [0, 4, 4, 256]),
+                            ((1, 5120, 5120), [1, 2, 1, 256]), ((64, 5120, 5120), [0, 5, 4, 256]), ((64, 5120, 13824), [0, 8, 6, 240]),
+                            ((64, 12288, 4096), [1, 3, 1, 256]), ((64, 22016, 4096), [1, 6, 1, 256]),
+                            ((128, 22016, 4096), [1, 6, 1, 256]), ((128, 32000, 4096), [1, 8, 1, 256]),
+                            ((64, 40000, 4096), [1, 5, 1, 512])]:
+        lib.ghd_debug_cut(M, N, K, 256, 0, out)
+        assert list(out)[:4] == want, (M, N, K, list(out))
 
 
 def attn_share(lib, nh, ntile, j, G, head):
@@ -182,15 +85,39 @@ def tile_range(lib, ntiles, gx, i):
 
 
 @pytest.mark.parametrize("gx", [32, 2, 7, 64, 96, 256])
-def test_tile_range_is_the_general_share(gx):
-    """The division-free form that the kernels evaluate equals the general work share, for
-    every workgroup, from one tile to the most that a launch has."""
+def test_tile_range_is_the_even_deal(gx):
+    """The division-free form that the kernels evaluate, from one tile to the most that a launch has:
+    XCD x has the tiles [x n / 8, (x + 1) n / 8), its workgroup w the w-th of gx equal runs of them."""
     lib = B.lib()
     for ntiles in list(range(1, 70)) + [255, 256, 257, 320, 1376, 2000, 8 * gx, 8 * gx + 1, 64 * gx, 64 * gx - 3, 16384]:
         for i in range(0, 8 * gx, 1 if gx <= 32 else 37):
-            want = share(lib, ntiles, 1, (i % 8) * gx + i // 8, 8 * gx)[:2]
+            x, w = i % 8, i // 8
+            i0, U = ntiles * x // 8, ntiles * (x + 1) // 8 - ntiles * x // 8
+            ge = min(U, gx)                                            # workgroups that get a tile
+            want = [i0 + U * w // ge, i0 + U * (w + 1) // ge] if w < ge else [0, 0]
             got = tile_range(lib, ntiles, gx, i)
             assert got == want or (got[0] == got[1] and want[0] == want[1]), (ntiles, gx, i)
+
+
+@pytest.mark.parametrize("ntiles,gx", [(768, 32), (256, 32), (1376, 32), (2000, 64), (320, 32), (3, 32), (16384, 256), (41, 7)])
+def test_tile_ranges_cover_every_tile_once(ntiles, gx):
+    """Contiguous in workgroup order inside an XCD, balanced within one tile, nothing left out."""
+    lib = B.lib()
+    covered = 0
+    for x in range(8):
+        pos, sizes = ntiles * x // 8, []
+        for w in range(gx):
+            c0, c1 = tile_range(lib, ntiles, gx, w * 8 + x)
+            if c0 == c1:
+                continue
+            assert c0 == pos and c1 > c0
+            sizes.append(c1 - c0)
+            pos = c1
+        assert pos == ntiles * (x + 1) // 8
+        covered += sum(sizes)
+        if sizes:
+            assert max(sizes) - min(sizes) <= 1 and len(sizes) == min(gx, sum(sizes))
+    assert covered == ntiles
 
 
 @pytest.mark.parametrize("M", [1, 16, 17, 33, 48, 64, 65, 96, 97, 128])
