@@ -28,8 +28,8 @@
  *     they never synchronise.  `ws` is caller-provided device scratch of at
  *     least the size the matching *_workspace_bytes function returns, 256-byte
  *     aligned.
- *   - Concurrency: the persistent kernels need every compute unit (all their
- *     workgroups wait for each other), so two calls that overlap in time on one
+ *   - Concurrency: kernels whose workgroups exchange partial results need every
+ *     compute unit (they wait for each other), so two calls that overlap in time on one
  *     GPU - from two streams or two threads - slow each other down and may run
  *     into the bounded waits (reported through ghd_step_status, never a hang).
  *     Calls that share a workspace must be ordered on one stream.  The library
@@ -251,16 +251,20 @@ ghd_status ghd_verify_stack_argmax(const ghd_model_cfg *cfg, const ghd_layer_wei
                                    int32_t *amax_dev, float *logits, float *x_out, void *ws,
                                    size_t ws_bytes, void *stream);
 
-/* Every linear layer and every attention runs in a launch of a persistent kernel
- * (one workgroup per compute unit, all resident; a layer's QKV layer and attention
- * may share one) whose workgroups hand partial results to each other; every wait is bounded and gives up rather than hang
- * (for instance if other work on the GPU keeps some workgroups from becoming
- * resident).  This call synchronises `stream` and reports the status word the
- * last ghd_linear_skinny / ghd_tree_attention / ghd_verify_layer /
- * ghd_verify_stack call left in its workspace `ws`: 0 = completed, otherwise
- * the code of the wait that gave up (3: a workgroup did not run on the expected
- * XCD) and the outputs are invalid (a workgroup whose wait gave up writes no
- * results for the item it waited for).  The word is sticky: every call's set-up
+/* Every linear layer and every attention is one launch (a layer's QKV layer and
+ * attention may share one).  Where several workgroups work on one item - parts of a
+ * linear layer's block of tiles, parts of a head's keys, a QKV layer's workgroups and
+ * the attention behind it - they hand partial results to each other: such a launch
+ * has at most one workgroup per compute unit, all resident, and every wait is bounded
+ * and gives up rather than hang (for instance if other work on the GPU keeps some
+ * workgroups from becoming resident).  Linear layers dealt out in whole tiles
+ * exchange nothing, wait for nothing and may have more workgroups than that.  This
+ * call synchronises `stream` and reports the status word the last
+ * ghd_linear_skinny / ghd_tree_attention / ghd_verify_layer / ghd_verify_stack call
+ * left in its workspace `ws`: 0 = completed, otherwise the code of the wait that gave
+ * up (3: the workgroups of an item did not all run on one XCD, through whose L2 they
+ * exchange; which XCD that is does not matter) and the outputs are invalid (a
+ * workgroup whose wait gave up writes no results for the item it waited for).  The word is sticky: every call's set-up
  * clears the status for the launches that follow but keeps the first non-zero
  * status it finds, so a caller who asks only every so often still learns that
  * some call since ghd_step_status_reset (or since the first use of the

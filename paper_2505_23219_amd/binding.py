@@ -178,7 +178,8 @@ def ghd_tree_mask(parent: torch.Tensor) -> torch.Tensor:
 
 
 def ghd_step_status(ws: torch.Tensor) -> int:
-    """Synchronises the stream; 0 = the last step on `ws` completed, 1 = a bounded wait gave up."""
+    """Synchronises the stream; 0 = the last step on `ws` completed, otherwise the code of the wait that
+    gave up (3: workgroups that exchange results ran on different XCDs)."""
     st = C.c_int32(-1)
     _check(lib().ghd_step_status(_ptr(ws), C.byref(st), _stream()), "ghd_step_status")
     return int(st.value)

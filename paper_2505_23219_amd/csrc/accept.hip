@@ -195,9 +195,10 @@ __global__ __launch_bounds__(128) void k_accept(const float* __restrict__ seg_v,
 // alone: the root always is, and with it as much of the path as follows the node order.  What
 // has to move usually fits the registers, K and V at once; longer paths go through LDS.  The path
 // comes from the device result of the acceptance kernel; its entries are clamped, so that
-// whatever that buffer holds no access leaves the tree rows.  (Bound by latency, a few rows per
-// workgroup: 8.5 us for 32 layers x 32 heads in four dependent steps with K and V one after the
-// other, 7.3 us in two.)
+// whatever that buffer holds no access leaves the tree rows.
+// Bound by the lines it touches: V is channel-major, so a row that moves costs a 128-byte line of
+// every channel, 17 MB read and as much written back for 32 layers x 32 heads x 128 channels (6.5 us at
+// a copy's rate).  8.5 us there in four dependent steps with K and V one after the other, 7.3 us now.
 struct CommitArgs {
     half_t* k[kCommitMaxLayers];
     half_t* v[kCommitMaxLayers];
