@@ -69,7 +69,8 @@ enum {
 #define GHD_OUT_F32 0u      /* y is float  [M, ldy] */
 #define GHD_OUT_F16 1u      /* y is fp16   [M, ldy] */
 
-/* Limits: L <= 48, nh <= 256, H <= 43520, F <= 65536, V <= 262144, F % 8 == 0. */
+/* Limits: L <= 48, nh <= 256, H <= 43520, F <= 65536, F % 8 == 0, V <= 262144 (with
+ * more than 64 tree nodes V <= 131072). */
 typedef struct {
     int32_t H;            /* hidden size                         */
     int32_t nh;           /* attention heads (multi-head: kv heads == heads) */

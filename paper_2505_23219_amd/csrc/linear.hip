@@ -78,7 +78,7 @@ size_t linear_part_floats(int M, int G)
 // ---- how a launch is cut ----------------------------------------------------------------
 // The estimate (microseconds) that chooses among the ways; its terms were fitted to launches
 // at 1 to 128 rows of 1280 x 1280 to 5120 x 13824 matrices, which it meets within 5 to 10%:
-//   weights: what HBM streams at best, or the longest share's at what one compute unit gets;
+//   weights: at what HBM streams, or the longest share's at what one compute unit gets;
 //   x: comes on top, not beside it - a compute unit's vector memory path keeps some 16 KB on
 //   their way, in order, so x from the L2 waits its turn among weights from HBM.  [4096, 11008] at
 //   64 rows: 31 us whole-tile (1.4 MB of x per workgroup), 26 in parts of 2 tiles (0.7 MB), 22.6
@@ -89,7 +89,7 @@ size_t linear_part_floats(int M, int G)
 // more for parts (counters have to be zeroed, and x packed); with whole tiles it can read x
 // as it lies, which costs about twice the x time (64-byte pieces of 128-byte lines), where
 // that is less than the launch.
-constexpr double kStreamBytesPerUs = 6.4e6;    // what a launch streams from HBM at best (measured)
+constexpr double kStreamBytesPerUs = 6.4e6;    // what a launch of 0.1 to 0.2 GB streams from HBM (measured)
 constexpr double kCuStreamBytesPerUs = 40e3;
 constexpr double kCuReadBytesPerUs = 55e3;
 constexpr double kXBytesPerUs = 80e3;
