@@ -317,7 +317,9 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
     static_assert(!(FOLDED && HALVED), "one way or the other");
     // What came before: FOLDED: the sums of earlier k-steps; HALVED: those of the first half that
     // stay in registers, as many as there are registers for.  The last NSTEP fragments are not set
-    // aside but added up step by step (all of them that way: 78 us for [32000, 4096] at 128 rows, 66).
+    // aside but added up step by step, before the others of a step, which cover the wait for their
+    // products ([32000, 4096] at 128 rows: 64 us with 22 of them; 78 with all 26 that the LDS does not
+    // hold, after the others).
     constexpr int NSTEP = HALVED && NF - S::ASIDE > 13 ? NF - S::ASIDE - (NF > 60 ? 4 : 12) : 0;
     constexpr int NB = FOLDED ? NF : HALVED ? NF - S::ASIDE - NSTEP : 0;
     floatx4 acc[R][MT], before[NB > 0 ? NB : 1];
@@ -382,7 +384,6 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
         for (int tt = 0; tt < R; ++tt)
 #pragma unroll
             for (int bb = 0; bb < MT; ++bb) {
-                // (those that are added up step by step first: the additions wait for the products)
                 const int t = NSTEP ? R - 1 - tt : tt, b = NSTEP ? MT - 1 - bb : bb;
                 if (t * MT + b >= NF - NSTEP) acc[t][b] += __builtin_amdgcn_mfma_f32_16x16x32_f16(wr[p][t], xf[b], zero4, 0, 0, 0);
                 else acc[t][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wr[p][t], xf[b], acc[t][b], 0, 0, 0);
