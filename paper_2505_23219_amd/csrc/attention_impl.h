@@ -18,11 +18,17 @@
 // row at a time, so they must not carry the non-temporal hint: the other half of the line is
 // then fetched again, 30.2 us.)
 //
-// Above (attn_staged), the workgroup shares tiles through LDS; wavefronts 0-3 take the first 32
-// keys of a tile, 4-7 the last 32, each for its own 16 (or 32) rows.  Each wavefront reading units by
-// itself was slower there: the states of eight wavefronts with all rows take 4 us to merge, and
-// with the rows split over groups of wavefronts every unit is read once per group (13B-shaped layer,
-// 64 rows, 8192 cached tokens, launch with the QKV layer: 75.7 us staged, 86 and 96 us).
+// Above (attn_staged), the workgroup shares tiles through LDS, where they are loaded without passing
+// through registers: a ring of buffers, a barrier a tile, and one copy of the code for a tile.  With up to
+// 64 rows wavefronts 0-3 take the first 32 keys of a tile, 4-7 the last 32, each for its own 16 rows; with
+// more a wavefront takes 16 rows and all keys.  What bounds it: at many tiles per workgroup HBM (13B-shaped
+// layer, 8192 cached tokens: 1.2 us a tile of 32 KB on each compute unit, 6.9 TB/s); at few the chain of latencies around
+// the tiles.  The same through registers, four tiles ahead, took seven copies of a tile's code (28 KB, each
+// fetched when it is first run) and a final merge of a row per wavefront: attention of 24 heads, 48
+// rows, 3001 cached tokens 20.5 us a call, now 17.9; launch with the QKV layer and 128 rows at 2048 cached
+// tokens 61 us, now 52.  Each wavefront reading units by itself was slower there: the states of eight
+// wavefronts with all rows take 4 us to merge, and with the rows split over groups of wavefronts every unit is
+// read once per group (13B-shaped layer, 64 rows, 8192 cached tokens, launch with the QKV layer: 10 and 20 us more).
 #pragma once
 #include "persist.h"
 
@@ -93,9 +99,39 @@ __host__ __device__ __forceinline__ AttnTiles attn_tiles(const AttnHeads& s, int
     return t;
 }
 
+// A workgroup's heads and its tiles of the first of them.  (Some eight integer divisions and a read of
+// the argument block: the launch that shares itself with the QKV layer has them done while its first
+// weights are on their way, 1.2 us that came between the stores of q and the gate before.)
+struct AttnPlan {
+    AttnHeads heads;
+    AttnTiles tiles;
+};
+__host__ __device__ __forceinline__ AttnPlan attn_plan(int nh, int ntile, int tmin, int j, int G)
+{
+    AttnPlan p;
+    p.heads = attn_heads(nh, j, G);
+    p.tiles = p.heads.h_lo < p.heads.h_hi ? attn_tiles(p.heads, p.heads.h_lo, ntile, tmin) : AttnTiles{};
+    return p;
+}
+
 // 2^x for x <= 0 (softmax weights): the hardware instruction; results below the smallest
 // normal number flush to zero, which is what a weight that small should be.
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// op over the four lanes that share lane % 16, in all of them: by swaps of rows of lanes, which leave the
+// LDS alone (a shuffle through it waits behind the operands that it is reading: 0.15 us a tile)
+template <class Op>
+__device__ __forceinline__ float over_groups(float x, Op op)
+{
+    typedef uint32_t pair __attribute__((ext_vector_type(2)));
+    const uint32_t u = __float_as_uint(x);
+    const pair a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const uint32_t v = __float_as_uint(op(__uint_as_float(a[0]), __uint_as_float(a[1])));
+    const pair b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float max_over_groups(float x) { return over_groups(x, [](float a, float b) { return fmaxf(a, b); }); }
+__device__ __forceinline__ float sum_over_groups(float x) { return over_groups(x, [](float a, float b) { return a + b; }); }
 
 // `gate` is called once by every workgroup (all threads), before the first read of q or of a
 // cache row from kv_len on; it returns false if the launch is to be abandoned.  A kernel that
@@ -126,9 +162,74 @@ __device__ __forceinline__ int hidden(int v)
     return v;
 }
 
+// four columns of a row of the attention's output
+__device__ __forceinline__ void store_attn_out(const FusedArgs& a, GLOBAL half_t* out, int m, int col, floatx4 v)
+{
+    const half4 h = {(half_t)v[0], (half_t)v[1], (half_t)v[2], (half_t)v[3]};
+    const size_t at = a.att_out_packed ? xpk_index(m, col, a.Mpad >> 4) : (size_t)m * a.nh * a.d + col;
+    *(GLOBAL half4*)(out + at) = h;
+}
+
+// The end of a head that the workgroups first .. first + np - 1 share, of which this is number `me`: once
+// the partial states of all are stored, each merges its share of the rows.  Returns false if they never
+// came.
+template <int D>
+__device__ __forceinline__ bool finish_parts(const FusedArgs& a, GLOBAL half_t* out, int head, int first, int np, int me,
+                                             uint32_t epoch, int* wait_ok)
+{
+    const int tid = hidden(threadIdx.x), M = a.M, Mpad = a.Mpad;
+    const auto o_part = gp(a.o_part), ml_part = gp(a.ml_part);
+    wait_own_stores();
+    __syncthreads();   // partial state acknowledged by the L2
+    uint32_t* const cnt = a.sync + kCntAttn + head * kCntStride;
+    const int r0 = M * me / np, r1 = M * (me + 1) / np;        // the rows this part merges
+    if (tid == 0) {
+        uint32_t* const word = epoch_word(cnt, epoch);
+        arrive(word);
+        if (r0 < r1) *wait_ok = bounded_wait(a.sync, word, (uint32_t)np, (uint32_t)np, 2000u);
+        if (me == 0) clear_next(cnt, epoch);
+    }
+    if (r0 >= r1) return true;
+    __syncthreads();
+    if (!*wait_ok) return false;    // the other parts never arrived: nothing sensible to write
+    // a thread per four channels of a row; parts in index order, eight of them in flight
+    constexpr int CH = D / 4;
+    for (int i = tid; i < (r1 - r0) * CH; i += kFT) {
+        const int m = r0 + i / CH, ch = i % CH * 4;
+        float mx = -INFINITY, den = 0.f;
+        floatx4 num = {0.f, 0.f, 0.f, 0.f};
+        for (int p0 = 0; p0 < np; p0 += 8) {
+            floatx2 ml[8];
+            floatx4 o[8];
+#pragma unroll
+            for (int p = 0; p < 8; ++p) {
+                const size_t row = (size_t)(first + min(p0 + p, np - 1)) * Mpad + m;
+                ml[p] = *(GLOBAL const floatx2*)(ml_part + row * 2);
+                o[p] = *(GLOBAL const floatx4*)(o_part + row * D + ch);
+            }
+            float mnew = mx;
+#pragma unroll
+            for (int p = 0; p < 8; ++p) mnew = fmaxf(mnew, ml[p][0]);
+            const float w0 = (mx == -INFINITY) ? 0.f : fast_exp2(mx - mnew);
+            mx = mnew;
+            num *= w0;
+            den *= w0;
+#pragma unroll
+            for (int p = 0; p < 8; ++p) {
+                const float w = (p0 + p >= np || ml[p][0] == -INFINITY) ? 0.f : fast_exp2(ml[p][0] - mx);
+                den += w * ml[p][1];
+                num += w * o[p];
+            }
+        }
+        // (a row that sees no key at all, possible with a caller's mask and an empty cache, gets zeros)
+        store_attn_out(a, out, m, head * D + ch, den > 0.f ? num / den : (floatx4){0.f, 0.f, 0.f, 0.f});
+    }
+    return true;
+}
+
 template <int MT, int D, bool PREFETCH, class Gate>
-__device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const half_t* q_, const half_t* kc_,
-                                            const half_t* vc_, half_t* out_, uint32_t epoch, Gate gate)
+__device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const AttnPlan& plan, const half_t* q_,
+                                            const half_t* kc_, const half_t* vc_, half_t* out_, uint32_t epoch, Gate gate)
 {
     constexpr int DS = D / 32, DT = D / 16;
     DirectLds<MT, D>& sm = *reinterpret_cast<DirectLds<MT, D>*>(cx.lds);
@@ -137,7 +238,6 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const h
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int M = a.M, nh = a.nh, kv_len = a.kv_len, T = a.kv_len + a.M, Mpad = a.Mpad;
     const float scale_log2e = a.scale_log2e;
-    uint32_t* const sync = a.sync;
     const auto q = gp(q_), kc = gp(kc_), vc = gp(vc_);
     const auto out = gp(out_);
     const auto o_part = gp(a.o_part), ml_part = gp(a.ml_part);
@@ -149,7 +249,7 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const h
     // gets its own run of workgroups, each taking a contiguous range of the head's key
     // tiles; otherwise every workgroup takes whole heads.  A head is therefore always
     // finished inside one XCD (partial states go through that XCD's L2).
-    const AttnHeads hs = attn_heads(nh, cx.j, cx.G);
+    const AttnHeads hs = plan.heads;
     const int hx0 = hs.hx0, h_lo = hs.h_lo, h_hi = hs.h_hi;
     // (bits from M on, which a caller's mask may have set, are never looked at: a mask bit is
     // only consulted for keys kv_len <= key < kv_len + M)
@@ -163,11 +263,11 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const h
     }
 
     bool gated = false;
-    for (int hl = h_lo; hl < h_hi; ++hl) {
+    for (int hl = h_lo; hl < (PREFETCH ? min(h_hi, h_lo + 1) : h_hi); ++hl) {
         const int lane = hidden(threadIdx.x & 63), c = lane & 15, g4 = lane >> 4;
         const int head = hx0 + hl;
         // the workgroups first .. first + np - 1 split this head's tiles
-        const AttnTiles ts = attn_tiles(hs, hl, ntile, kDirectTiles);
+        const AttnTiles ts = hl == h_lo ? plan.tiles : attn_tiles(hs, hl, ntile, kDirectTiles);
         const int first = ts.first, np = ts.np, me = ts.me;
         if (me >= np) continue;                            // more workgroups than parts
         const auto kh = kc + (size_t)head * a.stride_head;
@@ -296,8 +396,7 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const h
                     any = __ballot(mine) != 0ull;          // no row of the tile sees the unit: leave it out
                 }
                 if (!any) continue;
-                tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
-                tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+                tmax = max_over_groups(tmax);
                 const float mnew = fmaxf(mrun[t], tmax);
                 const float muse = (mnew == -INFINITY) ? 0.f : mnew;
                 const float alpha = fast_exp2(mrun[t] - muse);
@@ -327,18 +426,11 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const h
         // ---- the wavefronts' states meet in LDS and are merged in wavefront order; a head in one
         //      part is finished by that
         const int lane_ = hidden(lane);
-        auto store_out = [&](int m, int col, floatx4 v) {
-            const half4 h = {(half_t)v[0], (half_t)v[1], (half_t)v[2], (half_t)v[3]};
-            const size_t at = a.att_out_packed ? xpk_index(m, col, Mpad >> 4) : (size_t)m * nh * D + col;
-            *(GLOBAL half4*)(out + at) = h;
-        };
         {
         const int lane = lane_, c = lane & 15, g4 = lane >> 4;
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
-            float l = lrun[t];
-            l += __shfl_xor(l, 16);
-            l += __shfl_xor(l, 32);
+            const float l = sum_over_groups(lrun[t]);
             if (lane < 16) {
                 sm.m[wave][t][c] = mrun[t];
                 sm.l[wave][t][c] = l;
@@ -368,7 +460,7 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const h
             if (np == 1) {
                 // (a row that sees no key at all, possible with a caller's mask and an empty
                 // cache, gets zeros)
-                store_out(m, head * D + e * 16 + g4 * 4, l > 0.f ? o / l : (floatx4){0.f, 0.f, 0.f, 0.f});
+                store_attn_out(a, out, m, head * D + e * 16 + g4 * 4, l > 0.f ? o / l : (floatx4){0.f, 0.f, 0.f, 0.f});
             } else {
                 const size_t row = (size_t)cx.j * Mpad + m;
                 *(GLOBAL floatx4*)(o_part + row * D + e * 16 + g4 * 4) = o;
@@ -376,54 +468,7 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const h
             }
         }
         }
-        if (np > 1) {
-            const int tid = hidden(threadIdx.x);
-            wait_own_stores();
-            __syncthreads();   // partial state acknowledged by the L2
-            uint32_t* const cnt = sync + kCntAttn + head * kCntStride;
-            const int r0 = M * me / np, r1 = M * (me + 1) / np;        // the rows this part merges
-            if (tid == 0) {
-                uint32_t* const word = epoch_word(cnt, epoch);
-                arrive(word);
-                if (r0 < r1) sm.wait_ok = bounded_wait(sync, word, (uint32_t)np, (uint32_t)np, 2000u);
-                if (me == 0) clear_next(cnt, epoch);
-            }
-            if (r0 < r1) {
-                __syncthreads();
-                if (!sm.wait_ok) return false;    // the other parts never arrived: nothing sensible to write
-                // a thread per four channels of a row; parts in index order, eight of them in flight
-                constexpr int CH = D / 4;
-                for (int i = tid; i < (r1 - r0) * CH; i += kFT) {
-                    const int m = r0 + i / CH, ch = i % CH * 4;
-                    float mx = -INFINITY, den = 0.f;
-                    floatx4 num = {0.f, 0.f, 0.f, 0.f};
-                    for (int p0 = 0; p0 < np; p0 += 8) {
-                        floatx2 ml[8];
-                        floatx4 o[8];
-#pragma unroll
-                        for (int p = 0; p < 8; ++p) {
-                            const size_t row = (size_t)(first + min(p0 + p, np - 1)) * Mpad + m;
-                            ml[p] = *(GLOBAL const floatx2*)(ml_part + row * 2);
-                            o[p] = *(GLOBAL const floatx4*)(o_part + row * D + ch);
-                        }
-                        float mnew = mx;
-#pragma unroll
-                        for (int p = 0; p < 8; ++p) mnew = fmaxf(mnew, ml[p][0]);
-                        const float w0 = (mx == -INFINITY) ? 0.f : fast_exp2(mx - mnew);
-                        mx = mnew;
-                        num *= w0;
-                        den *= w0;
-#pragma unroll
-                        for (int p = 0; p < 8; ++p) {
-                            const float w = (p0 + p >= np || ml[p][0] == -INFINITY) ? 0.f : fast_exp2(ml[p][0] - mx);
-                            den += w * ml[p][1];
-                            num += w * o[p];
-                        }
-                    }
-                    store_out(m, head * D + ch, den > 0.f ? num / den : (floatx4){0.f, 0.f, 0.f, 0.f});
-                }
-            }
-        }
+        if (np > 1 && !finish_parts<D>(a, out, head, first, np, me, epoch, &sm.wait_ok)) return false;
         // a workgroup that goes on to another head reuses its LDS and its partial-state slot
         // (a workgroup with several heads has them to itself: np = 1)
         if (hl + 1 < h_hi) __syncthreads();
@@ -433,430 +478,314 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const h
     return true;
 }
 
-// ---- more query rows: tiles staged through LDS, shared by the wavefronts ----------------------
+// ---- more query rows: tiles in LDS, shared by the wavefronts -----------------------------------
 template <int MT, int D>
 struct StagedLds {
-    static constexpr int MTW = (MT + 3) / 4;
-    static constexpr int KS = D + 8;    // halves per K row (padded)
-    static constexpr int VS = 64 + 8;   // halves per V^T row (padded, rows stay 16-byte aligned)
-    // two tile buffers: while one tile is being multiplied, the next one is staged
-    half_t k[2][64 * KS];
-    half_t vt[2][D * VS];
-    // state of the wavefronts working on the second key half, handed to their partners on
-    // the first half when a head ends: [row-tile slot][tile][fragment][lane]
-    floatx4 o2[4][MTW][D / 16][64];
-    float m2[4][MTW][64];
-    float l2[4][MTW][64];
-    int wait_ok;      // thread 0's verdict on a bounded wait, for the whole workgroup
+    static constexpr int NB = D == 128 ? 4 : 8;        // tile buffers
+    static constexpr uint32_t KB = 64 * D * 2;         // bytes of a tile's K, and of its V^T
+    char tile[NB][2 * KB];
+    uint32_t mask[GHD_MAX_M * 4];
+    int wait_ok;                                       // thread 0's verdict on a bounded wait, for the whole workgroup
+    // what the two wavefronts of a row tile exchange when a head ends: their softmax statistics and, in a
+    // tile buffer that is free then, half of their output fragments
+    float m[4][2][16], l[4][2][16];
+    typedef floatx4 HalfOut[4][2][D / 32][64];
+    static_assert(sizeof(HalfOut) <= 2 * KB, "fits a buffer");
 };
 
-template <int MT, int D, bool PREFETCH, class Gate>
-__device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const half_t* q, const half_t* kc,
-                                            const half_t* vc, half_t* out, uint32_t epoch, Gate gate)
+// 16 bytes a lane from base + off straight into the LDS, lane after lane from `lds` on (the same for all
+// lanes): no registers.  The waits for it are written out (wait_loads, then a barrier).
+typedef __attribute__((address_space(3))) void* LdsPtr;
+__device__ __forceinline__ void to_lds(GLOBAL const char* base, uint32_t off, uint32_t lds)
 {
-    constexpr int MTW = (MT + 3) / 4;   // 16-row tiles per wavefront
-    constexpr int DS = D / 32, DT = D / 16, CPR = D / 8;
-    constexpr int NLD = 64 * CPR / kFT; // 16-byte pieces per thread per tile, for K and for V alike
-    constexpr int NT = (MT <= 4) ? 4 : 2;   // tiles in flight
-    using L = StagedLds<MT, D>;
-    L& sm = *reinterpret_cast<L*>(cx.lds);
+    __builtin_amdgcn_global_load_lds((GLOBAL void*)(base + off), (LdsPtr)(uintptr_t)lds, 16, 0, 0);
+}
+__device__ __forceinline__ void to_lds_nt(GLOBAL const char* base, uint32_t off, uint32_t lds)     // non-temporal
+{
+    __builtin_amdgcn_global_load_lds((GLOBAL void*)(base + off), (LdsPtr)(uintptr_t)lds, 16, 0, 2);
+}
+__device__ __forceinline__ void to_lds_word(GLOBAL const char* base, uint32_t off, uint32_t lds)   // 4 bytes a lane
+{
+    __builtin_amdgcn_global_load_lds((GLOBAL void*)(base + off), (LdsPtr)(uintptr_t)lds, 4, 0, 0);
+}
+// waits until at most n of this wavefront's loads are on their way
+template <int N>
+__device__ __forceinline__ void wait_loads()
+{
+    static_assert(N < 64, "six bits");
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | (N >> 4) << 14);
+}
 
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+// a barrier that waits for this wavefront's own use of the LDS, but not for what it has requested (which
+// __syncthreads() would, had any of it the LDS for its destination)
+__device__ __forceinline__ void barrier_lds()
+{
+    pin_order();
+    __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    pin_order();
+}
+// ... until all but its youngest n tiles are there (n <= MOST; uniform)
+template <int PER_TILE, int MOST>
+__device__ __forceinline__ void wait_tiles_of(int n)
+{
+    if constexpr (MOST > 0) {
+        if (n < MOST) return wait_tiles_of<PER_TILE, MOST - 1>(n);
+    }
+    wait_loads<PER_TILE * MOST>();
+}
+
+template <int MT, int D, bool PREFETCH, class Gate>
+__device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const AttnPlan& plan, const half_t* q_,
+                                            const half_t* kc_, const half_t* vc_, half_t* out_, uint32_t epoch, Gate gate)
+{
+    constexpr int DS = D / 32, DT = D / 16;
+    constexpr int HALVES = MT <= 4 ? 2 : 1;            // wavefronts that share a row tile, each for its keys
+    constexpr int UNITS = 2 / HALVES;                  // 32-key units of a tile that a wavefront works on
+    constexpr int PIECES = D / 64;                     // 1 KiB pieces of a tile's K that a wavefront requests (as many of V)
+    constexpr int LPT = 2 * PIECES;                    // loads per tile
+    using L = StagedLds<MT, D>;
+    constexpr int NB = L::NB;
+    constexpr uint32_t KB = L::KB, TB = 2 * KB;
+    L& sm = *reinterpret_cast<L*>(cx.lds);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)cx.lds;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, g4 = lane >> 4;
-    const int kh = wave >> 2, wq = wave & 3;   // key half of the tile, row-tile slot
-    // scalars of the argument block used inside the loops, as plain locals
+    const int wq = HALVES == 2 ? wave & 3 : wave, half = HALVES == 2 ? wave >> 2 : 0;    // row tile, key half
     const int M = a.M, nh = a.nh, kv_len = a.kv_len, T = a.kv_len + a.M, Mpad = a.Mpad;
     const float scale_log2e = a.scale_log2e;
-    uint32_t* const sync = a.sync;
-    float* const o_part = a.o_part;
-    float* const ml_part = a.ml_part;
+    const auto q = gp(q_), kc = gp(kc_), vc = gp(vc_);
+    const auto out = gp(out_);
+    const auto o_part = gp(a.o_part), ml_part = gp(a.ml_part);
     const int ntile = (T + 63) >> 6;
-
-    // Work shares.  Heads are dealt to the 8 XCDs in contiguous blocks.  Inside an XCD a
-    // workgroup works on one head at a time: with fewer heads than workgroups, every head
-    // gets its own run of workgroups, each taking a contiguous range of the head's key
-    // tiles; otherwise every workgroup takes whole heads.  A head is therefore always
-    // finished inside one XCD (partial states go through that XCD's L2), and the tile loop
-    // of a head has no head change in it.
-    const AttnHeads hs = attn_heads(nh, cx.j, cx.G);
+    const int mrow = wq * 16 + c;
+    const bool mok = mrow < M, wave_active = wq * 16 < M;
+    const AttnHeads hs = plan.heads;
     const int hx0 = hs.hx0, h_lo = hs.h_lo, h_hi = hs.h_hi;
 
-    // per-wave query rows
-    int mrow[MTW];
-    bool mok[MTW];
-    uint64_t alo[MTW], ahi[MTW];
-    bool wave_active = false;
+    // What this lane requests of every tile.  A KiB of the LDS is 8 (or 4) consecutive rows of a tile: K
+    // rows are keys, V^T rows channels.  The 16-byte pieces of a row lie in an order of their own
+    // (piece p of row r in place p ^ f(r)), so that the 16 rows that an MFMA operand takes the same
+    // piece of are spread over all banks.
+    constexpr int KR = 512 / D;                        // K rows of a KiB: 4 or 8
+    const uint32_t st_tok2 = (uint32_t)a.stride_tok * 2, st_ch2 = (uint32_t)a.v_stride_ch * 2;
+    const int k_row = wave * PIECES * KR + lane / (D / 8);                   // (piece i: i * KR rows on)
+    const uint32_t k_piece = D == 128 ? (uint32_t)((lane & 15) ^ ((lane >> 4) | (wave & 3) << 2)) * 16
+                                      : (uint32_t)((lane & 7) ^ (((lane >> 4) & 1) | (wave & 3) << 1)) * 16;
+    const int v_ch = wave * PIECES * 8 + (lane >> 3);                        // (piece i: i * 8 channels on)
+    const uint32_t v_last = st_ch2 - 16;
+    // where it finds the operands of its MFMAs (see attn_direct: row i of S^T's 16-key tile jx is key
+    // (i / 4) * 8 + jx * 4 + i % 4 of a unit)
+    uint32_t k_at[DS], v_at[2];
 #pragma unroll
-    for (int t = 0; t < MTW; ++t) {
-        int mt = wq * MTW + t;
-        mrow[t] = mt * 16 + c;
-        mok[t] = mrow[t] < M;
-        wave_active = wave_active || (mt * 16 < M);
-        alo[t] = mok[t] ? a.mask[2 * mrow[t]] : 0;
-        ahi[t] = mok[t] ? a.mask[2 * mrow[t] + 1] : 0;
-        // (bits from M on, which a caller's mask may have set, are never looked at: a mask bit
-        // is only consulted for keys kv_len <= key < kv_len + M)
-    }
-    // K piece id -> (row id / CPR, 8 channels id % CPR); V^T piece id -> (channel id / 8,
-    // 8 keys id % 8).  Offsets inside a head fit 32 bits (checked on the host).
-    int k_off[NLD], v_off[NLD], k_row[NLD];
+    for (int ds = 0; ds < DS; ++ds)
+        k_at[ds] = (uint32_t)((c >> 2) * 8 + (c & 3)) * (D * 2) + (uint32_t)((ds * 4 + g4) ^ (D == 128 ? c : c >> 1)) * 16;
 #pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-        int id = tid + kFT * i;
-        k_row[i] = id / CPR;
-        k_off[i] = (id % CPR) * 8;
-        v_off[i] = (id >> 3) * (int)a.v_stride_ch + (id & 7) * 8;
-    }
-    const int v_last = (int)a.v_stride_ch - 8, st_tok = (int)a.stride_tok;
-    const std::integral_constant<int, 0> s0;
-    const std::integral_constant<int, 1> s1;
-    const std::integral_constant<int, NT == 4 ? 2 : 0> s2;
-    const std::integral_constant<int, NT == 4 ? 3 : 1> s3;
+    for (int un = 0; un < 2; ++un) v_at[un] = KB + (uint32_t)c * 128 + (uint32_t)((un * 4 + g4) ^ (c >> 1)) * 16;
+
+    // the masks of all rows, four words each: a word a thread (rows past the last read the last word;
+    // bits from M on, which a caller's mask may have set, are never looked at)
+    auto request_masks = [&]() {
+        to_lds_word((GLOBAL const char*)gp(a.mask), (uint32_t)min(tid, M * 4 - 1) * 4, lds0 + (uint32_t)offsetof(L, mask) + wave * 256);
+    };
 
     bool gated = false;
-    for (int hl = h_lo; hl < h_hi; ++hl) {
+    for (int hl = h_lo; hl < (PREFETCH ? min(h_hi, h_lo + 1) : h_hi); ++hl) {
         const int head = hx0 + hl;
         // the workgroups first .. first + np - 1 split this head's tiles
-        const AttnTiles ts = attn_tiles(hs, hl, ntile, 1);
+        const AttnTiles ts = hl == h_lo ? plan.tiles : attn_tiles(hs, hl, ntile, 1);
         const int first = ts.first, np = ts.np, me = ts.me, t0 = ts.t0, t1 = ts.t1;
         if (me >= np) continue;                            // more workgroups than tiles
-        const half_t* kh_ = kc + (size_t)head * a.stride_head;
-        const half_t* vh_ = vc + (size_t)head * a.v_stride_head;
+        const auto kh = (GLOBAL const char*)(kc + (size_t)head * a.stride_head);
+        const auto vh = (GLOBAL const char*)(vc + (size_t)head * a.v_stride_head);
 
-        // running state of this head
-        float mrun[MTW], lrun[MTW];
-        floatx4 oacc[MTW][DT];
+        // Keys from T on read the last one; V^T pieces past the capacity, which hold no key, the last
+        // piece.  (Offsets inside a head fit 32 bits: checked on the host.)
+        auto request = [&](int tile) {
+            const uint32_t at = lds0 + (uint32_t)((tile - t0) & (NB - 1)) * TB + (uint32_t)wave * (PIECES * 1024);
 #pragma unroll
-        for (int t = 0; t < MTW; ++t) {
-            mrun[t] = -INFINITY;
-            lrun[t] = 0.f;
+            for (int i = 0; i < PIECES; ++i)
+                to_lds_nt(kh, (uint32_t)min(tile * 64 + k_row + i * KR, T - 1) * st_tok2 + k_piece, at + i * 1024);
 #pragma unroll
-            for (int e = 0; e < DT; ++e) oacc[t][e] = (floatx4){0.f, 0.f, 0.f, 0.f};
-        }
-
-        // NT tiles in flight: registers of set (tile - t0) % NT hold a tile until it is
-        // staged.  A workgroup has few tiles (about 4 at 2048 cached tokens), so the time to
-        // the first byte dominates unless all of them are requested at once.  The loads
-        // are unconditional: past the last tile they all read one valid 16-byte piece (a
-        // broadcast), which keeps the wait counts of the loop exact.
-        half8 kreg[NT][NLD], vreg[NT][NLD];
-        int l_tile = t0;                                   // next tile to request
-        auto load_tile = [&](auto set) {
-            constexpr int S = decltype(set)::value;
-            const bool real = l_tile < t1;
-#pragma unroll
-            for (int i = 0; i < NLD; ++i) {
-                int key = min(l_tile * 64 + k_row[i], T - 1);
-                const half_t* kp = kh_ + key * st_tok + k_off[i];
-                // keys past the capacity are never touched: the last piece is read instead
-                // and zeroed when it is staged
-                int over = max(l_tile * 64 + (int)((tid + kFT * i) & 7) * 8 - v_last, 0);
-                const half_t* vp = vh_ + v_off[i] + l_tile * 64 - over;
-                kreg[S][i] = __builtin_nontemporal_load((const half8*)(real ? kp : kc));
-                vreg[S][i] = __builtin_nontemporal_load((const half8*)(real ? vp : vc));
-            }
-            ++l_tile;
-        };
-        auto store_tile = [&](auto set, int tile) {
-            constexpr int S = decltype(set)::value;
-#pragma unroll
-            for (int i = 0; i < NLD; ++i) {
-                int id = tid + kFT * i;
-                *(half8*)(&sm.k[S & 1][k_row[i] * L::KS + k_off[i]]) = kreg[S][i];
-                int vch = id >> 3, seg = id & 7;
-                half8 v = vreg[S][i];
-                int nvalid = T - (tile * 64 + seg * 8);  // rows from T on hold no data: zero them,
-                if (nvalid < 8) {                        // a stray NaN times a zero weight is a NaN
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        if (e >= nvalid) v[e] = (half_t)0;
-                }
-                *(half8*)(&sm.vt[S & 1][vch * L::VS + seg * 8]) = v;
+            for (int i = 0; i < PIECES; ++i) {
+                const int ch = v_ch + i * 8;
+                const uint32_t key2 = (uint32_t)tile * 128 + (uint32_t)((lane & 7) ^ ((ch >> 1) & 7)) * 16;
+                to_lds_nt(vh, (uint32_t)ch * st_ch2 + min(key2, v_last), at + KB + i * 1024);
             }
         };
-        // Requests, in tile order: [tiles known before the gate] gate [queries] [the rest].
+        // Requests, in order: [tiles known before the gate] gate, queries, [the rest].  A tile is known
+        // if it ends at least 64 rows below kv_len: no cache line of it holds a row that this launch
+        // writes, whatever the strides and the alignment of the cache.  The queries take the last
+        // buffer until its first tile is requested; every wavefront brings its own.
+        const int up_front = min(t1 - t0, NB - 1);
         int n_pre = 0;
         if (!gated) {
-            if constexpr (PREFETCH) {
-                // past this share's last tile (a dummy load), or at least 64 rows below
-                // kv_len: no cache line of such a tile holds a row that this launch writes,
-                // whatever the strides and the alignment of the cache
-                auto early = [&]() { return l_tile >= t1 || l_tile * 64 + 128 <= kv_len; };
-                if (early()) {
-                    load_tile(s0);
-                    n_pre = 1;
-                    if (early()) {
-                        load_tile(s1);
-                        n_pre = 2;
-                        if constexpr (NT == 4) {
-                            if (early()) {
-                                load_tile(s2);
-                                n_pre = 3;
-                                if (early()) {
-                                    load_tile(s3);
-                                    n_pre = 4;
-                                }
-                            }
-                        }
-                    }
-                }
-            }
+            // (loads return in order: the wavefront that polls at the gate requests nothing before)
+            const bool polls = PREFETCH && wave == 0;
+            if (!polls) request_masks();
+            if constexpr (PREFETCH)
+                for (; !polls && n_pre < up_front && (t0 + n_pre) * 64 + 128 <= kv_len; ++n_pre) request(t0 + n_pre);
             if (!gate()) return false;
             gated = true;
+            if (polls) request_masks();
         }
-        half8 qf[MTW][DS];
+        {
+            const uint32_t at = lds0 + (NB - 1) * TB + (uint32_t)wave * (DS * 1024);
+            const uint32_t off = ((uint32_t)min(mrow, M - 1) * (uint32_t)nh + (uint32_t)head) * (D * 2) + g4 * 16;
 #pragma unroll
-        for (int t = 0; t < MTW; ++t) {
-#pragma unroll
-            for (int s = 0; s < DS; ++s) {
-                half8 v = {0, 0, 0, 0, 0, 0, 0, 0};
-                if (mok[t]) v = *(const half8*)(q + ((size_t)mrow[t] * nh + head) * D + s * 32 + g4 * 8);
-                qf[t][s] = v;
-            }
+            for (int ds = 0; ds < DS; ++ds) to_lds((GLOBAL const char*)q, off + ds * 64, at + ds * 1024);
         }
-        if (n_pre < 1) load_tile(s0);
-        if (n_pre < 2) load_tile(s1);
-        if constexpr (NT == 4) {
-            if (n_pre < 3) load_tile(s2);
-            if (n_pre < 4) load_tile(s3);
-        }
-        // The tiles alternate between the two LDS buffers (register set S goes to buffer
-        // S & 1: the number of sets is even).  While tile i is multiplied out of one buffer,
-        // tile i + 1 is staged into the other and its registers are refilled - one barrier
-        // per tile.  Past the share's last tile the staged data is a dummy nobody reads.
-        int p_tile = t0;                                   // the tile being processed
-        store_tile(s0, t0);
-        load_tile(s0);
-        auto do_tile = [&](auto set, auto next) {
-            constexpr int B = decltype(set)::value & 1;
-            const int tile = p_tile++;
-            __syncthreads();            // tile staged by everybody; the other buffer is free
-            store_tile(next, tile + 1);
-            load_tile(next);
-        if (!wave_active) return;
-        const int key0 = tile * 64 + kh * 32;    // this wavefront's 32 keys
-        const bool committed = key0 + 32 <= kv_len;   // every key visible to every row
+        for (int n = n_pre; n < up_front; ++n) request(t0 + n);
+
+        // waits for all but the youngest n tiles
+        auto wait_tiles = [&](int n) {
+            wait_tiles_of<LPT, NB - 2>(n);
+            pin_order();
+        };
+        // running state of this head
+        float mrun = -INFINITY, lrun = 0.f;
+        floatx4 oacc[DT];
 #pragma unroll
-        for (int t = 0; t < MTW; ++t) {
-            floatx4 s[2];
-            float tmax = -INFINITY;
-            if (committed) {
+        for (int e = 0; e < DT; ++e) oacc[e] = (floatx4){0.f, 0.f, 0.f, 0.f};
+        wait_tiles(up_front - max(n_pre, 1));              // the queries and the first tile are there
+        half8 qf[DS];
+        {
+            const char* at = sm.tile[NB - 1] + wave * (DS * 1024) + lane * 16;
+#pragma unroll
+            for (int ds = 0; ds < DS; ++ds) qf[ds] = *(const half8*)(at + ds * 1024);
+        }
+
+        for (int tile = t0; tile < t1; ++tile) {
+            // A barrier a tile: the tile is there for everybody, and everybody is done with the one before,
+            // whose buffer is requested into.
+            if (tile > t0) wait_tiles(min(t1 - 1 - tile, NB - 2));
+            barrier_lds();
+            if (tile + NB - 1 < t1) request(tile + NB - 1);
+            if (!wave_active) continue;
+            const char* const buf = sm.tile[(tile - t0) & (NB - 1)];
+#pragma unroll 1
+            for (int uu = 0; uu < UNITS; ++uu) {
+                const int un = HALVES == 2 ? half : uu, key0 = tile * 64 + un * 32;
+                const char* const kp = buf + un * (32 * D * 2);
+                const char* const vp = buf + (un ? v_at[1] : v_at[0]);
+                floatx4 s[2];
 #pragma unroll
                 for (int jx = 0; jx < 2; ++jx) {
                     s[jx] = (floatx4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int ds = 0; ds < DS; ++ds) {
-                        half8 kf = *(const half8*)(&sm.k[B][(kh * 32 + jx * 16 + c) * L::KS + ds * 32 + g4 * 8]);
-                        s[jx] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, qf[t][ds], s[jx], 0, 0, 0);
-                    }
-                    s[jx] *= scale_log2e;
-                    tmax = fmaxf(tmax, fmaxf(fmaxf(s[jx][0], s[jx][1]), fmaxf(s[jx][2], s[jx][3])));
+                    for (int ds = 0; ds < DS; ++ds)
+                        s[jx] = __builtin_amdgcn_mfma_f32_16x16x32_f16(*(const half8*)(kp + k_at[ds] + jx * (4 * D * 2)), qf[ds], s[jx], 0, 0, 0);
                 }
-            } else {
-                bool sub_any[2];
+                half8 vf[DT];
 #pragma unroll
-                for (int jx = 0; jx < 2; ++jx) {
-                    const int kbase = key0 + jx * 16;
-                    bool vis_any;
-                    if (kbase + 16 <= kv_len) {
-                        vis_any = true;
-                    } else {
-                        bool mine = false;
+                for (int e = 0; e < DT; ++e) vf[e] = *(const half8*)(vp + e * 2048);
+                float tmax = -INFINITY;
+                if (key0 + 32 <= kv_len) {                 // every key visible to every row
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            int key = kbase + g4 * 4 + r;
-                            bool vis = key < kv_len;
-                            if (key >= kv_len && key < T) {
-                                int jn = key - kv_len;
-                                vis = (jn < 64 ? (alo[t] >> jn) : (ahi[t] >> (jn - 64))) & 1ull;
-                            }
-                            mine = mine || (vis && mok[t]);
-                        }
-                        vis_any = __ballot(mine) != 0ull;
+                    for (int jx = 0; jx < 2; ++jx) {
+                        s[jx] *= scale_log2e;
+                        tmax = fmaxf(tmax, fmaxf(fmaxf(s[jx][0], s[jx][1]), fmaxf(s[jx][2], s[jx][3])));
                     }
-                    sub_any[jx] = vis_any;
-                    s[jx] = (floatx4){0.f, 0.f, 0.f, 0.f};
-                    if (vis_any) {
+                } else {
+                    const uint32_t* mw = sm.mask + mrow * 4;
+                    const uint64_t lo = mw[0] | (uint64_t)mw[1] << 32, hi = mw[2] | (uint64_t)mw[3] << 32;
+                    bool mine = false;
 #pragma unroll
-                        for (int ds = 0; ds < DS; ++ds) {
-                            half8 kf = *(const half8*)(&sm.k[B][(kh * 32 + jx * 16 + c) * L::KS + ds * 32 + g4 * 8]);
-                            s[jx] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, qf[t][ds], s[jx], 0, 0, 0);
-                        }
-                    }
-                }
-                if (!(sub_any[0] || sub_any[1])) continue;
-#pragma unroll
-                for (int jx = 0; jx < 2; ++jx) {
-                    const int kbase = key0 + jx * 16;
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        int key = kbase + g4 * 4 + r;
-                        bool vis = sub_any[jx] && key < kv_len;
-                        if (sub_any[jx] && key >= kv_len && key < T) {
-                            int jn = key - kv_len;
-                            vis = (jn < 64 ? (alo[t] >> jn) : (ahi[t] >> (jn - 64))) & 1ull;
-                        }
-                        float v = vis ? s[jx][r] * scale_log2e : -INFINITY;
-                        s[jx][r] = v;
+                    for (int i = 0; i < 8; ++i) {
+                        const int key = key0 + g4 * 8 + i, jn = key - kv_len;
+                        bool vis = key < kv_len;
+                        if (jn >= 0 && key < T) vis = ((jn < 64 ? lo >> jn : hi >> (jn - 64)) & 1ull) != 0;
+                        mine = mine || (vis && mok);
+                        const float v = vis ? s[i >> 2][i & 3] * scale_log2e : -INFINITY;
+                        s[i >> 2][i & 3] = v;
                         tmax = fmaxf(tmax, v);
                     }
-                }
-            }
-            tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
-            tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-            float mnew = fmaxf(mrun[t], tmax);
-            float muse = (mnew == -INFINITY) ? 0.f : mnew;
-            float alpha = fast_exp2(mrun[t] - muse);
-            mrun[t] = mnew;
-            float lsum = 0.f;
-            half8 pf;
+                    if (__ballot(mine) == 0ull) continue;  // no row of the tile sees the unit: leave it out
+                    // keys from T on hold no data: zero them, a stray NaN times a zero weight is a NaN
+                    const int nvalid = T - key0 - g4 * 8;
+                    if (key0 + 32 > T) {
 #pragma unroll
-            for (int jx = 0; jx < 2; ++jx)
+                        for (int e = 0; e < DT; ++e)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    float pv = fast_exp2(s[jx][r] - muse);
-                    lsum += pv;
-                    pf[jx * 4 + r] = (half_t)pv;
-                }
-            lrun[t] = lrun[t] * alpha + lsum;
-#pragma unroll
-            for (int e = 0; e < DT; ++e) {
-                oacc[t][e] *= alpha;
-                const half_t* vrow = &sm.vt[B][(e * 16 + c) * L::VS + kh * 32];
-                half4 a0 = *(const half4*)(vrow + g4 * 4);
-                half4 a1 = *(const half4*)(vrow + 16 + g4 * 4);
-                half8 vf = {a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
-                oacc[t][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf, pf, oacc[t][e], 0, 0, 0);
-            }
-        }
-    };
-        // Whole groups of NT tiles run in a branch-free loop; the rest is a chain of nested
-        // conditions, so every tile is only reachable through its predecessor and the number
-        // of loads younger than the one being waited for is known.
-        {
-            int u = t0;
-            if constexpr (NT == 4) {
-                for (; u + 3 < t1; u += 4) {
-                    do_tile(s0, s1);
-                    do_tile(s1, s2);
-                    do_tile(s2, s3);
-                    do_tile(s3, s0);
-                }
-                if (u < t1) {
-                    do_tile(s0, s1);
-                    if (u + 1 < t1) {
-                        do_tile(s1, s2);
-                        if (u + 2 < t1) do_tile(s2, s3);
+                            for (int i = 0; i < 8; ++i)
+                                if (i >= nvalid) vf[e][i] = (half_t)0;
                     }
                 }
+                tmax = max_over_groups(tmax);
+                const float mnew = fmaxf(mrun, tmax);
+                const float muse = (mnew == -INFINITY) ? 0.f : mnew;
+                const float alpha = fast_exp2(mrun - muse);
+                mrun = mnew;
+                float lsum = 0.f;
+                half8 pf;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const float pv = fast_exp2(s[i >> 2][i & 3] - muse);
+                    lsum += pv;
+                    pf[i] = (half_t)pv;
+                }
+                lrun = lrun * alpha + lsum;
+                // (the maximum of most rows settles early: usually nothing has to be rescaled)
+                if (__ballot(alpha != 1.0f)) {
+#pragma unroll
+                    for (int e = 0; e < DT; ++e) oacc[e] *= alpha;
+                }
+#pragma unroll
+                for (int e = 0; e < DT; ++e) oacc[e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf[e], pf, oacc[e], 0, 0, 0);
+            }
+        }
+
+        // ---- end of this workgroup's share of the head.  The two wavefronts of a row tile exchange half of
+        //      their output fragments each and merge the other half (online-softmax rescale); a head in
+        //      one part is finished by that
+        lrun = sum_over_groups(lrun);
+        const auto state = o_part + ((size_t)cx.j * Mpad + mrow) * D + g4 * 4;
+        auto store = [&](auto n, int e0, const floatx4* o) {
+            if (!mok) return;
+            if (np > 1) {
+#pragma unroll
+                for (int e = 0; e < decltype(n)::value; ++e) *(GLOBAL floatx4*)(state + (e0 + e) * 16) = o[e];
             } else {
-                for (; u + 1 < t1; u += 2) {
-                    do_tile(s0, s1);
-                    do_tile(s1, s0);
-                }
-                if (u < t1) do_tile(s0, s1);
+#pragma unroll
+                for (int e = 0; e < decltype(n)::value; ++e)
+                    store_attn_out(a, out, mrow, head * D + (e0 + e) * 16 + g4 * 4, lrun > 0.f ? o[e] / lrun : (floatx4){0.f, 0.f, 0.f, 0.f});
             }
-        }
-
-        // ---- end of this workgroup's share of the head: the wavefronts of the second key
-        //      half hand their state over through LDS, their partners merge it into their
-        //      own (online-softmax rescale) and store the workgroup's partial state
+        };
+        if constexpr (HALVES == 2) {
+            // (the buffer after the last tile's: everybody was done with it at the last barrier)
+            auto& other = *reinterpret_cast<typename L::HalfOut*>(sm.tile[(t1 - t0) & (NB - 1)]);
+            constexpr int HE = DT / 2;
+            if (wave_active) {
 #pragma unroll
-        for (int t = 0; t < MTW; ++t) {
-            float l = lrun[t];
-            l += __shfl_xor(l, 16);
-            l += __shfl_xor(l, 32);
-            lrun[t] = l;
-        }
-        if (kh == 1 && wave_active) {
-#pragma unroll
-            for (int t = 0; t < MTW; ++t) {
-#pragma unroll
-                for (int e = 0; e < DT; ++e) sm.o2[wq][t][e][lane] = oacc[t][e];
-                sm.m2[wq][t][lane] = mrun[t];
-                sm.l2[wq][t][lane] = lrun[t];
-            }
-        }
-        __syncthreads();
-        if (kh == 0 && wave_active) {
-#pragma unroll
-            for (int t = 0; t < MTW; ++t) {
-                float mb = sm.m2[wq][t][lane], lb = sm.l2[wq][t][lane];
-                float mx = fmaxf(mrun[t], mb);
-                float wa = (mrun[t] == -INFINITY) ? 0.f : fast_exp2(mrun[t] - mx);
-                float wb = (mb == -INFINITY) ? 0.f : fast_exp2(mb - mx);
-                float l = lrun[t] * wa + lb * wb;
-                if (!mok[t]) continue;
-                size_t row = (size_t)cx.j * Mpad + mrow[t];
-#pragma unroll
-                for (int e = 0; e < DT; ++e) {
-                    floatx4 ob = sm.o2[wq][t][e][lane];
-                    *(floatx4*)(o_part + row * D + e * 16 + g4 * 4) = oacc[t][e] * wa + ob * wb;
-                }
-                if (g4 == 0) {
-                    ml_part[row * 2] = mx;
-                    ml_part[row * 2 + 1] = l;
+                for (int e = 0; e < HE; ++e) other[wq][half][e][lane] = half ? oacc[e] : oacc[HE + e];
+                if (lane < 16) {
+                    sm.m[wq][half][c] = mrun;
+                    sm.l[wq][half][c] = lrun;
                 }
             }
-        }
-        wait_own_stores();
-        __syncthreads();   // partial state acknowledged by the L2; hand-over buffers free again
-
-        // ---- merge: every workgroup of the head combines its share of the rows
-        if (tid == 0) {
-            uint32_t* const cnt = sync + kCntAttn + head * kCntStride;
-            uint32_t* const word = epoch_word(cnt, epoch);
-            arrive(word);
-            sm.wait_ok = bounded_wait(sync, word, (uint32_t)np, (uint32_t)np, 2000u);
-            if (me == 0) clear_next(cnt, epoch);
-        }
-        __syncthreads();
-        if (!sm.wait_ok) return false;    // the other parts never arrived: nothing sensible to write
-        int r0 = M * me / np, r1 = M * (me + 1) / np;
-        for (int m = r0 + wave; m < r1; m += 8) {
-            // lane p holds the statistics of part p (np <= 64: one XCD's workgroups)
-            float mq = -INFINITY, lq = 0.f;
-            size_t rowq = 0;
-            if (lane < np) {
-                rowq = (size_t)(first + lane) * Mpad + m;
-                mq = ml_part[rowq * 2];
-                lq = ml_part[rowq * 2 + 1];
+            __syncthreads();
+            if (wave_active) {
+                const float mb = sm.m[wq][half ^ 1][c], lb = sm.l[wq][half ^ 1][c];
+                const float mx = fmaxf(mrun, mb);
+                const float wa = (mrun == -INFINITY) ? 0.f : fast_exp2(mrun - mx);
+                const float wb = (mb == -INFINITY) ? 0.f : fast_exp2(mb - mx);
+                // (the first half's share comes first in either wavefront's sum)
+                lrun = half ? lb * wb + lrun * wa : lrun * wa + lb * wb;
+                mrun = mx;
+                floatx4 o[HE];
+#pragma unroll
+                for (int e = 0; e < HE; ++e) o[e] = (half ? oacc[HE + e] : oacc[e]) * wa + other[wq][half ^ 1][e][lane] * wb;
+                store(std::integral_constant<int, HE>{}, half * HE, o);
             }
-            float mx = mq;
-            for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-            float wq_ = (mq == -INFINITY) ? 0.f : fast_exp2(mq - mx);
-            float den = wq_ * lq;
-            for (int off = 32; off > 0; off >>= 1) den += __shfl_xor(den, off);
-            // weighted sum of the parts' outputs, parts in index order, 8 loads in flight
-            float num[D / 64];
-#pragma unroll
-            for (int e = 0; e < D / 64; ++e) num[e] = 0.f;
-            for (int q0 = 0; q0 < np; q0 += 8) {
-                float t[8][D / 64], w8[8];
-#pragma unroll
-                for (int qi = 0; qi < 8; ++qi) {
-                    int qq = min(q0 + qi, np - 1);
-                    size_t row = (size_t)__shfl((long long)rowq, qq);
-                    w8[qi] = (q0 + qi < np) ? __shfl(wq_, qq) : 0.f;
-#pragma unroll
-                    for (int e = 0; e < D / 64; ++e) t[qi][e] = o_part[row * D + e * 64 + lane];
-                }
-#pragma unroll
-                for (int qi = 0; qi < 8; ++qi)
-#pragma unroll
-                    for (int e = 0; e < D / 64; ++e) num[e] += w8[qi] * t[qi][e];
-            }
-#pragma unroll
-            for (int e = 0; e < D / 64; ++e) {
-                // a row that sees no key at all (possible with a caller's mask and an empty
-                // cache) gets zeros
-                const int col = head * D + e * 64 + lane;
-                const size_t at = a.att_out_packed ? xpk_index(m, col, Mpad >> 4) : (size_t)m * nh * D + col;
-                out[at] = (half_t)(den > 0.f ? num[e] / den : 0.f);
-            }
+        } else {
+            store(std::integral_constant<int, DT>{}, 0, oacc);
         }
-        // a workgroup that goes on to another head reuses its partial-state slot: wait until
-        // the other parts have read it
+        if (np > 1) {
+            if (mok && half == 0 && g4 == 0) *(GLOBAL floatx2*)(ml_part + ((size_t)cx.j * Mpad + mrow) * 2) = (floatx2){mrun, lrun};
+            if (!finish_parts<D>(a, out, head, first, np, me, epoch, &sm.wait_ok)) return false;
+        }
+        // a workgroup that goes on to another head reuses its LDS (it has its heads to itself: np = 1)
         if (hl + 1 < h_hi) __syncthreads();
     }
     // a workgroup without a share of any head still checks in
@@ -869,15 +798,16 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const h
 template <int MT, int D>
 struct AttnOf {
     static constexpr bool DIRECT = MT <= 2;
+    static constexpr int TMIN = DIRECT ? kDirectTiles : 1;         // tiles that a part has at least
     using Lds = std::conditional_t<DIRECT, DirectLds<MT, D>, StagedLds<layout_tiles(MT), D>>;
 };
 
 template <int MT, int D, bool PREFETCH = false, class Gate = NoGate>
-__device__ __forceinline__ bool attn_phase(const FusedArgs& a, Ctx& cx, const half_t* q, const half_t* kc,
+__device__ __forceinline__ bool attn_phase(const FusedArgs& a, Ctx& cx, const AttnPlan& plan, const half_t* q, const half_t* kc,
                                            const half_t* vc, half_t* out, uint32_t epoch, Gate gate = Gate())
 {
-    if constexpr (AttnOf<MT, D>::DIRECT) return attn_direct<MT, D, PREFETCH>(a, cx, q, kc, vc, out, epoch, gate);
-    else return attn_staged<layout_tiles(MT), D, PREFETCH>(a, cx, q, kc, vc, out, epoch, gate);
+    if constexpr (AttnOf<MT, D>::DIRECT) return attn_direct<MT, D, PREFETCH>(a, cx, plan, q, kc, vc, out, epoch, gate);
+    else return attn_staged<layout_tiles(MT), D, PREFETCH>(a, cx, plan, q, kc, vc, out, epoch, gate);
 }
 
 }  // namespace ghd

@@ -10,7 +10,9 @@ __global__ __launch_bounds__(kFT) void k_attention(const FusedArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     Ctx cx = make_ctx(lds);
-    attn_phase<MT, D>(a, cx, a.att_q, a.att_k, a.att_v, a.att_out, a.att_epoch);
+    const AttnPlan plan = attn_plan(a.nh, (a.kv_len + a.M + 63) >> 6, AttnOf<MT, D>::TMIN, cx.j, cx.G);
+    attn_phase<MT, D>(a, cx, plan, a.att_q, a.att_k, a.att_v, a.att_out, a.att_epoch);
+    wait_loads<0>();       // (nothing is on its way to the LDS when the workgroup ends)
 }
 
 // ---------------------------------------------------------------------------

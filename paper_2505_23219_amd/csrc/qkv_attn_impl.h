@@ -23,16 +23,22 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
     int c0, c1;
     tile_range(ntiles, cut, magic, blockIdx.x, &c0, &c1);
     const int lane = threadIdx.x & 63, xcd = blockIdx.x & 7, Gx = cut;
-    if (c0 < c1)
-        gemm_group<MT, R, 8, false, stretches_whole(MT, R)>(
-            h, lds, c0, c1 - c0, 0, nks, []() {},
-            [&](ArgPtr la, int, floatx4 v, int m, int n0, const float* s_rinv) {
-                epilogue(la, v, m, n0, lane, s_rinv);
-            });
     Ctx cx;
     cx.G = 8 * Gx;
     cx.j = xcd * Gx + (blockIdx.x >> 3);
     cx.lds = lds;
+    AttnPlan plan;
+    auto make_plan = [&]() {       // (while the first weights are on their way)
+        const ArgPtr la = late_args();
+        plan = attn_plan(la->nh, (la->kv_len + la->M + 63) >> 6, AttnOf<MT, D>::TMIN, cx.j, cx.G);
+    };
+    if (c0 >= c1) make_plan();
+    else
+        gemm_group<MT, R, 8, false, stretches_whole(MT, R)>(
+            h, lds, c0, c1 - c0, 0, nks, make_plan,
+            [&](ArgPtr la, int, floatx4 v, int m, int n0, const float* s_rinv) {
+                epilogue(la, v, m, n0, lane, s_rinv);
+            });
     // ---- the XCD's workgroups meet.  Every one of them counts itself in once its part of
     //      q16 and of the cache rows is acknowledged by the L2 they share (the wait below
     //      covers loads too, so it comes before the attention requests anything) ...
@@ -66,7 +72,7 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
         if (threadIdx.x == 0)
             *s_ok = last ? same_xcd(a.sync, word, (uint32_t)Gx)
                         : bounded_wait(a.sync, go + cx.j * kCntStride, round, (uint32_t)Gx, 3000u);
-        __syncthreads();
+        barrier_lds();
         if (!*s_ok) return false;
         // Nothing of q16 or of the tree's cache rows should be in this compute unit's L1 (it
         // has not read them in this launch); dropping the L1's contents makes that independent
@@ -75,7 +81,8 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
         invalidate_l1();
         return true;
     };
-    attn_phase<MT, D, true>(a, cx, a.att_q, a.att_k, a.att_v, a.att_out, a.att_epoch, gate);
+    attn_phase<MT, D, true>(a, cx, plan, a.att_q, a.att_k, a.att_v, a.att_out, a.att_epoch, gate);
+    wait_loads<0>();       // (nothing is on its way to the LDS when the workgroup ends)
 }
 
 // the instantiations for one number of row tiles of x: head dim 128, wide QKV matrices of 3

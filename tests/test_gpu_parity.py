@@ -252,6 +252,21 @@ def test_tree_attention(B, model, orc32, M, nh, d, kv_len, tree):
     assert ok, (ma, mr)
 
 
+# Above 32 rows: row tiles that are full, begun and absent (33, 48, 49, 64, 65, 81, 128); one tile of keys and
+# one more or fewer than a workgroup has buffers for (4 of 128 channels, 8 of 64), heads of one part and heads
+# in parts of unequal length (256 heads: one workgroup each; 1 head: 32 of them), keys that end inside
+# a piece of 8.  Tolerance as above.
+@pytest.mark.parametrize("M,nh,d,kv_len,tree", [
+    (33, 256, 64, 0, "rand5"), (33, 256, 64, 479, "rand5"), (48, 256, 64, 481, "chain"), (64, 256, 64, 540, "wide"),
+    (49, 256, 128, 79, "rand5"), (64, 256, 128, 128, "rand5"), (64, 256, 128, 192, "chain"), (64, 256, 128, 257, "rand5"),
+    (65, 256, 128, 190, "rand5"), (81, 256, 128, 240, "star"), (65, 256, 64, 449, "rand5"), (128, 256, 64, 385, "chain"),
+    (33, 1, 128, 4091, "rand5"), (64, 1, 64, 8190, "rand5"), (128, 1, 128, 8063, "rand5"), (97, 9, 64, 2047, "chain"),
+    (34, 20, 128, 30, "rand5"), (113, 24, 128, 1500, "rand5"),
+])
+def test_tree_attention_tile_ring(B, model, orc32, M, nh, d, kv_len, tree):
+    test_tree_attention(B, model, orc32, M, nh, d, kv_len, tree)
+
+
 @pytest.mark.parametrize("M,nh,d,kv_len,tree", [(8, 4, 64, 128, "rand3"), (40, 3, 128, 333, "rand5"),
                                                 (64, 8, 128, 1000, "chain")])
 def test_tree_attention_token_major_keys(B, model, orc32, M, nh, d, kv_len, tree):
