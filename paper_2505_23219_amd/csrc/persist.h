@@ -104,13 +104,15 @@ __device__ __forceinline__ bool bounded_wait(uint32_t* sync, uint32_t* p, uint32
 {
     uint32_t v = poll(p);
     if ((v & 0xffffu) < target) {
+        // (whether another workgroup has given up is looked at now and then only: a load from behind the
+        // L2 in every turn made the turns three times as long, and what is waited for is seen that much later)
         const long long t0 = wall_clock64();
-        while (((v = poll(p)) & 0xffffu) < target) {
-            if (wall_clock64() - t0 > kWaitTicks || ld_relaxed(sync + kSyncStatus) != 0) {
+        for (int turn = 1; ((v = poll(p)) & 0xffffu) < target; ++turn) {
+            if (wall_clock64() - t0 > kWaitTicks || (turn % 64 == 0 && ld_relaxed(sync + kSyncStatus) != 0)) {
                 atomicCAS(sync + kSyncStatus, 0u, code);
                 return false;
             }
-            __builtin_amdgcn_s_sleep(8);
+            __builtin_amdgcn_s_sleep(1);
         }
     }
     return same_xcd(sync, v, n);

@@ -53,14 +53,16 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
     __syncthreads();       // also: the linear phase's use of the LDS is over
     bool last = false;
     uint32_t word = 0;
-    if (threadIdx.x == 0) {
-        word = arrive(epoch_word(cnt, a.att_epoch));
+    if (threadIdx.x < 64) {
+        // (a line a lane: one lane storing to all of them kept the others waiting 1.5 us longer)
+        if (lane == 0) word = arrive(epoch_word(cnt, a.att_epoch));
+        word = (uint32_t)__builtin_amdgcn_readfirstlane((int)word);
         last = (word & 0xffffu) == (uint32_t)Gx;
         if (last) {
-            for (int w = 0; w < Gx; ++w)
-                __hip_atomic_store(go + (xcd * Gx + w) * kCntStride, (word & 0xffff0000u) | round, __ATOMIC_RELAXED,
+            if (lane < Gx)
+                __hip_atomic_store(go + (xcd * Gx + lane) * kCntStride, (word & 0xffff0000u) | round, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
-            clear_next(cnt, a.att_epoch);
+            if (lane == 0) clear_next(cnt, a.att_epoch);
         }
     }
     // ... and waits for the others at the attention's gate, after it has set up its indices
