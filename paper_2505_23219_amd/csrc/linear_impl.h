@@ -112,8 +112,8 @@ __host__ __device__ constexpr int stretches_parts(int MT, int R) { return folded
 constexpr int kFirstSet = 18;
 
 // What the residual epilogue reads: four columns of a row of the residual stream and of the next
-// norm's gain.  (Requested behind the stream's first loads, or before the wait for the other
-// parts, they delay the weights behind them by more than they save: 0.9% of a 64-row step.)
+// norm's gain.  (Requested behind the stream's first loads they delay the weights behind them by more
+// than they save: 0.9% of a 64-row step.)
 struct ResidOperands {
     floatx4 x;
     half4 g;
@@ -129,117 +129,151 @@ __device__ __forceinline__ ResidOperands resid_operands(ArgPtr a, int m, int n0)
 }
 
 // ---------------------------------------------------------------------------
-// epilogue of one 16x16 output fragment: lane (c, g4) holds y[m][n0 .. n0+3]
+// epilogue of NB 16x16 output fragments: lane (c, g4) holds y[m][n0 .. n0+3] of each; m past the last row
+// stands for no fragment.  What is worked out is worked out for all of them before any is stored: with one
+// or two wavefronts on a SIMD a fragment by itself is one chain of latencies.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void epilogue(ArgPtr a, floatx4 v, int m, int n0, int lane, const float* s_rinv)
+template <int NB>
+__device__ __forceinline__ void epilogue(ArgPtr a, floatx4 (&v)[NB], int (&m)[NB], int (&n0)[NB], int lane, const float* s_rinv,
+                                         const ResidOperands* ahead = nullptr)
 {
-    // Everything below depends on the fragment's position: the (empty) asm keeps the compiler
+    // Everything below depends on the fragments' positions: the (empty) asm keeps the compiler
     // from working parts of it out ahead of the weight stream, before the kernel's first loads.
-    asm volatile("" : "+v"(m), "+v"(n0));
-    const bool mok = m < a->M;
-    const int mtp = a->Mpad >> 4, N = a->lin_N, epi = a->lin_epi;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) asm volatile("" : "+v"(m[i]), "+v"(n0[i]));
+    const int M = a->M, mtp = a->Mpad >> 4, N = a->lin_N, epi = a->lin_epi;
     const int64_t ldo = a->lin_ldy;
-    if (a->lin_rscale) v *= s_rinv[m];
+    if (a->lin_rscale) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) v[i] *= s_rinv[min(m[i], GHD_MAX_M - 1)];
+    }
     if (epi == EPI_STORE_F32) {
         if (a->lin_amax) {
-            // the row's best output among this tile's 16 columns: (largest value, lowest column).
+            // the row's best output among a tile's 16 columns: (largest value, lowest column).
             // Greedy acceptance (section 2.3) only needs the row argmax, so the finish of the
             // LM head leaves one candidate per tile and row instead of (or besides) the logits.
-            float bv = -INFINITY;
-            int bi = 0x7fffffff;
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (n0 + r < N && v[r] > bv) {
-                    bv = v[r];
-                    bi = n0 + r;
-                }
+            for (int i = 0; i < NB; ++i) {
+                float bv = -INFINITY;
+                int bi = 0x7fffffff;
 #pragma unroll
-            for (int off = 16; off < 64; off <<= 1) {
-                const float ov = __shfl_xor(bv, off);
-                const int oi = __shfl_xor(bi, off);
-                if (ov > bv || (ov == bv && oi < bi)) {
-                    bv = ov;
-                    bi = oi;
+                for (int r = 0; r < 4; ++r)
+                    if (n0[i] + r < N && v[i][r] > bv) {
+                        bv = v[i][r];
+                        bi = n0[i] + r;
+                    }
+#pragma unroll
+                for (int off = 16; off < 64; off <<= 1) {
+                    const float ov = __shfl_xor(bv, off);
+                    const int oi = __shfl_xor(bi, off);
+                    if (ov > bv || (ov == bv && oi < bi)) {
+                        bv = ov;
+                        bi = oi;
+                    }
                 }
-            }
-            if (lane < 16 && mok) {
-                const floatx2 best = {bv, __int_as_float(bi)};
-                *(GLOBAL floatx2*)(gp((float*)a->lin_amax) + ((size_t)(n0 >> 4) * a->Mpad + m) * 2) = best;
+                if (lane < 16 && m[i] < M) {
+                    const floatx2 best = {bv, __int_as_float(bi)};
+                    *(GLOBAL floatx2*)(gp((float*)a->lin_amax) + ((size_t)(n0[i] >> 4) * a->Mpad + m[i]) * 2) = best;
+                }
             }
         }
-        if (!mok || !a->lin_y) return;
-        auto o = gp((float*)a->lin_y) + (size_t)m * ldo + n0;
-        if (n0 + 3 < N && (ldo & 3) == 0) *(GLOBAL floatx4*)o = v;
-        else
-            for (int r = 0; r < 4; ++r)
-                if (n0 + r < N) o[r] = v[r];
+        if (!a->lin_y) return;
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            if (m[i] >= M) continue;
+            auto o = gp((float*)a->lin_y) + (size_t)m[i] * ldo + n0[i];
+            if (n0[i] + 3 < N && (ldo & 3) == 0) *(GLOBAL floatx4*)o = v[i];
+            else
+                for (int r = 0; r < 4; ++r)
+                    if (n0[i] + r < N) o[r] = v[i][r];
+        }
     } else if (epi == EPI_STORE_F16) {
-        if (!mok) return;
-        auto o = gp((half_t*)a->lin_y) + (size_t)m * ldo + n0;
-        for (int r = 0; r < 4; ++r)
-            if (n0 + r < N) o[r] = (half_t)v[r];
-    } else if (epi == EPI_RESID) {
-        // x += y; sums of squares of the new x over this tile's 16 columns, per row
-        float s = 0.f;
-        if (mok && n0 < N) {
-            const ResidOperands r = resid_operands(a, m, n0);
-            const floatx4 xn = r.x + v;
-            *(GLOBAL floatx4*)(gp((float*)a->lin_y) + (size_t)m * ldo + n0) = xn;
-            s = xn[0] * xn[0] + xn[1] * xn[1] + xn[2] * xn[2] + xn[3] * xn[3];
-            if (a->lin_gnext) {
-                half4 o;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) o[q] = (half_t)(xn[q] * (float)r.g[q] * kXgScale);
-                *(GLOBAL half4*)(gp(a->xg16) + xpk_index(m, n0, mtp)) = o;
-            }
+        for (int i = 0; i < NB; ++i) {
+            if (m[i] >= M) continue;
+            auto o = gp((half_t*)a->lin_y) + (size_t)m[i] * ldo + n0[i];
+            for (int r = 0; r < 4; ++r)
+                if (n0[i] + r < N) o[r] = (half_t)v[i][r];
         }
-        s += __shfl_xor(s, 16);
-        s += __shfl_xor(s, 32);
-        if (lane < 16 && n0 < N) gp(a->ss)[(size_t)(n0 >> 4) * a->Mpad + m] = s;
+    } else if (epi == EPI_RESID) {
+        // x += y; sums of squares of the new x over a tile's 16 columns, per row
+        ResidOperands ops[NB];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) ops[i] = ahead ? ahead[i] : resid_operands(a, m[i], n0[i]);
+        floatx4 xn[NB];
+        half4 o[NB];
+        float sq[NB];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            xn[i] = ops[i].x + v[i];
+            sq[i] = m[i] < M && n0[i] < N ? xn[i][0] * xn[i][0] + xn[i][1] * xn[i][1] + xn[i][2] * xn[i][2] + xn[i][3] * xn[i][3] : 0.f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) o[i][q] = (half_t)(xn[i][q] * (float)ops[i].g[q] * kXgScale);
+            sq[i] += __shfl_xor(sq[i], 16);
+            sq[i] += __shfl_xor(sq[i], 32);
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            if (n0[i] < N && m[i] < M) {
+                *(GLOBAL floatx4*)(gp((float*)a->lin_y) + (size_t)m[i] * ldo + n0[i]) = xn[i];
+                if (a->lin_gnext) *(GLOBAL half4*)(gp(a->xg16) + xpk_index(m[i], n0[i], mtp)) = o[i];
+            }
+            // (rows past M too, of the tiles that there are: the next norm adds them up)
+            if (lane < 16 && n0[i] < N && m[i] < a->Mpad) gp(a->ss)[(size_t)(n0[i] >> 4) * a->Mpad + m[i]] = sq[i];
+        }
     } else if (epi == EPI_SWIGLU) {
         // packed rows: (gate f, gate f+1, up f, up f+1)
-        if (!mok) return;
-        int f = (n0 >> 4) * 8 + ((n0 & 15) >> 2) * 2;
-        if (f >= a->F) return;
         // silu with the hardware's exp2 and reciprocal: a few ulp, far below the fp16 rounding
         // of the result (and 0.3 us per launch on the critical path)
-        float a0 = __fdividef(v[0], 1.0f + __expf(-v[0])) * v[2];
-        float a1 = __fdividef(v[1], 1.0f + __expf(-v[1])) * v[3];
-        half2_ h = {(half_t)a0, (half_t)a1};
-        *(GLOBAL half2_*)(gp((half_t*)a->lin_y) + xpk_index(m, f, mtp)) = h;
+        half2_ h[NB];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const float a0 = __fdividef(v[i][0], 1.0f + __expf(-v[i][0])) * v[i][2];
+            const float a1 = __fdividef(v[i][1], 1.0f + __expf(-v[i][1])) * v[i][3];
+            h[i] = (half2_){(half_t)a0, (half_t)a1};
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int f = (n0[i] >> 4) * 8 + ((n0[i] & 15) >> 2) * 2;
+            if (m[i] < M && f < a->F) *(GLOBAL half2_*)(gp((half_t*)a->lin_y) + xpk_index(m[i], f, mtp)) = h[i];
+        }
     } else {   // EPI_QKV: packed rows of a head: (j, j+1, j+d/2, j+1+d/2)
-        if (!mok || n0 >= N) return;
-        const int nh = a->nh, d = a->d;
-        const int H = nh * d, hd = d >> 1;
-        const QkvRow qr = qkv_row(n0, nh, d);
-        const int part = qr.part, head = qr.head, ph = qr.ph;
-        int jj = (ph >> 2) * 2;
-        float o0 = v[0], o1 = v[1], o2 = v[2], o3 = v[3];
-        if (part < 2) {
+        const int nh = a->nh, d = a->d, H = nh * d, hd = d >> 1;
+        QkvRow qr[NB];
+        floatx4 cs[NB];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            qr[i] = qkv_row(n0[i], nh, d);
             // (cos, sin) of channels jj and jj + 1 (jj is even: 16 bytes, aligned)
-            const floatx4 cs = *(GLOBAL const floatx4*)(gp((const float*)a->rope) + ((size_t)m * hd + jj) * 2);
-            o0 = v[0] * cs[0] - v[2] * cs[1];
-            o2 = v[2] * cs[0] + v[0] * cs[1];
-            o1 = v[1] * cs[2] - v[3] * cs[3];
-            o3 = v[3] * cs[2] + v[1] * cs[3];
+            cs[i] = (floatx4){1.f, 0.f, 1.f, 0.f};
+            if (m[i] < M && qr[i].part < 2)
+                cs[i] = *(GLOBAL const floatx4*)(gp((const float*)a->rope) + ((size_t)m[i] * hd + (qr[i].ph >> 2) * 2) * 2);
         }
-        if (part == 2) {
-            // V is kept channel-major: row kv_len + m of channels jj, jj+1, jj+d/2, jj+1+d/2
-            auto col = gp(a->lin_vc) + (size_t)head * a->v_stride_head + (size_t)(a->kv_len + m);
-            col[(size_t)jj * a->v_stride_ch] = (half_t)o0;
-            col[(size_t)(jj + 1) * a->v_stride_ch] = (half_t)o1;
-            col[(size_t)(jj + hd) * a->v_stride_ch] = (half_t)o2;
-            col[(size_t)(jj + 1 + hd) * a->v_stride_ch] = (half_t)o3;
-            return;
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            if (m[i] >= M || n0[i] >= N) continue;
+            const int part = qr[i].part, head = qr[i].head, jj = (qr[i].ph >> 2) * 2;
+            if (part == 2) {
+                // V is kept channel-major: row kv_len + m of channels jj, jj+1, jj+d/2, jj+1+d/2
+                auto col = gp(a->lin_vc) + (size_t)head * a->v_stride_head + (size_t)(a->kv_len + m[i]);
+                col[(size_t)jj * a->v_stride_ch] = (half_t)v[i][0];
+                col[(size_t)(jj + 1) * a->v_stride_ch] = (half_t)v[i][1];
+                col[(size_t)(jj + hd) * a->v_stride_ch] = (half_t)v[i][2];
+                col[(size_t)(jj + 1 + hd) * a->v_stride_ch] = (half_t)v[i][3];
+                continue;
+            }
+            const float o0 = v[i][0] * cs[i][0] - v[i][2] * cs[i][1], o2 = v[i][2] * cs[i][0] + v[i][0] * cs[i][1];
+            const float o1 = v[i][1] * cs[i][2] - v[i][3] * cs[i][3], o3 = v[i][3] * cs[i][2] + v[i][1] * cs[i][3];
+            auto dst = (part == 0)
+                           ? gp(a->q16) + (size_t)m[i] * H + head * d + jj
+                           : gp(a->lin_kc) + (size_t)head * a->stride_head + (size_t)(a->kv_len + m[i]) * a->stride_tok + jj;
+            *(GLOBAL half2_*)dst = (half2_){(half_t)o0, (half_t)o1};
+            *(GLOBAL half2_*)(dst + hd) = (half2_){(half_t)o2, (half_t)o3};
         }
-        auto dst = (part == 0)
-                       ? gp(a->q16) + (size_t)m * H + head * d + jj
-                       : gp(a->lin_kc) + (size_t)head * a->stride_head + (size_t)(a->kv_len + m) * a->stride_tok + jj;
-        half2_ lo = {(half_t)o0, (half_t)o1}, hi = {(half_t)o2, (half_t)o3};
-        *(GLOBAL half2_*)dst = lo;
-        *(GLOBAL half2_*)(dst + hd) = hi;
     }
 }
+
+constexpr int kNoRow = 1 << 20;      // m of a fragment that is not there
 
 template <int MT, int R, int NW>
 struct LinShape {
@@ -248,6 +282,7 @@ struct LinShape {
     static constexpr int CAP = 128 / NW;                     // ... reduced per round through LDS, at most
     static constexpr int ROUNDS = (NF + CAP - 1) / CAP;
     static constexpr int FR = (NF + ROUNDS - 1) / ROUNDS;    // ... and per round
+    static constexpr int NB = NW == 4 ? 4 : FR > NW ? 2 : 1; // that a wavefront finishes at a time
     static constexpr size_t small_bytes = (128 + 1024 + 4) * sizeof(float);
     // HALVED: fragments of the first half that a wavefront keeps in the LDS; the rest stay in registers
     static constexpr int ROOM = (160 * 1024 - (int)small_bytes) / (NW * 1024);
@@ -262,8 +297,9 @@ struct LinShape {
 // One workgroup's share: the tiles first .. first + count - 1 (count <= R; the other slots
 // re-read the first tile, and what they accumulate is never looked at) over the k-steps
 // k0 .. k1 - 1.  `finish(a, f, v, m, n0, s_rinv)` is called by one wavefront for every
-// fragment f = slot * MT + row tile with the workgroup's sum v; `early()` runs between the
-// stream's first loads and its first wait.
+// fragment f = slot * MT + row tile with the workgroup's sum v, up to two fragments at a time (one that is
+// not there has a row past all others); `early()` runs between the stream's first loads and its first
+// wait.
 //
 // ROWS: x is row-major and read as it lies (16 rows x 64 bytes per load), which saves a
 // separate packing launch; columns from K on are not read.  STRETCHES: see folded().
@@ -539,19 +575,32 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
         for (int ff = 0; ff < FR; ++ff)
             if (r0 + ff < NF) red[(wave * FR + ff) * 64 + lane] = acc[(r0 + ff) / MT][(r0 + ff) % MT];
         __syncthreads();
-        for (int ff = wave; ff < FR && r0 + ff < NF; ff += NW) {
+        constexpr int NB = S::NB;
+#pragma unroll 1
+        for (int f0 = 0; f0 < FR; f0 += NB * NW) {
+            floatx4 v[NB], part[NB][NW];
+            int f[NB], m[NB], n0[NB];
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const int ff = f0 + i * NW + wave;
+                f[i] = r0 + ff;
+                const int t = f[i] / MT, b = f[i] % MT;
+                m[i] = ff < FR && f[i] < NF && t < count ? b * 16 + c : kNoRow;
+                n0[i] = (first + t) * 16 + g4 * 4;
+                // (what is read for a fragment that is not there is not looked at)
+#pragma unroll
+                for (int w = 0; w < NW; ++w) part[i][w] = red[(w * FR + min(ff, FR - 1)) * 64 + lane];
+            }
             // (pairs of pairs: half the roundings of one sum after the other)
-            floatx4 part[NW];
 #pragma unroll
-            for (int w = 0; w < NW; ++w) part[w] = red[(w * FR + ff) * 64 + lane];
+            for (int i = 0; i < NB; ++i) {
 #pragma unroll
-            for (int d = 1; d < NW; d *= 2)
+                for (int d = 1; d < NW; d *= 2)
 #pragma unroll
-                for (int w = 0; w < NW; w += 2 * d) part[w] += part[w + d];
-            const floatx4 v = part[0];
-            const int f = r0 + ff, t = f / MT, b = f % MT;
-            if (t >= count) continue;
-            finish(a, f, v, b * 16 + c, (first + t) * 16 + g4 * 4, s_rinv);
+                    for (int w = 0; w < NW; w += 2 * d) part[i][w] += part[i][w + d];
+                v[i] = part[i][0];
+            }
+            finish(a, f, v, m, n0, s_rinv);
         }
     }
 }
@@ -596,9 +645,7 @@ __global__ __launch_bounds__(waves_of(MT, R) * 64) void k_linear(const half8* W,
     const int lane = threadIdx.x & 63;
     gemm_group<MT, R, waves_of(MT, R), ROWS, stretches_whole(MT, R)>(
         h, lds, c0, c1 - c0, 0, nks, solo,
-        [&](ArgPtr a, int, floatx4 v, int m, int n0, const float* s_rinv) {
-            epilogue(a, v, m, n0, lane, s_rinv);
-        });
+        [&](ArgPtr a, auto&, auto& v, auto& m, auto& n0, const float* s_rinv) { epilogue(a, v, m, n0, lane, s_rinv); });
 }
 
 // ---- parts --------------------------------------------------------------------------
@@ -616,7 +663,7 @@ __global__ __launch_bounds__(512) void k_linear_parts(const half8* W, const half
     const int first = (bx * 8 + xcd) * R;
     if (first >= ntiles) return;
     const int count = min(R, ntiles - first);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int k0 = nks * part / S, k1 = nks * (part + 1) / S;
     constexpr int NF = R * MT;
     const int f0 = count * MT * part / S, f1 = count * MT * (part + 1) / S;     // what this part finishes
@@ -626,8 +673,9 @@ __global__ __launch_bounds__(512) void k_linear_parts(const half8* W, const half
     const int slot0 = bx * S * 8 + xcd;
     gemm_group<MT, R, 8, false, stretches_parts(MT, R)>(
         h, lds, first, count, k0, k1, []() {},
-        [&](ArgPtr a, int f, floatx4 v, int, int, const float*) {
-            *(GLOBAL floatx4*)(gp(a->part) + ((size_t)(slot0 + part * 8) * NF + f) * 256 + lane * 4) = v;
+        [&](ArgPtr a, auto& f, auto& v, auto& m, auto&, const float*) {
+            for (int i = 0; i < (int)(sizeof(f) / sizeof(f[0])); ++i)
+                if (m[i] != kNoRow) *(GLOBAL floatx4*)(gp(a->part) + ((size_t)(slot0 + part * 8) * NF + f[i]) * 256 + lane * 4) = v[i];
         });
     const ArgPtr a = late_args();
     const float* s_rinv = (const float*)(lds + LinShape<MT, R, 8>::template red_bytes<(stretches_parts(MT, R) > 1)>);
@@ -639,6 +687,17 @@ __global__ __launch_bounds__(512) void k_linear_parts(const half8* W, const half
     };
     wait_own_stores();                       // the partials are in the L2
     __syncthreads();
+    // What the residual epilogue reads is requested while the workgroup waits, where there is much of it, but not by
+    // the wavefront that polls (loads return in order: its polls would come back behind them): the last
+    // wavefront has the first fragment.  [5120, 13824] at 64 rows and [4096, 11008]: 0.5 us a launch.
+    constexpr bool AHEAD = MT > 2;
+    const int mine = f0 + (AHEAD ? 7 - wave : wave);
+    ResidOperands ops[1] = {};
+    int m[1], n0[1];
+    if (AHEAD && wave != 0 && mine < f1 && a->lin_epi == EPI_RESID) {
+        position(mine, m, n0);
+        ops[0] = resid_operands(a, m[0], n0[0]);
+    }
     uint32_t* const cnt = a->sync + a->lin_cnt + slot0 * kCntStride;
     if (tid == 0) {
         uint32_t* const word = epoch_word(cnt, a->lin_epoch);
@@ -648,11 +707,13 @@ __global__ __launch_bounds__(512) void k_linear_parts(const half8* W, const half
     }
     __syncthreads();
     if (!*s_wait_ok) return;                 // the other parts never arrived: nothing sensible to write
-    for (int f = f0 + wave; f < f1; f += 8) {
+    for (int f = mine; f < f1; f += 8) {
         // the parts in index order (fixed order: the result does not depend on timing), eight
         // loads in flight at a time
         const auto src = gp((const float*)a->part) + ((size_t)slot0 * NF + f) * 256 + lane * 4;
-        floatx4 v = {0.f, 0.f, 0.f, 0.f};
+        position(f, m, n0);
+        if ((!AHEAD || wave == 0 || f != mine) && a->lin_epi == EPI_RESID) ops[0] = resid_operands(a, m[0], n0[0]);
+        floatx4 v[1] = {{0.f, 0.f, 0.f, 0.f}};
         for (int p0 = 0; p0 < S; p0 += 8) {
             floatx4 t[8];
 #pragma unroll
@@ -660,11 +721,9 @@ __global__ __launch_bounds__(512) void k_linear_parts(const half8* W, const half
                 if (p0 + q < S) t[q] = *(GLOBAL const floatx4*)(src + (size_t)(p0 + q) * (8 * NF * 256));
 #pragma unroll
             for (int q = 0; q < 8; ++q)
-                if (p0 + q < S) v += t[q];
+                if (p0 + q < S) v[0] += t[q];
         }
-        int m, n0;
-        position(f, &m, &n0);
-        epilogue(a, v, m, n0, lane, s_rinv);
+        epilogue(a, v, m, n0, lane, s_rinv, ops);
     }
 }
 

@@ -36,9 +36,7 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
     else
         gemm_group<MT, R, 8, false, stretches_whole(MT, R)>(
             h, lds, c0, c1 - c0, 0, nks, make_plan,
-            [&](ArgPtr la, int, floatx4 v, int m, int n0, const float* s_rinv) {
-                epilogue(la, v, m, n0, lane, s_rinv);
-            });
+            [&](ArgPtr la, auto&, auto& v, auto& m, auto& n0, const float* s_rinv) { epilogue(la, v, m, n0, lane, s_rinv); });
     // ---- the XCD's workgroups meet.  Every one of them counts itself in once its part of
     //      q16 and of the cache rows is acknowledged by the L2 they share (the wait below
     //      covers loads too, so it comes before the attention requests anything) ...

@@ -36,6 +36,26 @@ def test_linear_kernels_at_their_edges(B, M):
     assert len(kinds) >= 5, kinds
 
 
+@pytest.mark.parametrize("M", [33, 49, 65, 97, 128])
+@pytest.mark.parametrize("out16", [False, True])
+def test_shares_whose_fragments_are_finished_several_at_a_time(B, M, out16):
+    """Shares of six, seven and eight tiles, whose fragments are odd and even in number for a wavefront of eight or
+    of four.  fp32 results: as above; fp16: each rounded once, by 2^-11 of itself at most, as is
+    then the 2-norm of the errors."""
+    say("several fragments", M, out16)
+    for N, K in [(24010, 96), (28001, 96), (32000, 96)]:
+        g = torch.Generator(device="cuda").manual_seed(N + M)
+        x = torch.randn((M, K), generator=g, device="cuda").to(torch.float16)
+        W = (torch.randn((N, K), generator=g, device="cuda") * 0.02).to(torch.float16)
+        ws = B.workspace(B.lib().ghd_linear_workspace_bytes(M, N, K))
+        ws.fill_(0xFF)
+        y = torch.full((M, N), float("nan"), dtype=torch.float16 if out16 else torch.float32, device="cuda")
+        B.ghd_linear_skinny(x, B.ghd_pack_weight(W), N, ws=ws, y=y)
+        ref = x.double() @ W.double().t()
+        err = float((y.double() - ref).norm() / ref.norm())
+        assert err < (2.0 ** -11 if out16 else max(2e-7, 4 * 2.0 ** -24 * K ** 0.5)), (N, K, err)
+
+
 def test_every_stream_gives_the_same_result(B):
     """The XCD that a dispatch begins with depends on the hardware queue it goes through.
     Several streams in turn (more than there are queues), each with a small launch of its own in
