@@ -136,8 +136,15 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+# The handle of the calling thread's current stream on its current device, without the Stream object that
+# torch.cuda.current_stream() makes of it (2.7 us a call on an EPYC host, as long as a launch; 0.3 us this way).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dev(t: torch.Tensor, dtype) -> torch.Tensor:
