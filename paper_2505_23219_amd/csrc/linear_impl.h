@@ -578,6 +578,7 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
         constexpr int NB = S::NB;
 #pragma unroll 1
         for (int f0 = 0; f0 < FR; f0 += NB * NW) {
+            if (f0 + wave >= FR || r0 + f0 + wave >= NF || (r0 + f0 + wave) / MT >= count) break;     // (nor any later one)
             floatx4 v[NB], part[NB][NW];
             int f[NB], m[NB], n0[NB];
 #pragma unroll
