@@ -465,11 +465,16 @@ static ghd_status attention_call(void* out, const void* q, const void* k_cache, 
     if (ws_bytes < ghd_attention_workspace_bytes(M, kv_len, nh, d)) return GHD_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     Ws w = carve(ws, 2, M, 0, 0, d);
-    ghd_status s = launch_fused_setup(w.sync, parent_dev, M, mpad_of(M), kv_len, d, 1.f, w.mask,
-                                      nullptr, nullptr, nullptr, 0, nullptr, nullptr, nullptr, st);
-    if (s) return s;
+    const bool alone = attention_alone(M, kv_len, d);
+    if (!alone) {
+        ghd_status s = launch_fused_setup(w.sync, parent_dev, M, mpad_of(M), kv_len, d, 1.f, w.mask,
+                                          nullptr, nullptr, nullptr, 0, nullptr, nullptr, nullptr, st);
+        if (s) return s;
+    }
     FusedArgs a = {};
     a.mode = MODE_ATTN;
+    a.att_alone = alone;
+    a.att_parent = alone ? parent_dev : nullptr;
     a.M = M;
     a.Mpad = mpad_of(M);
     a.kv_len = kv_len;

@@ -133,6 +133,39 @@ __device__ __forceinline__ float over_groups(float x, Op op)
 __device__ __forceinline__ float max_over_groups(float x) { return over_groups(x, [](float a, float b) { return fmaxf(a, b); }); }
 __device__ __forceinline__ float sum_over_groups(float x) { return over_groups(x, [](float a, float b) { return a + b; }); }
 
+// The ancestor masks of a tree in LDS (mask[2 * node], low and high word) from parent[], by pointer doubling: after
+// round k a node has its 2^k nearest ancestors-or-self and the node 2^k edges up.  All threads call; a barrier
+// is left to the caller.  A parent that is not an earlier node is taken as "no parent".
+__device__ __forceinline__ void masks_from_parent(GLOBAL const int32_t* parent, int M, uint64_t* mask, int32_t* s_up)
+{
+    const int i = threadIdx.x;
+    int up = -1;
+    uint64_t lo = 0, hi = 0;
+    if (i < M) {
+        up = parent[i];
+        if (up < 0 || up >= i) up = -1;
+        if (i < 64) lo = 1ull << i; else hi = 1ull << (i - 64);
+    }
+    for (int span = 1; span < M; span <<= 1) {
+        if (i < M) {
+            mask[2 * i] = lo;
+            mask[2 * i + 1] = hi;
+            s_up[i] = up;
+        }
+        barrier_lds();
+        if (up >= 0) {
+            lo |= mask[2 * up];
+            hi |= mask[2 * up + 1];
+            up = s_up[up];
+        }
+        barrier_lds();
+    }
+    if (i < M) {
+        mask[2 * i] = lo;
+        mask[2 * i + 1] = hi;
+    }
+}
+
 // `gate` is called once by every workgroup (all threads), before the first read of q or of a
 // cache row from kv_len on; it returns false if the launch is to be abandoned.  A kernel that
 // produces those in the same launch waits there for their producers; with PREFETCH a
@@ -151,6 +184,7 @@ struct DirectLds {
     floatx4 o[8][MT][D / 16][64];                    // the wavefronts' outputs, when they are merged
     float m[8][MT][16], l[8][MT][16];                // ... and their softmax statistics
     uint64_t mask[MT * 16][2];
+    int32_t up[MT * 16];
     int wait_ok;                                     // thread 0's verdict on a bounded wait, for the whole workgroup
 };
 
@@ -256,7 +290,7 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const A
     uint64_t mask_lo = 0, mask_hi = 0;
     {
         const auto mask = gp(a.mask);
-        if (tid < M) {
+        if (tid < M && !a.att_parent) {
             mask_lo = mask[2 * tid];
             mask_hi = mask[2 * tid + 1];
         }
@@ -327,7 +361,8 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const A
             load_v(u);
         }
         pin_order();           // (all requests are out before the first of them is waited for)
-        if (tid < MT * 16) {
+        if (!PREFETCH && a.att_parent) masks_from_parent(gp(a.att_parent), M, &sm.mask[0][0], sm.up);
+        else if (tid < MT * 16) {
             sm.mask[tid][0] = mask_lo;
             sm.mask[tid][1] = mask_hi;
         }
@@ -484,7 +519,8 @@ struct StagedLds {
     static constexpr int NB = D == 128 ? 4 : 8;        // tile buffers
     static constexpr uint32_t KB = 64 * D * 2;         // bytes of a tile's K, and of its V^T
     char tile[NB][2 * KB];
-    uint32_t mask[GHD_MAX_M * 4];
+    alignas(8) uint32_t mask[GHD_MAX_M * 4];
+    int32_t up[GHD_MAX_M];
     int wait_ok;                                       // thread 0's verdict on a bounded wait, for the whole workgroup
     // what the two wavefronts of a row tile exchange when a head ends: their softmax statistics and, in a
     // tile buffer that is free then, half of their output fragments
@@ -516,15 +552,6 @@ __device__ __forceinline__ void wait_loads()
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | (N >> 4) << 14);
 }
 
-// a barrier that waits for this wavefront's own use of the LDS, but not for what it has requested (which
-// __syncthreads() would, had any of it the LDS for its destination)
-__device__ __forceinline__ void barrier_lds()
-{
-    pin_order();
-    __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0)
-    __builtin_amdgcn_s_barrier();
-    pin_order();
-}
 // ... until all but its youngest n tiles are there (n <= MOST; uniform)
 template <int PER_TILE, int MOST>
 __device__ __forceinline__ void wait_tiles_of(int n)
@@ -623,7 +650,7 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const A
         if (!gated) {
             // (loads return in order: the wavefront that polls at the gate requests nothing before)
             const bool polls = PREFETCH && wave == 0;
-            if (!polls) request_masks();
+            if (!polls && !a.att_parent) request_masks();
             if constexpr (PREFETCH)
                 for (; !polls && n_pre < up_front && (t0 + n_pre) * 64 + 128 <= kv_len; ++n_pre) request(t0 + n_pre);
             if (!gate()) return false;
@@ -637,6 +664,8 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const A
             for (int ds = 0; ds < DS; ++ds) to_lds((GLOBAL const char*)q, off + ds * 64, at + ds * 1024);
         }
         for (int n = n_pre; n < up_front; ++n) request(t0 + n);
+
+        if (!PREFETCH && a.att_parent) masks_from_parent(gp(a.att_parent), M, (uint64_t*)sm.mask, sm.up);
 
         // waits for all but the youngest n tiles
         auto wait_tiles = [&](int n) {

@@ -176,6 +176,8 @@ struct FusedArgs {
     const half_t *att_q, *att_k, *att_v;
     half_t* att_out;
     int att_out_packed;    // output in the packed activation layout (else row-major [M, nh, d])
+    const int32_t* att_parent;   // the tree, where the attention works the masks out by itself (see attention_alone)
+    int att_alone;         // no head is shared and there was no set-up launch
     int64_t lin_ldx;       // lin_row_major: elements from row to row of lin_x
     int lin_row_major;     // lin_x is the caller's row-major array (a call of its own), else packed
     int lin_solo;          // a whole-tile call of its own: there was no set-up launch
@@ -200,6 +202,8 @@ __host__ __device__ constexpr int row_tiles(int M)
 // row tiles of the packed activation layout (and of all that is laid out by Mpad) for MT row tiles
 __host__ __device__ constexpr int layout_tiles(int MT) { return MT <= 2 ? MT : MT <= 4 ? 4 : 8; }
 LinCut choose_cut(int M, int N, int K, int G, bool solo);
+
+bool attention_alone(int M, int kv_len, int d);     // is an attention call of its own one launch?
 
 ghd_status launch_linear(const FusedArgs& a, hipStream_t st);
 ghd_status launch_qkv_attn(const FusedArgs& a, hipStream_t st);

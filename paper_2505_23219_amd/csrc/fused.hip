@@ -10,7 +10,9 @@ __global__ __launch_bounds__(kFT) void k_attention(const FusedArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     Ctx cx = make_ctx(lds);
-    const AttnPlan plan = attn_plan(a.nh, (a.kv_len + a.M + 63) >> 6, AttnOf<MT, D>::TMIN, cx.j, cx.G);
+    const int ntile = (a.kv_len + a.M + 63) >> 6;
+    const AttnPlan plan = attn_plan(a.nh, ntile, a.att_alone ? ntile : AttnOf<MT, D>::TMIN, cx.j, cx.G);
+    if (a.att_alone && blockIdx.x == 0 && threadIdx.x == 0) carry_status(a.sync);
     attn_phase<MT, D>(a, cx, plan, a.att_q, a.att_k, a.att_v, a.att_out, a.att_epoch);
     wait_loads<0>();       // (nothing is on its way to the LDS when the workgroup ends)
 }
@@ -25,6 +27,7 @@ static ghd_status launch_attention_t(const FusedArgs& a, hipStream_t st)
     const size_t lds = sizeof(typename AttnOf<MT, D>::Lds);
     ghd_status s = launch_resident_checked((const void*)k_attention<MT, D>, kFT, lds, &G);
     if (s) return s;
+    if (a.att_alone) G = 8 * ceil_div(a.nh, 8) < G ? 8 * ceil_div(a.nh, 8) : G;
     hipLaunchKernelGGL((k_attention<MT, D>), dim3(G), dim3(kFT), lds, st, a);
     return check_launch();
 }
@@ -66,6 +69,18 @@ void attn_share_on_host(int nh, int ntile, int tmin, int j, int G, int head, int
     out[3] = ts.t0;
     out[4] = ts.t1;
     out[5] = 1;
+}
+
+// An attention call whose heads are one workgroup's each needs no counter and so no launch before its own (3 us of
+// the host's time and as much of the GPU's); the tree's masks are worked out by every workgroup while the
+// cache is on its way.  Against that stands one workgroup's way through all of a head's keys, where up to
+// 32 of them share it otherwise.  Microseconds a call, one launch and two, 32 heads of 128 (24, 64, 128 rows):
+// 4 tiles of 64 keys 11.1 and 12.7, 10.6 and 12.6, 14.7 and 15.0; 6 tiles 13.3 and 14.4, 13.2 and 12.9, -;
+// 5 heads, 5 tiles, 128 rows 14.6 and 12.7; heads of 64: 8 tiles 9.5 and 11.2, 12.5 and 11.2, 18.2 and 12.7.
+bool attention_alone(int M, int kv_len, int d)
+{
+    const int64_t ntile = ((int64_t)kv_len + M + 63) / 64;
+    return M <= 32 ? ntile * d <= 6 * 128 : ntile <= (M <= 64 ? 4 : 3);
 }
 
 // ---- setup kernel ------------------------------------------------------------

@@ -49,6 +49,16 @@ __device__ __forceinline__ uint32_t ld_relaxed(const uint32_t* p)
 // workgroup, not their stores still on the way to the L2.)  s_waitcnt vmcnt(0).
 __device__ __forceinline__ void wait_own_stores() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
+// a barrier that waits for this wavefront's own use of the LDS, but not for what it has requested (which
+// __syncthreads() would, had any of it the LDS for its destination)
+__device__ __forceinline__ void barrier_lds()
+{
+    pin_order();
+    __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    pin_order();
+}
+
 // Invalidates this compute unit's vector L1 (workgroup-scope buffer_inv): loads that follow
 // are served by the L2.
 __device__ __forceinline__ void invalidate_l1() { asm volatile("buffer_inv sc0" ::: "memory"); }

@@ -267,6 +267,27 @@ def test_tree_attention_tile_ring(B, model, orc32, M, nh, d, kv_len, tree):
     test_tree_attention(B, model, orc32, M, nh, d, kv_len, tree)
 
 
+# Either side of what is one launch, masks and all (up to 768 keys of 64 or 384 of 128 channels at up to 32 rows, 256
+# at up to 64, 192 above): trees as deep as they get, few and many heads, and a caller's mask.  Tolerance as
+# above; the status word of the call before is kept as by any other call.
+@pytest.mark.parametrize("M,nh,d,kv_len,tree", [
+    (1, 3, 128, 383, "chain"), (1, 256, 64, 767, "chain"), (32, 9, 128, 352, "chain"), (32, 9, 128, 353, "chain"),
+    (31, 40, 64, 737, "rand5"), (31, 2, 64, 738, "rand5"), (33, 8, 64, 223, "chain"), (33, 8, 64, 224, "chain"),
+    (64, 5, 128, 192, "chain"), (64, 33, 128, 193, "star"), (65, 7, 128, 127, "chain"), (65, 7, 128, 128, "rand5"),
+    (128, 1, 64, 64, "chain"), (128, 31, 128, 64, "rand5"), (127, 6, 128, 66, "chain")])
+def test_attention_in_one_launch_and_in_two(B, model, orc32, M, nh, d, kv_len, tree):
+    test_tree_attention(B, model, orc32, M, nh, d, kv_len, tree)
+    if tree == "rand5":
+        test_masked_attention(B, model, orc32, M, nh, d, kv_len, "random", True)
+    ws = torch.zeros(B.lib().ghd_attention_workspace_bytes(M, kv_len, nh, d), dtype=torch.uint8, device="cuda")
+    words = ws[:16].view(torch.int32)
+    words[1], words[3] = 7, 0x67686453              # the status that a call left in a workspace that is known
+    q, kc, vc = attention_case(M, nh, d, kv_len, make_tree(tree, M), 41)
+    B.ghd_tree_attention(q.cuda(), *model.upload_cache(kc, vc), torch.from_numpy(make_tree(tree, M)).cuda(), kv_len, ws=ws)
+    assert B.ghd_step_status(ws) == 7
+    B._check(B.lib().ghd_step_status_reset(B._ptr(ws), B._stream()), "ghd_step_status_reset")     # (the memory is used again)
+
+
 @pytest.mark.parametrize("M,nh,d,kv_len,tree", [(8, 4, 64, 128, "rand3"), (40, 3, 128, 333, "rand5"),
                                                 (64, 8, 128, 1000, "chain")])
 def test_tree_attention_token_major_keys(B, model, orc32, M, nh, d, kv_len, tree):
