@@ -949,6 +949,9 @@ void ghd_debug_cut(int M, int N, int K, int G, int solo, int* out5)
     out5[4] = c.rows;
 }
 
+/* out2 = {row tiles of x per workgroup, groups of workgroups with different ones} of the same launch. */
+void ghd_debug_groups(int M, int N, int K, int G, int solo, int* out2) { groups_on_host(M, N, K, G, solo != 0, out2); }
+
 /* Does a linear call with these arguments read x as the caller's array (1), or a copy (0)? */
 int ghd_debug_linear_reads_x(const void* y, const void* x, int M, int N, int K, int64_t ldx, int64_t ldy, uint32_t flags)
 {

@@ -190,6 +190,7 @@ ghd_status launch_fused(const FusedArgs& a, hipStream_t st);
 struct LinCut {
     int whole, tiles, parts, grid;
     int rows;              // x is read row-major as it lies
+    int mt, groups;        // row tiles of x that a workgroup has, and (whole tiles) groups of workgroups with different ones
 };
 // the most tiles a part has
 constexpr int parts_max_tiles(int MT) { return 32 / MT < 8 ? 32 / MT : 8; }     // (eight wavefronts)
@@ -211,6 +212,7 @@ bool qkv_attn_available(int M, int d, int nh);
 ghd_status launch_resident_checked(const void* kernel, int threads, size_t lds, int* grid = nullptr);
 int fused_grid_size();
 void exchange_on_host(const int* xcd, int epochs, int n, int* ok);
+void groups_on_host(int M, int N, int K, int G, bool solo, int* out);
 void tile_range_on_host(int ntiles, int gx, int i, int* out);
 void attn_share_on_host(int nh, int ntile, int tmin, int j, int G, int head, int* out);
 

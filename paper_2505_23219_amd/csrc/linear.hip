@@ -85,7 +85,9 @@ size_t linear_part_floats(int M, int G)
 //   of 4 (0.34 MB), 23.3 of 8;
 //   parts: the exchange, its partial sums, and a little for every part.
 // Whole tiles read all of x in every workgroup, so they are for wide matrices, and for narrow
-// ones where x is small; parts divide x with the k range.  A call of its own pays one launch
+// ones where x is small; parts divide x with the k range; groups of workgroups divide its rows, and exchange
+// nothing.  (Layers of 20 heads of 64 at 37 rows 41.7 us without groups, 39.7 with them; 5 heads of 128 at 128 rows
+// 44.7 and 40.0; [572, 2856] called by itself at 64 rows 10.0 and 6.9.)  A call of its own pays one launch
 // more for parts (counters have to be zeroed, and x packed); with whole tiles it can read x
 // as it lies, which costs about twice the x time (64-byte pieces of 128-byte lines), where
 // that is less than the launch.
@@ -116,11 +118,27 @@ LinCut choose_cut(int M, int N, int K, int G, bool solo)
     best.tiles = U <= Gx * P ? 1 : ceil_div(U, Gx * P);
     best.parts = 1;
     best.grid = 8 * Gx * P;
+    best.mt = mt;
+    best.groups = 1;
     // (up to 16 rows only the rows that there are get read)
     const double row_cost = mt == 1 ? M / 8.0 : 2.0;
     best.rows = solo && mt <= kRowsMaxMT && (row_cost - 1.0) * mt * P * lay.nks * 1024.0 / kXBytesPerUs < kPrepareUs;
     double best_us = share_us(best.tiles * P, mt * P * (best.rows ? row_cost : 1.0), lay.nks) + (solo && !best.rows ? kPrepareUs : 0.0);
     if (lay.rb == 1) return best;
+    // Groups of workgroups with some of the rows each (1, 2 or 4 row tiles, of which the packed activation layout
+    // holds a whole number), while that leaves a tile at most for each.  Weights are then read once per group,
+    // from the L2 but for the first, and x once in all.
+    for (int m = 1; m < mt && m <= 4; m *= 2) {
+        const int groups = ceil_div(ceil_div(M, 16), m), gx = Gx / groups;
+        if (groups < 2 || gx < 2 || U > gx) continue;
+        for (int rows = 0; rows <= (solo && M <= 64 ? 1 : 0); ++rows) {
+            const double us = share_us(1, m * (rows ? 2.0 : 1.0), lay.nks) + (solo && !rows ? kPrepareUs : 0.0);
+            if (us < best_us) {
+                best_us = us;
+                best = LinCut{1, 1, 1, 8 * gx * groups, rows, m, groups};
+            }
+        }
+    }
     for (int r = 1; r <= parts_max_tiles(mt); ++r) {
         const int per_xcd = ceil_div(ceil_div(lay.ntiles, r), 8);
         if (per_xcd > Gx) continue;
@@ -131,7 +149,7 @@ LinCut choose_cut(int M, int N, int K, int G, bool solo)
                           (solo ? kPrepareUs : 0.0);
         if (us < best_us) {
             best_us = us;
-            best = LinCut{0, r, S, per_xcd * S * 8, 0};
+            best = LinCut{0, r, S, per_xcd * S * 8, 0, mt, 1};
         }
     }
     return best;
@@ -142,7 +160,7 @@ ghd_status launch_linear(const FusedArgs& a, hipStream_t st)
     const int G = fused_grid_size();
     if (G <= 0) return hip_fail(hipErrorInvalidDevice);
     const LinCut cut = choose_cut(a.M, a.lin_N, a.lin_K, G, a.lin_row_major != 0);
-    switch (row_tiles(a.M)) {
+    switch (cut.mt) {
     case 1: return launch_linear_mt1(a, cut, st);
     case 2: return launch_linear_mt2(a, cut, st);
     case 3: return launch_linear_mt3(a, cut, st);
@@ -181,6 +199,14 @@ ghd_status launch_qkv_attn(const FusedArgs& a, hipStream_t st)
 }
 
 // The kernels' arithmetic evaluated on the host, for tests of its invariants.
+// (row tiles of a workgroup, groups of rows) of a cut
+void groups_on_host(int M, int N, int K, int G, bool solo, int* out)
+{
+    const LinCut cut = choose_cut(M, N, K, G, solo);
+    out[0] = cut.mt;
+    out[1] = cut.groups;
+}
+
 void tile_range_on_host(int ntiles, int gx, int i, int* out)
 {
     tile_range(ntiles, gx, (uint32_t)(0x100000000ull / (uint64_t)gx + 1), i, out, out + 1);

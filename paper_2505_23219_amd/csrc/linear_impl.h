@@ -16,7 +16,8 @@
 //
 // Two ways of dealing a matrix out (chosen on the host, see choose_cut).  Whole tiles: a
 // workgroup has a run of consecutive tiles over the whole k range; nothing is exchanged
-// between workgroups, every workgroup reads all of x.  Parts: a workgroup has 1/S of the k
+// between workgroups, every workgroup reads all of x - or, where tiles are few, all of some of its rows: groups
+// of workgroups have the same tiles and different rows.  Parts: a workgroup has 1/S of the k
 // range of a block of R tiles; it reads only that part of x, stores the block's partial sums,
 // and the S workgroups of a block, which run on one XCD, finish it jointly at the end of the
 // launch, parts added in index order, so results never depend on timing.
@@ -128,6 +129,8 @@ __device__ __forceinline__ ResidOperands resid_operands(ArgPtr a, int m, int n0)
     return r;
 }
 
+constexpr int kNoRow = 1 << 20;      // m of a fragment that is not there
+
 // ---------------------------------------------------------------------------
 // epilogue of NB 16x16 output fragments: lane (c, g4) holds y[m][n0 .. n0+3] of each; m past the last row
 // stands for no fragment.  What is worked out is worked out for all of them before any is stored: with one
@@ -145,7 +148,7 @@ __device__ __forceinline__ void epilogue(ArgPtr a, floatx4 (&v)[NB], int (&m)[NB
     const int64_t ldo = a->lin_ldy;
     if (a->lin_rscale) {
 #pragma unroll
-        for (int i = 0; i < NB; ++i) v[i] *= s_rinv[min(m[i], GHD_MAX_M - 1)];
+        for (int i = 0; i < NB; ++i) v[i] *= s_rinv[m[i] == kNoRow ? m[0] : m[i]];      // (the first one is there)
     }
     if (epi == EPI_STORE_F32) {
         if (a->lin_amax) {
@@ -273,8 +276,6 @@ __device__ __forceinline__ void epilogue(ArgPtr a, floatx4 (&v)[NB], int (&m)[NB
     }
 }
 
-constexpr int kNoRow = 1 << 20;      // m of a fragment that is not there
-
 template <int MT, int R, int NW>
 struct LinShape {
     static constexpr int THREADS = NW * 64;
@@ -296,7 +297,7 @@ struct LinShape {
 
 // One workgroup's share: the tiles first .. first + count - 1 (count <= R; the other slots
 // re-read the first tile, and what they accumulate is never looked at) over the k-steps
-// k0 .. k1 - 1.  `finish(a, f, v, m, n0, s_rinv)` is called by one wavefront for every
+// k0 .. k1 - 1, for the row tiles rt0 .. rt0 + MT - 1 of x.  `finish(a, f, v, m, n0, s_rinv)` is called by one wavefront for every
 // fragment f = slot * MT + row tile with the workgroup's sum v, up to two fragments at a time (one that is
 // not there has a row past all others); `early()` runs between the stream's first loads and its first
 // wait.
@@ -304,7 +305,7 @@ struct LinShape {
 // ROWS: x is row-major and read as it lies (16 rows x 64 bytes per load), which saves a
 // separate packing launch; columns from K on are not read.  STRETCHES: see folded().
 template <int MT, int R, int NW, bool ROWS, int STRETCHES, class Early, class Finish>
-__device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int first, int count, int k0, int k1,
+__device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int first, int count, int k0, int k1, int rt0,
                                            Early early, Finish finish)
 {
     using S = LinShape<MT, R, NW>;
@@ -345,7 +346,7 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
     if constexpr (ROWS) {
         const int M = (h.flags >> kHeadM) & 255;
 #pragma unroll
-        for (int b = 0; b < MT; ++b) xrow[b] = h.x + (int64_t)min(b * 16 + c, M - 1) * (int64_t)h.aux;
+        for (int b = 0; b < MT; ++b) xrow[b] = h.x + (int64_t)min((rt0 + b) * 16 + c, M - 1) * (int64_t)h.aux;
     }
 
     half8 wr[PD][R], xr[PD][MT];
@@ -393,7 +394,7 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
 #pragma unroll
             for (int b = 0; b < MT; ++b) xr[p][b] = *(const half8*)(xrow[b] + col);
         } else {
-            const char* xq = (const char*)h.x + ((size_t)(uint32_t)(s * mtp) << 10);
+            const char* xq = (const char*)h.x + ((size_t)(uint32_t)(s * mtp + rt0) << 10);
 #pragma unroll
             for (int b = 0; b < MT; ++b) xr[p][b] = *(const half8*)(xq + (b << 10) + lane16);
         }
@@ -489,7 +490,7 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
             floatx4 sst[8];
 #pragma unroll
             for (int q = 0; q < 8; ++q)
-                sst[q] = *(GLOBAL const floatx4*)(ss + (size_t)min(t0 + q * P, n_ss - 1) * (MTP * 16) + rq * 4);
+                sst[q] = *(GLOBAL const floatx4*)(ss + (size_t)min(t0 + q * P, n_ss - 1) * (mtp * 16) + rt0 * 16 + rq * 4);
 #pragma unroll
             for (int q = 0; q < 8; ++q)
                 if (t0 + q * P < n_ss) rs4 += sst[q];
@@ -586,7 +587,7 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
                 const int ff = f0 + i * NW + wave;
                 f[i] = r0 + ff;
                 const int t = f[i] / MT, b = f[i] % MT;
-                m[i] = ff < FR && f[i] < NF && t < count ? b * 16 + c : kNoRow;
+                m[i] = ff < FR && f[i] < NF && t < count ? (rt0 + b) * 16 + c : kNoRow;
                 n0[i] = (first + t) * 16 + g4 * 4;
                 // (what is read for a fragment that is not there is not looked at)
 #pragma unroll
@@ -601,7 +602,7 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
                     for (int w = 0; w < NW; w += 2 * d) part[i][w] += part[i][w + d];
                 v[i] = part[i][0];
             }
-            finish(a, f, v, m, n0, s_rinv);
+            finish(a, f, v, m, n0, s_rinv - rt0 * 16);
         }
     }
 }
@@ -631,8 +632,10 @@ __global__ __launch_bounds__(waves_of(MT, R) * 64) void k_linear(const half8* W,
 {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const LinHead h = {W, x, aux, nks, K, ntiles, cut, magic, flags};
+    // the group of rows, and the workgroup's number in it
+    const int w = blockIdx.x >> 3, group = (int)(((uint64_t)(uint32_t)w * magic) >> 32);
     int c0, c1;
-    tile_range(ntiles, cut, magic, blockIdx.x, &c0, &c1);
+    tile_range(ntiles, cut, magic, (w - group * cut) << 3 | (blockIdx.x & 7), &c0, &c1);
     // A call of its own that is dealt out in whole tiles needs nothing that a set-up kernel
     // prepares; the workspace's status words are brought up to date here (nothing else in
     // the launch touches them).
@@ -645,7 +648,7 @@ __global__ __launch_bounds__(waves_of(MT, R) * 64) void k_linear(const half8* W,
     }
     const int lane = threadIdx.x & 63;
     gemm_group<MT, R, waves_of(MT, R), ROWS, stretches_whole(MT, R)>(
-        h, lds, c0, c1 - c0, 0, nks, solo,
+        h, lds, c0, c1 - c0, 0, nks, group * MT, solo,
         [&](ArgPtr a, auto&, auto& v, auto& m, auto& n0, const float* s_rinv) { epilogue(a, v, m, n0, lane, s_rinv); });
 }
 
@@ -673,7 +676,7 @@ __global__ __launch_bounds__(512) void k_linear_parts(const half8* W, const half
     // workgroups apart
     const int slot0 = bx * S * 8 + xcd;
     gemm_group<MT, R, 8, false, stretches_parts(MT, R)>(
-        h, lds, first, count, k0, k1, []() {},
+        h, lds, first, count, k0, k1, 0, []() {},
         [&](ArgPtr a, auto& f, auto& v, auto& m, auto&, const float*) {
             for (int i = 0; i < (int)(sizeof(f) / sizeof(f[0])); ++i)
                 if (m[i] != kNoRow) *(GLOBAL floatx4*)(gp(a->part) + ((size_t)(slot0 + part * 8) * NF + f[i]) * 256 + lane * 4) = v[i];
@@ -739,7 +742,7 @@ static inline LinHead head_of(const FusedArgs& a, const LinCut& cut)
     h.nks = lay.nks;
     h.K = a.lin_K;
     h.ntiles = lay.ntiles;
-    h.cut = cut.whole ? cut.grid / 8 : cut.parts;
+    h.cut = cut.whole ? cut.grid / 8 / cut.groups : cut.parts;
     h.magic = (uint32_t)((cut.whole ? 0x100000000ull : 0x10000ull) / (uint64_t)h.cut + 1);
     h.flags = (uint32_t)(lay.blk == kWideBlock ? 3 : 2) << kHeadBlk | (uint32_t)(a.Mpad / 16) << kHeadMtp |
               (uint32_t)a.M << kHeadM | (uint32_t)(a.lin_solo != 0) << kHeadSolo;

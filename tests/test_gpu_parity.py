@@ -11,6 +11,8 @@ bit-identical.  Floating-point tolerances:
 """
 import sys
 
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -464,6 +466,20 @@ def test_verify_layer_small_shapes(B, model, orc32, M, kv_len, tree):
     say("layer small", M, kv_len, tree)
     shape = wl.ModelShape("small", H=512, nh=4, d=128, F=1376, V=100, L=1)
     run_layer_case(B, model, orc32, shape, M, kv_len, make_tree(tree, M), 5)
+
+
+@pytest.mark.parametrize("M,nh,d", [(17, 5, 64), (33, 20, 64), (49, 4, 128), (65, 5, 64), (81, 12, 64), (97, 4, 64), (128, 7, 64)])
+def test_verify_layer_in_row_groups(B, model, orc32, M, nh, d):
+    """Layers of few tiles, whose output and down projections are dealt out in groups of rows (of one, two
+    or four row tiles; the last group's rows begun, full or partly past x)."""
+    say("layer row groups", M, nh, d)
+    shape = wl.ModelShape("groups", H=nh * d, nh=nh, d=d, F=(nh * d * 27 // 10) // 8 * 8, V=100, L=1)
+    out, used = (ctypes.c_int * 2)(), 0
+    for N, K in ((shape.H, shape.H), (shape.H, shape.F), (3 * shape.H, shape.H)):
+        B.lib().ghd_debug_groups(M, N, K, 256, 0, out)
+        used += out[1] > 1
+    assert used
+    run_layer_case(B, model, orc32, shape, M, 90, make_tree("rand5", M), 6)
 
 
 @pytest.mark.parametrize("M,kv_len,tree", [(1, 130, "chain"), (16, 77, "rand3"), (64, 200, "rand5"), (128, 64, "rand5")])

@@ -146,6 +146,39 @@ def test_linear_cut_covers_every_tile_and_fits(M):
                     assert grid == per_xcd * parts * 8 <= 256 and per_xcd * 8 * tiles >= ntiles
 
 
+@pytest.mark.parametrize("M", [1, 17, 32, 33, 37, 48, 64, 65, 80, 96, 97, 128])
+def test_row_groups_cover_every_row_once(M):
+    """Whole tiles dealt out to several groups of workgroups: every group has all the tiles, at most one a
+    workgroup, and its own rows; together they have all rows, and none reads past the rows of
+    the packed activation layout.  Narrow matrices of few tiles only, and nothing else is in groups."""
+    lib = B.lib()
+    cut, grp = (C.c_int * 5)(), (C.c_int * 2)()
+    seen = 0
+    for N in (1, 40, 300, 896, 1024, 1280, 2048, 2049, 4096, 9000, 10240):
+        for K in (8, 688, 896, 3416, 11008):
+            for solo in (0, 1):
+                lib.ghd_debug_cut(M, N, K, 256, solo, cut)
+                lib.ghd_debug_groups(M, N, K, 256, solo, grp)
+                whole, tiles, parts, grid, rows = list(cut)
+                mt, groups = list(grp)
+                ntiles, need = (N + 15) // 16, (M + 15) // 16
+                layout = 1 if need <= 1 else 2 if need <= 2 else 4 if need <= 4 else 8
+                if groups == 1:
+                    assert mt >= need
+                    continue
+                seen += 1
+                assert whole and tiles == 1 and ntiles < 640 and mt in (1, 2, 4)
+                assert mt * (groups - 1) < need <= mt * groups <= layout
+                gx = grid // 8 // groups
+                assert gx >= 2 and grid == 8 * gx * groups <= 256
+                ranges = [tile_range(lib, ntiles, gx, i) for i in range(8 * gx)]
+                assert sorted(t for a, b in ranges for t in range(a, b)) == list(range(ntiles))
+                # (the kernel's way from a workgroup's number to its group: a multiplication)
+                magic = (1 << 32) // gx + 1
+                assert [(w * magic) >> 32 for w in range(gx * groups)] == [w // gx for w in range(gx * groups)]
+    assert seen > 0 or M <= 16
+
+
 @pytest.mark.parametrize("tmin", [1, 2, 4])
 @pytest.mark.parametrize("nh,ntile", [(32, 33), (40, 129), (32, 1), (4, 3), (256, 2), (7, 9), (1, 40), (100, 17)])
 def test_attention_parts_are_not_made_too_small(nh, ntile, tmin):
