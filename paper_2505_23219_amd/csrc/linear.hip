@@ -86,8 +86,8 @@ size_t linear_part_floats(int M, int G)
 //   parts: the exchange, its partial sums, and a little for every part.
 // Whole tiles read all of x in every workgroup, so they are for wide matrices, and for narrow
 // ones where x is small; parts divide x with the k range; groups of workgroups divide its rows, and exchange
-// nothing.  (Layers of 20 heads of 64 at 37 rows 41.6 us without groups, 40.7 with them; 5 heads of 128 at 128 rows
-// 44.7 and 41.5; 4 heads of 64 at 128 rows 35.4 and 30.9.)  A call of its own pays one launch
+// nothing.  (Layers of 20 heads of 64 at 37 rows 41.6 us without groups, 39.9 with them; 5 heads of 128 at 128 rows
+// 44.7 and 40.4; 4 heads of 64 at 128 rows 35.4 and 30.1.)  A call of its own pays one launch
 // more for parts (counters have to be zeroed, and x packed); with whole tiles it can read x
 // as it lies, which costs about twice the x time (64-byte pieces of 128-byte lines), where
 // that is less than the launch.
@@ -99,13 +99,15 @@ constexpr double kPartsUs = 1.6, kPartsFragmentUs = 0.1, kPartsPartUs = 0.25;
 constexpr double kPrepareUs = 2.5;
 
 // How often a cut's sums are rounded, in k-steps of one chain (see folded; an addition counts for a quarter of
-// one): a wavefront's chain, cut short where it is long, and the additions of parts.
+// one): a wavefront's chain, cut short where it is long, and the additions of sets and of parts.
 static double chain_steps(const WLayout& lay, const LinCut& cut)
 {
-    const int waves = cut.whole ? waves_of(cut.mt, cut.tiles) : 8;
+    const int waves = cut.whole ? waves_of(cut.mt, cut.tiles) : 8, sets = cut.groups > 1 ? single_sets(cut.mt) : 0;
     const double chain = (double)ceil_div(lay.nks, cut.parts) / waves, more = cut.parts > 1 ? cut.parts / 4.0 : 0.0;
-    if (!long_chains(lay, cut, waves)) return chain + more;
-    const double cut_short = folded(cut.mt, cut.tiles) ? kFoldSteps + chain / kFoldSteps / 4.0 : chain / 2.0 + 0.25;
+    double cut_short = chain;
+    if (sets) cut_short = 1.0 + chain / sets / 4.0 + (sets > 2 ? 0.5 : sets > 1 ? 0.25 : 0.0);
+    else if (long_chains(lay, cut, waves))
+        cut_short = folded(cut.mt, cut.tiles) ? kFoldSteps + chain / kFoldSteps / 4.0 : chain / 2.0 + 0.25;
     return (cut_short < chain ? cut_short : chain) + more;
 }
 
@@ -152,16 +154,16 @@ LinCut choose_cut(int M, int N, int K, int G, bool solo)
     // Groups of workgroups with some of the rows each (1, 2 or 4 row tiles, of which the packed activation layout
     // holds a whole number), while that leaves a tile at most for each.  Weights are then read once per group,
     // from the L2 but for the first, and x once in all.  Not where that would round sums more often than
-    // the cut it stands in for (parts have shorter chains; a step less is asked for, as the count is rough: without
-    // that the error of [1280, 3416] at 80 rows was 8% larger than in parts).
-    const double steps = chain_steps(lay, best) - (best.whole ? 0.0 : 1.0);
+    // the cut it stands in for (parts have shorter chains; the count is rough, so more than half a step less is
+    // asked for), nor for less than half a microsecond instead of parts ([1280, 3416] at 64 rows: 0.6 us slower).
+    const double steps = chain_steps(lay, best) - (best.whole ? 0.0 : 0.6), us_to_beat = best_us - (best.whole ? 0.0 : 0.5);
     for (int m = 1; m < mt && m <= 4; m *= 2) {
         const int groups = ceil_div(ceil_div(M, 16), m), gx = Gx / groups;
         if (groups < 2 || gx < 2 || U > gx) continue;
         for (int rows = 0; rows <= (solo && M <= 64 ? 1 : 0); ++rows) {
             const double us = share_us(1, m * (rows ? 2.0 : 1.0), lay.nks) + (solo && !rows ? kPrepareUs : 0.0);
             const LinCut cut = {1, 1, 1, 8 * gx * groups, rows, m, groups};
-            if (us < best_us && chain_steps(lay, cut) <= steps) {
+            if (us < best_us && us < us_to_beat && chain_steps(lay, cut) <= steps) {
                 best_us = us;
                 best = cut;
             }

@@ -92,10 +92,16 @@ __host__ __device__ constexpr int pd_of(int MT, int R, int NW)
 //   STRETCHES, where there are no registers for that: a wavefront's range is taken in halves, and the
 //   sums of the first are set aside, in the LDS that the reduction uses later and in what registers
 //   are left; the last fragments of the largest groups are added up step by step instead.
+// And in row groups SINGLE: every k-step's product is added to one of up to four sets of sums in turn, which
+// are added in pairs at the end.  Groups then round less than the parts they stand in for ([300, 3416] at 64 rows:
+// 8.4e-8, in parts 9.4e-8), and stand in for more of them ([1280, 1280] at 64 rows: 7.0 us, in parts 10.0).  Without
+// groups it only costs: [3457, 4872] at 27 rows took 14.1 us instead of 13.7.
 // [2048, 13824] at 1 row: 2.8e-7 of the result in one chain, 1.2e-7 folded (12.6 and 12.9 us);
 // [22016, 4096] at 128 rows, four wavefronts: 2.1e-7 in one chain, 1.5e-7 in halves (47.4 and 49.3 us).
 constexpr int kFoldSteps = 2;
 __host__ __device__ constexpr bool folded(int MT, int R) { return R * MT <= (R <= 3 ? 18 : 16); }
+__host__ __device__ constexpr bool grouped(int MT, int R) { return R == 1 && (MT == 1 || MT == 2 || MT == 4); }
+__host__ __device__ constexpr int single_sets(int MT) { return pd_of(MT, 1, 8) < 4 ? pd_of(MT, 1, 8) : 4; }
 // Stretches that a range is taken in: two halves, or three where the chains of an even deal are less
 // than half as long.  (Of more than three whole tiles on eight wavefronts only wide matrices are dealt
 // out, whose chains are never long.)
@@ -304,7 +310,7 @@ struct LinShape {
 //
 // ROWS: x is row-major and read as it lies (16 rows x 64 bytes per load), which saves a
 // separate packing launch; columns from K on are not read.  STRETCHES: see folded().
-template <int MT, int R, int NW, bool ROWS, int STRETCHES, class Early, class Finish>
+template <int MT, int R, int NW, bool ROWS, int STRETCHES, int SETS, class Early, class Finish>
 __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int first, int count, int k0, int k1, int rt0,
                                            Early early, Finish finish)
 {
@@ -350,7 +356,7 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
     }
 
     half8 wr[PD][R], xr[PD][MT];
-    constexpr bool FOLDED = folded(MT, R), HALVED = STRETCHES > 1;
+    constexpr bool SINGLE = SETS > 0, FOLDED = folded(MT, R) && !SINGLE, HALVED = STRETCHES > 1;
     static_assert(!(FOLDED && HALVED), "one way or the other");
     // What came before: FOLDED: the sums of earlier k-steps; HALVED: those of the first half that
     // stay in registers, as many as there are registers for.  The last NSTEP fragments are not set
@@ -365,6 +371,11 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
     for (int f = 0; f < NF; ++f) acc[f / MT][f % MT] = zero4;
 #pragma unroll
     for (int f = 0; f < NB; ++f) before[f] = zero4;
+    floatx4 sums[SINGLE ? SETS : 1][SINGLE ? NF : 1];
+    if constexpr (SINGLE) {
+#pragma unroll
+        for (int i = 0; i < SETS * NF; ++i) sums[i / NF][i % NF] = zero4;
+    }
     const bool long_chains = (h.flags >> kHeadLong) & 1;
     auto fold = [&]() {
         if (!long_chains) return;              // (uniform)
@@ -422,7 +433,8 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
 #pragma unroll
             for (int bb = 0; bb < MT; ++bb) {
                 const int t = NSTEP ? R - 1 - tt : tt, b = NSTEP ? MT - 1 - bb : bb;
-                if (t * MT + b >= NF - NSTEP) acc[t][b] += __builtin_amdgcn_mfma_f32_16x16x32_f16(wr[p][t], xf[b], zero4, 0, 0, 0);
+                if constexpr (SINGLE) sums[p % SETS][t * MT + b] += __builtin_amdgcn_mfma_f32_16x16x32_f16(wr[p][t], xf[b], zero4, 0, 0, 0);
+                else if (t * MT + b >= NF - NSTEP) acc[t][b] += __builtin_amdgcn_mfma_f32_16x16x32_f16(wr[p][t], xf[b], zero4, 0, 0, 0);
                 else acc[t][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wr[p][t], xf[b], acc[t][b], 0, 0, 0);
             }
     };
@@ -537,6 +549,16 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
         }
         drain(drain, std::integral_constant<int, 0>{}, s);
     }
+    if constexpr (SINGLE) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+#pragma unroll
+            for (int d = 1; d < SETS; d *= 2)
+#pragma unroll
+                for (int i = 0; i + d < SETS; i += 2 * d) sums[i][f] += sums[i + d][f];
+            acc[f / MT][f % MT] = sums[0][f];
+        }
+    }
     if constexpr (FOLDED) {
         if (long_chains) {
 #pragma unroll
@@ -625,7 +647,8 @@ __host__ __device__ __forceinline__ void tile_range(int ntiles, int gx, uint32_t
 }
 
 // ---- whole tiles ----------------------------------------------------------------------
-template <int MT, int R, bool ROWS>
+// GROUPS: of workgroups, with the same tiles and different rows of x.
+template <int MT, int R, bool ROWS, bool GROUPS>
 __global__ __launch_bounds__(waves_of(MT, R) * 64) void k_linear(const half8* W, const half_t* x, uint64_t aux, int nks, int K,
                                                     int ntiles, int cut, uint32_t magic, uint32_t flags,
                                                     const FusedArgs)
@@ -633,7 +656,7 @@ __global__ __launch_bounds__(waves_of(MT, R) * 64) void k_linear(const half8* W,
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const LinHead h = {W, x, aux, nks, K, ntiles, cut, magic, flags};
     // the group of rows, and the workgroup's number in it
-    const int w = blockIdx.x >> 3, group = (int)(((uint64_t)(uint32_t)w * magic) >> 32);
+    const int w = blockIdx.x >> 3, group = GROUPS ? (int)(((uint64_t)(uint32_t)w * magic) >> 32) : 0;
     int c0, c1;
     tile_range(ntiles, cut, magic, (w - group * cut) << 3 | (blockIdx.x & 7), &c0, &c1);
     // A call of its own that is dealt out in whole tiles needs nothing that a set-up kernel
@@ -647,7 +670,7 @@ __global__ __launch_bounds__(waves_of(MT, R) * 64) void k_linear(const half8* W,
         return;
     }
     const int lane = threadIdx.x & 63;
-    gemm_group<MT, R, waves_of(MT, R), ROWS, stretches_whole(MT, R)>(
+    gemm_group<MT, R, waves_of(MT, R), ROWS, stretches_whole(MT, R), GROUPS ? single_sets(MT) : 0>(
         h, lds, c0, c1 - c0, 0, nks, group * MT, solo,
         [&](ArgPtr a, auto&, auto& v, auto& m, auto& n0, const float* s_rinv) { epilogue(a, v, m, n0, lane, s_rinv); });
 }
@@ -675,7 +698,7 @@ __global__ __launch_bounds__(512) void k_linear_parts(const half8* W, const half
     // partial sums: one slot of NF fragments per workgroup; the block's parts are eight
     // workgroups apart
     const int slot0 = bx * S * 8 + xcd;
-    gemm_group<MT, R, 8, false, stretches_parts(MT, R)>(
+    gemm_group<MT, R, 8, false, stretches_parts(MT, R), 0>(
         h, lds, first, count, k0, k1, 0, []() {},
         [&](ArgPtr a, auto& f, auto& v, auto& m, auto&, const float*) {
             for (int i = 0; i < (int)(sizeof(f) / sizeof(f[0])); ++i)
@@ -787,10 +810,15 @@ ghd_status launch_linear_r(const FusedArgs& a, const LinCut& cut, hipStream_t st
     if (cut.tiles == R && cut.whole) {
         constexpr int threads = waves_of(MT, R) * 64;
         constexpr size_t lds = LinShape<MT, R, waves_of(MT, R)>::template lds_bytes<(stretches_whole(MT, R) > 1)>;
+        if constexpr (grouped(MT, R))
+            if (cut.groups > 1)
+                return launch_linear_kernel(cut.rows ? k_linear<MT, R, true, true> : k_linear<MT, R, false, true>, a, cut,
+                                            threads, lds, st);
+        if (cut.groups > 1) return GHD_ERR_SHAPE;
         if constexpr (MT <= kRowsMaxMT)
-            if (cut.rows) return launch_linear_kernel(k_linear<MT, R, true>, a, cut, threads, lds, st);
+            if (cut.rows) return launch_linear_kernel(k_linear<MT, R, true, false>, a, cut, threads, lds, st);
         if (cut.rows) return GHD_ERR_SHAPE;
-        return launch_linear_kernel(k_linear<MT, R, false>, a, cut, threads, lds, st);
+        return launch_linear_kernel(k_linear<MT, R, false, false>, a, cut, threads, lds, st);
     }
     if constexpr (R <= parts_max_tiles(MT))
         if (cut.tiles == R)

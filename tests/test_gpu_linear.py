@@ -56,6 +56,28 @@ def test_shares_whose_fragments_are_finished_several_at_a_time(B, M, out16):
         assert err < (2.0 ** -11 if out16 else max(2e-7, 4 * 2.0 ** -24 * K ** 0.5)), (N, K, err)
 
 
+@pytest.mark.parametrize("M", [17, 32, 33, 49, 64, 65, 81, 128])
+def test_row_groups_add_products_to_sets_of_sums(B, M):
+    """Matrices of few tiles, which are dealt out in groups of rows: k ranges of no step, a step or two and of ragged
+    lengths for a wavefront, whose products go to sets of sums in turn.  Tolerance as above."""
+    say("row groups' sums", M)
+    used, out = 0, (ctypes.c_int * 2)()
+    for N, K in [(5, 8), (300, 40), (1280, 264), (100, 1000), (572, 2856), (1280, 1280), (2048, 2048), (80, 3960)]:
+        B.lib().ghd_debug_groups(M, N, K, 256, 1, out)
+        used += out[1] > 1
+        g = torch.Generator(device="cuda").manual_seed(N + M)
+        x = torch.randn((M, K), generator=g, device="cuda").to(torch.float16)
+        W = (torch.randn((N, K), generator=g, device="cuda") * 0.02).to(torch.float16)
+        ws = B.workspace(B.lib().ghd_linear_workspace_bytes(M, N, K))
+        ws.fill_(0xFF)
+        y = B.ghd_linear_skinny(x, B.ghd_pack_weight(W), N, ws=ws)
+        assert B.ghd_step_status(ws) == 0
+        ref = x.double() @ W.double().t()
+        err = float((y.double() - ref).norm() / ref.norm())
+        assert err < max(2e-7, 4 * 2.0 ** -24 * K ** 0.5), (N, K, err)
+    assert used
+
+
 def test_every_stream_gives_the_same_result(B):
     """The XCD that a dispatch begins with depends on the hardware queue it goes through.
     Several streams in turn (more than there are queues), each with a small launch of its own in
