@@ -175,6 +175,51 @@ struct NoGate {
     __device__ __forceinline__ bool operator()() const { return true; }
 };
 
+// Adds a unit of 32 keys to a running state: scores s (times log2 e; -inf where a row does not see the key), their
+// largest `tmax` in all four lanes of a row, V^T operands vf.  The probabilities of the product are fp16, and the
+// largest of those that share a maximum is exactly 1, so the more keys share one the more is rounded.  APART:
+// the unit's probabilities are taken against its own maximum and its product is added to the state in fp32.
+// So do calls in one launch, since a head split over workgroups would have given each unit a state of its own:
+// without it their outputs were 0.7% (up to 32 rows) and 1.1% (33 to 64) further from 64 bits than in two
+// launches, 4% at the worst.  (32 heads of 128: 48 rows, 4 tiles 10.3 -> 10.8 us a call, in two launches 11.6;
+// 128 rows, 3 tiles 12.4 -> 13.1 and 14.5.)
+template <int DT, bool APART>
+__device__ __forceinline__ void add_unit(float& mrun, float& lrun, floatx4 (&oacc)[DT], const floatx4 (&s)[2],
+                                         const half8 (&vf)[DT], float tmax)
+{
+    const float mnew = fmaxf(mrun, tmax);
+    const float muse = (mnew == -INFINITY) ? 0.f : mnew;
+    const float alpha = fast_exp2(mrun - muse);
+    const float mine = APART && tmax != -INFINITY ? tmax : muse;
+    mrun = mnew;
+    float lsum = 0.f;
+    half8 pf;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const float pv = fast_exp2(s[i >> 2][i & 3] - mine);
+        lsum += pv;
+        pf[i] = (half_t)pv;
+    }
+    // (the maximum of most rows settles early: usually nothing has to be rescaled)
+    if (__ballot(alpha != 1.0f)) {
+#pragma unroll
+        for (int e = 0; e < DT; ++e) oacc[e] *= alpha;
+    }
+    if constexpr (APART) {
+        const float beta = fast_exp2(mine - muse);
+        lrun = lrun * alpha + lsum * beta;
+#pragma unroll
+        for (int e = 0; e < DT; ++e) {
+            const floatx4 o = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf[e], pf, (floatx4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            oacc[e] += o * beta;
+        }
+    } else {
+        lrun = lrun * alpha + lsum;
+#pragma unroll
+        for (int e = 0; e < DT; ++e) oacc[e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf[e], pf, oacc[e], 0, 0, 0);
+    }
+}
+
 // ---- up to 32 query rows: every wavefront works on units of its own ----------------------
 // a part should have a unit for each of the eight wavefronts
 constexpr int kDirectTiles = 4;
@@ -261,7 +306,7 @@ __device__ __forceinline__ bool finish_parts(const FusedArgs& a, GLOBAL half_t* 
     return true;
 }
 
-template <int MT, int D, bool PREFETCH, class Gate>
+template <int MT, int D, bool PREFETCH, bool ALONE, class Gate>
 __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const AttnPlan& plan, const half_t* q_,
                                             const half_t* kc_, const half_t* vc_, half_t* out_, uint32_t epoch, Gate gate)
 {
@@ -290,7 +335,7 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const A
     uint64_t mask_lo = 0, mask_hi = 0;
     {
         const auto mask = gp(a.mask);
-        if (tid < M && !a.att_parent) {
+        if (tid < M && !(ALONE && a.att_parent)) {
             mask_lo = mask[2 * tid];
             mask_hi = mask[2 * tid + 1];
         }
@@ -361,7 +406,7 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const A
             load_v(u);
         }
         pin_order();           // (all requests are out before the first of them is waited for)
-        if (!PREFETCH && a.att_parent) masks_from_parent(gp(a.att_parent), M, &sm.mask[0][0], sm.up);
+        if (ALONE && a.att_parent) masks_from_parent(gp(a.att_parent), M, &sm.mask[0][0], sm.up);
         else if (tid < MT * 16) {
             sm.mask[tid][0] = mask_lo;
             sm.mask[tid][1] = mask_hi;
@@ -431,29 +476,7 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const A
                     any = __ballot(mine) != 0ull;          // no row of the tile sees the unit: leave it out
                 }
                 if (!any) continue;
-                tmax = max_over_groups(tmax);
-                const float mnew = fmaxf(mrun[t], tmax);
-                const float muse = (mnew == -INFINITY) ? 0.f : mnew;
-                const float alpha = fast_exp2(mrun[t] - muse);
-                mrun[t] = mnew;
-                float lsum = 0.f;
-                half8 pf;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const float pv = fast_exp2(s[t][i >> 2][i & 3] - muse);
-                    lsum += pv;
-                    pf[i] = (half_t)pv;
-                }
-                lrun[t] = lrun[t] * alpha + lsum;
-                // (the maximum of most rows settles early: usually nothing has to be rescaled)
-                if (__ballot(alpha != 1.0f)) {
-#pragma unroll
-                    for (int e = 0; e < DT; ++e) oacc[t][e] *= alpha;
-                }
-#pragma unroll
-                for (int e = 0; e < DT; ++e) {
-                    oacc[t][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf[e], pf, oacc[t][e], 0, 0, 0);
-                }
+                add_unit<DT, ALONE>(mrun[t], lrun[t], oacc[t], s[t], vf, max_over_groups(tmax));
             }
             if (u + 8 < u1) load_v(u + 8);
         }
@@ -562,7 +585,7 @@ __device__ __forceinline__ void wait_tiles_of(int n)
     wait_loads<PER_TILE * MOST>();
 }
 
-template <int MT, int D, bool PREFETCH, class Gate>
+template <int MT, int D, bool PREFETCH, bool ALONE, class Gate>
 __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const AttnPlan& plan, const half_t* q_,
                                             const half_t* kc_, const half_t* vc_, half_t* out_, uint32_t epoch, Gate gate)
 {
@@ -650,7 +673,7 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const A
         if (!gated) {
             // (loads return in order: the wavefront that polls at the gate requests nothing before)
             const bool polls = PREFETCH && wave == 0;
-            if (!polls && !a.att_parent) request_masks();
+            if (!polls && !(ALONE && a.att_parent)) request_masks();
             if constexpr (PREFETCH)
                 for (; !polls && n_pre < up_front && (t0 + n_pre) * 64 + 128 <= kv_len; ++n_pre) request(t0 + n_pre);
             if (!gate()) return false;
@@ -665,18 +688,26 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const A
         }
         for (int n = n_pre; n < up_front; ++n) request(t0 + n);
 
-        if (!PREFETCH && a.att_parent) masks_from_parent(gp(a.att_parent), M, (uint64_t*)sm.mask, sm.up);
+        if (ALONE && a.att_parent) masks_from_parent(gp(a.att_parent), M, (uint64_t*)sm.mask, sm.up);
 
         // waits for all but the youngest n tiles
         auto wait_tiles = [&](int n) {
             wait_tiles_of<LPT, NB - 2>(n);
             pin_order();
         };
-        // running state of this head
-        float mrun = -INFINITY, lrun = 0.f;
-        floatx4 oacc[DT];
+        // running state of this head: one for each unit of a tile, which come together when the head ends
+        // (one for both rounds more, see add_unit: outputs 1.8% further from 64 bits at 65 to 128 rows, and a
+        // 7B-shaped layer of 128 rows took 152.1 us instead of 152.4)
+        constexpr int STATES = ALONE ? 1 : UNITS;
+        float mrun[STATES], lrun[STATES];
+        floatx4 oacc[STATES][DT];
 #pragma unroll
-        for (int e = 0; e < DT; ++e) oacc[e] = (floatx4){0.f, 0.f, 0.f, 0.f};
+        for (int uu = 0; uu < STATES; ++uu) {
+            mrun[uu] = -INFINITY;
+            lrun[uu] = 0.f;
+#pragma unroll
+            for (int e = 0; e < DT; ++e) oacc[uu][e] = (floatx4){0.f, 0.f, 0.f, 0.f};
+        }
         wait_tiles(up_front - max(n_pre, 1));              // the queries and the first tile are there
         half8 qf[DS];
         {
@@ -693,7 +724,7 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const A
             if (tile + NB - 1 < t1) request(tile + NB - 1);
             if (!wave_active) continue;
             const char* const buf = sm.tile[(tile - t0) & (NB - 1)];
-#pragma unroll 1
+#pragma unroll STATES
             for (int uu = 0; uu < UNITS; ++uu) {
                 const int un = HALVES == 2 ? half : uu, key0 = tile * 64 + un * 32;
                 const char* const kp = buf + un * (32 * D * 2);
@@ -741,34 +772,28 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const A
                                 if (i >= nvalid) vf[e][i] = (half_t)0;
                     }
                 }
-                tmax = max_over_groups(tmax);
-                const float mnew = fmaxf(mrun, tmax);
-                const float muse = (mnew == -INFINITY) ? 0.f : mnew;
-                const float alpha = fast_exp2(mrun - muse);
-                mrun = mnew;
-                float lsum = 0.f;
-                half8 pf;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const float pv = fast_exp2(s[i >> 2][i & 3] - muse);
-                    lsum += pv;
-                    pf[i] = (half_t)pv;
-                }
-                lrun = lrun * alpha + lsum;
-                // (the maximum of most rows settles early: usually nothing has to be rescaled)
-                if (__ballot(alpha != 1.0f)) {
-#pragma unroll
-                    for (int e = 0; e < DT; ++e) oacc[e] *= alpha;
-                }
-#pragma unroll
-                for (int e = 0; e < DT; ++e) oacc[e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf[e], pf, oacc[e], 0, 0, 0);
+                add_unit<DT, ALONE>(mrun[uu % STATES], lrun[uu % STATES], oacc[uu % STATES], s, vf, max_over_groups(tmax));
             }
         }
 
         // ---- end of this workgroup's share of the head.  The two wavefronts of a row tile exchange half of
         //      their output fragments each and merge the other half (online-softmax rescale); a head in
         //      one part is finished by that
-        lrun = sum_over_groups(lrun);
+        // (fixed order: the first half's share comes first)
+        const auto merge = [](float& ma, float mb, float& wa, float& wb) {
+            const float mx = fmaxf(ma, mb);
+            wa = (ma == -INFINITY) ? 0.f : fast_exp2(ma - mx);
+            wb = (mb == -INFINITY) ? 0.f : fast_exp2(mb - mx);
+            ma = mx;
+        };
+        float m = mrun[0], l = sum_over_groups(lrun[0]);
+        if constexpr (STATES == 2) {
+            float wa, wb;
+            merge(m, mrun[1], wa, wb);
+            l = l * wa + sum_over_groups(lrun[1]) * wb;
+#pragma unroll
+            for (int e = 0; e < DT; ++e) oacc[0][e] = oacc[0][e] * wa + oacc[1][e] * wb;
+        }
         const auto state = o_part + ((size_t)cx.j * Mpad + mrow) * D + g4 * 4;
         auto store = [&](auto n, int e0, const floatx4* o) {
             if (!mok) return;
@@ -778,7 +803,7 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const A
             } else {
 #pragma unroll
                 for (int e = 0; e < decltype(n)::value; ++e)
-                    store_attn_out(a, out, mrow, head * D + (e0 + e) * 16 + g4 * 4, lrun > 0.f ? o[e] / lrun : (floatx4){0.f, 0.f, 0.f, 0.f});
+                    store_attn_out(a, out, mrow, head * D + (e0 + e) * 16 + g4 * 4, l > 0.f ? o[e] / l : (floatx4){0.f, 0.f, 0.f, 0.f});
             }
         };
         if constexpr (HALVES == 2) {
@@ -787,31 +812,28 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const A
             constexpr int HE = DT / 2;
             if (wave_active) {
 #pragma unroll
-                for (int e = 0; e < HE; ++e) other[wq][half][e][lane] = half ? oacc[e] : oacc[HE + e];
+                for (int e = 0; e < HE; ++e) other[wq][half][e][lane] = half ? oacc[0][e] : oacc[0][HE + e];
                 if (lane < 16) {
-                    sm.m[wq][half][c] = mrun;
-                    sm.l[wq][half][c] = lrun;
+                    sm.m[wq][half][c] = m;
+                    sm.l[wq][half][c] = l;
                 }
             }
             __syncthreads();
             if (wave_active) {
                 const float mb = sm.m[wq][half ^ 1][c], lb = sm.l[wq][half ^ 1][c];
-                const float mx = fmaxf(mrun, mb);
-                const float wa = (mrun == -INFINITY) ? 0.f : fast_exp2(mrun - mx);
-                const float wb = (mb == -INFINITY) ? 0.f : fast_exp2(mb - mx);
-                // (the first half's share comes first in either wavefront's sum)
-                lrun = half ? lb * wb + lrun * wa : lrun * wa + lb * wb;
-                mrun = mx;
+                float wa, wb;
+                merge(m, mb, wa, wb);
+                l = half ? lb * wb + l * wa : l * wa + lb * wb;
                 floatx4 o[HE];
 #pragma unroll
-                for (int e = 0; e < HE; ++e) o[e] = (half ? oacc[HE + e] : oacc[e]) * wa + other[wq][half ^ 1][e][lane] * wb;
+                for (int e = 0; e < HE; ++e) o[e] = (half ? oacc[0][HE + e] : oacc[0][e]) * wa + other[wq][half ^ 1][e][lane] * wb;
                 store(std::integral_constant<int, HE>{}, half * HE, o);
             }
         } else {
-            store(std::integral_constant<int, DT>{}, 0, oacc);
+            store(std::integral_constant<int, DT>{}, 0, oacc[0]);
         }
         if (np > 1) {
-            if (mok && half == 0 && g4 == 0) *(GLOBAL floatx2*)(ml_part + ((size_t)cx.j * Mpad + mrow) * 2) = (floatx2){mrun, lrun};
+            if (mok && half == 0 && g4 == 0) *(GLOBAL floatx2*)(ml_part + ((size_t)cx.j * Mpad + mrow) * 2) = (floatx2){m, l};
             if (!finish_parts<D>(a, out, head, first, np, me, epoch, &sm.wait_ok)) return false;
         }
         // a workgroup that goes on to another head reuses its LDS (it has its heads to itself: np = 1)
@@ -831,12 +853,13 @@ struct AttnOf {
     using Lds = std::conditional_t<DIRECT, DirectLds<MT, D>, StagedLds<layout_tiles(MT), D>>;
 };
 
-template <int MT, int D, bool PREFETCH = false, class Gate = NoGate>
+// ALONE: no head is shared and there was no set-up launch (see attention_alone)
+template <int MT, int D, bool PREFETCH = false, bool ALONE = false, class Gate = NoGate>
 __device__ __forceinline__ bool attn_phase(const FusedArgs& a, Ctx& cx, const AttnPlan& plan, const half_t* q, const half_t* kc,
                                            const half_t* vc, half_t* out, uint32_t epoch, Gate gate = Gate())
 {
-    if constexpr (AttnOf<MT, D>::DIRECT) return attn_direct<MT, D, PREFETCH>(a, cx, plan, q, kc, vc, out, epoch, gate);
-    else return attn_staged<layout_tiles(MT), D, PREFETCH>(a, cx, plan, q, kc, vc, out, epoch, gate);
+    if constexpr (AttnOf<MT, D>::DIRECT) return attn_direct<MT, D, PREFETCH, ALONE>(a, cx, plan, q, kc, vc, out, epoch, gate);
+    else return attn_staged<layout_tiles(MT), D, PREFETCH, ALONE>(a, cx, plan, q, kc, vc, out, epoch, gate);
 }
 
 }  // namespace ghd

@@ -5,42 +5,42 @@
 namespace ghd {
 
 
-template <int MT, int D>
+template <int MT, int D, bool ALONE>
 __global__ __launch_bounds__(kFT) void k_attention(const FusedArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     Ctx cx = make_ctx(lds);
     const int ntile = (a.kv_len + a.M + 63) >> 6;
-    const AttnPlan plan = attn_plan(a.nh, ntile, a.att_alone ? ntile : AttnOf<MT, D>::TMIN, cx.j, cx.G);
-    if (a.att_alone && blockIdx.x == 0 && threadIdx.x == 0) carry_status(a.sync);
-    attn_phase<MT, D>(a, cx, plan, a.att_q, a.att_k, a.att_v, a.att_out, a.att_epoch);
+    const AttnPlan plan = attn_plan(a.nh, ntile, ALONE ? ntile : AttnOf<MT, D>::TMIN, cx.j, cx.G);
+    if (ALONE && blockIdx.x == 0 && threadIdx.x == 0) carry_status(a.sync);
+    attn_phase<MT, D, false, ALONE>(a, cx, plan, a.att_q, a.att_k, a.att_v, a.att_out, a.att_epoch);
     wait_loads<0>();       // (nothing is on its way to the LDS when the workgroup ends)
 }
 
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-template <int MT, int D>
+template <int MT, int D, bool ALONE>
 static ghd_status launch_attention_t(const FusedArgs& a, hipStream_t st)
 {
     int G = 0;
     const size_t lds = sizeof(typename AttnOf<MT, D>::Lds);
-    ghd_status s = launch_resident_checked((const void*)k_attention<MT, D>, kFT, lds, &G);
+    ghd_status s = launch_resident_checked((const void*)k_attention<MT, D, ALONE>, kFT, lds, &G);
     if (s) return s;
-    if (a.att_alone) G = 8 * ceil_div(a.nh, 8) < G ? 8 * ceil_div(a.nh, 8) : G;
-    hipLaunchKernelGGL((k_attention<MT, D>), dim3(G), dim3(kFT), lds, st, a);
+    if (ALONE) G = 8 * ceil_div(a.nh, 8) < G ? 8 * ceil_div(a.nh, 8) : G;
+    hipLaunchKernelGGL((k_attention<MT, D, ALONE>), dim3(G), dim3(kFT), lds, st, a);
     return check_launch();
 }
 
-template <int D>
+template <int D, bool ALONE>
 static ghd_status launch_attention_d(const FusedArgs& a, hipStream_t st)
 {
     // (above 32 rows the attention has wavefronts for 4 or 8 row tiles)
     switch (layout_tiles(row_tiles(a.M))) {
-    case 1: return launch_attention_t<1, D>(a, st);
-    case 2: return launch_attention_t<2, D>(a, st);
-    case 4: return launch_attention_t<4, D>(a, st);
-    default: return launch_attention_t<8, D>(a, st);
+    case 1: return launch_attention_t<1, D, ALONE>(a, st);
+    case 2: return launch_attention_t<2, D, ALONE>(a, st);
+    case 4: return launch_attention_t<4, D, ALONE>(a, st);
+    default: return launch_attention_t<8, D, ALONE>(a, st);
     }
 }
 
@@ -49,7 +49,8 @@ ghd_status launch_fused(const FusedArgs& a, hipStream_t st)
 {
     if (a.mode == MODE_LINEAR) return launch_linear(a, st);
     if (a.mode == MODE_QKV_ATTN) return launch_qkv_attn(a, st);
-    return a.d == 64 ? launch_attention_d<64>(a, st) : launch_attention_d<128>(a, st);
+    if (a.att_alone) return a.d == 64 ? launch_attention_d<64, true>(a, st) : launch_attention_d<128, true>(a, st);
+    return a.d == 64 ? launch_attention_d<64, false>(a, st) : launch_attention_d<128, false>(a, st);
 }
 
 // The attention's work shares on the host: for workgroup j and head `head`,

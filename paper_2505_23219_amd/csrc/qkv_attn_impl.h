@@ -81,7 +81,7 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
         invalidate_l1();
         return true;
     };
-    attn_phase<MT, D, true>(a, cx, plan, a.att_q, a.att_k, a.att_v, a.att_out, a.att_epoch, gate);
+    attn_phase<MT, D, true, false>(a, cx, plan, a.att_q, a.att_k, a.att_v, a.att_out, a.att_epoch, gate);
     wait_loads<0>();       // (nothing is on its way to the LDS when the workgroup ends)
 }
 
