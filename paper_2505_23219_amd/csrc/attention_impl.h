@@ -133,19 +133,15 @@ __device__ __forceinline__ float over_groups(float x, Op op)
 __device__ __forceinline__ float max_over_groups(float x) { return over_groups(x, [](float a, float b) { return fmaxf(a, b); }); }
 __device__ __forceinline__ float sum_over_groups(float x) { return over_groups(x, [](float a, float b) { return a + b; }); }
 
-// The ancestor masks of a tree in LDS (mask[2 * node], low and high word) from parent[], by pointer doubling: after
-// round k a node has its 2^k nearest ancestors-or-self and the node 2^k edges up.  All threads call; a barrier
-// is left to the caller.  A parent that is not an earlier node is taken as "no parent".
-__device__ __forceinline__ void masks_from_parent(GLOBAL const int32_t* parent, int M, uint64_t* mask, int32_t* s_up)
+// The ancestor masks of a tree in LDS (mask[2 * node], low and high word) by pointer doubling, from `up` = parent[i] in
+// thread i: after round k a node has its 2^k nearest ancestors-or-self and the node 2^k edges up.  All threads
+// call; a barrier is left to the caller.  A parent that is not an earlier node is taken as "no parent".
+__device__ __forceinline__ void masks_from_parent(int up, int M, uint64_t* mask, int32_t* s_up)
 {
     const int i = threadIdx.x;
-    int up = -1;
     uint64_t lo = 0, hi = 0;
-    if (i < M) {
-        up = parent[i];
-        if (up < 0 || up >= i) up = -1;
-        if (i < 64) lo = 1ull << i; else hi = 1ull << (i - 64);
-    }
+    if (up < 0 || up >= i || i >= M) up = -1;
+    if (i < 64) lo = 1ull << i; else hi = 1ull << (i & 63);
     for (int span = 1; span < M; span <<= 1) {
         if (i < M) {
             mask[2 * i] = lo;
@@ -164,6 +160,27 @@ __device__ __forceinline__ void masks_from_parent(GLOBAL const int32_t* parent, 
         mask[2 * i] = lo;
         mask[2 * i + 1] = hi;
     }
+}
+
+// A call in one launch gets what its masks are made from, a word a thread, before anything else, and has it when
+// it requests queries and cache (the work shares are worked out in between): the masks are then made while those are on
+// their way.  Loads return in order: requested behind the cache, parent[] came back behind it, and the
+// rounds of the doubling began when all else was there.
+__device__ __forceinline__ uint32_t mask_source(const FusedArgs& a)
+{
+    const int tid = threadIdx.x;
+    uint32_t word = 0;
+    if (a.att_parent) {
+        if (tid < a.M) word = (uint32_t)gp(a.att_parent)[tid];
+    } else if (tid < a.M * 4) {
+        word = ((GLOBAL const uint32_t*)gp(a.mask))[tid];
+    }
+    return word;
+}
+__device__ __forceinline__ void masks_from_source(const FusedArgs& a, uint32_t word, uint64_t* mask, int32_t* s_up)
+{
+    if (a.att_parent) masks_from_parent((int)word, a.M, mask, s_up);
+    else if ((int)threadIdx.x < a.M * 4) ((uint32_t*)mask)[threadIdx.x] = word;
 }
 
 // `gate` is called once by every workgroup (all threads), before the first read of q or of a
@@ -335,7 +352,7 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const A
     uint64_t mask_lo = 0, mask_hi = 0;
     {
         const auto mask = gp(a.mask);
-        if (tid < M && !(ALONE && a.att_parent)) {
+        if (tid < M && !ALONE) {
             mask_lo = mask[2 * tid];
             mask_hi = mask[2 * tid + 1];
         }
@@ -389,6 +406,8 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const A
             if (!gate()) return false;
             gated = true;
         }
+        const int source = ALONE ? hidden(cx.source) : 0;      // (it is there)
+        pin_order();
         half8 qf[MT][DS];
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
@@ -406,7 +425,7 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const A
             load_v(u);
         }
         pin_order();           // (all requests are out before the first of them is waited for)
-        if (ALONE && a.att_parent) masks_from_parent(gp(a.att_parent), M, &sm.mask[0][0], sm.up);
+        if constexpr (ALONE) masks_from_source(a, source, &sm.mask[0][0], sm.up);
         else if (tid < MT * 16) {
             sm.mask[tid][0] = mask_lo;
             sm.mask[tid][1] = mask_hi;
@@ -673,13 +692,15 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const A
         if (!gated) {
             // (loads return in order: the wavefront that polls at the gate requests nothing before)
             const bool polls = PREFETCH && wave == 0;
-            if (!polls && !(ALONE && a.att_parent)) request_masks();
+            if (!polls && !ALONE) request_masks();
             if constexpr (PREFETCH)
                 for (; !polls && n_pre < up_front && (t0 + n_pre) * 64 + 128 <= kv_len; ++n_pre) request(t0 + n_pre);
             if (!gate()) return false;
             gated = true;
             if (polls) request_masks();
         }
+        const int source = ALONE ? hidden(cx.source) : 0;      // (it is there)
+        pin_order();
         {
             const uint32_t at = lds0 + (NB - 1) * TB + (uint32_t)wave * (DS * 1024);
             const uint32_t off = ((uint32_t)min(mrow, M - 1) * (uint32_t)nh + (uint32_t)head) * (D * 2) + g4 * 16;
@@ -688,7 +709,7 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const A
         }
         for (int n = n_pre; n < up_front; ++n) request(t0 + n);
 
-        if (ALONE && a.att_parent) masks_from_parent(gp(a.att_parent), M, (uint64_t*)sm.mask, sm.up);
+        if constexpr (ALONE) masks_from_source(a, source, (uint64_t*)sm.mask, sm.up);
 
         // waits for all but the youngest n tiles
         auto wait_tiles = [&](int n) {

@@ -10,6 +10,7 @@ __global__ __launch_bounds__(kFT) void k_attention(const FusedArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     Ctx cx = make_ctx(lds);
+    if constexpr (ALONE) cx.source = (int)mask_source(a);
     const int ntile = (a.kv_len + a.M + 63) >> 6;
     const AttnPlan plan = attn_plan(a.nh, ntile, ALONE ? ntile : AttnOf<MT, D>::TMIN, cx.j, cx.G);
     if (ALONE && blockIdx.x == 0 && threadIdx.x == 0) carry_status(a.sync);

@@ -28,6 +28,7 @@ __device__ __forceinline__ void pin_order()
 struct Ctx {
     int j, G;            // logical workgroup index, number of workgroups
     char* lds;           // dynamic LDS
+    int source;          // attention in one launch: see mask_source
 };
 
 __device__ __forceinline__ uint32_t ld_relaxed(const uint32_t* p)
