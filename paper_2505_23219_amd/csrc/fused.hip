@@ -74,15 +74,22 @@ void attn_share_on_host(int nh, int ntile, int tmin, int j, int G, int head, int
 }
 
 // An attention call whose heads are one workgroup's each needs no counter and so no launch before its own (3 us of
-// the host's time and as much of the GPU's); the tree's masks are worked out by every workgroup while the
-// cache is on its way.  Against that stands one workgroup's way through all of a head's keys, where up to
-// 32 of them share it otherwise.  Microseconds a call, one launch and two, 32 heads of 128 (24, 64, 128 rows):
-// 4 tiles of 64 keys 11.1 and 12.7, 10.6 and 12.6, 14.7 and 15.0; 6 tiles 13.3 and 14.4, 13.2 and 12.9, -;
-// 5 heads, 5 tiles, 128 rows 14.6 and 12.7; heads of 64: 8 tiles 9.5 and 11.2, 12.5 and 11.2, 18.2 and 12.7.
+// the host's time and as much of the GPU's).  Against that stands one workgroup's way through all of a head's
+// keys, where up to 32 of them share it otherwise.  Where the line lies was measured with 2, 8 and 32 heads, which
+// differ by 0.3 us or less.  Microseconds a call of 8 heads under a tree, in two launches (10.5 to 11.4 at least,
+// the host's time) and in one:
+//   d = 64:  8 rows, 12 tiles of 64 keys 10.6 and 9.6; 32 rows, 10 tiles 11.1 and 10.3, 12 tiles 11.3 and 11.2;
+//            64 rows, 4 tiles 10.7 and 8.5; 65 rows, 3 tiles 10.7 and 9.7, 4 tiles 10.6 and 10.9;
+//            128 rows, 3 tiles 11.6 and 10.1, 4 tiles 11.5 and 11.3
+//   d = 128: 8 rows, 6 tiles 11.5 and 10.3; 32 rows, 6 tiles 15.3 and 14.3; 64 rows, 4 tiles 11.6 and 10.8, 5 tiles
+//            11.8 and 11.8; 72 rows, 2 tiles 12.5 and 10.6, 3 tiles 11.8 and 12.3; 88 rows, 3 tiles 12.5 and
+//            12.3, 4 tiles 12.1 and 14.1; 128 rows, 3 tiles 14.3 and 12.9, 4 tiles 13.7 and 14.7
 bool attention_alone(int M, int kv_len, int d)
 {
     const int64_t ntile = ((int64_t)kv_len + M + 63) / 64;
-    return M <= 32 ? ntile * d <= 6 * 128 : ntile <= (M <= 64 ? 4 : 3);
+    if (M <= 32) return ntile * d <= 6 * 128;
+    if (M <= 64) return ntile <= 4;
+    return ntile <= (d == 128 && M <= 80 ? 2 : 3);
 }
 
 // ---- setup kernel ------------------------------------------------------------

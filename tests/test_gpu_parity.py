@@ -270,13 +270,16 @@ def test_tree_attention_tile_ring(B, model, orc32, M, nh, d, kv_len, tree):
 
 
 # Either side of what is one launch, masks and all (up to 768 keys of 64 or 384 of 128 channels at up to 32 rows, 256
-# at up to 64, 192 above): trees as deep as they get, few and many heads, and a caller's mask.  Tolerance as
-# above; the status word of the call before is kept as by any other call.
+# at up to 64, 192 above, but 128 of 128 channels at up to 80): trees as deep as they get, few and many heads, and a
+# caller's mask.  Tolerance as above; the status word of the call before is kept as by any other call.
 @pytest.mark.parametrize("M,nh,d,kv_len,tree", [
     (1, 3, 128, 383, "chain"), (1, 256, 64, 767, "chain"), (32, 9, 128, 352, "chain"), (32, 9, 128, 353, "chain"),
     (31, 40, 64, 737, "rand5"), (31, 2, 64, 738, "rand5"), (33, 8, 64, 223, "chain"), (33, 8, 64, 224, "chain"),
     (64, 5, 128, 192, "chain"), (64, 33, 128, 193, "star"), (65, 7, 128, 127, "chain"), (65, 7, 128, 128, "rand5"),
-    (128, 1, 64, 64, "chain"), (128, 31, 128, 64, "rand5"), (127, 6, 128, 66, "chain")])
+    (128, 1, 64, 64, "chain"), (128, 31, 128, 64, "rand5"), (127, 6, 128, 66, "chain"), (17, 5, 64, 751, "rand5"),
+    (17, 5, 64, 752, "chain"), (80, 5, 128, 48, "rand5"),
+    (80, 5, 128, 49, "rand5"), (81, 5, 128, 111, "rand5"), (81, 5, 128, 112, "chain"), (80, 5, 64, 112, "rand5"),
+    (80, 5, 64, 113, "chain")])
 def test_attention_in_one_launch_and_in_two(B, model, orc32, M, nh, d, kv_len, tree):
     test_tree_attention(B, model, orc32, M, nh, d, kv_len, tree)
     if tree == "rand5":
