@@ -31,6 +31,8 @@ struct Ctx {
     int source;          // attention in one launch: see mask_source
 };
 
+// What waits look with: a load at the scope of the counting atomics, past this compute unit's L1.  (A
+// read-modify-write that changes nothing, atomicOr(p, 0), is compiled to the same load.)
 __device__ __forceinline__ uint32_t ld_relaxed(const uint32_t* p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -63,13 +65,6 @@ __device__ __forceinline__ void barrier_lds()
 // Invalidates this compute unit's vector L1 (workgroup-scope buffer_inv): loads that follow
 // are served by the L2.
 __device__ __forceinline__ void invalidate_l1() { asm volatile("buffer_inv sc0" ::: "memory"); }
-
-__device__ __forceinline__ uint32_t poll(uint32_t* p)
-{
-    // a read-modify-write that changes nothing: it is served where the counting atomics
-    // are, so it sees them at once (a device-scope load lags them by several microseconds)
-    return atomicOr(p, 0u);
-}
 
 // The workgroups that exchange something count themselves in on a line: arrivals in the low
 // half of a word, the sum of the arrivals' XCD numbers in the high half.  Which XCD a
@@ -107,18 +102,18 @@ __device__ __forceinline__ bool same_xcd(uint32_t* sync, uint32_t word, uint32_t
 
 // Waits until the low half of p has come to `target`, then looks at the XCDs of the n arrivals
 // summed up in the high half.  Gives up (and raises the status word to `code`) after kWaitTicks of
-// wall-clock time, or as soon as another workgroup has given up, so that a launch that is not fully
+// wall-clock time, or within 64 looks of another workgroup's giving up, so that a launch that is not fully
 // resident ends with an error instead of hanging.  One thread calls.  Returns false if what was
 // waited for is not there, or not visible here.
 __device__ __forceinline__ bool bounded_wait(uint32_t* sync, uint32_t* p, uint32_t target, uint32_t n,
                                              uint32_t code)
 {
-    uint32_t v = poll(p);
+    uint32_t v = ld_relaxed(p);
     if ((v & 0xffffu) < target) {
-        // (whether another workgroup has given up is looked at now and then only: a load from behind the
-        // L2 in every turn made the turns three times as long, and what is waited for is seen that much later)
+        // (whether another workgroup has given up is looked at now and then only: a second load in every turn, and
+        // eight times the sleep, made the turns three times as long, and what is waited for is seen that much later)
         const long long t0 = wall_clock64();
-        for (int turn = 1; ((v = poll(p)) & 0xffffu) < target; ++turn) {
+        for (int turn = 1; ((v = ld_relaxed(p)) & 0xffffu) < target; ++turn) {
             if (wall_clock64() - t0 > kWaitTicks || (turn % 64 == 0 && ld_relaxed(sync + kSyncStatus) != 0)) {
                 atomicCAS(sync + kSyncStatus, 0u, code);
                 return false;
