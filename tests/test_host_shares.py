@@ -126,7 +126,7 @@ def test_linear_cut_covers_every_tile_and_fits(M):
     on each XCD), with a k-step for each of eight wavefronts, of no more tiles than there are
     accumulators for."""
     lib = B.lib()
-    out = (C.c_int * 5)()
+    out, grp = (C.c_int * 5)(), (C.c_int * 2)()
     for N in (1, 16, 64, 130, 1000, 1280, 4096, 5003, 5120, 10224, 10240, 22016, 32000, 262144):
         for K in (8, 40, 256, 688, 1280, 3416, 4096, 11008, 65536):
             for solo in (0, 1):
@@ -135,13 +135,17 @@ def test_linear_cut_covers_every_tile_and_fits(M):
                 ntiles, nks = (N + 15) // 16, (K + 31) // 32
                 mt = (M + 15) // 16 if M <= 64 else 6 if M <= 96 else 8
                 assert 1 <= tiles <= 8 and grid % 8 == 0
+                lib.ghd_debug_groups(M, N, K, 256, solo, grp)
                 if whole:
-                    assert parts == 1
-                    ranges = [tile_range(lib, ntiles, grid // 8, i) for i in range(grid)]
-                    assert max(b - a for a, b in ranges) <= tiles and sum(b - a for a, b in ranges) == ntiles
+                    # (groups of workgroups with different rows of x have the same tiles each)
+                    gx = grid // 8 // grp[1]
+                    assert parts == 1 and grid == 8 * gx * grp[1]
+                    ranges = [tile_range(lib, ntiles, gx, i) for i in range(8 * gx)]
+                    assert max(b - a for a, b in ranges) <= tiles
+                    assert sorted(t for a, b in ranges for t in range(a, b)) == list(range(ntiles))
                     assert not rows or (solo and mt <= 4)
                 else:
-                    assert not rows and tiles * mt <= 32 and 2 <= parts <= nks // 8 and ntiles < 640
+                    assert grp[1] == 1 and not rows and tiles * mt <= 32 and 2 <= parts <= nks // 8 and ntiles < 640
                     per_xcd = grid // 8 // parts
                     assert grid == per_xcd * parts * 8 <= 256 and per_xcd * 8 * tiles >= ntiles
 
