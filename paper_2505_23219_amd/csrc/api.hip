@@ -439,7 +439,7 @@ size_t ghd_attention_workspace_bytes(int M, int kv_len, int nh, int d)
 }
 
 // the visibility of the tree rows comes either from parent[] (masks built by the set-up
-// kernel) or from the caller's masks
+// kernel, or by the attention itself where the call is one launch) or from the caller's masks
 static ghd_status attention_call(void* out, const void* q, const void* k_cache, const void* v_cache,
                                  const int32_t* parent_dev, const uint64_t* mask_dev, int M, int kv_len,
                                  int nh, int d, int64_t k_stride_head, int64_t k_stride_tok,

@@ -102,10 +102,10 @@ constexpr double kPrepareUs = 2.5;
 // one): a wavefront's chain, cut short where it is long, and the additions of sets and of parts.
 static double chain_steps(const WLayout& lay, const LinCut& cut)
 {
-    const int waves = cut.whole ? waves_of(cut.mt, cut.tiles) : 8, sets = cut.groups > 1 ? single_sets(cut.mt) : 0;
+    const int waves = cut.whole ? waves_of(cut.mt, cut.tiles) : 8;
     const double chain = (double)ceil_div(lay.nks, cut.parts) / waves, more = cut.parts > 1 ? cut.parts / 4.0 : 0.0;
     double cut_short = chain;
-    if (sets) cut_short = 1.0 + chain / sets / 4.0 + (sets > 2 ? 0.5 : sets > 1 ? 0.25 : 0.0);
+    if (cut.groups > 1) cut_short = 1.0 + chain / kSingleSets / 4.0 + 0.5;      // (two additions bring the sets together)
     else if (long_chains(lay, cut, waves))
         cut_short = folded(cut.mt, cut.tiles) ? kFoldSteps + chain / kFoldSteps / 4.0 : chain / 2.0 + 0.25;
     return (cut_short < chain ? cut_short : chain) + more;

@@ -92,7 +92,7 @@ __host__ __device__ constexpr int pd_of(int MT, int R, int NW)
 //   STRETCHES, where there are no registers for that: a wavefront's range is taken in halves, and the
 //   sums of the first are set aside, in the LDS that the reduction uses later and in what registers
 //   are left; the last fragments of the largest groups are added up step by step instead.
-// And in row groups SINGLE: every k-step's product is added to one of up to four sets of sums in turn, which
+// And in row groups SINGLE: every k-step's product is added to one of four sets of sums in turn, which
 // are added in pairs at the end.  Groups then round less than the parts they stand in for ([300, 3416] at 64 rows:
 // 8.4e-8, in parts 9.4e-8), and stand in for more of them ([1280, 1280] at 64 rows: 7.0 us, in parts 10.0).  Without
 // groups it only costs: [3457, 4872] at 27 rows took 14.1 us instead of 13.7.
@@ -101,7 +101,7 @@ __host__ __device__ constexpr int pd_of(int MT, int R, int NW)
 constexpr int kFoldSteps = 2;
 __host__ __device__ constexpr bool folded(int MT, int R) { return R * MT <= (R <= 3 ? 18 : 16); }
 __host__ __device__ constexpr bool grouped(int MT, int R) { return R == 1 && (MT == 1 || MT == 2 || MT == 4); }
-__host__ __device__ constexpr int single_sets(int MT) { return pd_of(MT, 1, 8) < 4 ? pd_of(MT, 1, 8) : 4; }
+constexpr int kSingleSets = 4;       // (one for each k-step of the ring)
 // Stretches that a range is taken in: two halves, or three where the chains of an even deal are less
 // than half as long.  (Of more than three whole tiles on eight wavefronts only wide matrices are dealt
 // out, whose chains are never long.)
@@ -304,9 +304,9 @@ struct LinShape {
 // One workgroup's share: the tiles first .. first + count - 1 (count <= R; the other slots
 // re-read the first tile, and what they accumulate is never looked at) over the k-steps
 // k0 .. k1 - 1, for the row tiles rt0 .. rt0 + MT - 1 of x.  `finish(a, f, v, m, n0, s_rinv)` is called by one wavefront for every
-// fragment f = slot * MT + row tile with the workgroup's sum v, up to two fragments at a time (one that is
-// not there has a row past all others); `early()` runs between the stream's first loads and its first
-// wait.
+// fragment f = slot * MT + row tile with the workgroup's sum v, LinShape::NB fragments at a time: one, two, or four
+// in workgroups of four wavefronts (one that is not there has a row past all others); `early()` runs between
+// the stream's first loads and its first wait.
 //
 // ROWS: x is row-major and read as it lies (16 rows x 64 bytes per load), which saves a
 // separate packing launch; columns from K on are not read.  STRETCHES: see folded().
@@ -358,6 +358,7 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
     half8 wr[PD][R], xr[PD][MT];
     constexpr bool SINGLE = SETS > 0, FOLDED = folded(MT, R) && !SINGLE, HALVED = STRETCHES > 1;
     static_assert(!(FOLDED && HALVED), "one way or the other");
+    static_assert(!SINGLE || SETS == PD, "a set for each k-step of the ring");
     // What came before: FOLDED: the sums of earlier k-steps; HALVED: those of the first half that
     // stay in registers, as many as there are registers for.  The last NSTEP fragments are not set
     // aside but added up step by step, before the others of a step, which cover the wait for their
@@ -670,7 +671,7 @@ __global__ __launch_bounds__(waves_of(MT, R) * 64) void k_linear(const half8* W,
         return;
     }
     const int lane = threadIdx.x & 63;
-    gemm_group<MT, R, waves_of(MT, R), ROWS, stretches_whole(MT, R), GROUPS ? single_sets(MT) : 0>(
+    gemm_group<MT, R, waves_of(MT, R), ROWS, stretches_whole(MT, R), GROUPS ? kSingleSets : 0>(
         h, lds, c0, c1 - c0, 0, nks, group * MT, solo,
         [&](ArgPtr a, auto&, auto& v, auto& m, auto& n0, const float* s_rinv) { epilogue(a, v, m, n0, lane, s_rinv); });
 }
