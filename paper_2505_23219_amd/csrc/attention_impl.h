@@ -198,8 +198,8 @@ struct NoGate {
 // the unit's probabilities are taken against its own maximum and its product is added to the state in fp32.
 // So do calls in one launch, since a head split over workgroups would have given each unit a state of its own:
 // without it their outputs were 0.7% (up to 32 rows) and 1.1% (33 to 64) further from 64 bits than in two
-// launches, 4% at the worst.  (32 heads of 128: 48 rows, 4 tiles 10.3 -> 10.8 us a call, in two launches 11.6;
-// 128 rows, 3 tiles 12.4 -> 13.1 and 14.5.)
+// launches, 4% at the worst.  (32 heads of 128: 48 rows, 4 tiles 10.3 -> 10.6 us a call, in two launches 11.6;
+// 128 rows, 3 tiles 12.4 -> 12.9 and 14.5; 32 rows, 6 tiles 13.8 -> 14.3 and 15.6.)
 template <int DT, bool APART>
 __device__ __forceinline__ void add_unit(float& mrun, float& lrun, floatx4 (&oacc)[DT], const floatx4 (&s)[2],
                                          const half8 (&vf)[DT], float tmax)
@@ -724,7 +724,7 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const A
         };
         // running state of this head: one for each unit of a tile, which come together when the head ends
         // (one for both rounds more, see add_unit: outputs 1.8% further from 64 bits at 65 to 128 rows, and a
-        // 7B-shaped layer of 128 rows took 152.1 us instead of 152.4)
+        // 7B-shaped layer of 128 rows took 0.3 us of 152 less)
         constexpr int STATES = ALONE ? 1 : UNITS;
         float mrun[STATES], lrun[STATES];
         floatx4 oacc[STATES][DT];
