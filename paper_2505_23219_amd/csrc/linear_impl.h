@@ -111,12 +111,14 @@ __host__ __device__ constexpr int stretches_whole(int MT, int R)
 }
 __host__ __device__ constexpr int stretches_parts(int MT, int R) { return folded(MT, R) ? 1 : 2; }
 
-// Of eight wavefronts, w and w + 4 share a SIMD, and the first of the two gets its data sooner
-// throughout the stream: with equal ranges wavefronts 0-3 end 2.5-6 us before 4-7, which then
-// stream on alone, no faster.  So the first four split kFirstSet/32 of the k range between them
-// (measured on one box, alternating builds: 16 -> 3949 us per 64-row step, 17 -> 3896,
-// 18 -> 3871, 19 -> 3899).
-constexpr int kFirstSet = 18;
+// The wavefronts of a workgroup take the k-steps in turn, so that together they read one run of a tile
+// block from front to back; with a range of its own each (the first of a SIMD's two got 18/32, since
+// it gets its data sooner) the memory saw eight runs per workgroup at a time.  us a call, weights from HBM:
+//   rows   matrix           ranges   in turn
+//      1   [22016, 4096]     28.6     27.4
+//     16   [32000, 4096]     40.9     38.9
+//     64   [32000, 4096]     48.8     48.1
+//     16   7B-shaped layer   89.9     87.0
 
 // What the residual epilogue reads: four columns of a row of the residual stream and of the next
 // norm's gain.  (Requested behind the stream's first loads they delay the weights behind them by more
@@ -326,18 +328,14 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
     float* s_tmp = s_rinv + 128;                           // 1024 floats
     const half8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
 
-    // this wavefront's k-steps
-    const int n = k1 - k0;
-    int ws, we;
-    if constexpr (NW == 8) {
-        const int n_a = n * kFirstSet / 32, w4 = wave & 3;
-        ws = wave < 4 ? k0 + n_a * w4 / 4 : k0 + n_a + (n - n_a) * w4 / 4;
-        we = wave < 4 ? k0 + n_a * (w4 + 1) / 4 : k0 + n_a + (n - n_a) * (w4 + 1) / 4;
-    } else {
-        ws = k0 + n * wave / NW;
-        we = k0 + n * (wave + 1) / NW;
-    }
-    const int s_hi = max(we - 1, k0);       // loads never go past the wavefront's last k-step
+    // this wavefront's k-steps: k0 + turn + i * NW for i < we.  (The turns go round so that what is left
+    // over after the last whole round is spread over the pairs that the reduction adds up, and sums of
+    // unlike size meet late: in the order of the wavefronts K = 136 and 320 rounded 5% worse.)
+    const int turn = NW == 8 ? (wave & 1) << 2 | (wave & 2) | wave >> 2 : (wave & 1) << 1 | wave >> 1;
+    const int n = k1 - k0, we = (n - turn + NW - 1) / NW;
+    const int i_hi = max(we - 1, 0);        // loads never go past the wavefront's last k-step
+    const int kw = min(k0 + turn, k1 - 1);  // (a wavefront without a k-step requests the last one)
+    auto step_of = [&](int i) { return kw + i * NW; };
     const int blk_sh = (h.flags >> kHeadBlk) & 15;
     const int mtp = ROWS ? 0 : (h.flags >> kHeadMtp) & 15;
 
@@ -399,8 +397,9 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
         }
     };
 
-    auto load = [&](auto slot, int s) {
+    auto load = [&](auto slot, int i) {
         constexpr int p = decltype(slot)::value;
+        const int s = step_of(i);
         if constexpr (ROWS) {
             const int col = min(s * 32 + g4 * 8, h.K - 8);
 #pragma unroll
@@ -417,12 +416,12 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
         }
     };
     // MASKED: columns from K on count as zeros (the x fragments are zeroed: one select for all slots)
-    auto compute = [&](auto masked, auto slot, int s) {
+    auto compute = [&](auto masked, auto slot, int i) {
         constexpr int p = decltype(slot)::value;
         constexpr bool MASKED = decltype(masked)::value;
         half8 xf[MT];
         if constexpr (MASKED) {
-            const bool use = s * 32 + g4 * 8 < h.K;
+            const bool use = step_of(i) * 32 + g4 * 8 < h.K;
 #pragma unroll
             for (int b = 0; b < MT; ++b) xf[b] = use ? xr[p][b] : zero8;
         } else {
@@ -442,7 +441,7 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
     auto prologue = [&](auto self, auto slot) {
         constexpr int p = decltype(slot)::value;
         if constexpr (p < PD) {
-            load(slot, min(ws + p, s_hi));
+            load(slot, min(p, i_hi));
             pin_order();
             self(self, std::integral_constant<int, p + 1>{});
         }
@@ -514,8 +513,8 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
         }
     }
 
-    if (ws < we) {
-        int s = ws;
+    if (we > 0) {
+        int s = 0;
         if constexpr (FOLDED) {
             constexpr int ROUNDS = (kFoldSteps + PD - 1) / PD;
             for (; s + (ROUNDS + 1) * PD <= we; s += ROUNDS * PD) {
@@ -534,7 +533,7 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
             if constexpr (STRETCHES == 2 && NW == 8) {
                 // (written out twice, what is set aside needs no registers in the first stretch)
                 if (long_chains) {
-                    stream(ws + (we - ws) / 2);
+                    stream(we / 2);
                     set_aside(false);
                 }
                 stream(we);
@@ -542,7 +541,7 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
                 // (once: the code is fetched while it runs)
                 const int stretches = long_chains ? STRETCHES : 1;
                 for (int i = 1;; ++i) {
-                    stream(i == stretches ? we : ws + (we - ws) * i / STRETCHES);
+                    stream(i == stretches ? we : we * i / STRETCHES);
                     if (i == stretches) break;
                     set_aside(i > 1);
                 }
@@ -568,7 +567,7 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
     }
     if constexpr (HALVED) {
         if (long_chains) {
-            if (ws < we) {
+            if (we > 0) {
 #pragma unroll
                 for (int f = 0; f < NF - NSTEP; ++f) {
                     if (f < S::ASIDE) acc[f / MT][f % MT] += aside[f * 64];
