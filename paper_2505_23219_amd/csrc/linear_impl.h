@@ -119,6 +119,14 @@ __host__ __device__ constexpr int stretches_parts(int MT, int R) { return folded
 //     16   [32000, 4096]     40.9     38.9
 //     64   [32000, 4096]     48.8     48.1
 //     16   7B-shaped layer   89.9     87.0
+// Above 64 rows x takes more of the way into a compute unit than weights do, the wavefronts drift apart
+// over it, and a barrier in every turn of the ring keeps them together (it waits for no load):
+//     96   [32000, 4096]     59.5     59.3, with the barrier 55.9
+//    128   [22016, 4096]     51.7     51.3                   47.5
+//    128   [4096, 11008]     32.8     32.9                   31.7
+// Not with 8 tiles by 128 rows, whose ring holds one k-step: [32000, 4096] 67.5, with the barrier 75.7; up to 64
+// rows it costs 0 to 1%.
+__host__ __device__ constexpr bool keeps_step(int MT, int R) { return MT > 4 && R * MT <= 56; }
 
 // What the residual epilogue reads: four columns of a row of the residual stream and of the next
 // norm's gain.  (Requested behind the stream's first loads they delay the weights behind them by more
@@ -446,9 +454,17 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
             self(self, std::integral_constant<int, p + 1>{});
         }
     };
+    const int common = n / NW;              // k-steps that every wavefront has
     auto ring = [&](auto self, auto slot, int s) {
         constexpr int p = decltype(slot)::value;
         if constexpr (p < PD) {
+            if constexpr (p == 0 && keeps_step(MT, R)) {
+                // (a turn that every wavefront takes: all come to as many barriers)
+                if (s + 2 * PD <= common) {
+                    __builtin_amdgcn_s_barrier();
+                    pin_order();
+                }
+            }
             compute(std::false_type{}, slot, s + p);
             pin_order();
             load(slot, s + p + PD);
