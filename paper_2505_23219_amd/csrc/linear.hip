@@ -83,7 +83,13 @@ size_t linear_part_floats(int M, int G)
 //   their way, in order, so x from the L2 waits its turn among weights from HBM.  [4096, 11008] at
 //   64 rows: 31 us whole-tile (1.4 MB of x per workgroup), 26 in parts of 2 tiles (0.7 MB), 22.6
 //   of 4 (0.34 MB), 23.3 of 8;
-//   parts: the exchange, its partial sums, and a little for every part.
+//   parts: the exchange, its partial sums, and a little for every part;
+//   whole tiles of a narrow matrix: that one tile's KiB out of every four that lie together are read, which counts
+//   up to 16 rows (and is not asked of calls of their own, which have a launch less in whole tiles); and, at 17 to 32
+//   rows, what workgroups with a tile more than others need alone.  us a layer, in whole tiles and in parts: [2560, 6904]
+//   at 1 to 16 rows 53.5 to 55.1 and 51.9 to 53.4; [2048, 5504] 45.1 to 46.7 and 44.1 to 45.2; [5120, 5120] at 24
+//   to 32 rows 130.0 to 131.6 and 126.3 to 127.3; [4096, 4096] at 1 row 84.2 and 85.2, in whole tiles still.  (At 65 rows
+//   and more the same allowance made layers of 8 to 17 heads of 128 4% slower: their gate|up comes out in parts.)
 // Whole tiles read all of x in every workgroup, so they are for wide matrices, and for narrow
 // ones where x is small; parts divide x with the k range; groups of workgroups divide its rows, and exchange
 // nothing.  (Layers of 20 heads of 64 at 37 rows 41.6 us without groups, 39.9 with them; 5 heads of 128 at 128 rows
@@ -96,6 +102,7 @@ constexpr double kCuStreamBytesPerUs = 40e3;
 constexpr double kCuReadBytesPerUs = 55e3;
 constexpr double kXBytesPerUs = 80e3;
 constexpr double kPartsUs = 1.6, kPartsFragmentUs = 0.1, kPartsPartUs = 0.25;
+constexpr double kNarrowWholeUs = 1.0, kUnevenStepUs = 0.03;     // (the latter a k-step)
 constexpr double kPrepareUs = 2.5;
 
 // How often a cut's sums are rounded, in k-steps of one chain (see folded; an addition counts for a quarter of
@@ -138,6 +145,8 @@ LinCut choose_cut(int M, int N, int K, int G, bool solo)
     best.rows = solo && mt <= kRowsMaxMT && (row_cost - 1.0) * mt * P * lay.nks * 1024.0 / kXBytesPerUs < kPrepareUs;
     double best_us = share_us(best.tiles * P, mt * P * (best.rows ? row_cost : 1.0), lay.nks) + (solo && !best.rows ? kPrepareUs : 0.0);
     if (lay.rb == 1) return best;
+    if (mt == 1 && U <= Gx && !solo) best_us += kNarrowWholeUs;
+    if (mt == 2 && U > Gx) best_us += (best.tiles * P - (double)U / Gx) * lay.nks * kUnevenStepUs;
     for (int r = 1; r <= parts_max_tiles(mt); ++r) {
         const int per_xcd = ceil_div(ceil_div(lay.ntiles, r), 8);
         if (per_xcd > Gx) continue;

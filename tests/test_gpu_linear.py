@@ -175,3 +175,44 @@ def test_linear_sums_are_not_left_in_long_chains(B, M, N, K):
         den += float((ref ** 2).sum())
     err = (num / den) ** 0.5
     assert err < 1.1 * (5.5e-15 + 1.4e-15 * chain) ** 0.5, err
+
+
+@pytest.mark.parametrize("M", [1, 40, 64, 96, 128])
+@pytest.mark.parametrize("steps", [1, 3, 7, 8, 9, 15, 16, 17, 31, 33, 50])
+def test_wavefronts_take_the_k_steps_in_turn(B, M, steps):
+    """k-steps of 32 columns that leave wavefronts with none, or with one more than others: in turns of eight and of
+    four wavefronts, with and without the barrier that keeps them together, the last k-step whole and ragged.
+    Bound as in test_linear_kernels_at_their_edges."""
+    say("k-steps in turn", M, steps)
+    for N, K in [(300, 32 * steps), (9000, 32 * steps - 24), (23000, 32 * steps - 8)]:
+        g = torch.Generator(device="cuda").manual_seed(N + K + M)
+        x = torch.randn((M, K), generator=g, device="cuda").to(torch.float16)
+        W = (torch.randn((N, K), generator=g, device="cuda") * 0.02).to(torch.float16)
+        ws = B.workspace(B.lib().ghd_linear_workspace_bytes(M, N, K))
+        ws.fill_(0xFF)
+        y = B.ghd_linear_skinny(x, B.ghd_pack_weight(W), N, ws=ws)
+        assert B.ghd_step_status(ws) == 0
+        ref = x.double() @ W.double().t()
+        err = float((y.double() - ref).norm() / ref.norm())
+        assert err < max(2e-7, 4 * 2.0 ** -24 * K ** 0.5), (N, K, err)
+
+
+@pytest.mark.parametrize("M,N,K,whole", [(1, 2560, 6904, 0), (16, 1536, 4096, 0), (5, 2048, 5504, 0), (24, 5120, 5120, 0),
+                                         (16, 5120, 5120, 1), (32, 4608, 4608, 0), (1, 4096, 4096, 1), (16, 1536, 1536, 1)])
+def test_narrow_matrices_inside_a_step(B, M, N, K, whole):
+    """Narrow matrices as a step's launches cut them (a call whose result meets its input is cut so too): in
+    parts or whole tiles on either side of the line.  Bound as in test_linear_in_place."""
+    say("narrow, inside a step", M, N, K)
+    out = (ctypes.c_int * 5)()
+    B.lib().ghd_debug_cut(M, N, K, 256, 0, out)
+    assert out[0] == whole
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    x = torch.randn((M, K), generator=g, device="cuda").to(torch.float16)
+    W = (torch.randn((N, K), generator=g, device="cuda") * 0.02).to(torch.float16)
+    ref = x.double() @ W.double().t()
+    y = x[:, :N]
+    ws = B.workspace(B.lib().ghd_linear_workspace_bytes(M, N, K))
+    B.ghd_linear_skinny(x, B.ghd_pack_weight(W), N, ws=ws, y=y)
+    assert B.ghd_step_status(ws) == 0
+    err = (y.double() - ref).abs()
+    assert bool((err <= 2.0 ** -11 * ref.abs() + 2e-6 * ref.std() + 2.0 ** -25).all()), float(err.max())
