@@ -47,25 +47,44 @@ struct AttnHeads {
     int h_lo, h_hi;    // this workgroup's heads, local to the XCD (empty if h_lo == h_hi)
 };
 
-__host__ __device__ __forceinline__ AttnHeads attn_heads(int nh, int j, int G)
+// n / d for 0 <= n < 2^20, d > 0, by the reciprocal: (n + 1/2) / d lies 1/(2 d) or more from a whole number, and what
+// the reciprocal and the product round is below n / d * 2^-22.  (The compiler's integer division is some twenty instructions,
+// each of which waits for the one before; eight of them and the read of the argument block were 1.1 us
+// before an attention call's first request.)
+__host__ __device__ __forceinline__ float recip(int d)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    return __builtin_amdgcn_rcpf((float)d);
+#else
+    return 1.0f / (float)d;
+#endif
+}
+__host__ __device__ __forceinline__ int div_small(int n, int d) { return (int)(((float)n + 0.5f) * recip(d)); }
+
+// (of workgroup w of XCD x, which has Gx of them and the heads hx0 .. hx1 - 1)
+__host__ __device__ __forceinline__ AttnHeads attn_heads_of(int hx0, int hx1, int x, int w, int Gx)
 {
     AttnHeads s;
-    const int nx = (G % 8 == 0) ? 8 : 1;
-    s.Gx = G / nx;
-    s.x = j / s.Gx;
-    s.w = j - s.x * s.Gx;
-    s.hx0 = nh * s.x / nx;
-    s.Hx = nh * (s.x + 1) / nx - s.hx0;
+    s.Gx = Gx;
+    s.x = x;
+    s.w = w;
+    s.hx0 = hx0;
+    s.Hx = hx1 - hx0;
     s.h_lo = s.h_hi = 0;
     if (s.Hx == 0) return s;
-    if (s.Hx >= s.Gx) {
-        s.h_lo = s.Hx * s.w / s.Gx;
-        s.h_hi = s.Hx * (s.w + 1) / s.Gx;
+    if (s.Hx >= Gx) {
+        s.h_lo = div_small(s.Hx * w, Gx);
+        s.h_hi = div_small(s.Hx * (w + 1), Gx);
     } else {
-        s.h_lo = ((s.w + 1) * s.Hx - 1) / s.Gx;    // the head whose run of workgroups contains w
+        s.h_lo = div_small((w + 1) * s.Hx - 1, Gx);    // the head whose run of workgroups contains w
         s.h_hi = s.h_lo + 1;
     }
     return s;
+}
+
+__host__ __device__ __forceinline__ AttnHeads attn_heads(int nh, int x, int w, int Gx)
+{
+    return attn_heads_of(nh * x >> 3, nh * (x + 1) >> 3, x, w, Gx);
 }
 
 struct AttnTiles {
@@ -73,7 +92,7 @@ struct AttnTiles {
     int t0, t1;          // its key tiles (empty, with me >= np, when there are more workgroups than tiles)
 };
 
-// tmin: tiles a part should have at least.  A part's wavefronts work in parallel, so splitting a
+// tmin: tiles a part should have at least (0: a head is one part).  A part's wavefronts work in parallel, so splitting a
 // head further than a unit for each of them only adds to the exchange.
 __host__ __device__ __forceinline__ AttnTiles attn_tiles(const AttnHeads& s, int hl, int ntile, int tmin)
 {
@@ -82,37 +101,48 @@ __host__ __device__ __forceinline__ AttnTiles attn_tiles(const AttnHeads& s, int
     t.np = 1;
     t.me = 0;
     if (s.Hx < s.Gx) {
-        int wl0 = s.Gx * hl / s.Hx;                        // head hl's run of local workgroups
-        int wl1 = s.Gx * (hl + 1) / s.Hx;
+        const int wl0 = div_small(s.Gx * hl, s.Hx);        // head hl's run of local workgroups
+        const int wl1 = div_small(s.Gx * (hl + 1), s.Hx);
         t.first = s.x * s.Gx + wl0;
-        const int most = (ntile + tmin - 1) / tmin;
+        const int most = tmin == 0 ? 1 : tmin == 1 ? ntile : (ntile + tmin - 1) / tmin;
         t.np = (wl1 - wl0 < most) ? wl1 - wl0 : most;
         t.me = s.w - wl0;
     }
-    // boundaries rounded up: when the tiles do not divide evenly the longer ranges come first,
+    // boundaries ntile * me / np rounded up: when the tiles do not divide evenly the longer ranges come first,
     // and the last workgroup, whose range ends with the (costlier) tree tile, gets a shorter one
     t.t0 = t.t1 = 0;
     if (t.me < t.np) {
-        t.t0 = (ntile * t.me + t.np - 1) / t.np;
-        t.t1 = (ntile * (t.me + 1) + t.np - 1) / t.np;
+        // ntile = q * np + r; the estimate of q is a few off where ntile has more bits than a float
+        const int guess = (int)((float)ntile * recip(t.np)), left = ntile - guess * t.np;
+        const int more = (int)floorf(((float)left + 0.5f) * recip(t.np));
+        const int q = guess + more, r = left - more * t.np;
+        t.t0 = q * t.me + div_small(r * t.me + t.np - 1, t.np);
+        t.t1 = q * (t.me + 1) + div_small(r * (t.me + 1) + t.np - 1, t.np);
     }
     return t;
 }
 
-// A workgroup's heads and its tiles of the first of them.  (Some eight integer divisions and a read of
-// the argument block: the launch that shares itself with the QKV layer has them done while its first
-// weights are on their way, 1.2 us that came between the stores of q and the gate before.)
+// A workgroup's heads and its tiles of the first of them.  (The launch that shares itself with the QKV layer has it
+// done while its first weights are on their way.)
 struct AttnPlan {
     AttnHeads heads;
     AttnTiles tiles;
 };
-__host__ __device__ __forceinline__ AttnPlan attn_plan(int nh, int ntile, int tmin, int j, int G)
+__host__ __device__ __forceinline__ AttnPlan attn_plan(int nh, int ntile, int tmin, int x, int w, int Gx)
 {
     AttnPlan p;
-    p.heads = attn_heads(nh, j, G);
+    p.heads = attn_heads(nh, x, w, Gx);
     p.tiles = p.heads.h_lo < p.heads.h_hi ? attn_tiles(p.heads, p.heads.h_lo, ntile, tmin) : AttnTiles{};
     return p;
 }
+
+// What a launch needs for its first requests of the cache; the rest is in the argument block, read behind them.
+struct AttnFirst {
+    const half_t *k, *v;
+    int64_t k_head, v_head;          // elements from head to head
+    uint32_t st_tok, st_ch;          // ... from key to key of K, and from channel to channel of V
+    int T, M, nh;                    // keys with the tree's, rows, heads
+};
 
 // 2^x for x <= 0 (softmax weights): the hardware instruction; results below the smallest
 // normal number flush to zero, which is what a weight that small should be.
@@ -166,21 +196,15 @@ __device__ __forceinline__ void masks_from_parent(int up, int M, uint64_t* mask,
 // it requests queries and cache (the work shares are worked out in between): the masks are then made while those are on
 // their way.  Loads return in order: requested behind the cache, parent[] came back behind it, and the
 // rounds of the doubling began when all else was there.
-__device__ __forceinline__ uint32_t mask_source(const FusedArgs& a)
+__device__ __forceinline__ uint32_t mask_source(const void* source, bool parents, int M)
 {
-    const int tid = threadIdx.x;
-    uint32_t word = 0;
-    if (a.att_parent) {
-        if (tid < a.M) word = (uint32_t)gp(a.att_parent)[tid];
-    } else if (tid < a.M * 4) {
-        word = ((GLOBAL const uint32_t*)gp(a.mask))[tid];
-    }
-    return word;
+    const int tid = threadIdx.x, n = parents ? M : M * 4;
+    return tid < n ? ((GLOBAL const uint32_t*)gp((const uint32_t*)source))[tid] : 0u;
 }
-__device__ __forceinline__ void masks_from_source(const FusedArgs& a, uint32_t word, uint64_t* mask, int32_t* s_up)
+__device__ __forceinline__ void masks_from_source(bool parents, int M, uint32_t word, uint64_t* mask, int32_t* s_up)
 {
-    if (a.att_parent) masks_from_parent((int)word, a.M, mask, s_up);
-    else if ((int)threadIdx.x < a.M * 4) ((uint32_t*)mask)[threadIdx.x] = word;
+    if (parents) masks_from_parent((int)word, M, mask, s_up);
+    else if ((int)threadIdx.x < M * 4) ((uint32_t*)mask)[threadIdx.x] = word;
 }
 
 // `gate` is called once by every workgroup (all threads), before the first read of q or of a
@@ -281,8 +305,8 @@ __device__ __forceinline__ bool finish_parts(const FusedArgs& a, GLOBAL half_t* 
     const int r0 = M * me / np, r1 = M * (me + 1) / np;        // the rows this part merges
     if (tid == 0) {
         uint32_t* const word = epoch_word(cnt, epoch);
-        arrive(word);
-        if (r0 < r1) *wait_ok = bounded_wait(a.sync, word, (uint32_t)np, (uint32_t)np, 2000u);
+        const uint32_t seen = arrive(word);
+        if (r0 < r1) *wait_ok = bounded_wait(a.sync, word, seen, (uint32_t)np, (uint32_t)np, 2000u);
         if (me == 0) clear_next(cnt, epoch);
     }
     if (r0 >= r1) return true;
@@ -323,22 +347,19 @@ __device__ __forceinline__ bool finish_parts(const FusedArgs& a, GLOBAL half_t* 
     return true;
 }
 
-template <int MT, int D, bool PREFETCH, bool ALONE, class Gate>
-__device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const AttnPlan& plan, const half_t* q_,
-                                            const half_t* kc_, const half_t* vc_, half_t* out_, uint32_t epoch, Gate gate)
+template <int MT, int D, bool PREFETCH, bool ALONE, class Late, class Gate>
+__device__ __forceinline__ bool attn_direct(const AttnFirst& f, Late late, Ctx& cx, const AttnPlan& plan, Gate gate)
 {
     constexpr int DS = D / 32, DT = D / 16;
     DirectLds<MT, D>& sm = *reinterpret_cast<DirectLds<MT, D>*>(cx.lds);
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int M = a.M, nh = a.nh, kv_len = a.kv_len, T = a.kv_len + a.M, Mpad = a.Mpad;
-    const float scale_log2e = a.scale_log2e;
-    const auto q = gp(q_), kc = gp(kc_), vc = gp(vc_);
-    const auto out = gp(out_);
-    const auto o_part = gp(a.o_part), ml_part = gp(a.ml_part);
+    const int M = f.M, nh = f.nh, T = f.T, kv_len = T - M;
+    constexpr int Mpad = MT * 16;
+    const auto kc = gp(f.k), vc = gp(f.v);
     const int ntile = (T + 63) >> 6, nunit = (T + 31) >> 5;
-    const uint32_t st_tok = (uint32_t)a.stride_tok, st_ch = (uint32_t)a.v_stride_ch;
+    const uint32_t st_tok = f.st_tok, st_ch = f.st_ch;
 
     // Work shares.  Heads are dealt to the 8 XCDs in contiguous blocks.  Inside an XCD a
     // workgroup works on one head at a time: with fewer heads than workgroups, every head
@@ -350,13 +371,14 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const A
     // (bits from M on, which a caller's mask may have set, are never looked at: a mask bit is
     // only consulted for keys kv_len <= key < kv_len + M)
     uint64_t mask_lo = 0, mask_hi = 0;
-    {
-        const auto mask = gp(a.mask);
+    auto request_masks = [&]() {
+        const auto mask = gp(late().mask);
         if (tid < M && !ALONE) {
             mask_lo = mask[2 * tid];
             mask_hi = mask[2 * tid + 1];
         }
-    }
+    };
+    if constexpr (PREFETCH) request_masks();
 
     bool gated = false;
     for (int hl = h_lo; hl < (PREFETCH ? min(h_hi, h_lo + 1) : h_hi); ++hl) {
@@ -366,8 +388,8 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const A
         const AttnTiles ts = hl == h_lo ? plan.tiles : attn_tiles(hs, hl, ntile, kDirectTiles);
         const int first = ts.first, np = ts.np, me = ts.me;
         if (me >= np) continue;                            // more workgroups than parts
-        const auto kh = kc + (size_t)head * a.stride_head;
-        const auto vh = vc + (size_t)head * a.v_stride_head;
+        const auto kh = kc + (int64_t)head * f.k_head;
+        const auto vh = vc + (int64_t)head * f.v_head;
         const int u1 = min(2 * ts.t1, nunit);
         int u = 2 * ts.t0 + wave;                          // this wavefront's unit
 
@@ -394,18 +416,26 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const A
 #pragma unroll
             for (int e = 0; e < DT; ++e) vf[e] = load16((GLOBAL const char*)vh + (size_t)(e * 16 * st_ch) * 2, off);
         };
-        // Requests, in order: [a unit of earlier steps] gate, queries, [the unit otherwise].  No
+        // Requests, in order: [a unit known before the gate] gate, queries, [the unit otherwise].  Without a gate the
+        // first unit is requested before the argument block is read.  With one, no
         // cache line of a unit that ends 64 rows or more below kv_len can hold a row that this
         // launch writes, whatever the strides and the alignment of the cache.
-        const bool early = PREFETCH && !gated && u < u1 && u * 32 + 96 <= kv_len;
+        const bool early = !gated && u < u1 && (!PREFETCH || u * 32 + 96 <= kv_len);
         if (early) {
             load_k(u);
             load_v(u);
+            pin_order();
         }
         if (!gated) {
             if (!gate()) return false;
+            if constexpr (!PREFETCH) request_masks();
             gated = true;
         }
+        const FusedArgs& a = late();
+        const float scale_log2e = a.scale_log2e;
+        const auto q = gp(a.att_q);
+        const auto out = gp(a.att_out);
+        const auto o_part = gp(a.o_part), ml_part = gp(a.ml_part);
         int source = 0;
         if constexpr (ALONE) {
             source = hidden(cx.source);                    // (it is there)
@@ -428,7 +458,7 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const A
             load_v(u);
         }
         pin_order();           // (all requests are out before the first of them is waited for)
-        if constexpr (ALONE) masks_from_source(a, source, &sm.mask[0][0], sm.up);
+        if constexpr (ALONE) masks_from_source(cx.parents, M, source, &sm.mask[0][0], sm.up);
         else if (tid < MT * 16) {
             sm.mask[tid][0] = mask_lo;
             sm.mask[tid][1] = mask_hi;
@@ -548,7 +578,7 @@ __device__ __forceinline__ bool attn_direct(const FusedArgs& a, Ctx& cx, const A
             }
         }
         }
-        if (np > 1 && !finish_parts<D>(a, out, head, first, np, me, epoch, &sm.wait_ok)) return false;
+        if (np > 1 && !finish_parts<D>(a, out, head, first, np, me, a.att_epoch, &sm.wait_ok)) return false;
         // a workgroup that goes on to another head reuses its LDS and its partial-state slot
         // (a workgroup with several heads has them to itself: np = 1)
         if (hl + 1 < h_hi) __syncthreads();
@@ -607,9 +637,8 @@ __device__ __forceinline__ void wait_tiles_of(int n)
     wait_loads<PER_TILE * MOST>();
 }
 
-template <int MT, int D, bool PREFETCH, bool ALONE, class Gate>
-__device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const AttnPlan& plan, const half_t* q_,
-                                            const half_t* kc_, const half_t* vc_, half_t* out_, uint32_t epoch, Gate gate)
+template <int MT, int D, bool PREFETCH, bool ALONE, class Late, class Gate>
+__device__ __forceinline__ bool attn_staged(const AttnFirst& f, Late late, Ctx& cx, const AttnPlan& plan, Gate gate)
 {
     constexpr int DS = D / 32, DT = D / 16;
     constexpr int HALVES = MT <= 4 ? 2 : 1;            // wavefronts that share a row tile, each for its keys
@@ -625,11 +654,9 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const A
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, g4 = lane >> 4;
     const int wq = HALVES == 2 ? wave & 3 : wave, half = HALVES == 2 ? wave >> 2 : 0;    // row tile, key half
-    const int M = a.M, nh = a.nh, kv_len = a.kv_len, T = a.kv_len + a.M, Mpad = a.Mpad;
-    const float scale_log2e = a.scale_log2e;
-    const auto q = gp(q_), kc = gp(kc_), vc = gp(vc_);
-    const auto out = gp(out_);
-    const auto o_part = gp(a.o_part), ml_part = gp(a.ml_part);
+    const int M = f.M, nh = f.nh, T = f.T, kv_len = T - M;
+    constexpr int Mpad = MT * 16;
+    const auto kc = gp(f.k), vc = gp(f.v);
     const int ntile = (T + 63) >> 6;
     const int mrow = wq * 16 + c;
     const bool mok = mrow < M, wave_active = wq * 16 < M;
@@ -641,7 +668,7 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const A
     // (piece p of row r in place p ^ f(r)), so that the 16 rows that an MFMA operand takes the same
     // piece of are spread over all banks.
     constexpr int KR = 512 / D;                        // K rows of a KiB: 4 or 8
-    const uint32_t st_tok2 = (uint32_t)a.stride_tok * 2, st_ch2 = (uint32_t)a.v_stride_ch * 2;
+    const uint32_t st_tok2 = f.st_tok * 2, st_ch2 = f.st_ch * 2;
     const int k_row = wave * PIECES * KR + lane / (D / 8);                   // (piece i: i * KR rows on)
     const uint32_t k_piece = D == 128 ? (uint32_t)((lane & 15) ^ ((lane >> 4) | (wave & 3) << 2)) * 16
                                       : (uint32_t)((lane & 7) ^ (((lane >> 4) & 1) | (wave & 3) << 1)) * 16;
@@ -659,7 +686,7 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const A
     // the masks of all rows, four words each: a word a thread (rows past the last read the last word;
     // bits from M on, which a caller's mask may have set, are never looked at)
     auto request_masks = [&]() {
-        to_lds_word((GLOBAL const char*)gp(a.mask), (uint32_t)min(tid, M * 4 - 1) * 4, lds0 + (uint32_t)offsetof(L, mask) + wave * 256);
+        to_lds_word((GLOBAL const char*)gp(late().mask), (uint32_t)min(tid, M * 4 - 1) * 4, lds0 + (uint32_t)offsetof(L, mask) + wave * 256);
     };
 
     bool gated = false;
@@ -669,8 +696,8 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const A
         const AttnTiles ts = hl == h_lo ? plan.tiles : attn_tiles(hs, hl, ntile, 1);
         const int first = ts.first, np = ts.np, me = ts.me, t0 = ts.t0, t1 = ts.t1;
         if (me >= np) continue;                            // more workgroups than tiles
-        const auto kh = (GLOBAL const char*)(kc + (size_t)head * a.stride_head);
-        const auto vh = (GLOBAL const char*)(vc + (size_t)head * a.v_stride_head);
+        const auto kh = (GLOBAL const char*)(kc + (int64_t)head * f.k_head);
+        const auto vh = (GLOBAL const char*)(vc + (int64_t)head * f.v_head);
 
         // Keys from T on read the last one; V^T pieces past the capacity, which hold no key, the last
         // piece.  (Offsets inside a head fit 32 bits: checked on the host.)
@@ -686,7 +713,8 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const A
                 to_lds_nt(vh, (uint32_t)ch * st_ch2 + min(key2, v_last), at + KB + i * 1024);
             }
         };
-        // Requests, in order: [tiles known before the gate] gate, queries, [the rest].  A tile is known
+        // Requests, in order: [tiles known before the gate] gate, queries, [the rest].  Without a gate the first tile is
+        // requested before the argument block is read.  With one, a tile is known
         // if it ends at least 64 rows below kv_len: no cache line of it holds a row that this launch
         // writes, whatever the strides and the alignment of the cache.  The queries take the last
         // buffer until its first tile is requested; every wavefront brings its own.
@@ -695,6 +723,7 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const A
         if (!gated) {
             // (loads return in order: the wavefront that polls at the gate requests nothing before)
             const bool polls = PREFETCH && wave == 0;
+            if constexpr (!PREFETCH) request(t0), n_pre = 1, pin_order();
             if (!polls && !ALONE) request_masks();
             if constexpr (PREFETCH)
                 for (; !polls && n_pre < up_front && (t0 + n_pre) * 64 + 128 <= kv_len; ++n_pre) request(t0 + n_pre);
@@ -702,6 +731,11 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const A
             gated = true;
             if (polls) request_masks();
         }
+        const FusedArgs& a = late();
+        const float scale_log2e = a.scale_log2e;
+        const auto q = gp(a.att_q);
+        const auto out = gp(a.att_out);
+        const auto o_part = gp(a.o_part), ml_part = gp(a.ml_part);
         int source = 0;
         if constexpr (ALONE) {
             source = hidden(cx.source);                    // (it is there)
@@ -715,7 +749,7 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const A
         }
         for (int n = n_pre; n < up_front; ++n) request(t0 + n);
 
-        if constexpr (ALONE) masks_from_source(a, source, (uint64_t*)sm.mask, sm.up);
+        if constexpr (ALONE) masks_from_source(cx.parents, M, source, (uint64_t*)sm.mask, sm.up);
 
         // waits for all but the youngest n tiles
         auto wait_tiles = [&](int n) {
@@ -868,7 +902,7 @@ __device__ __forceinline__ bool attn_staged(const FusedArgs& a, Ctx& cx, const A
         }
         if (np > 1) {
             if (mok && half == 0 && g4 == 0) *(GLOBAL floatx2*)(ml_part + ((size_t)cx.j * Mpad + mrow) * 2) = (floatx2){m, l};
-            if (!finish_parts<D>(a, out, head, first, np, me, epoch, &sm.wait_ok)) return false;
+            if (!finish_parts<D>(a, out, head, first, np, me, a.att_epoch, &sm.wait_ok)) return false;
         }
         // a workgroup that goes on to another head reuses its LDS (it has its heads to itself: np = 1)
         if (hl + 1 < h_hi) __syncthreads();
@@ -884,16 +918,16 @@ template <int MT, int D>
 struct AttnOf {
     static constexpr bool DIRECT = MT <= 2;
     static constexpr int TMIN = DIRECT ? kDirectTiles : 1;         // tiles that a part has at least
+    static_assert((kDirectTiles & (kDirectTiles - 1)) == 0, "divided by");
     using Lds = std::conditional_t<DIRECT, DirectLds<MT, D>, StagedLds<layout_tiles(MT), D>>;
 };
 
-// ALONE: no head is shared and there was no set-up launch (see attention_alone)
-template <int MT, int D, bool PREFETCH = false, bool ALONE = false, class Gate = NoGate>
-__device__ __forceinline__ bool attn_phase(const FusedArgs& a, Ctx& cx, const AttnPlan& plan, const half_t* q, const half_t* kc,
-                                           const half_t* vc, half_t* out, uint32_t epoch, Gate gate = Gate())
+// ALONE: no head is shared and there was no set-up launch (see attention_alone).  `late` gives the argument block.
+template <int MT, int D, bool PREFETCH = false, bool ALONE = false, class Late, class Gate = NoGate>
+__device__ __forceinline__ bool attn_phase(const AttnFirst& f, Late late, Ctx& cx, const AttnPlan& plan, Gate gate = Gate())
 {
-    if constexpr (AttnOf<MT, D>::DIRECT) return attn_direct<MT, D, PREFETCH, ALONE>(a, cx, plan, q, kc, vc, out, epoch, gate);
-    else return attn_staged<layout_tiles(MT), D, PREFETCH, ALONE>(a, cx, plan, q, kc, vc, out, epoch, gate);
+    if constexpr (AttnOf<MT, D>::DIRECT) return attn_direct<MT, D, PREFETCH, ALONE>(f, late, cx, plan, gate);
+    else return attn_staged<layout_tiles(MT), D, PREFETCH, ALONE>(f, late, cx, plan, gate);
 }
 
 }  // namespace ghd

@@ -5,16 +5,35 @@
 namespace ghd {
 
 
+// The first twelve words are what the first requests of the cache need (see AttnFirst); `source`: see mask_source.  With
+// those read from the argument block and the shares worked out by integer divisions the first request went out
+// 2.2 to 2.8 us after the start of a call's last launch.  us a call, then and now: 24 heads of 128, 48 rows, 3001 cached
+// 18.3 and 17.4; 32 heads of 128, 1 row, 2048 cached 13.3 and 12.7; 16 heads, 32 rows, 8000 cached 22.7 and 21.6; 8 heads of 64,
+// 100 rows, 1000 cached 11.4 and 11.0.
+constexpr int kAttM = 0, kAttNh = 8, kAttGx = 17, kAttParents = 23, kAttFar = 24;    // bits of `flags`: M, nh, workgroups per XCD, ...
+static_assert(kRangeWgs / 8 < 64 && GHD_MAX_M < 256, "fits its bits");
 template <int MT, int D, bool ALONE>
-__global__ __launch_bounds__(kFT) void k_attention(const FusedArgs a)
+__global__ __launch_bounds__(kFT) void k_attention(const half_t* k, const half_t* v, const void* source, uint32_t k_head8,
+                                                   uint32_t v_head8, uint32_t st_tok, uint32_t st_ch, int T, uint32_t flags,
+                                                   const FusedArgs)
 {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    Ctx cx = make_ctx(lds);
-    if constexpr (ALONE) cx.source = (int)mask_source(a);
-    const int ntile = (a.kv_len + a.M + 63) >> 6;
-    const AttnPlan plan = attn_plan(a.nh, ntile, ALONE ? ntile : AttnOf<MT, D>::TMIN, cx.j, cx.G);
-    if (ALONE && blockIdx.x == 0 && threadIdx.x == 0) carry_status(a.sync);
-    attn_phase<MT, D, false, ALONE>(a, cx, plan, a.att_q, a.att_k, a.att_v, a.att_out, a.att_epoch);
+    const int M = flags >> kAttM & 255, nh = flags >> kAttNh & 511, Gx = flags >> kAttGx & 63;
+    Ctx cx;
+    cx.G = 8 * Gx;
+    cx.j = (blockIdx.x & 7) * Gx + (blockIdx.x >> 3);
+    cx.lds = lds;
+    cx.parents = flags >> kAttParents & 1;
+    if constexpr (ALONE) cx.source = (int)mask_source(source, cx.parents, M);
+    AttnFirst f = {k, v, (int64_t)k_head8 * 8, (int64_t)v_head8 * 8, st_tok, st_ch, T, M, nh};
+    if (flags >> kAttFar & 1) {              // (heads 64 GiB apart)
+        f.k_head = late_args()->stride_head;
+        f.v_head = late_args()->v_stride_head;
+    }
+    const AttnPlan plan = attn_plan(nh, (T + 63) >> 6, ALONE ? 0 : AttnOf<MT, D>::TMIN, blockIdx.x & 7, blockIdx.x >> 3, Gx);
+    const auto late = []() -> const FusedArgs& { return *(const FusedArgs*)late_args(); };
+    attn_phase<MT, D, false, ALONE>(f, late, cx, plan);
+    if (ALONE && blockIdx.x == 0 && threadIdx.x == 0) carry_status(late().sync);
     wait_loads<0>();       // (nothing is on its way to the LDS when the workgroup ends)
 }
 
@@ -29,7 +48,13 @@ static ghd_status launch_attention_t(const FusedArgs& a, hipStream_t st)
     ghd_status s = launch_resident_checked((const void*)k_attention<MT, D, ALONE>, kFT, lds, &G);
     if (s) return s;
     if (ALONE) G = 8 * ceil_div(a.nh, 8) < G ? 8 * ceil_div(a.nh, 8) : G;
-    hipLaunchKernelGGL((k_attention<MT, D, ALONE>), dim3(G), dim3(kFT), lds, st, a);
+    // (strides are multiples of 8, and inside a head they fit 32 bits: checked where the call came in)
+    const bool far = ((a.stride_head | a.v_stride_head) >> 35) != 0;
+    const bool parents = ALONE && a.att_parent;
+    const uint32_t flags = (uint32_t)a.M << kAttM | (uint32_t)a.nh << kAttNh | (uint32_t)(G / 8) << kAttGx | (uint32_t)parents << kAttParents | (uint32_t)far << kAttFar;
+    const void* source = parents ? (const void*)a.att_parent : (const void*)a.mask;
+    hipLaunchKernelGGL((k_attention<MT, D, ALONE>), dim3(G), dim3(kFT), lds, st, a.att_k, a.att_v, source, (uint32_t)(a.stride_head >> 3),
+                       (uint32_t)(a.v_stride_head >> 3), (uint32_t)a.stride_tok, (uint32_t)a.v_stride_ch, a.kv_len + a.M, flags, a);
     return check_launch();
 }
 
@@ -59,7 +84,8 @@ ghd_status launch_fused(const FusedArgs& a, hipStream_t st)
 // one of j's heads at all (otherwise the first five are -1).
 void attn_share_on_host(int nh, int ntile, int tmin, int j, int G, int head, int* out)
 {
-    const AttnHeads hs = attn_heads(nh, j, G);
+    const int Gx = G / 8;        // (a grid that the 8 XCDs do not divide counts as one of them)
+    const AttnHeads hs = G % 8 ? attn_heads_of(0, nh, 0, j, G) : attn_heads(nh, j / Gx, j % Gx, Gx);
     for (int i = 0; i < 6; ++i) out[i] = -1;
     out[5] = 0;
     const int hl = head - hs.hx0;

@@ -47,19 +47,7 @@ constexpr int kHeadMtp = 4;      // bits 4-7: row tiles of the packed activation
 constexpr int kHeadM = 8;        // bits 8-15: rows of x
 constexpr int kHeadSolo = 16;    // bit 16: a call of its own, without a set-up kernel
 constexpr int kHeadLong = 17;    // bit 17: chains of sums are cut short (see folded)
-constexpr int kTailAt = 48;      // byte offset of FusedArgs in the kernel arguments
 static_assert(sizeof(LinHead) == kTailAt && alignof(FusedArgs) == 8, "kernel argument layout");
-
-// FusedArgs as it lies in the kernel arguments.  The (empty) asm makes the pointer opaque:
-// no read through it is moved ahead of this point.
-typedef const __attribute__((address_space(4))) FusedArgs* ArgPtr;
-__device__ __forceinline__ ArgPtr late_args()
-{
-    typedef const __attribute__((address_space(4))) char* kernarg_bytes;
-    kernarg_bytes p = (kernarg_bytes)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(p)::"memory");
-    return (ArgPtr)(p + kTailAt);
-}
 
 // wavefronts of a workgroup
 __host__ __device__ constexpr int waves_of(int MT, int R) { return MT > 4 && R * MT > 32 ? 4 : 8; }
@@ -744,8 +732,8 @@ __global__ __launch_bounds__(512) void k_linear_parts(const half8* W, const half
     uint32_t* const cnt = a->sync + a->lin_cnt + slot0 * kCntStride;
     if (tid == 0) {
         uint32_t* const word = epoch_word(cnt, a->lin_epoch);
-        arrive(word);
-        *s_wait_ok = bounded_wait(a->sync, word, (uint32_t)S, (uint32_t)S, 1000u + a->lin_epi);
+        const uint32_t seen = arrive(word);
+        *s_wait_ok = bounded_wait(a->sync, word, seen, (uint32_t)S, (uint32_t)S, 1000u + a->lin_epi);
         if (part == 0) clear_next(cnt, a->lin_epoch);
     }
     __syncthreads();

@@ -25,10 +25,25 @@ __device__ __forceinline__ void pin_order()
     __builtin_amdgcn_sched_barrier(0);
 }
 
+// Kernels whose first loads must not wait for the argument block have what those need in their first twelve words,
+// which the hardware puts into scalar registers (see LinHead), and the block behind them.
+constexpr int kTailAt = 48;      // byte offset of FusedArgs in the kernel arguments
+// FusedArgs as it lies in the kernel arguments.  The (empty) asm makes the pointer opaque:
+// no read through it is moved ahead of this point.
+typedef const __attribute__((address_space(4))) FusedArgs* ArgPtr;
+__device__ __forceinline__ ArgPtr late_args()
+{
+    typedef const __attribute__((address_space(4))) char* kernarg_bytes;
+    kernarg_bytes p = (kernarg_bytes)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p)::"memory");
+    return (ArgPtr)(p + kTailAt);
+}
+
 struct Ctx {
     int j, G;            // logical workgroup index, number of workgroups
     char* lds;           // dynamic LDS
     int source;          // attention in one launch: see mask_source
+    bool parents;        // ... whether that is parent[]
 };
 
 // What waits look with: a load at the scope of the counting atomics, past this compute unit's L1.  (A
@@ -104,11 +119,11 @@ __device__ __forceinline__ bool same_xcd(uint32_t* sync, uint32_t word, uint32_t
 // summed up in the high half.  Gives up (and raises the status word to `code`) after kWaitTicks of
 // wall-clock time, or within 64 looks of another workgroup's giving up, so that a launch that is not fully
 // resident ends with an error instead of hanging.  One thread calls.  Returns false if what was
-// waited for is not there, or not visible here.
-__device__ __forceinline__ bool bounded_wait(uint32_t* sync, uint32_t* p, uint32_t target, uint32_t n,
+// waited for is not there, or not visible here.  `v` is what was seen of p already: who arrives last knows it from its
+// own arrival, and everybody waits for that one (0.1 us of an attention call).
+__device__ __forceinline__ bool bounded_wait(uint32_t* sync, uint32_t* p, uint32_t v, uint32_t target, uint32_t n,
                                              uint32_t code)
 {
-    uint32_t v = ld_relaxed(p);
     if ((v & 0xffffu) < target) {
         // (whether another workgroup has given up is looked at now and then only: a second load in every turn, and
         // eight times the sleep, made the turns three times as long, and what is waited for is seen that much later)
@@ -151,19 +166,6 @@ __device__ __forceinline__ void zero_sync(uint32_t* sync, int block)
         if (i > 0 && i < n) ((word4*)sync)[i] = (word4){0u, 0u, 0u, 0u};
     }
     if (block == 0 && threadIdx.x == 0) carry_status(sync);
-}
-
-// Workgroups are dealt round-robin to the 8 XCDs (of which the grid is a multiple, see
-// launch_resident_checked); neighbours in the work sequence, which share heads and exchange partial
-// results, get the same XCD.
-__device__ __forceinline__ Ctx make_ctx(char* lds)
-{
-    Ctx cx;
-    const int G = gridDim.x, i = blockIdx.x;
-    cx.G = G;
-    cx.j = (i % 8) * (G / 8) + i / 8;
-    cx.lds = lds;
-    return cx;
 }
 
 }  // namespace ghd

@@ -30,7 +30,7 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
     AttnPlan plan;
     auto make_plan = [&]() {       // (while the first weights are on their way)
         const ArgPtr la = late_args();
-        plan = attn_plan(la->nh, (la->kv_len + la->M + 63) >> 6, AttnOf<MT, D>::TMIN, cx.j, cx.G);
+        plan = attn_plan(la->nh, (la->kv_len + la->M + 63) >> 6, AttnOf<MT, D>::TMIN, xcd, blockIdx.x >> 3, Gx);
     };
     if (c0 >= c1) make_plan();
     else
@@ -71,7 +71,7 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
         int* s_ok = &reinterpret_cast<typename AttnOf<MT, D>::Lds*>(cx.lds)->wait_ok;
         if (threadIdx.x == 0)
             *s_ok = last ? same_xcd(a.sync, word, (uint32_t)Gx)
-                        : bounded_wait(a.sync, go + cx.j * kCntStride, round, (uint32_t)Gx, 3000u);
+                        : bounded_wait(a.sync, go + cx.j * kCntStride, ld_relaxed(go + cx.j * kCntStride), round, (uint32_t)Gx, 3000u);
         barrier_lds();
         if (!*s_ok) return false;
         // Nothing of q16 or of the tree's cache rows should be in this compute unit's L1 (it
@@ -81,7 +81,9 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
         invalidate_l1();
         return true;
     };
-    attn_phase<MT, D, true, false>(a, cx, plan, a.att_q, a.att_k, a.att_v, a.att_out, a.att_epoch, gate);
+    const AttnFirst f = {a.att_k, a.att_v, a.stride_head, a.v_stride_head, (uint32_t)a.stride_tok, (uint32_t)a.v_stride_ch, a.kv_len + a.M, a.M, a.nh};
+    const auto late = [&]() -> const FusedArgs& { return a; };
+    attn_phase<MT, D, true, false>(f, late, cx, plan, gate);
     wait_loads<0>();       // (nothing is on its way to the LDS when the workgroup ends)
 }
 

@@ -224,3 +224,34 @@ def test_exchange_counts_each_launch_by_itself(n):
     xcd[stray * n] = (xcd[stray * n] + 1) % 8
     lib.ghd_debug_exchange((C.c_int * len(xcd))(*xcd), epochs, n, ok)
     assert ok[stray] < n and [o for e, o in enumerate(ok) if e != stray] == [n] * (epochs - 1)
+
+
+def test_attention_shares_are_those_of_integer_division():
+    """The kernels divide by reciprocals in floats: the same heads and tile boundaries as whole-number division
+    gives, over all head counts, grids and lengths that a call may have."""
+    import random
+    rng = random.Random(7)
+    lib, out = B.lib(), (C.c_int * 6)()
+    for _ in range(40000):
+        nh, G, tmin = rng.randint(1, 256), 8 * rng.choice([32, rng.randint(2, 32)]), rng.choice([1, 4])
+        most = (2 ** 31 - 1) // 64 // 64           # keys of 64 channels or more, offsets of 32 bits
+        ntile = min(rng.choice([rng.randint(1, 70), rng.randint(1, 3000), rng.randint(1, most), most]), (2 ** 31 - 1) // nh)
+        j = rng.randrange(G)
+        Gx = G // 8
+        x, w = j // Gx, j % Gx
+        h0, h1 = nh * x // 8, nh * (x + 1) // 8
+        if h0 == h1:
+            continue
+        head, Hx = rng.randrange(h0, h1), h1 - h0
+        hl = head - h0
+        lo, hi = (Hx * w // Gx, Hx * (w + 1) // Gx) if Hx >= Gx else (((w + 1) * Hx - 1) // Gx, ((w + 1) * Hx - 1) // Gx + 1)
+        want = [-1] * 5 + [0]
+        if lo <= hl < hi:
+            first, n, me = j, 1, 0
+            if Hx < Gx:
+                a, b = Gx * hl // Hx, Gx * (hl + 1) // Hx
+                first, n, me = x * Gx + a, min(b - a, -(-ntile // tmin)), w - a
+            t = [-(-ntile * i // n) for i in (me, me + 1)] if me < n else [0, 0]
+            want = [first, n, me] + t + [1]
+        lib.ghd_debug_attn_share_min(nh, ntile, tmin, j, G, head, out)
+        assert list(out) == want, (nh, ntile, tmin, G, j, head)
