@@ -72,14 +72,17 @@ static bool linear_shape_ok(int N, int K)
 
 static bool linear_admitted(int M, int N, int K) { return linear_admitted(M, N, K, grid_for_sizing()); }
 
+static bool meet(const void* a, size_t a_bytes, const void* b, size_t b_bytes)
+{
+    return (uintptr_t)a < (uintptr_t)b + b_bytes && (uintptr_t)b < (uintptr_t)a + a_bytes;
+}
+
 // A linear call of its own may read x as the caller's array only if nothing is written there
 // meanwhile: workgroups that are done store y while others still read x.  (The rows' extents are
 // compared, not the elements: two halves of one wide buffer count as meeting.)
 static bool extents_meet(const void* y, int64_t ldy, int N, size_t y_size, const void* x, int64_t ldx, int K, int M)
 {
-    const uintptr_t y0 = (uintptr_t)y, y1 = y0 + ((size_t)(M - 1) * (size_t)ldy + N) * y_size;
-    const uintptr_t x0 = (uintptr_t)x, x1 = x0 + ((size_t)(M - 1) * (size_t)ldx + K) * sizeof(half_t);
-    return y0 < x1 && x0 < y1;
+    return meet(y, ((size_t)(M - 1) * (size_t)ldy + N) * y_size, x, ((size_t)(M - 1) * (size_t)ldx + K) * sizeof(half_t));
 }
 
 // How a linear call of its own is cut.
@@ -596,18 +599,24 @@ static ghd_status verify_stack_impl(const ghd_model_cfg* cfg, const ghd_layer_we
     hipStream_t st = (hipStream_t)stream;
     Ws lw = carve(ws, 0, M, cfg->H, cfg->F, cfg->d, 0, cfg->V);
     const int H = cfg->H;
+    // The residual stream is kept in x_out itself, where the caller wants it (a copy at the end was a launch more: 4 us of the
+    // smallest stack's 32), unless x_out meets what is read while it is written.
+    const size_t x_bytes = (size_t)M * H * sizeof(float);
+    const bool copied = x_out && (meet(x_out, x_bytes, x_in, x_bytes / 2) || meet(x_out, x_bytes, parent_dev, M * sizeof(int32_t)) ||
+                                  meet(x_out, x_bytes, ws, ws_bytes));
+    float* const x = x_out && !copied ? x_out : lw.x;
     // x = widen(x_in) with its sums of squares
     if ((s = launch_fused_setup(lw.sync, parent_dev, M, mpad_of(M), kv_len, cfg->d, cfg->rope_base,
-                                lw.mask, lw.rope, lw.x, (const half_t*)x_in, H, lw.ss,
+                                lw.mask, lw.rope, x, (const half_t*)x_in, H, lw.ss,
                                 (const half_t*)layers_host[0].g_attn, lw.xg16, st)))
         return s;
     for (int l = 0; l < cfg->L; ++l) {
         const half_t* next_g = (const half_t*)(l + 1 < cfg->L ? layers_host[l + 1].g_attn : g_final);
-        if ((s = run_layer(cfg, layers_host + l, kv_host + l, lw.x, M, kv_len, lw, next_g,
+        if ((s = run_layer(cfg, layers_host + l, kv_host + l, x, M, kv_len, lw, next_g,
                            (uint32_t)l, st)))
             return s;
     }
-    if (x_out) {
+    if (copied) {
         hipError_t e = hipMemcpyAsync(x_out, lw.x, (size_t)M * H * sizeof(float),
                                       hipMemcpyDeviceToDevice, st);
         if (e != hipSuccess) return hip_fail(e);
@@ -616,7 +625,7 @@ static ghd_status verify_stack_impl(const ghd_model_cfg* cfg, const ghd_layer_we
     // (largest logit, lowest column) candidate per 16-column tile and row
     LinearCall lm = {Wlm, cfg->V, H, EPI_STORE_F32, lw.xg16, true, nullptr,
                      logits, cfg->V, nullptr, kCntLm, 0, amax_dev ? lw.amax_tbl : nullptr};
-    if ((s = step_linear(cfg, lw, lw.x, M, kv_len, lm, st))) return s;
+    if ((s = step_linear(cfg, lw, x, M, kv_len, lm, st))) return s;
     if (amax_dev) return launch_amax_merge(lw.amax_tbl, (cfg->V + 15) / 16, mpad_of(M), M, amax_dev, st);
     return GHD_OK;
 }

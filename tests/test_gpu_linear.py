@@ -216,3 +216,30 @@ def test_narrow_matrices_inside_a_step(B, M, N, K, whole):
     assert B.ghd_step_status(ws) == 0
     err = (y.double() - ref).abs()
     assert bool((err <= 2.0 ** -11 * ref.abs() + 2e-6 * ref.std() + 2.0 ** -25).all()), float(err.max())
+
+
+@pytest.mark.parametrize("M", [1, 8, 70])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_residual_stream_where_the_caller_wants_it(B, M, shift):
+    """The final residual stream in a buffer of its own, in one whose storage is x_in's (at its start, or its middle), and not
+    asked for: the same logits and the same x, bit for bit."""
+    from paper_2505_23219_amd import model, workloads as wl
+    say("x_out", M, shift)
+    s = wl.ModelShape("x_out", H=256, nh=4, d=64, F=688, V=1000, L=2)
+    kv = 100
+    caches = [model.upload_cache(*wl.kv_cache(s, 192, kv, 5, l)) for l in range(s.L)]
+    stack = model.build_stack(s, 192, [model.upload_layer(wl.layer_weights(s, 5, l), s.d) for l in range(s.L)], caches,
+                              model.upload_head(wl.head_weights(s, 5)))
+    x16 = wl.activations(M, s.H, 5).cuda()
+    parent = torch.from_numpy(wl.tree_random(M, 5, 5)).cuda()
+    ws = B.workspace(B.ghd_workspace_bytes(stack.cfg, M, kv))
+    x_out = torch.full((M, s.H), float("nan"), dtype=torch.float32, device="cuda")
+    logits = B.ghd_verify_stack(stack, x16, parent, kv, x_out=x_out, ws=ws)
+    shared = torch.empty((M, s.H), dtype=torch.float32, device="cuda")
+    x_in = shared.view(-1).view(torch.float16)[shift * M * s.H:][:M * s.H].view(M, s.H)
+    x_in.copy_(x16)
+    both = B.ghd_verify_stack(stack, x_in, parent, kv, x_out=shared, ws=ws)
+    neither = B.ghd_verify_stack(stack, x16, parent, kv, ws=ws)
+    assert bool(torch.isfinite(logits).all()) and torch.equal(both, logits) and torch.equal(neither, logits)
+    assert torch.equal(shared, x_out)
+    assert B.ghd_step_status(ws) == 0
