@@ -961,6 +961,14 @@ void ghd_debug_cut(int M, int N, int K, int G, int solo, int* out5)
 /* out2 = {row tiles of x per workgroup, groups of workgroups with different ones} of the same launch. */
 void ghd_debug_groups(int M, int N, int K, int G, int solo, int* out2) { groups_on_host(M, N, K, G, solo != 0, out2); }
 
+/* Where row p of a packed QKV matrix comes from, by the packing's arithmetic and by the epilogue's: part, head, position of each. */
+void ghd_debug_qkv_row(int p, int nh, int d, int* out6)
+{
+    const QkvRow a = qkv_row(p, nh, d), b = qkv_row_fast(p, nh, d);
+    const int v[6] = {a.part, a.head, a.ph, b.part, b.head, b.ph};
+    for (int i = 0; i < 6; ++i) out6[i] = v[i];
+}
+
 /* Does a linear call with these arguments read x as the caller's array (1), or a copy (0)? */
 int ghd_debug_linear_reads_x(const void* y, const void* x, int M, int N, int K, int64_t ldx, int64_t ldy, uint32_t flags)
 {

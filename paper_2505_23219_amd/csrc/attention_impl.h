@@ -47,20 +47,6 @@ struct AttnHeads {
     int h_lo, h_hi;    // this workgroup's heads, local to the XCD (empty if h_lo == h_hi)
 };
 
-// n / d for 0 <= n < 2^20, d > 0, by the reciprocal: (n + 1/2) / d lies 1/(2 d) or more from a whole number, and what
-// the reciprocal and the product round is below n / d * 2^-22.  (The compiler's integer division is some twenty instructions,
-// each of which waits for the one before; eight of them and the read of the argument block were 1.1 us
-// before an attention call's first request.)
-__host__ __device__ __forceinline__ float recip(int d)
-{
-#ifdef __HIP_DEVICE_COMPILE__
-    return __builtin_amdgcn_rcpf((float)d);
-#else
-    return 1.0f / (float)d;
-#endif
-}
-__host__ __device__ __forceinline__ int div_small(int n, int d) { return (int)(((float)n + 0.5f) * recip(d)); }
-
 // (of workgroup w of XCD x, which has Gx of them and the heads hx0 .. hx1 - 1)
 __host__ __device__ __forceinline__ AttnHeads attn_heads_of(int hx0, int hx1, int x, int w, int Gx)
 {

@@ -89,6 +89,33 @@ __host__ __device__ inline QkvRow qkv_row(int p, int nh, int d)
     return r;
 }
 
+// n / d for 0 <= n < 2^20, d > 0, by the reciprocal: (n + 1/2) / d lies 1/(2 d) or more from a whole number, and what
+// the reciprocal and the product round is below n / d * 2^-22.  (The compiler's integer division is some twenty instructions,
+// each of which waits for the one before; eight of them and the read of the argument block were 1.1 us
+// before an attention call's first request.)
+__host__ __device__ __forceinline__ float recip(int d)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    return __builtin_amdgcn_rcpf((float)d);
+#else
+    return 1.0f / (float)d;
+#endif
+}
+__host__ __device__ __forceinline__ int div_small(int n, int d) { return (int)(((float)n + 0.5f) * recip(d)); }
+
+// the same for a head dimension of 64 or 128 and p below 2^20, without whole-number divisions
+__host__ __device__ __forceinline__ QkvRow qkv_row_fast(int p, int nh, int d)
+{
+    QkvRow r;
+    const int lg = d == 64 ? 6 : 7, hpx = qkv_grouped(nh) ? nh >> 3 : nh, hd = hpx << lg;     // heads that lie together, and their rows
+    const int x = qkv_grouped(nh) ? div_small(p, 3 * hd) : 0, q = p - x * (3 * hd);
+    r.part = (q >= hd) + (q >= 2 * hd);
+    const int hn = q - r.part * hd;
+    r.head = x * hpx + (hn >> lg);
+    r.ph = hn & (d - 1);
+    return r;
+}
+
 // channel of packed position ph inside a head
 __host__ __device__ inline int qkv_channel(int ph, int d)
 {

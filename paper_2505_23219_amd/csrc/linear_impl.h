@@ -250,7 +250,7 @@ __device__ __forceinline__ void epilogue(ArgPtr a, floatx4 (&v)[NB], int (&m)[NB
         floatx4 cs[NB];
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
-            qr[i] = qkv_row(n0[i], nh, d);
+            qr[i] = qkv_row_fast(n0[i], nh, d);
             // (cos, sin) of channels jj and jj + 1 (jj is even: 16 bytes, aligned)
             cs[i] = (floatx4){1.f, 0.f, 1.f, 0.f};
             if (m[i] < M && qr[i].part < 2)

@@ -255,3 +255,15 @@ def test_attention_shares_are_those_of_integer_division():
             want = [first, n, me] + t + [1]
         lib.ghd_debug_attn_share_min(nh, ntile, tmin, j, G, head, out)
         assert list(out) == want, (nh, ntile, tmin, G, j, head)
+
+
+def test_rows_of_the_qkv_matrix_are_found_without_division():
+    """Every row of QKV matrices of all head counts: the epilogue's arithmetic finds the part, head and position that the
+    packing put there."""
+    lib, out = B.lib(), (C.c_int * 6)()
+    for nh in list(range(1, 42)) + [64, 100, 128, 256]:
+        for d in (64, 128):
+            n = 3 * nh * d
+            for p in range(0, n, 4) if n < 20000 else sorted({*range(0, n, 244), *range(0, n, nh * d // 8), n - 4}):
+                lib.ghd_debug_qkv_row(p, nh, d, out)
+                assert list(out[:3]) == list(out[3:]), (p, nh, d, list(out))
