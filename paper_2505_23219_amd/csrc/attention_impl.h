@@ -193,6 +193,19 @@ __device__ __forceinline__ void masks_from_source(bool parents, int M, uint32_t 
     else if ((int)threadIdx.x < M * 4) ((uint32_t*)mask)[threadIdx.x] = word;
 }
 
+// Which of the eight keys from `key` on a row sees, a bit each, by its mask in the LDS (four words; bits from M on are
+// never looked at): committed keys, and of the tree's rows those of the mask; none from T on.  (One shift across two
+// words for the eight instead of one of 64 bits and two choices for each: an instruction here is a wait of the whole
+// call.  40 heads of 128, 4 rows, 300 cached 9.14 us and 9.49; a 7B-shaped layer of 16 rows 87.3 and 87.9.)
+__device__ __forceinline__ uint32_t seen_keys(const uint32_t* mask, int key, int kv_len, int T)
+{
+    const int jn = key - kv_len, at = max(jn, 0), w = min(at >> 5, 3);
+    const uint32_t lo = mask[w], hi = w < 3 ? mask[min(w + 1, 3)] : 0u;
+    uint32_t bits = __builtin_amdgcn_alignbit(hi, lo, (uint32_t)at);       // (by at modulo 32)
+    if (jn < 0) bits = jn <= -8 ? 0xffu : bits << -jn | ((1u << -jn) - 1);
+    return bits & ((1u << min(max(T - key, 0), 8)) - 1);
+}
+
 // `gate` is called once by every workgroup (all threads), before the first read of q or of a
 // cache row from kv_len on; it returns false if the launch is to be abandoned.  A kernel that
 // produces those in the same launch waits there for their producers; with PREFETCH a
@@ -499,15 +512,11 @@ __device__ __forceinline__ bool attn_direct(const AttnFirst& f, Late late, Ctx& 
                     }
                 } else {
                     const int row = t * 16 + c;
-                    const uint64_t lo = sm.mask[row][0], hi = sm.mask[row][1];
-                    bool mine = false;
+                    const uint32_t seen = seen_keys((const uint32_t*)sm.mask[row], key0 + g4 * 8, kv_len, T);
+                    const bool mine = seen != 0 && row < M;
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
-                        const int key = key0 + g4 * 8 + i, jn = key - kv_len;
-                        bool vis = key < kv_len;
-                        if (jn >= 0 && key < T) vis = ((jn < 64 ? lo >> jn : hi >> (jn - 64)) & 1ull) != 0;
-                        mine = mine || (vis && row < M);
-                        const float v = vis ? s[t][i >> 2][i & 3] * scale_log2e : -INFINITY;
+                        const float v = seen >> i & 1 ? s[t][i >> 2][i & 3] * scale_log2e : -INFINITY;
                         s[t][i >> 2][i & 3] = v;
                         tmax = fmaxf(tmax, v);
                     }
@@ -631,6 +640,11 @@ __device__ __forceinline__ bool attn_staged(const AttnFirst& f, Late late, Ctx& 
     constexpr int UNITS = 2 / HALVES;                  // 32-key units of a tile that a wavefront works on
     constexpr int PIECES = D / 64;                     // 1 KiB pieces of a tile's K that a wavefront requests (as many of V)
     constexpr int LPT = 2 * PIECES;                    // loads per tile
+    // Masked units by seen_keys(), except with 128 channels up to 64 rows, where the loop over the other tiles came out
+    // slower beside it (4 heads, 48 rows, 16000 cached 19.7 us and 20.0; 64, 64 rows, 900 cached 15.9 and 15.5).  With
+    // it and without: 8 heads of 128, 128 rows, 60 cached 11.7 us and 13.0; 16, 3000 cached 19.0 and 19.3; 40 heads of
+    // 64, 33 rows, 6000 cached 18.7 and 19.2.
+    constexpr bool COMPACT = HALVES == 1 || D == 64;
     using L = StagedLds<MT, D>;
     constexpr int NB = L::NB;
     constexpr uint32_t KB = L::KB, TB = 2 * KB;
@@ -802,19 +816,26 @@ __device__ __forceinline__ bool attn_staged(const AttnFirst& f, Late late, Ctx& 
                         tmax = fmaxf(tmax, fmaxf(fmaxf(s[jx][0], s[jx][1]), fmaxf(s[jx][2], s[jx][3])));
                     }
                 } else {
-                    const uint32_t* mw = sm.mask + mrow * 4;
-                    const uint64_t lo = mw[0] | (uint64_t)mw[1] << 32, hi = mw[2] | (uint64_t)mw[3] << 32;
                     bool mine = false;
+                    if constexpr (COMPACT) {
+                        const uint32_t seen = seen_keys(sm.mask + mrow * 4, key0 + g4 * 8, kv_len, T);
+                        mine = seen != 0 && mok;
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        const int key = key0 + g4 * 8 + i, jn = key - kv_len;
-                        bool vis = key < kv_len;
-                        if (jn >= 0 && key < T) vis = ((jn < 64 ? lo >> jn : hi >> (jn - 64)) & 1ull) != 0;
-                        mine = mine || (vis && mok);
-                        const float v = vis ? s[i >> 2][i & 3] * scale_log2e : -INFINITY;
-                        s[i >> 2][i & 3] = v;
-                        tmax = fmaxf(tmax, v);
+                        for (int i = 0; i < 8; ++i) s[i >> 2][i & 3] = seen >> i & 1 ? s[i >> 2][i & 3] * scale_log2e : -INFINITY;
+                    } else {
+                        const uint32_t* mw = sm.mask + mrow * 4;
+                        const uint64_t lo = mw[0] | (uint64_t)mw[1] << 32, hi = mw[2] | (uint64_t)mw[3] << 32;
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) {
+                            const int key = key0 + g4 * 8 + i, jn = key - kv_len;
+                            bool vis = key < kv_len;
+                            if (jn >= 0 && key < T) vis = ((jn < 64 ? lo >> jn : hi >> (jn - 64)) & 1ull) != 0;
+                            mine = mine || (vis && mok);
+                            s[i >> 2][i & 3] = vis ? s[i >> 2][i & 3] * scale_log2e : -INFINITY;
+                        }
                     }
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) tmax = fmaxf(tmax, s[i >> 2][i & 3]);
                     if (__ballot(mine) == 0ull) continue;  // no row of the tile sees the unit: leave it out
                     // keys from T on hold no data: zero them, a stray NaN times a zero weight is a NaN
                     const int nvalid = T - key0 - g4 * 8;

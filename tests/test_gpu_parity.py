@@ -938,6 +938,16 @@ def test_masked_attention(B, model, orc32, M, nh, d, kv_len, kind, extra):
     assert ok, (ma, mr)
 
 
+# Eight keys are looked up with one shift across two words of a row's mask: every distance of the tree's first key from
+# a multiple of eight, rows at both sides of a word's edge, bits past the tree set.
+@pytest.mark.parametrize("M,nh,d,kv_len", [
+    (1, 3, 128, 1), (8, 8, 64, 2), (31, 4, 128, 203), (32, 4, 64, 396), (33, 20, 64, 1005), (63, 4, 64, 62), (64, 4, 64, 767), (65, 4, 128, 300),
+    (95, 4, 64, 6), (96, 4, 128, 1001), (97, 4, 64, 2), (127, 3, 128, 155), (128, 4, 128, 1004), (128, 8, 64, 7)])
+def test_masked_attention_at_the_edges_of_mask_words(B, model, orc32, M, nh, d, kv_len):
+    for kind in ("random", "sparse"):
+        test_masked_attention(B, model, orc32, M, nh, d, kv_len, kind, True)
+
+
 def test_masked_attention_rows_without_keys_give_zeros(B, model, orc32):
     M, nh, d = 70, 2, 128
     mask = pattern("random", M, 5)
