@@ -285,3 +285,34 @@ def test_topk_is_exact_on_the_logits_it_read(B, V, K, R):
     t = tokens.cpu().numpy()
     head = lambda depth: min(depth, K) - 1
     assert t[0] == 3 % V and t[1] == top[head(1), 0] and t[2] == top[head(1), min(1, R - 1)] and t[3] == top[head(2), R - 1]
+
+
+@pytest.mark.parametrize("H,M", [(8, 1), (4096, 65), (4104, 128), (8192, 64), (8200, 128), (12296, 2)])
+def test_normalised_row_and_node_tokens(B, H, M):
+    """Heads that pick single channels out of the normalised row, so that the logits are its values: against 64 bits,
+    around what a thread keeps of a row.  And the tokens of a chain with as many heads as there may be, deeper
+    than the heads, and with ranks past R."""
+    K, V, R = 16, 16, 4
+    gen = torch.Generator().manual_seed(H + M)
+    cols = torch.randint(0, H, (K * V,), generator=gen)
+    cols[0], cols[1] = 0, H - 1
+    W = torch.zeros(K * V, H, dtype=torch.float16)
+    W[torch.arange(K * V), cols] = 1.0
+    g = (1.0 + 0.1 * torch.randn(H, generator=gen)).to(torch.float16)
+    x = torch.randn(M, H, generator=gen) * 3.0
+    last = M - 1
+    res = torch.tensor([1, 7] + [last] + [0] * (M - 1), dtype=torch.int32)
+    parent = torch.arange(-1, M - 1, dtype=torch.int32)
+    rank = (torch.arange(M) % (R + 2)).to(torch.int32)
+    say("normalised row H=%d M=%d" % (H, M))
+    tokens, topk, logits = B.ghd_draft_tokens(g.cuda(), B.ghd_pack_weight(W.cuda()), K, R, V, 1e-6, x.cuda(), res.cuda(),
+                                              parent.cuda(), rank.cuda())
+    row = x[last].double().numpy()
+    want = (row / np.sqrt((row * row).mean() + 1e-6) * g.double().numpy())[cols.numpy()]
+    got = logits.cpu().numpy().reshape(-1)
+    # one rounding to fp16 (2^-11 of a value, 2^-25 below the normal ones); the fp32 before it is a thousandth of that
+    assert np.all(np.abs(got - want) <= 2.0 ** -11 * 1.01 * np.abs(want) + 2.0 ** -25)
+    top, t = topk.cpu().numpy(), tokens.cpu().numpy()
+    assert t[0] == 7
+    for i in range(1, M):
+        assert t[i] == top[min(i, K) - 1, min(int(rank[i]), R - 1)], i
