@@ -119,14 +119,65 @@ bool attention_alone(int M, int kv_len, int d)
 }
 
 // ---- setup kernel ------------------------------------------------------------
-// Blocks 0..kTreeBlocks-1: tree tables (every block walks the parents itself; block 0
-// writes the ancestor masks, each thread one element of the rotary table: the double-precision
-// sine and cosine are the longest chain of the launch).  The next kZeroBlocks
+// Blocks 0..kRopeBlocks-1: the rotary table, a thread per element (the double-precision sine and cosine
+// behind the node's depth are the longest chain of the launch); the next one: the ancestor masks.  The next kZeroBlocks
 // blocks zero the sync block.  Further blocks: one per 16-column tile of the residual stream,
 // writing x = widen(x_in), the tile's sums of squares and the gain-scaled fp16 image.
-constexpr int kTreeBlocks = 32;      // a thread per element of the largest rotary table
-static_assert(kTreeBlocks * 256 >= GHD_MAX_M * 64, "128 rows of 64 pairs");
+constexpr int kRopeBlocks = 32;      // a thread per element of the largest rotary table
+static_assert(kRopeBlocks * 256 >= GHD_MAX_M * 64, "128 rows of 64 pairs");
+constexpr int kTreeBlocks = kRopeBlocks + 1;
 constexpr int kZeroBlocks = 64;
+
+// Depths, and ancestor sets where they are wanted, by pointer doubling: after round k a node knows how many edges lead to
+// its farthest known ancestor, which is up to 2^k edges up, the node above that one (-1 past the root), and which nodes
+// lie between.  As many rounds as the deepest node needs; a parent that is not an earlier
+// node is taken as "no parent".  Every wavefront does it by itself, two nodes a lane (i and i + 64), an exchange of lanes a
+// round instead of LDS arrays and two barriers.  us a layer, then and now: 20 heads of 64, 37 rows 37.65 and 37.25; 13B-shaped, 64
+// rows 169.4 and 168.5; 7B-shaped, 16 rows 86.99 and 86.85.
+struct TreeNodes {
+    int link[2];                     // depth << 8 | up + 1
+    uint64_t lo[2], hi[2];           // ancestors-or-self
+    __device__ __forceinline__ int depth(int node) const
+    {
+        const int a = __shfl(link[0], node & 63), b = __shfl(link[1], node & 63);
+        return (node < 64 ? a : b) >> 8;
+    }
+};
+template <bool SETS>
+__device__ __forceinline__ TreeNodes tree_nodes(const int32_t* __restrict__ parent, int M, int lane)
+{
+    static_assert(GHD_MAX_M == 128, "two nodes a lane; up + 1 fits 8 bits");
+    TreeNodes t;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int i = u * 64 + lane, up = parent[min(i, M - 1)];
+        t.link[u] = i < M && up >= 0 && up < i ? 1 << 8 | (up + 1) : 0;
+        t.lo[u] = u == 0 ? 1ull << lane : 0;
+        t.hi[u] = u == 1 ? 1ull << lane : 0;
+    }
+    while (__ballot(((t.link[0] | t.link[1]) & 255) != 0)) {
+        const TreeNodes was = t;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const bool on = (was.link[u] & 255) != 0;
+            const int from = on ? (was.link[u] & 255) - 1 : 0;
+            auto of = [&](const auto (&v)[2]) {
+                const auto a = __shfl(v[0], from & 63), b = __shfl(v[1], from & 63);
+                return from < 64 ? a : b;
+            };
+            const int o = of(was.link);
+            if (on) t.link[u] = ((was.link[u] & ~255) + (o & ~255)) | (o & 255);
+            if constexpr (SETS) {
+                const uint64_t lo = of(was.lo), hi = of(was.hi);
+                if (on) {
+                    t.lo[u] |= lo;
+                    t.hi[u] |= hi;
+                }
+            }
+        }
+    }
+    return t;
+}
 
 __global__ __launch_bounds__(256) void k_fused_setup(uint32_t* __restrict__ sync,
                                                      const int32_t* __restrict__ parent, int M,
@@ -139,58 +190,30 @@ __global__ __launch_bounds__(256) void k_fused_setup(uint32_t* __restrict__ sync
                                                      half_t* __restrict__ xg16)
 {
     int tid = threadIdx.x;
-    if (blockIdx.x < kTreeBlocks) {
-        // Ancestor sets and depths by pointer doubling: after round k a node knows its 2^k
-        // nearest ancestors-or-self, how many edges lead to the farthest of them, and the
-        // node 2^k edges up (-1 past the root).  ceil(log2 M) rounds whatever the depth; a
-        // parent that is not an earlier node is taken as "no parent".
-        __shared__ int32_t s_up[GHD_MAX_M];
-        __shared__ int32_t s_depth[GHD_MAX_M];
-        __shared__ uint64_t s_lo[GHD_MAX_M], s_hi[GHD_MAX_M];
-        if (!parent || (blockIdx.x > 0 && !rope)) return;
-        // This thread's element of the rotary table: its frequency base^(-2j/d), in double, while
-        // parent[] is on its way.
+    if (blockIdx.x < kRopeBlocks) {
         const int half = d / 2, e = blockIdx.x * 256 + tid;
-        const bool turn = rope && e < M * half;
-        if (blockIdx.x > 0 && blockIdx.x * 256 >= M * half) return;
-        const double freq = turn ? exp2(-2.0 / d * log2((double)rope_base) * (e % half)) : 0.0;
-        int up = -1, dep = 0;
-        uint64_t lo = 0, hi = 0;
-        if (tid < M) {
-            up = parent[tid];
-            if (up < 0 || up >= tid) up = -1;
-            dep = up >= 0 ? 1 : 0;
-            if (tid < 64) lo = 1ull << tid; else hi = 1ull << (tid - 64);
-        }
-        for (int span = 1; span < M; span <<= 1) {
-            if (tid < M) {
-                s_up[tid] = up;
-                s_depth[tid] = dep;
-                s_lo[tid] = lo;
-                s_hi[tid] = hi;
-            }
-            __syncthreads();
-            if (tid < M && up >= 0) {
-                lo |= s_lo[up];
-                hi |= s_hi[up];
-                dep += s_depth[up];
-                up = s_up[up];
-            }
-            __syncthreads();
-        }
-        if (tid < M) {
-            s_depth[tid] = dep;
-            if (blockIdx.x == 0) {
-                mask[2 * tid] = lo;
-                mask[2 * tid + 1] = hi;
-            }
-        }
-        __syncthreads();
-        if (turn) {
-            const double ang = (double)(kv_len + s_depth[e / half]) * freq;
-            double sn, cs;
-            sincos(ang, &sn, &cs);
-            rope[e] = make_float2((float)cs, (float)sn);
+        if (!parent || !rope || blockIdx.x * 256 >= M * half) return;
+        // This thread's element: its frequency base^(-2j/d), in double, while parent[] is on its way.
+        const int row = e / half;
+        const double freq = exp2(-2.0 / d * log2((double)rope_base) * (e - row * half));
+        const TreeNodes t = tree_nodes<false>(parent, M, tid & 63);
+        const int depth = t.depth(row);
+        if (e >= M * half) return;
+        const double ang = (double)(kv_len + depth) * freq;
+        double sn, cs;
+        sincos(ang, &sn, &cs);
+        rope[e] = make_float2((float)cs, (float)sn);
+        return;
+    }
+    if (blockIdx.x < kTreeBlocks) {
+        if (!parent || tid >= 64) return;
+        const TreeNodes t = tree_nodes<true>(parent, M, tid);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int i = u * 64 + tid;
+            if (i >= M) continue;
+            mask[2 * i] = t.lo[u];
+            mask[2 * i + 1] = t.hi[u];
         }
         return;
     }

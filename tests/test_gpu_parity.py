@@ -132,6 +132,27 @@ def test_tree_mask_bit_exact(B, orc32):
         assert np.array_equal(got, bits), list(parent)
 
 
+@pytest.mark.parametrize("M", [1, 2, 63, 64, 65, 127, 128])
+def test_tree_mask_across_the_two_nodes_of_a_lane(B, orc32, M):
+    """Two nodes a lane, i and i + 64: chains, stars, parents that jump across the line, several roots, and parents
+    that are no earlier node (taken as roots)."""
+    rng = np.random.default_rng(M)
+    i = np.arange(M)
+    trees = [i - 1, np.where(i > 0, 0, -1), np.where(i >= 64, i - 64, i - 1), np.where(i > 0, i // 2, -1) - (i == 1),
+             np.array([rng.integers(-1, k) if k else -1 for k in i])]
+    for up in trees:
+        up = np.where((up < 0) | (up >= i), -1, up).astype(np.int32)
+        want = [{k} for k in i]
+        for k in i:
+            if up[k] >= 0:
+                want[k] = want[k] | want[up[k]]
+        bits = np.array([[sum(1 << (b - 64 * w) for b in s if b // 64 == w) for w in (0, 1)] for s in want], dtype=np.uint64)
+        for parent in (up, np.where(up < 0, i + (i % 2) * M, up).astype(np.int32)):      # (itself, or one past all)
+            say("tree mask M=%d" % M)
+            got = B.ghd_tree_mask(torch.from_numpy(parent).cuda()).cpu().numpy().view(np.uint64)
+            assert np.array_equal(got.reshape(M, 2), bits)
+
+
 LINEAR_CASES = [(1, 64, 64), (3, 130, 688), (8, 1000, 256), (16, 256, 256), (17, 48, 96),
                 (33, 688 * 2, 256), (64, 256, 688), (100, 130, 520), (128, 512, 1024),
                 (16, 12288, 4096), (64, 4096, 11008), (1, 4096, 4096),
