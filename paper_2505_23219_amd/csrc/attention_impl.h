@@ -149,48 +149,106 @@ __device__ __forceinline__ float over_groups(float x, Op op)
 __device__ __forceinline__ float max_over_groups(float x) { return over_groups(x, [](float a, float b) { return fmaxf(a, b); }); }
 __device__ __forceinline__ float sum_over_groups(float x) { return over_groups(x, [](float a, float b) { return a + b; }); }
 
-// The ancestor masks of a tree in LDS (mask[2 * node], low and high word) by pointer doubling, from `up` = parent[i] in
-// thread i: after round k a node has its 2^k nearest ancestors-or-self and the node 2^k edges up.  All threads
-// call; a barrier is left to the caller.  A parent that is not an earlier node is taken as "no parent".
-__device__ __forceinline__ void masks_from_parent(int up, int M, uint64_t* mask, int32_t* s_up)
-{
-    const int i = threadIdx.x;
-    uint64_t lo = 0, hi = 0;
-    if (up < 0 || up >= i || i >= M) up = -1;
-    if (i < 64) lo = 1ull << i; else hi = 1ull << (i & 63);
-    for (int span = 1; span < M; span <<= 1) {
-        if (i < M) {
-            mask[2 * i] = lo;
-            mask[2 * i + 1] = hi;
-            s_up[i] = up;
-        }
-        barrier_lds();
-        if (up >= 0) {
-            lo |= mask[2 * up];
-            hi |= mask[2 * up + 1];
-            up = s_up[up];
-        }
-        barrier_lds();
+// Depths, and ancestor sets where they are wanted, by pointer doubling: after round k a node knows how many edges lead to
+// its farthest known ancestor, which is up to 2^k edges up, the node above that one (-1 past the root), and which nodes
+// lie between.  As many rounds as the deepest node needs; a parent that is not an earlier
+// node is taken as "no parent".  A wavefront does it by itself, one or two nodes a lane (i and i + 64), with exchanges of
+// lanes instead of LDS arrays and two barriers a round.  Nodes from 64 on double among themselves; what lies above the
+// node at which they leave for the first 64 is added at the end (both halves in one: 20 exchanges a round instead of 6, and
+// calls of 65 to 128 rows under a chain 0.7 us slower than with barriers).
+template <int NODES>
+struct TreeNodes {
+    int link[NODES];          // depth << 8 | up + 1
+    uint64_t own[NODES];      // ancestors-or-self among the node's own 64
+    uint64_t first;           // ... and, of the second node, among the first 64
+    __device__ __forceinline__ int depth(int node) const
+    {
+        const int a = __shfl(link[0], node & 63), b = __shfl(link[NODES - 1], node & 63);
+        return (node < 64 ? a : b) >> 8;
     }
-    if (i < M) {
-        mask[2 * i] = lo;
-        mask[2 * i + 1] = hi;
+};
+// (up0, up1: parent[lane] and parent[lane + 64]; what they are from M on is not looked at)
+template <int NODES, bool SETS>
+__device__ __forceinline__ TreeNodes<NODES> tree_nodes(int up0, int up1, int M, int lane)
+{
+    static_assert(GHD_MAX_M == 128, "two nodes a lane; up + 1 fits 8 bits");
+    TreeNodes<NODES> t;
+    t.first = 0;
+    bool on[NODES], any = false;                 // whether the node above is one of the same 64
+    auto look = [&]() {
+        any = false;
+#pragma unroll
+        for (int u = 0; u < NODES; ++u) {
+            on[u] = (t.link[u] & 255) > u * 64;
+            any = any || on[u];
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < NODES; ++u) {
+        const int i = u * 64 + lane, up = u ? up1 : up0;
+        t.link[u] = i < M && up >= 0 && up < i ? 1 << 8 | (up + 1) : 0;
+        t.own[u] = 1ull << lane;
+    }
+    for (look(); __ballot(any); look()) {
+#pragma unroll
+        for (int u = 0; u < NODES; ++u) {
+            const int from = on[u] ? (t.link[u] & 255) - 1 - u * 64 : 0, o = __shfl(t.link[u], from);
+            if constexpr (SETS) {
+                const uint64_t more = __shfl(t.own[u], from);
+                if (on[u]) t.own[u] |= more;
+            }
+            if (on[u]) t.link[u] = ((t.link[u] & ~255) + (o & ~255)) | (o & 255);
+        }
+    }
+    if constexpr (NODES > 1) {
+        const int up = t.link[1] & 255, from = up ? up - 1 : 0, o = __shfl(t.link[0], from);
+        if (up) t.link[1] += o & ~255;
+        if constexpr (SETS) {
+            const uint64_t more = __shfl(t.own[0], from);
+            if (up) t.first = more;
+        }
+    }
+    return t;
+}
+
+// Node `lane` (and lane + 64) to its mask (low and high word)
+template <int NODES, class Mask>
+__device__ __forceinline__ void store_masks(const TreeNodes<NODES>& t, int M, int lane, Mask mask)
+{
+#pragma unroll
+    for (int u = 0; u < NODES; ++u) {
+        const int i = u * 64 + lane;
+        if (i >= M) continue;
+        mask[2 * i] = u ? t.first : t.own[0];
+        mask[2 * i + 1] = u ? t.own[u] : 0;
     }
 }
 
-// A call in one launch gets what its masks are made from, a word a thread, before anything else, and has it when
+// A call in one launch gets what its masks are made from before anything else, and has it when
 // it requests queries and cache (the work shares are worked out in between): the masks are then made while those are on
 // their way.  Loads return in order: requested behind the cache, parent[] came back behind it, and the
-// rounds of the doubling began when all else was there.
-__device__ __forceinline__ uint32_t mask_source(const void* source, bool parents, int M)
+// rounds of the doubling began when all else was there.  Masks: a word a thread; parent[]: the first wavefront has all of it.
+template <bool TWO>
+__device__ __forceinline__ void mask_source(Ctx& cx, const void* source, int M)
 {
-    const int tid = threadIdx.x, n = parents ? M : M * 4;
-    return tid < n ? ((GLOBAL const uint32_t*)gp((const uint32_t*)source))[tid] : 0u;
+    const int tid = threadIdx.x, n = cx.parents ? min(M, 64) : M * 4;
+    const auto words = gp((const uint32_t*)source);
+    cx.source[0] = tid < n ? (int)words[tid] : 0;
+    cx.source[1] = TWO && cx.parents && tid < 64 && tid + 64 < M ? (int)words[tid + 64] : 0;
 }
-__device__ __forceinline__ void masks_from_source(bool parents, int M, uint32_t word, uint64_t* mask, int32_t* s_up)
+// (The first wavefront makes a tree's masks in registers: reads of LDS arrays would wait for all that is on its way to the
+// LDS.  us a call under a wide tree, with the doubling in LDS arrays and now: 32 heads of 128, 4 rows, 120 cached 6.5 and 6.3; 32
+// of 64, 64 rows, 128 cached 7.2 and 6.5; 8 of 128, 128 rows, 60 cached 11.7 and 11.1, under a chain 12.1 and 11.7)
+template <bool TWO>
+__device__ __forceinline__ void masks_from_source(bool parents, int M, const int (&word)[2], uint64_t* mask)
 {
-    if (parents) masks_from_parent((int)word, M, mask, s_up);
-    else if ((int)threadIdx.x < M * 4) ((uint32_t*)mask)[threadIdx.x] = word;
+    const int tid = threadIdx.x;
+    if (!parents) {
+        if (tid < M * 4) ((uint32_t*)mask)[tid] = (uint32_t)word[0];
+    } else if (tid < 64) {
+        constexpr int NODES = TWO ? 2 : 1;
+        store_masks(tree_nodes<NODES, true>(word[0], word[1], M, tid), M, tid, mask);
+    }
 }
 
 // Which of the eight keys from `key` on a row sees, a bit each, by its mask in the LDS (four words; bits from M on are
@@ -269,7 +327,6 @@ struct DirectLds {
     floatx4 o[8][MT][D / 16][64];                    // the wavefronts' outputs, when they are merged
     float m[8][MT][16], l[8][MT][16];                // ... and their softmax statistics
     uint64_t mask[MT * 16][2];
-    int32_t up[MT * 16];
     int wait_ok;                                     // thread 0's verdict on a bounded wait, for the whole workgroup
 };
 
@@ -435,9 +492,10 @@ __device__ __forceinline__ bool attn_direct(const AttnFirst& f, Late late, Ctx& 
         const auto q = gp(a.att_q);
         const auto out = gp(a.att_out);
         const auto o_part = gp(a.o_part), ml_part = gp(a.ml_part);
-        int source = 0;
+        int source[2] = {0, 0};
         if constexpr (ALONE) {
-            source = hidden(cx.source);                    // (it is there)
+            source[0] = hidden(cx.source[0]);              // (it is there)
+            if constexpr (MT > 4) source[1] = hidden(cx.source[1]);
             pin_order();
         }
         half8 qf[MT][DS];
@@ -457,7 +515,7 @@ __device__ __forceinline__ bool attn_direct(const AttnFirst& f, Late late, Ctx& 
             load_v(u);
         }
         pin_order();           // (all requests are out before the first of them is waited for)
-        if constexpr (ALONE) masks_from_source(cx.parents, M, source, &sm.mask[0][0], sm.up);
+        if constexpr (ALONE) masks_from_source<false>(cx.parents, M, source, &sm.mask[0][0]);
         else if (tid < MT * 16) {
             sm.mask[tid][0] = mask_lo;
             sm.mask[tid][1] = mask_hi;
@@ -590,7 +648,6 @@ struct StagedLds {
     static constexpr uint32_t KB = 64 * D * 2;         // bytes of a tile's K, and of its V^T
     char tile[NB][2 * KB];
     alignas(8) uint32_t mask[GHD_MAX_M * 4];
-    int32_t up[GHD_MAX_M];
     int wait_ok;                                       // thread 0's verdict on a bounded wait, for the whole workgroup
     // what the two wavefronts of a row tile exchange when a head ends: their softmax statistics and, in a
     // tile buffer that is free then, half of their output fragments
@@ -736,9 +793,10 @@ __device__ __forceinline__ bool attn_staged(const AttnFirst& f, Late late, Ctx& 
         const auto q = gp(a.att_q);
         const auto out = gp(a.att_out);
         const auto o_part = gp(a.o_part), ml_part = gp(a.ml_part);
-        int source = 0;
+        int source[2] = {0, 0};
         if constexpr (ALONE) {
-            source = hidden(cx.source);                    // (it is there)
+            source[0] = hidden(cx.source[0]);              // (it is there)
+            if constexpr (MT > 4) source[1] = hidden(cx.source[1]);
             pin_order();
         }
         {
@@ -749,7 +807,7 @@ __device__ __forceinline__ bool attn_staged(const AttnFirst& f, Late late, Ctx& 
         }
         for (int n = n_pre; n < up_front; ++n) request(t0 + n);
 
-        if constexpr (ALONE) masks_from_source(cx.parents, M, source, (uint64_t*)sm.mask, sm.up);
+        if constexpr (ALONE) masks_from_source<(MT > 4)>(cx.parents, M, source, (uint64_t*)sm.mask);
 
         // waits for all but the youngest n tiles
         auto wait_tiles = [&](int n) {

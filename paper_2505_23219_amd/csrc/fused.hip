@@ -24,7 +24,7 @@ __global__ __launch_bounds__(kFT) void k_attention(const half_t* k, const half_t
     cx.j = (blockIdx.x & 7) * Gx + (blockIdx.x >> 3);
     cx.lds = lds;
     cx.parents = flags >> kAttParents & 1;
-    if constexpr (ALONE) cx.source = (int)mask_source(source, cx.parents, M);
+    if constexpr (ALONE) mask_source<(MT > 4)>(cx, source, M);
     AttnFirst f = {k, v, (int64_t)k_head8 * 8, (int64_t)v_head8 * 8, st_tok, st_ch, T, M, nh};
     if (flags >> kAttFar & 1) {              // (heads 64 GiB apart)
         f.k_head = late_args()->stride_head;
@@ -128,57 +128,6 @@ static_assert(kRopeBlocks * 256 >= GHD_MAX_M * 64, "128 rows of 64 pairs");
 constexpr int kTreeBlocks = kRopeBlocks + 1;
 constexpr int kZeroBlocks = 64;
 
-// Depths, and ancestor sets where they are wanted, by pointer doubling: after round k a node knows how many edges lead to
-// its farthest known ancestor, which is up to 2^k edges up, the node above that one (-1 past the root), and which nodes
-// lie between.  As many rounds as the deepest node needs; a parent that is not an earlier
-// node is taken as "no parent".  Every wavefront does it by itself, two nodes a lane (i and i + 64), an exchange of lanes a
-// round instead of LDS arrays and two barriers.  us a layer, then and now: 20 heads of 64, 37 rows 37.65 and 37.25; 13B-shaped, 64
-// rows 169.4 and 168.5; 7B-shaped, 16 rows 86.99 and 86.85.
-struct TreeNodes {
-    int link[2];                     // depth << 8 | up + 1
-    uint64_t lo[2], hi[2];           // ancestors-or-self
-    __device__ __forceinline__ int depth(int node) const
-    {
-        const int a = __shfl(link[0], node & 63), b = __shfl(link[1], node & 63);
-        return (node < 64 ? a : b) >> 8;
-    }
-};
-template <bool SETS>
-__device__ __forceinline__ TreeNodes tree_nodes(const int32_t* __restrict__ parent, int M, int lane)
-{
-    static_assert(GHD_MAX_M == 128, "two nodes a lane; up + 1 fits 8 bits");
-    TreeNodes t;
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int i = u * 64 + lane, up = parent[min(i, M - 1)];
-        t.link[u] = i < M && up >= 0 && up < i ? 1 << 8 | (up + 1) : 0;
-        t.lo[u] = u == 0 ? 1ull << lane : 0;
-        t.hi[u] = u == 1 ? 1ull << lane : 0;
-    }
-    while (__ballot(((t.link[0] | t.link[1]) & 255) != 0)) {
-        const TreeNodes was = t;
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const bool on = (was.link[u] & 255) != 0;
-            const int from = on ? (was.link[u] & 255) - 1 : 0;
-            auto of = [&](const auto (&v)[2]) {
-                const auto a = __shfl(v[0], from & 63), b = __shfl(v[1], from & 63);
-                return from < 64 ? a : b;
-            };
-            const int o = of(was.link);
-            if (on) t.link[u] = ((was.link[u] & ~255) + (o & ~255)) | (o & 255);
-            if constexpr (SETS) {
-                const uint64_t lo = of(was.lo), hi = of(was.hi);
-                if (on) {
-                    t.lo[u] |= lo;
-                    t.hi[u] |= hi;
-                }
-            }
-        }
-    }
-    return t;
-}
-
 __global__ __launch_bounds__(256) void k_fused_setup(uint32_t* __restrict__ sync,
                                                      const int32_t* __restrict__ parent, int M,
                                                      int Mpad, int kv_len, int d, float rope_base,
@@ -196,7 +145,8 @@ __global__ __launch_bounds__(256) void k_fused_setup(uint32_t* __restrict__ sync
         // This thread's element: its frequency base^(-2j/d), in double, while parent[] is on its way.
         const int row = e / half;
         const double freq = exp2(-2.0 / d * log2((double)rope_base) * (e - row * half));
-        const TreeNodes t = tree_nodes<false>(parent, M, tid & 63);
+        const int lane = tid & 63;
+        const TreeNodes<2> t = tree_nodes<2, false>(parent[min(lane, M - 1)], parent[min(lane + 64, M - 1)], M, lane);
         const int depth = t.depth(row);
         if (e >= M * half) return;
         const double ang = (double)(kv_len + depth) * freq;
@@ -207,14 +157,7 @@ __global__ __launch_bounds__(256) void k_fused_setup(uint32_t* __restrict__ sync
     }
     if (blockIdx.x < kTreeBlocks) {
         if (!parent || tid >= 64) return;
-        const TreeNodes t = tree_nodes<true>(parent, M, tid);
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int i = u * 64 + tid;
-            if (i >= M) continue;
-            mask[2 * i] = t.lo[u];
-            mask[2 * i + 1] = t.hi[u];
-        }
+        store_masks(tree_nodes<2, true>(parent[min(tid, M - 1)], parent[min(tid + 64, M - 1)], M, tid), M, tid, mask);
         return;
     }
     if (blockIdx.x < kTreeBlocks + kZeroBlocks) {

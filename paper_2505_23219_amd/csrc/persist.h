@@ -42,7 +42,7 @@ __device__ __forceinline__ ArgPtr late_args()
 struct Ctx {
     int j, G;            // logical workgroup index, number of workgroups
     char* lds;           // dynamic LDS
-    int source;          // attention in one launch: see mask_source
+    int source[2];       // attention in one launch: see mask_source
     bool parents;        // ... whether that is parent[]
 };
 

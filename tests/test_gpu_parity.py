@@ -151,6 +151,13 @@ def test_tree_mask_across_the_two_nodes_of_a_lane(B, orc32, M):
             say("tree mask M=%d" % M)
             got = B.ghd_tree_mask(torch.from_numpy(parent).cuda()).cpu().numpy().view(np.uint64)
             assert np.array_equal(got.reshape(M, 2), bits)
+            # an attention call in one launch makes the same masks by itself: the same as under the masks given
+            nh, d, kv_len, cap = 2, 64, 5, 192
+            gen = torch.Generator().manual_seed(M)
+            q, k, v = (torch.randn(n, generator=gen).to(torch.float16).cuda() for n in ((M, nh, d), (nh, cap, d), (nh, d, cap)))
+            by_tree = B.ghd_tree_attention(q, k, v, torch.from_numpy(parent).cuda(), kv_len)
+            by_mask = B.ghd_masked_attention(q, k, v, torch.from_numpy(bits.view(np.int64)).cuda(), kv_len)
+            assert torch.equal(by_tree, by_mask)
 
 
 LINEAR_CASES = [(1, 64, 64), (3, 130, 688), (8, 1000, 256), (16, 256, 256), (17, 48, 96),
