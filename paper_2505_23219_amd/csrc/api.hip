@@ -961,6 +961,9 @@ void ghd_debug_cut(int M, int N, int K, int G, int solo, int* out5)
 /* out2 = {row tiles of x per workgroup, groups of workgroups with different ones} of the same launch. */
 void ghd_debug_groups(int M, int N, int K, int G, int solo, int* out2) { groups_on_host(M, N, K, G, solo != 0, out2); }
 
+/* k-steps that a wavefront of the same launch takes in its turn. */
+int ghd_debug_run(int M, int N, int K, int G, int solo) { return run_on_host(M, N, K, G, solo != 0); }
+
 /* Where row p of a packed QKV matrix comes from, by the packing's arithmetic and by the epilogue's: part, head, position of each. */
 void ghd_debug_qkv_row(int p, int nh, int d, int* out6)
 {

@@ -240,6 +240,7 @@ ghd_status launch_resident_checked(const void* kernel, int threads, size_t lds, 
 int fused_grid_size();
 void exchange_on_host(const int* xcd, int epochs, int n, int* ok);
 void groups_on_host(int M, int N, int K, int G, bool solo, int* out);
+int run_on_host(int M, int N, int K, int G, bool solo);
 void tile_range_on_host(int ntiles, int gx, int i, int* out);
 void attn_share_on_host(int nh, int ntile, int tmin, int j, int G, int head, int* out);
 

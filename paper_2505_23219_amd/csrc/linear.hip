@@ -233,6 +233,8 @@ void groups_on_host(int M, int N, int K, int G, bool solo, int* out)
     out[1] = cut.groups;
 }
 
+int run_on_host(int M, int N, int K, int G, bool solo) { return run_of_launch(choose_cut(M, N, K, G, solo), w_layout(N, K).nks); }
+
 void tile_range_on_host(int ntiles, int gx, int i, int* out)
 {
     tile_range(ntiles, gx, (uint32_t)(0x100000000ull / (uint64_t)gx + 1), i, out, out + 1);

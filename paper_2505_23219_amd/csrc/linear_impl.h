@@ -116,6 +116,21 @@ __host__ __device__ constexpr int stretches_parts(int MT, int R) { return folded
 // rows it costs 0 to 1%.
 __host__ __device__ constexpr bool keeps_step(int MT, int R) { return MT > 4 && R * MT <= 56; }
 
+// A workgroup of one whole tile takes a single KiB out of every four of a block and, where x is read as it lies, 64 bytes of a
+// row for each: with turns of one k-step, neighbours of a memory page and the halves of a line of x go to
+// different wavefronts. So its wavefronts take four consecutive k-steps in their turn (as many as their ring holds), and
+// what is left over after whole rounds in runs of one to three, so that no chain gets longer. us a call, weights in the cache:
+//   rows   matrix           ranges   turns of one   of four
+//      8   [4096, 11008]    16.3     17.6           16.0
+//      9   [3311, 4960]      8.1      8.8            7.9
+//     16   [4096, 4096]      8.7      9.0            8.1
+//     18   [2879, 3680]      9.6      9.9            9.9
+// (From HBM, over 121 calls of 56 k-steps and more, ranges taken as 1: turns of one 0.94 to 1.12, of four 0.90 to 1.05.)  Below
+// 56 k-steps there are rounds too few: turns of one 2% faster from the cache, of four 2% from HBM.
+__host__ __device__ constexpr int run_of(int MT, int R) { return R == 1 && MT <= 4 ? 4 : 1; }
+constexpr int kRunSteps = 56;
+static inline int run_of_launch(const LinCut& cut, int nks) { return cut.whole && nks >= kRunSteps ? run_of(cut.mt, cut.tiles) : 1; }
+
 // What the residual epilogue reads: four columns of a row of the residual stream and of the next
 // norm's gain.  (Requested behind the stream's first loads they delay the weights behind them by more
 // than they save: 0.9% of a 64-row step.)
@@ -307,8 +322,9 @@ struct LinShape {
 // the stream's first loads and its first wait.
 //
 // ROWS: x is row-major and read as it lies (16 rows x 64 bytes per load), which saves a
-// separate packing launch; columns from K on are not read.  STRETCHES: see folded().
-template <int MT, int R, int NW, bool ROWS, int STRETCHES, int SETS, class Early, class Finish>
+// separate packing launch; columns from K on are not read.  STRETCHES: see folded().  RUN: k-steps of a wavefront's turn
+// (more than one: at least NW * RUN k-steps).
+template <int MT, int R, int NW, bool ROWS, int STRETCHES, int SETS, int RUN, class Early, class Finish>
 __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int first, int count, int k0, int k1, int rt0,
                                            Early early, Finish finish)
 {
@@ -324,14 +340,24 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
     float* s_tmp = s_rinv + 128;                           // 1024 floats
     const half8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
 
-    // this wavefront's k-steps: k0 + turn + i * NW for i < we.  (The turns go round so that what is left
+    // this wavefront's k-steps, i < we: k0 + turn + i * NW.  (The turns go round so that what is left
     // over after the last whole round is spread over the pairs that the reduction adds up, and sums of
-    // unlike size meet late: in the order of the wavefronts K = 136 and 320 rounded 5% worse.)
+    // unlike size meet late: in the order of the wavefronts K = 136 and 320 rounded 5% worse.)  RUN > 1: see run_of.
     const int turn = NW == 8 ? (wave & 1) << 2 | (wave & 2) | wave >> 2 : (wave & 1) << 1 | wave >> 1;
-    const int n = k1 - k0, we = (n - turn + NW - 1) / NW;
-    const int i_hi = max(we - 1, 0);        // loads never go past the wavefront's last k-step
-    const int kw = min(k0 + turn, k1 - 1);  // (a wavefront without a k-step requests the last one)
-    auto step_of = [&](int i) { return kw + i * NW; };
+    const int n = k1 - k0;
+    // RUN > 1, at least RUN k-steps for everybody: `runs` of them in whole rounds, then what is left in shorter runs
+    constexpr uint32_t ROUND = NW * RUN;
+    const int left = (uint32_t)n % ROUND, tail = (left + NW - 1) / NW, runs = (uint32_t)n / ROUND * RUN;
+    const int we = RUN == 1 ? (n - turn + NW - 1) / NW : runs + min(max(left - turn * tail, 0), tail);
+    const int i_hi = max(we - 1, 0);                  // loads never go past the wavefront's last k-step
+    const int kw = min(k0 + turn * RUN, k1 - 1);      // (a wavefront without a k-step requests the last one)
+    // the wavefront's k-step i, which takes a place of the ring (RUN > 1: i % RUN); `last`: it may be one of those left
+    auto step_of = [&](auto slot, int i, auto last) {
+        constexpr int p = decltype(slot)::value;
+        if constexpr (RUN == 1) return kw + i * NW;
+        else if (decltype(last)::value && i - p >= runs) return k0 + runs * NW + turn * tail + p;
+        else return kw + (i - p) * NW + p;
+    };
     const int blk_sh = (h.flags >> kHeadBlk) & 15;
     const int mtp = ROWS ? 0 : (h.flags >> kHeadMtp) & 15;
 
@@ -353,6 +379,7 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
     constexpr bool SINGLE = SETS > 0, FOLDED = folded(MT, R) && !SINGLE, HALVED = STRETCHES > 1;
     static_assert(!(FOLDED && HALVED), "one way or the other");
     static_assert(!SINGLE || SETS == PD, "a set for each k-step of the ring");
+    static_assert(RUN == 1 || (RUN == PD && NW * RUN <= kRunSteps && !keeps_step(MT, R)), "a run is a turn of the ring");
     // What came before: FOLDED: the sums of earlier k-steps; HALVED: those of the first half that
     // stay in registers, as many as there are registers for.  The last NSTEP fragments are not set
     // aside but added up step by step, before the others of a step, which cover the wait for their
@@ -393,9 +420,9 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
         }
     };
 
-    auto load = [&](auto slot, int i) {
+    auto load = [&](auto slot, int i, auto last) {
         constexpr int p = decltype(slot)::value;
-        const int s = step_of(i);
+        const int s = step_of(slot, i, last);
         if constexpr (ROWS) {
             const int col = min(s * 32 + g4 * 8, h.K - 8);
 #pragma unroll
@@ -412,12 +439,12 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
         }
     };
     // MASKED: columns from K on count as zeros (the x fragments are zeroed: one select for all slots)
-    auto compute = [&](auto masked, auto slot, int i) {
+    auto compute = [&](auto masked, auto slot, int i, auto last) {
         constexpr int p = decltype(slot)::value;
         constexpr bool MASKED = decltype(masked)::value;
         half8 xf[MT];
         if constexpr (MASKED) {
-            const bool use = step_of(i) * 32 + g4 * 8 < h.K;
+            const bool use = step_of(slot, i, last) * 32 + g4 * 8 < h.K;
 #pragma unroll
             for (int b = 0; b < MT; ++b) xf[b] = use ? xr[p][b] : zero8;
         } else {
@@ -437,7 +464,7 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
     auto prologue = [&](auto self, auto slot) {
         constexpr int p = decltype(slot)::value;
         if constexpr (p < PD) {
-            load(slot, min(p, i_hi));
+            load(slot, RUN == 1 ? min(p, i_hi) : p, std::false_type{});
             pin_order();
             self(self, std::integral_constant<int, p + 1>{});
         }
@@ -453,9 +480,9 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
                     pin_order();
                 }
             }
-            compute(std::false_type{}, slot, s + p);
+            compute(std::false_type{}, slot, s + p, std::false_type{});
             pin_order();
-            load(slot, s + p + PD);
+            load(slot, s + p + PD, std::false_type{});
             pin_order();
             self(self, std::integral_constant<int, p + 1>{}, s);
         }
@@ -465,11 +492,11 @@ __device__ __forceinline__ void gemm_group(const LinHead& h, char* lds, int firs
         constexpr int p = decltype(slot)::value;
         if constexpr (p < 2 * PD - 1) {
             auto step = [&]() {
-                compute(std::true_type{}, std::integral_constant<int, p % PD>{}, s + p);
+                compute(std::true_type{}, std::integral_constant<int, p % PD>{}, s + p, std::bool_constant<(p >= PD)>{});
                 pin_order();
                 if constexpr (FOLDED && p % kFoldSteps == kFoldSteps - 1) fold();
                 if constexpr (p < PD - 1) {
-                    if (s + p + PD < we) load(std::integral_constant<int, p % PD>{}, s + p + PD);
+                    if (s + p + PD < we) load(std::integral_constant<int, p % PD>{}, s + p + PD, std::true_type{});
                     pin_order();
                 }
             };
@@ -651,8 +678,8 @@ __host__ __device__ __forceinline__ void tile_range(int ntiles, int gx, uint32_t
 }
 
 // ---- whole tiles ----------------------------------------------------------------------
-// GROUPS: of workgroups, with the same tiles and different rows of x.
-template <int MT, int R, bool ROWS, bool GROUPS>
+// GROUPS: of workgroups, with the same tiles and different rows of x.  RUN: see run_of.
+template <int MT, int R, bool ROWS, bool GROUPS, int RUN>
 __global__ __launch_bounds__(waves_of(MT, R) * 64) void k_linear(const half8* W, const half_t* x, uint64_t aux, int nks, int K,
                                                     int ntiles, int cut, uint32_t magic, uint32_t flags,
                                                     const FusedArgs)
@@ -674,7 +701,7 @@ __global__ __launch_bounds__(waves_of(MT, R) * 64) void k_linear(const half8* W,
         return;
     }
     const int lane = threadIdx.x & 63;
-    gemm_group<MT, R, waves_of(MT, R), ROWS, stretches_whole(MT, R), GROUPS ? kSingleSets : 0>(
+    gemm_group<MT, R, waves_of(MT, R), ROWS, stretches_whole(MT, R), GROUPS ? kSingleSets : 0, RUN>(
         h, lds, c0, c1 - c0, 0, nks, group * MT, solo,
         [&](ArgPtr a, auto&, auto& v, auto& m, auto& n0, const float* s_rinv) { epilogue(a, v, m, n0, lane, s_rinv); });
 }
@@ -702,7 +729,7 @@ __global__ __launch_bounds__(512) void k_linear_parts(const half8* W, const half
     // partial sums: one slot of NF fragments per workgroup; the block's parts are eight
     // workgroups apart
     const int slot0 = bx * S * 8 + xcd;
-    gemm_group<MT, R, 8, false, stretches_parts(MT, R), 0>(
+    gemm_group<MT, R, 8, false, stretches_parts(MT, R), 0, 1>(
         h, lds, first, count, k0, k1, 0, []() {},
         [&](ArgPtr a, auto& f, auto& v, auto& m, auto&, const float*) {
             for (int i = 0; i < (int)(sizeof(f) / sizeof(f[0])); ++i)
@@ -814,15 +841,24 @@ ghd_status launch_linear_r(const FusedArgs& a, const LinCut& cut, hipStream_t st
     if (cut.tiles == R && cut.whole) {
         constexpr int threads = waves_of(MT, R) * 64;
         constexpr size_t lds = LinShape<MT, R, waves_of(MT, R)>::template lds_bytes<(stretches_whole(MT, R) > 1)>;
+        constexpr int RUN = run_of(MT, R);
+        const bool runs = run_of_launch(cut, w_layout(a.lin_N, a.lin_K).nks) > 1;
         if constexpr (grouped(MT, R))
-            if (cut.groups > 1)
-                return launch_linear_kernel(cut.rows ? k_linear<MT, R, true, true> : k_linear<MT, R, false, true>, a, cut,
+            if (cut.groups > 1) {
+                if (runs)
+                    return launch_linear_kernel(cut.rows ? k_linear<MT, R, true, true, RUN> : k_linear<MT, R, false, true, RUN>, a, cut,
+                                                threads, lds, st);
+                return launch_linear_kernel(cut.rows ? k_linear<MT, R, true, true, 1> : k_linear<MT, R, false, true, 1>, a, cut,
                                             threads, lds, st);
+            }
         if (cut.groups > 1) return GHD_ERR_SHAPE;
         if constexpr (MT <= kRowsMaxMT)
-            if (cut.rows) return launch_linear_kernel(k_linear<MT, R, true, false>, a, cut, threads, lds, st);
+            if (cut.rows)
+                return launch_linear_kernel(runs ? k_linear<MT, R, true, false, RUN> : k_linear<MT, R, true, false, 1>, a, cut, threads,
+                                            lds, st);
         if (cut.rows) return GHD_ERR_SHAPE;
-        return launch_linear_kernel(k_linear<MT, R, false, false>, a, cut, threads, lds, st);
+        return launch_linear_kernel(runs ? k_linear<MT, R, false, false, RUN> : k_linear<MT, R, false, false, 1>, a, cut, threads, lds,
+                                    st);
     }
     if constexpr (R <= parts_max_tiles(MT))
         if (cut.tiles == R)

@@ -34,7 +34,7 @@ __global__ __launch_bounds__(kFT) void k_qkv_attn(const half8* W, const half_t* 
     };
     if (c0 >= c1) make_plan();
     else
-        gemm_group<MT, R, 8, false, stretches_whole(MT, R), 0>(
+        gemm_group<MT, R, 8, false, stretches_whole(MT, R), 0, 1>(
             h, lds, c0, c1 - c0, 0, nks, 0, make_plan,
             [&](ArgPtr la, auto&, auto& v, auto& m, auto& n0, const float* s_rinv) { epilogue(la, v, m, n0, lane, s_rinv); });
     // ---- the XCD's workgroups meet.  Every one of them counts itself in once its part of

@@ -197,6 +197,32 @@ def test_wavefronts_take_the_k_steps_in_turn(B, M, steps):
         assert err < max(2e-7, 4 * 2.0 ** -24 * K ** 0.5), (N, K, err)
 
 
+@pytest.mark.parametrize("M", [1, 9, 16, 17, 33, 40, 64])
+@pytest.mark.parametrize("steps", [55, 56, 63, 64, 65, 71, 72, 73, 80, 81, 88, 89, 95, 96, 97, 127])
+def test_four_k_steps_in_a_turn(B, M, steps):
+    """Whole tiles of narrow matrices, around the line from which wavefronts take four k-steps in their turn: what whole
+    rounds leave over is nothing, one run to eight of one, two, three and four, the last k-step whole and ragged; x read as it
+    lies, and packed (y meets x).  Bounds as in test_linear_kernels_at_their_edges and test_linear_in_place."""
+    say("four k-steps in a turn", M, steps)
+    for K in (32 * steps, 32 * steps - 8):
+        N = 200
+        assert B.lib().ghd_debug_run(M, N, K, 256, 1) == (4 if steps >= 56 else 1)
+        g = torch.Generator(device="cuda").manual_seed(K + M)
+        x = torch.randn((M, K), generator=g, device="cuda").to(torch.float16)
+        W = (torch.randn((N, K), generator=g, device="cuda") * 0.02).to(torch.float16)
+        Wp, ref = B.ghd_pack_weight(W), x.double() @ W.double().t()
+        ws = B.workspace(B.lib().ghd_linear_workspace_bytes(M, N, K))
+        ws.fill_(0xFF)
+        y = B.ghd_linear_skinny(x, Wp, N, ws=ws)
+        assert B.ghd_step_status(ws) == 0
+        err = float((y.double() - ref).norm() / ref.norm())
+        assert err < max(2e-7, 4 * 2.0 ** -24 * K ** 0.5), (K, err)
+        y = x[:, :N]
+        B.ghd_linear_skinny(x, Wp, N, ws=ws, y=y)
+        err = (y.double() - ref).abs()
+        assert bool((err <= 2.0 ** -11 * ref.abs() + 2e-6 * ref.std() + 2.0 ** -25).all()), (K, float(err.max()))
+
+
 @pytest.mark.parametrize("M,N,K,whole", [(1, 2560, 6904, 0), (16, 1536, 4096, 0), (5, 2048, 5504, 0), (24, 5120, 5120, 0),
                                          (16, 5120, 5120, 1), (32, 4608, 4608, 0), (1, 4096, 4096, 1), (16, 1536, 1536, 1)])
 def test_narrow_matrices_inside_a_step(B, M, N, K, whole):

@@ -183,6 +183,17 @@ def test_row_groups_cover_every_row_once(M):
     assert seen > 0 or M <= 16
 
 
+def test_which_launches_take_four_k_steps_in_a_turn():
+    """Workgroups of one whole tile with up to 64 rows of x, from 56 k-steps on: with single k-steps in turn calls of their own of
+    5 to 16 rows were 2 to 12% slower than with a k range for each wavefront.  Nothing else."""
+    lib = B.lib()
+    for (M, N, K, solo), want in [((8, 4096, 11008, 1), 4), ((12, 1118, 3744, 1), 4), ((9, 3311, 4960, 1), 4), ((16, 4096, 4096, 1), 4),
+                                  ((18, 1365, 2704, 1), 4), ((40, 79, 4816, 1), 4), ((35, 2882, 2872, 1), 4), ((1, 4096, 4096, 0), 4),
+                                  ((8, 4096, 1792, 1), 4), ((8, 4096, 1760, 1), 1), ((8, 5000, 4096, 1), 1), ((80, 2000, 4096, 1), 1),
+                                  ((64, 22016, 4096, 0), 1), ((1, 4096, 11008, 0), 1), ((3, 655, 9584, 1), 1)]:
+        assert lib.ghd_debug_run(M, N, K, 256, solo) == want, (M, N, K, solo)
+
+
 @pytest.mark.parametrize("tmin", [1, 2, 4])
 @pytest.mark.parametrize("nh,ntile", [(32, 33), (40, 129), (32, 1), (4, 3), (256, 2), (7, 9), (1, 40), (100, 17)])
 def test_attention_parts_are_not_made_too_small(nh, ntile, tmin):
