@@ -90,6 +90,12 @@ size_t linear_part_floats(int M, int G)
 //   at 1 to 16 rows 53.5 to 55.1 and 51.9 to 53.4; [2048, 5504] 45.1 to 46.7 and 44.1 to 45.2; [5120, 5120] at 24
 //   to 32 rows 130.0 to 131.6 and 126.3 to 127.3; [4096, 4096] at 1 row 84.2 and 85.2, in whole tiles still.  (At 65 rows
 //   and more the same allowance made layers of 8 to 17 heads of 128 4% slower: their gate|up comes out in parts.)
+//   Calls of their own at 17 to 32 rows, us in whole tiles and in parts: where both pack x ([5120, 5120] at 24 rows 16.7 and
+//   13.8, [9375, 6256] at 26 25.6 and 23.9) as in a step; where whole tiles read x as it lies (up to 97 k-steps), parts are a
+//   launch more, and what whole tiles lose grows with the rows that there are: [4539, 2096] at 18 rows 7.5 and 8.9, [4478, 2384]
+//   at 19 8.7 and 9.6, [4173, 2616] at 21 9.7 and 9.9, [5454, 3080] at 24 12.0 and 11.1, [4478, 2616] at 29 10.9 and 10.1,
+//   [5027, 3080] at 32 13.4 and 10.9; with three tiles a workgroup [8748, 2848] at 17 11.7 and 13.6, [8931, 3080] at 29 16.2
+//   and 14.5.  (The estimate is off by up to a tenth: [4313, 2144] at 30 rows, 8.9 and 9.5, comes out in parts.)
 // Whole tiles read all of x in every workgroup, so they are for wide matrices, and for narrow
 // ones where x is small; parts divide x with the k range; groups of workgroups divide its rows, and exchange
 // nothing.  (Layers of 20 heads of 64 at 37 rows 41.6 us without groups, 39.9 with them; 5 heads of 128 at 128 rows
@@ -143,10 +149,13 @@ LinCut choose_cut(int M, int N, int K, int G, bool solo)
     // (up to 16 rows only the rows that there are get read)
     const double row_cost = mt == 1 ? M / 8.0 : 2.0;
     best.rows = solo && mt <= kRowsMaxMT && (row_cost - 1.0) * mt * P * lay.nks * 1024.0 / kXBytesPerUs < kPrepareUs;
-    double best_us = share_us(best.tiles * P, mt * P * (best.rows ? row_cost : 1.0), lay.nks) + (solo && !best.rows ? kPrepareUs : 0.0);
+    const bool uneven = mt == 2 && U > Gx;
+    // (of x as it lies, at 17 to 32 rows in uneven shares too, the rows that there are: see above)
+    const double x_cost = !best.rows ? 1.0 : uneven ? M / 16.0 : row_cost;
+    double best_us = share_us(best.tiles * P, mt * P * x_cost, lay.nks) + (solo && !best.rows ? kPrepareUs : 0.0);
     if (lay.rb == 1) return best;
     if (mt == 1 && U <= Gx && !solo) best_us += kNarrowWholeUs;
-    if (mt == 2 && U > Gx) best_us += (best.tiles * P - (double)U / Gx) * lay.nks * kUnevenStepUs;
+    if (uneven) best_us += (best.tiles * P - (double)U / Gx) * lay.nks * kUnevenStepUs;
     for (int r = 1; r <= parts_max_tiles(mt); ++r) {
         const int per_xcd = ceil_div(ceil_div(lay.ntiles, r), 8);
         if (per_xcd > Gx) continue;

@@ -183,6 +183,17 @@ def test_row_groups_cover_every_row_once(M):
     assert seen > 0 or M <= 16
 
 
+def test_uneven_shares_of_calls_that_read_x_as_it_lies():
+    """17 to 32 rows by narrow matrices of more tiles than workgroups, calls of their own: one launch in whole tiles that reads x as
+    it lies while rows are few, packing and parts where that is less (or x would be packed anyway)."""
+    lib, out = B.lib(), (C.c_int * 5)()
+    for (M, N, K), whole in [((18, 4539, 2096), 1), ((17, 4142, 2344), 1), ((17, 5027, 2848), 1), ((18, 4503, 2712), 1), ((19, 4478, 2384), 1),
+                             ((21, 4173, 2152), 1), ((17, 8748, 2848), 1), ((22, 8382, 2848), 1), ((28, 8626, 2848), 1),
+                             ((28, 4966, 3080), 0), ((30, 5099, 3048), 0), ((32, 5027, 3080), 0), ((24, 5120, 5120), 0), ((26, 9375, 6256), 0)]:
+        lib.ghd_debug_cut(M, N, K, 256, 1, out)
+        assert out[0] == whole and out[4] == whole, (M, N, K, list(out))
+
+
 def test_which_launches_take_four_k_steps_in_a_turn():
     """Workgroups of one whole tile with up to 64 rows of x, from 56 k-steps on: with single k-steps in turn calls of their own of
     5 to 16 rows were 2 to 12% slower than with a k range for each wavefront.  Nothing else."""
