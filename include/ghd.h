@@ -231,7 +231,12 @@ ghd_status ghd_verify_layer(const ghd_model_cfg *cfg, const ghd_layer_weights *w
 /* x_in fp16 [M, H] (hidden states of the tree tokens) -> logits float [M, V].
  * layers_host / kv_host: host arrays of length cfg->L holding device pointers.
  * g_final fp16 [H]; Wlm packed from [V, H].  x_out (optional, may be NULL)
- * receives the final residual stream, float [M, H]. */
+ * receives the final residual stream, float [M, H].  It is device memory that the
+ * pass works in: every layer reads and rewrites it, so until the pass is over, and
+ * after a wait that gave up, it holds an intermediate state.  It may share storage
+ * with x_in, parent_dev and the workspace (the stream is then kept in the workspace
+ * and copied, over them, when the layers are done), as long as it begins behind the
+ * ghd_workspace_bytes that the pass uses; with nothing else that the pass reads. */
 ghd_status ghd_verify_stack(const ghd_model_cfg *cfg, const ghd_layer_weights *layers_host,
                             const ghd_kv *kv_host, const void *g_final, const void *Wlm,
                             const void *x_in, const int32_t *parent_dev, int M, int kv_len,

@@ -319,6 +319,14 @@ class Stack:
         self.Wlm = head["Wlm"]
 
 
+def _device_x_out(x_out: Optional[torch.Tensor], x_in: torch.Tensor) -> Optional[torch.Tensor]:
+    """Where a pass keeps the residual stream that the caller wants: kernels read and write it in every layer, so for an
+    x_out in host memory that is a buffer of its own on x_in's GPU, to be copied, on the stream, at the end."""
+    if x_out is None or x_out.is_cuda:
+        return x_out
+    return torch.empty(x_out.shape, dtype=x_out.dtype, device=x_in.device)
+
+
 def ghd_verify_stack(stack: Stack, x_in: torch.Tensor, parent: torch.Tensor, kv_len: int,
                      logits: Optional[torch.Tensor] = None, x_out: Optional[torch.Tensor] = None,
                      ws: Optional[torch.Tensor] = None) -> torch.Tensor:
@@ -328,10 +336,13 @@ def ghd_verify_stack(stack: Stack, x_in: torch.Tensor, parent: torch.Tensor, kv_
         logits = torch.empty((M, cfg.V), dtype=torch.float32, device=x_in.device)
     if ws is None:
         ws = workspace(lib().ghd_workspace_bytes(C.byref(cfg), M, kv_len), x_in.device)
+    x_dev = _device_x_out(x_out, x_in)
     _check(lib().ghd_verify_stack(C.byref(cfg), stack.lw, stack.kv, _ptr(stack.g_final),
                                   _ptr(stack.Wlm), _ptr(_dev(x_in, torch.float16)),
                                   _ptr(_dev(parent, torch.int32)), M, kv_len, _ptr(logits),
-                                  _ptr(x_out), _ptr(ws), ws.numel(), _stream()), "ghd_verify_stack")
+                                  _ptr(x_dev), _ptr(ws), ws.numel(), _stream()), "ghd_verify_stack")
+    if x_dev is not x_out:
+        x_out.copy_(x_dev, non_blocking=True)
     return logits
 
 
@@ -346,10 +357,13 @@ def ghd_verify_stack_argmax(stack: Stack, x_in: torch.Tensor, parent: torch.Tens
         amax = torch.empty(M, dtype=torch.int32, device=x_in.device)
     if ws is None:
         ws = workspace(lib().ghd_workspace_bytes(C.byref(cfg), M, kv_len), x_in.device)
+    x_dev = _device_x_out(x_out, x_in)
     _check(lib().ghd_verify_stack_argmax(C.byref(cfg), stack.lw, stack.kv, _ptr(stack.g_final),
                                          _ptr(stack.Wlm), _ptr(_dev(x_in, torch.float16)),
                                          _ptr(_dev(parent, torch.int32)), M, kv_len, _ptr(amax), _ptr(logits),
-                                         _ptr(x_out), _ptr(ws), ws.numel(), _stream()), "ghd_verify_stack_argmax")
+                                         _ptr(x_dev), _ptr(ws), ws.numel(), _stream()), "ghd_verify_stack_argmax")
+    if x_dev is not x_out:
+        x_out.copy_(x_dev, non_blocking=True)
     return amax
 
 

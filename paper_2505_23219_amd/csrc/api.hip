@@ -578,6 +578,14 @@ ghd_status ghd_verify_layer(const ghd_model_cfg* cfg, const ghd_layer_weights* w
     return run_layer(cfg, w, kv, x, M, kv_len, lw, nullptr, 0, st);
 }
 
+// The residual stream is kept in x_out itself, where the caller wants it (a copy at the end was a launch more: 4 us of the
+// smallest stack's 32), unless x_out meets what is read while it is written.
+static bool x_out_copied(const void* x_out, const void* x_in, const void* parent, int M, int H, const void* ws, size_t ws_bytes)
+{
+    const size_t x_bytes = (size_t)M * H * sizeof(float);
+    return meet(x_out, x_bytes, x_in, x_bytes / 2) || meet(x_out, x_bytes, parent, M * sizeof(int32_t)) || meet(x_out, x_bytes, ws, ws_bytes);
+}
+
 static ghd_status verify_stack_impl(const ghd_model_cfg* cfg, const ghd_layer_weights* layers_host,
                                     const ghd_kv* kv_host, const void* g_final, const void* Wlm,
                                     const void* x_in, const int32_t* parent_dev, int M, int kv_len,
@@ -599,11 +607,7 @@ static ghd_status verify_stack_impl(const ghd_model_cfg* cfg, const ghd_layer_we
     hipStream_t st = (hipStream_t)stream;
     Ws lw = carve(ws, 0, M, cfg->H, cfg->F, cfg->d, 0, cfg->V);
     const int H = cfg->H;
-    // The residual stream is kept in x_out itself, where the caller wants it (a copy at the end was a launch more: 4 us of the
-    // smallest stack's 32), unless x_out meets what is read while it is written.
-    const size_t x_bytes = (size_t)M * H * sizeof(float);
-    const bool copied = x_out && (meet(x_out, x_bytes, x_in, x_bytes / 2) || meet(x_out, x_bytes, parent_dev, M * sizeof(int32_t)) ||
-                                  meet(x_out, x_bytes, ws, ws_bytes));
+    const bool copied = x_out && x_out_copied(x_out, x_in, parent_dev, M, H, ws, ws_bytes);
     float* const x = x_out && !copied ? x_out : lw.x;
     // x = widen(x_in) with its sums of squares
     if ((s = launch_fused_setup(lw.sync, parent_dev, M, mpad_of(M), kv_len, cfg->d, cfg->rope_base,
@@ -977,6 +981,12 @@ int ghd_debug_linear_reads_x(const void* y, const void* x, int M, int N, int K, 
 {
     bool as_it_lies;
     return linear_call_cut(y, x, M, N, K, ldx, ldy, flags, &as_it_lies).rows;
+}
+
+/* Is the final residual stream copied to x_out at the end of a pass (1), or kept there throughout (0)? */
+int ghd_debug_x_out_copied(const void* x_out, const void* x_in, const void* parent, int M, int H, const void* ws, size_t ws_bytes)
+{
+    return x_out_copied(x_out, x_in, parent, M, H, ws, ws_bytes);
 }
 
 /* The attention's shares; tmin: the fewest 64-key tiles that a part is made for. */

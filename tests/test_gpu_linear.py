@@ -269,3 +269,43 @@ def test_residual_stream_where_the_caller_wants_it(B, M, shift):
     assert bool(torch.isfinite(logits).all()) and torch.equal(both, logits) and torch.equal(neither, logits)
     assert torch.equal(shared, x_out)
     assert B.ghd_step_status(ws) == 0
+
+
+@pytest.mark.parametrize("M", [1, 70, 128])
+@pytest.mark.parametrize("where", ["parent", "parent_last", "workspace", "host", "pinned"])
+def test_residual_stream_where_it_is_copied(B, M, where):
+    """The final residual stream over parent[] (at its start, its last word), over the unused end of the workspace buffer,
+    and in host memory: the same logits, x and argmaxes as in a buffer of its own, bit for bit."""
+    from paper_2505_23219_amd import model, workloads as wl
+    say("x_out copied", M, where)
+    s = wl.ModelShape("x_out", H=256, nh=4, d=64, F=688, V=1000, L=2)
+    kv = 100
+    caches = [model.upload_cache(*wl.kv_cache(s, 256, kv, 5, l)) for l in range(s.L)]
+    stack = model.build_stack(s, 256, [model.upload_layer(wl.layer_weights(s, 5, l), s.d) for l in range(s.L)], caches,
+                              model.upload_head(wl.head_weights(s, 5)))
+    x16 = wl.activations(M, s.H, 5).cuda()
+    tree = torch.from_numpy(wl.tree_random(M, 5, 5)).cuda()
+    need = B.ghd_workspace_bytes(stack.cfg, M, kv)
+    ws = B.workspace(need)
+    want = torch.full((M, s.H), float("nan"), dtype=torch.float32, device="cuda")
+    logits = B.ghd_verify_stack(stack, x16, tree, kv, x_out=want, ws=ws)
+    amax = B.ghd_verify_stack_argmax(stack, x16, tree, kv, ws=ws)
+    for argmax in (False, True):
+        parent, buf = tree, torch.full((M * s.H,), float("nan"), dtype=torch.float32, device="cuda")
+        if where.startswith("parent"):
+            parent = buf.view(torch.int32)[:M] if where == "parent" else buf.view(torch.int32)[M * s.H - M:]
+            parent.copy_(tree)
+        elif where == "workspace":
+            at = (need + 255) // 256 * 256
+            ws = B.workspace(at + 4 * M * s.H)
+            buf = ws[at:at + 4 * M * s.H].view(torch.float32)
+        else:
+            buf = torch.full((M * s.H,), float("nan"), dtype=torch.float32, pin_memory=where == "pinned")
+        x_out = buf.view(M, s.H)
+        if argmax:
+            assert torch.equal(B.ghd_verify_stack_argmax(stack, x16, parent, kv, x_out=x_out, ws=ws), amax)
+        else:
+            assert torch.equal(B.ghd_verify_stack(stack, x16, parent, kv, x_out=x_out, ws=ws), logits)
+        torch.cuda.synchronize()
+        assert bool(torch.isfinite(want).all()) and torch.equal(x_out.cuda(), want)
+        assert B.ghd_step_status(ws) == 0

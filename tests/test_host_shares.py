@@ -289,3 +289,17 @@ def test_rows_of_the_qkv_matrix_are_found_without_division():
             for p in range(0, n, 4) if n < 20000 else sorted({*range(0, n, 244), *range(0, n, nh * d // 8), n - 4}):
                 lib.ghd_debug_qkv_row(p, nh, d, out)
                 assert list(out[:3]) == list(out[3:]), (p, nh, d, list(out))
+
+
+def test_which_x_out_the_residual_stream_is_not_kept_in():
+    """Copied at the end where a byte of x_out is one of x_in's, of parent[]'s or of the workspace buffer's; kept there beside them."""
+    fn = B.lib().ghd_debug_x_out_copied
+    fn.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_void_p, C.c_size_t]
+    M, H, ws_bytes = 7, 64, 4096
+    n = 4 * M * H
+    far = 1 << 30
+    for size, args in [(n // 2, lambda at: (at, far, far)), (4 * M, lambda at: (far, at, far)), (ws_bytes, lambda at: (far, far, at))]:
+        for x in (1 << 20, 1 << 40):
+            for at, meets in [(x - size, 0), (x - size + 1, 1), (x, 1), (x + n // 2, 1), (x + n - 1, 1), (x + n, 0)]:
+                x_in, parent, ws = args(at)
+                assert fn(x, x_in, parent, M, H, ws, ws_bytes) == meets, (size, x, at)
