@@ -47,15 +47,15 @@ struct AttnHeads {
     int h_lo, h_hi;    // this workgroup's heads, local to the XCD (empty if h_lo == h_hi)
 };
 
-// (of workgroup w of XCD x, which has Gx of them and the heads hx0 .. hx1 - 1)
-__host__ __device__ __forceinline__ AttnHeads attn_heads_of(int hx0, int hx1, int x, int w, int Gx)
+// (of workgroup w of XCD x, which has Gx of them)
+__host__ __device__ __forceinline__ AttnHeads attn_heads(int nh, int x, int w, int Gx)
 {
     AttnHeads s;
     s.Gx = Gx;
     s.x = x;
     s.w = w;
-    s.hx0 = hx0;
-    s.Hx = hx1 - hx0;
+    s.hx0 = nh * x >> 3;
+    s.Hx = (nh * (x + 1) >> 3) - s.hx0;
     s.h_lo = s.h_hi = 0;
     if (s.Hx == 0) return s;
     if (s.Hx >= Gx) {
@@ -66,11 +66,6 @@ __host__ __device__ __forceinline__ AttnHeads attn_heads_of(int hx0, int hx1, in
         s.h_hi = s.h_lo + 1;
     }
     return s;
-}
-
-__host__ __device__ __forceinline__ AttnHeads attn_heads(int nh, int x, int w, int Gx)
-{
-    return attn_heads_of(nh * x >> 3, nh * (x + 1) >> 3, x, w, Gx);
 }
 
 struct AttnTiles {
@@ -98,10 +93,9 @@ __host__ __device__ __forceinline__ AttnTiles attn_tiles(const AttnHeads& s, int
     // and the last workgroup, whose range ends with the (costlier) tree tile, gets a shorter one
     t.t0 = t.t1 = 0;
     if (t.me < t.np) {
-        // ntile = q * np + r; the estimate of q is a few off where ntile has more bits than a float
-        const int guess = (int)((float)ntile * recip(t.np)), left = ntile - guess * t.np;
-        const int more = (int)floorf(((float)left + 0.5f) * recip(t.np));
-        const int q = guess + more, r = left - more * t.np;
+        // ntile = q * np + r.  (ntile is below 2^19: offsets inside a head, of 64 channels or more, fit 31 bits, which
+        // every entry point checks; the products of the boundaries would not fit div_small)
+        const int q = div_small(ntile, t.np), r = ntile - q * t.np;
         t.t0 = q * t.me + div_small(r * t.me + t.np - 1, t.np);
         t.t1 = q * (t.me + 1) + div_small(r * (t.me + 1) + t.np - 1, t.np);
     }

@@ -84,8 +84,8 @@ ghd_status launch_fused(const FusedArgs& a, hipStream_t st)
 // one of j's heads at all (otherwise the first five are -1).
 void attn_share_on_host(int nh, int ntile, int tmin, int j, int G, int head, int* out)
 {
-    const int Gx = G / 8;        // (a grid that the 8 XCDs do not divide counts as one of them)
-    const AttnHeads hs = G % 8 ? attn_heads_of(0, nh, 0, j, G) : attn_heads(nh, j / Gx, j % Gx, Gx);
+    const int Gx = G / 8;        // (a grid that 8 does not divide, which no launch has, counts as the first of 8 XCDs)
+    const AttnHeads hs = G % 8 ? attn_heads(8 * nh, 0, j, G) : attn_heads(nh, j / Gx, j % Gx, Gx);
     for (int i = 0; i < 6; ++i) out[i] = -1;
     out[5] = 0;
     const int hl = head - hs.hx0;
