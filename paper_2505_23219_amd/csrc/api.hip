@@ -983,6 +983,9 @@ int ghd_debug_linear_reads_x(const void* y, const void* x, int M, int N, int K, 
     return linear_call_cut(y, x, M, N, K, ldx, ldy, flags, &as_it_lies).rows;
 }
 
+/* Units in the last place by which the calling thread's evaluation of the kernels' divisions has its reciprocals off. */
+void ghd_debug_recip_ulps(int ulps) { host_recip_ulps = ulps; }
+
 /* Is the final residual stream copied to x_out at the end of a pass (1), or kept there throughout (0)? */
 int ghd_debug_x_out_copied(const void* x_out, const void* x_in, const void* parent, int M, int H, const void* ws, size_t ws_bytes)
 {

@@ -93,12 +93,17 @@ __host__ __device__ inline QkvRow qkv_row(int p, int nh, int d)
 // the reciprocal and the product round is below n / d * 2^-22.  (The compiler's integer division is some twenty instructions,
 // each of which waits for the one before; eight of them and the read of the argument block were 1.1 us
 // before an attention call's first request.)
+// On the host, where only tests evaluate it: the hardware's reciprocal is within one unit in the last place of this one,
+// so results have to be the same with it as many units off as the thread has set.
+extern thread_local int host_recip_ulps;
 __host__ __device__ __forceinline__ float recip(int d)
 {
 #ifdef __HIP_DEVICE_COMPILE__
     return __builtin_amdgcn_rcpf((float)d);
 #else
-    return 1.0f / (float)d;
+    float r = 1.0f / (float)d;
+    for (int i = host_recip_ulps; i != 0; i += i > 0 ? -1 : 1) r = __builtin_nextafterf(r, i > 0 ? 2.0f : 0.0f);
+    return r;
 #endif
 }
 __host__ __device__ __forceinline__ int div_small(int n, int d) { return (int)(((float)n + 0.5f) * recip(d)); }

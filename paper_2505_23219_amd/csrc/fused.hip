@@ -79,6 +79,8 @@ ghd_status launch_fused(const FusedArgs& a, hipStream_t st)
     return a.d == 64 ? launch_attention_d<64, false>(a, st) : launch_attention_d<128, false>(a, st);
 }
 
+thread_local int host_recip_ulps = 0;
+
 // The attention's work shares on the host: for workgroup j and head `head`,
 // out[0..5] = first part, number of parts, this part's index, t0, t1, and whether `head` is
 // one of j's heads at all (otherwise the first five are -1).

@@ -303,3 +303,43 @@ def test_which_x_out_the_residual_stream_is_not_kept_in():
             for at, meets in [(x - size, 0), (x - size + 1, 1), (x, 1), (x + n // 2, 1), (x + n - 1, 1), (x + n, 0)]:
                 x_in, parent, ws = args(at)
                 assert fn(x, x_in, parent, M, H, ws, ws_bytes) == meets, (size, x, at)
+
+
+@pytest.fixture(params=[-1, 1])
+def recip_ulps(request):
+    """Reciprocals as far off as the hardware's may be."""
+    B.lib().ghd_debug_recip_ulps(request.param)
+    yield request.param
+    B.lib().ghd_debug_recip_ulps(0)
+
+
+def test_attention_shares_with_the_hardwares_reciprocals(recip_ulps):
+    test_attention_shares_are_those_of_integer_division()
+
+
+def test_rows_of_the_qkv_matrix_with_the_hardwares_reciprocals(recip_ulps):
+    test_rows_of_the_qkv_matrix_are_found_without_division()
+
+
+@pytest.mark.parametrize("ulps", [-1, 0, 1])
+def test_heads_that_are_one_part(ulps):
+    """Attention calls in one launch have the fewest tiles of a part at 0, a head a workgroup at most and as many workgroups as
+    that takes: every head is one workgroup's, with all its tiles, whatever the head count and the length."""
+    lib, out = B.lib(), (C.c_int * 6)()
+    lib.ghd_debug_recip_ulps(ulps)
+    try:
+        for nh in range(1, 257):
+            G = min(256, 8 * -(-nh // 8))
+            for ntile in (1, 2, 3, 7, 12, 64, 1000, 2 ** 19 - 1):
+                for head in {0, nh // 3, nh // 2, nh - 1}:
+                    whole = []
+                    for j in range(G):
+                        lib.ghd_debug_attn_share_min(nh, ntile, 0, j, G, head, out)
+                        first, n, me, t0, t1, mine = list(out)
+                        if mine and me < n:
+                            whole.append((first == j, n, me, t0, t1))
+                        else:
+                            assert t0 == t1 or not mine
+                    assert whole == [(True, 1, 0, 0, ntile)], (nh, ntile, head, whole)
+    finally:
+        lib.ghd_debug_recip_ulps(0)
