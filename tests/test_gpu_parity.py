@@ -1032,3 +1032,29 @@ def test_step_can_be_captured_in_a_graph(B, model, orc32):
             torch.cuda.synchronize()
             assert B.ghd_step_status(ws) == 0
             assert torch.equal(logits, want_logits) and torch.equal(res, want_res), rep
+
+
+def test_attention_with_heads_far_apart(B):
+    """Head strides on both sides of 2^35 elements (64 GiB), from which they are not among the kernel's preloaded
+    arguments, of K, of V and of both: the same outputs as with heads side by side, bit for bit."""
+    line, room = 1 << 35, 1 << 20
+    if torch.cuda.mem_get_info()[0] < 2 * (line + 2 * room) + (8 << 30):
+        pytest.skip("needs 72 GiB of GPU memory")
+    buf = torch.empty(line + 2 * room, dtype=torch.float16, device="cuda")       # (touched only where heads lie)
+    nh = 2
+    for M, d, kv_len in [(1, 128, 60), (20, 64, 700), (40, 128, 150), (64, 64, 900), (100, 128, 40), (128, 64, 500)]:
+        say("far heads", M, d, kv_len)
+        cap = (kv_len + M + 63) // 64 * 64
+        assert 2 * cap * d <= room
+        gen = torch.Generator().manual_seed(M)
+        q, k, v = (torch.randn(n, generator=gen).to(torch.float16).cuda() for n in ((M, nh, d), (nh, cap, d), (nh, d, cap)))
+        parent = torch.arange(-1, M - 1, dtype=torch.int32, device="cuda")
+        want = B.ghd_tree_attention(q, k, v, parent, kv_len)
+        for k_head, v_head in [(line, line), (line, cap * d), (cap * d, line), (line - 8, line - 8), (line + 8, line - 8)]:
+            k_far = buf.as_strided((nh, cap, d), (k_head, d, 1))
+            v_far = buf.as_strided((nh, d, cap), (v_head, cap, 1), room)
+            k_far.copy_(k)
+            v_far.copy_(v)
+            assert torch.equal(B.ghd_tree_attention(q, k_far, v_far, parent, kv_len), want), (M, d, k_head, v_head)
+    del buf, k_far, v_far
+    torch.cuda.empty_cache()
