@@ -93,9 +93,12 @@ __host__ __device__ __forceinline__ AttnTiles attn_tiles(const AttnHeads& s, int
     // and the last workgroup, whose range ends with the (costlier) tree tile, gets a shorter one
     t.t0 = t.t1 = 0;
     if (t.me < t.np) {
-        // ntile = q * np + r.  (ntile is below 2^19: offsets inside a head, of 64 channels or more, fit 31 bits, which
-        // every entry point checks; the products of the boundaries would not fit div_small)
-        const int q = div_small(ntile, t.np), r = ntile - q * t.np;
+        // ntile = q * np + r.  (The products of the boundaries do not fit div_small.  ntile does - it is below 2^19, since offsets
+        // inside a head of 64 channels or more fit 31 bits, which every entry point checks - but with it, fifteen
+        // instructions less, calls came out up to 1.5% slower: 40 heads of 64, 33 rows, 6000 cached 18.2 us and 18.5.)
+        const int guess = (int)((float)ntile * recip(t.np)), left = ntile - guess * t.np;
+        const int more = (int)floorf(((float)left + 0.5f) * recip(t.np));
+        const int q = guess + more, r = left - more * t.np;
         t.t0 = q * t.me + div_small(r * t.me + t.np - 1, t.np);
         t.t1 = q * (t.me + 1) + div_small(r * (t.me + 1) + t.np - 1, t.np);
     }
