@@ -25,8 +25,8 @@
 // layer, 8192 cached tokens: 1.2 us a tile of 32 KB on each compute unit, 6.9 TB/s); at few the chain of latencies around
 // the tiles.  The same through registers, four tiles ahead, took seven copies of a tile's code (28 KB, each
 // fetched when it is first run) and a final merge of a row per wavefront: attention of 24 heads, 48
-// rows, 3001 cached tokens 20.5 us a call, now 17.9; launch with the QKV layer and 128 rows at 2048 cached
-// tokens 61 us, now 52.  Each wavefront reading units by itself was slower there: the states of eight
+// rows, 3001 cached tokens 20.5 us a call, 17.9 through the ring when it came in and 17.0 now; launch with the QKV layer and
+// 128 rows at 2048 cached tokens 61 us, 52 and 50.  Each wavefront reading units by itself was slower there: the states of eight
 // wavefronts with all rows take 4 us to merge, and with the rows split over groups of wavefronts every unit is
 // read once per group (13B-shaped layer, 64 rows, 8192 cached tokens, launch with the QKV layer: 10 and 20 us more).
 #pragma once
@@ -234,8 +234,9 @@ __device__ __forceinline__ void mask_source(Ctx& cx, const void* source, int M)
     cx.source[1] = TWO && cx.parents && tid < 64 && tid + 64 < M ? (int)words[tid + 64] : 0;
 }
 // (The first wavefront makes a tree's masks in registers: reads of LDS arrays would wait for all that is on its way to the
-// LDS.  us a call under a wide tree, with the doubling in LDS arrays and now: 32 heads of 128, 4 rows, 120 cached 6.5 and 6.3; 32
-// of 64, 64 rows, 128 cached 7.2 and 6.5; 8 of 128, 128 rows, 60 cached 11.7 and 11.1, under a chain 12.1 and 11.7)
+// LDS.  us a call under a wide tree, from a graph, with the doubling in LDS arrays and now: 32 heads of 128, 4 rows, 120
+// cached 6.5 and 6.3; 32 of 64, 64 rows, 128 cached 7.2 and 6.5; 8 of 128, 128 rows, 60 cached 11.7 and 11.1, under a
+// chain 12.1 and 11.7)
 template <bool TWO>
 __device__ __forceinline__ void masks_from_source(bool parents, int M, const int (&word)[2], uint64_t* mask)
 {
@@ -694,10 +695,12 @@ __device__ __forceinline__ bool attn_staged(const AttnFirst& f, Late late, Ctx& 
     constexpr int UNITS = 2 / HALVES;                  // 32-key units of a tile that a wavefront works on
     constexpr int PIECES = D / 64;                     // 1 KiB pieces of a tile's K that a wavefront requests (as many of V)
     constexpr int LPT = 2 * PIECES;                    // loads per tile
-    // Masked units by seen_keys(), except with 128 channels up to 64 rows, where the loop over the other tiles came out
-    // slower beside it (4 heads, 48 rows, 16000 cached 19.7 us and 20.0; 64, 64 rows, 900 cached 15.9 and 15.5).  With
-    // it and without: 8 heads of 128, 128 rows, 60 cached 11.7 us and 13.0; 16, 3000 cached 19.0 and 19.3; 40 heads of
-    // 64, 33 rows, 6000 cached 18.7 and 19.2.
+    // Masked units by seen_keys(), except with 128 channels up to 64 rows: there the loop over the other tiles comes out
+    // slower beside it, and calls of many tiles lose what those of few win.  us a call, by the masks' words and by seen_keys:
+    // 4 heads, 48 rows, 16000 cached 19.5 and 19.8; 24, 3001 cached 15.4 and 15.5; 32, 64 rows, 2048 cached 15.6 and 15.7, 120
+    // cached 9.15 and 8.7; 64, 900 cached 15.5 and 15.3; 2, 40 rows, 1000 cached 10.4 and 10.1.  Elsewhere: 8 heads of
+    // 128, 128 rows, 60 cached 12.5 and 11.4; 16, 3000 cached 19.0 and 18.8; 16 heads of 64, 64 rows, 700 cached 10.0 and
+    // 9.6; 40, 33 rows, 6000 cached 19.0 and 18.9.
     constexpr bool COMPACT = HALVES == 1 || D == 64;
     using L = StagedLds<MT, D>;
     constexpr int NB = L::NB;

@@ -102,16 +102,18 @@ void attn_share_on_host(int nh, int ntile, int tmin, int j, int G, int head, int
 }
 
 // An attention call whose heads are one workgroup's each needs no counter and so no launch before its own (3 us of
-// the host's time and as much of the GPU's).  Against that stands one workgroup's way through all of a head's
-// keys, where up to 32 of them share it otherwise.  Where the line lies was measured with 2, 8 and 32 heads, which
-// differ by 0.3 us or less.  Microseconds a call of 8 heads under a tree, in two launches (10.5 to 11.4 at least,
-// the host's time) and in one:
-//   d = 64:  8 rows, 12 tiles of 64 keys 10.6 and 9.6; 32 rows, 10 tiles 11.1 and 10.3, 12 tiles 11.3 and 11.2;
-//            64 rows, 4 tiles 10.7 and 8.5; 65 rows, 3 tiles 10.7 and 9.7, 4 tiles 10.6 and 10.9;
-//            128 rows, 3 tiles 11.6 and 10.1, 4 tiles 11.5 and 11.3
-//   d = 128: 8 rows, 6 tiles 11.5 and 10.3; 32 rows, 6 tiles 15.3 and 14.3; 64 rows, 4 tiles 11.6 and 10.8, 5 tiles
-//            11.8 and 11.8; 72 rows, 2 tiles 12.5 and 10.6, 3 tiles 11.8 and 12.3; 88 rows, 3 tiles 12.5 and
-//            12.3, 4 tiles 12.1 and 14.1; 128 rows, 3 tiles 14.3 and 12.9, 4 tiles 13.7 and 14.7
+// the host's time, which makes two launches 10.5 us at least where calls are made one by one).  Against that stands one
+// workgroup's way through all of a head's keys, where up to 32 of them share it otherwise.  The line was drawn with calls made one
+// by one, of earlier kernels.  With the present ones, 8 heads under a tree, from a graph, us in two launches and in one (2 and 32
+// heads differ by 0.3 us or less), below the line and past it:
+//   d = 64:  8 rows, 12 tiles of 64 keys 8.5 and 8.9, 13 8.5 and 9.4; 32 rows, 12 tiles 10.2 and 10.1, 13 9.9 and 10.6;
+//            64 rows, 4 tiles 8.5 and 7.2, 5 8.5 and 7.9, 6 8.4 and 8.7; 65 rows, 3 tiles 8.6 and 8.3, 4 8.4 and 9.6;
+//            128 rows, 3 tiles 9.6 and 8.3, 4 9.2 and 9.6
+//   d = 128: 8 rows, 6 tiles 10.1 and 9.7, 7 10.8 and 10.6, 8 11.0 and 11.4; 32 rows, 6 tiles 14.2 and 12.7, 7 14.6 and
+//            13.8, 8 14.9 and 14.7; 64 rows, 4 tiles 10.5 and 9.4, 5 10.5 and 10.4, 6 10.5 and 11.3; 72 rows, 2 tiles 11.3
+//            and 9.2, 3 10.5 and 11.0; 80 rows, 3 tiles 11.0 and 10.7; 88 rows, 3 tiles 11.3 and 11.0, 4 10.8 and 12.6;
+//            128 rows, 3 tiles 12.9 and 10.9, 4 12.2 and 12.5
+// So it lies right or a tile short: 5 tiles of 64 channels at 33 to 64 rows and 7 of 128 up to 32 rows would gain up to 0.8 us.
 bool attention_alone(int M, int kv_len, int d)
 {
     const int64_t ntile = ((int64_t)kv_len + M + 63) / 64;

@@ -3,12 +3,12 @@
 // The step re-reads every weight once per decoding step and is bound by that stream
 // (Ghidorah, sections 2.1 and 2.2.2), so the kernel is built around it.  A workgroup has a
 // group of up to R row tiles (16 output features each) and a k range.  Its wavefronts
-// (eight) split the k range between them; each wavefront streams its k-steps of ALL the group's
+// (eight) take the range's k-steps in turn; each wavefront streams its k-steps of ALL the group's
 // tiles (W is the MFMA A operand, fetched with non-temporal 128-bit loads straight into
 // registers, a few k-steps ahead) together with the matching x fragments (the B operand,
 // from the L2), and keeps one fp32 accumulator fragment per (row tile, 16 rows of x).  There
-// is no LDS staging and no barrier inside the stream: the wavefronts run independently until
-// their k ranges end.  Then the partial fragments of every tile are added up through LDS,
+// is no LDS staging, and up to 64 rows no barrier inside the stream: the wavefronts run independently until
+// the range ends (above, a barrier in every turn keeps them together, see keeps_step).  Then the partial fragments of every tile are added up through LDS,
 // in pairs of pairs of wavefronts, and the reducing wavefront runs the layer's element-wise epilogue
 // (residual add + sums of squares for the next RMSNorm, rotary embedding + KV append, SwiGLU).
 // Where the accumulators would leave one of eight wavefronts no registers for a load ring
@@ -84,8 +84,8 @@ __host__ __device__ constexpr int pd_of(int MT, int R, int NW)
 // are added in pairs at the end.  Groups then round less than the parts they stand in for ([300, 3416] at 64 rows:
 // 8.4e-8, in parts 9.4e-8), and stand in for more of them ([1280, 1280] at 64 rows: 7.0 us, in parts 10.0).  Without
 // groups it only costs: [3457, 4872] at 27 rows took 14.1 us instead of 13.7.
-// [2048, 13824] at 1 row: 2.8e-7 of the result in one chain, 1.2e-7 folded (12.6 and 12.9 us);
-// [22016, 4096] at 128 rows, four wavefronts: 2.1e-7 in one chain, 1.5e-7 in halves (47.4 and 49.3 us).
+// [2048, 13824] at 1 row: 2.8e-7 of the result in one chain, 1.2e-7 folded (weights from HBM 13.1 and 13.3 us);
+// [22016, 4096] at 128 rows, four wavefronts: 2.1e-7 in one chain, 1.5e-7 in halves (45.3 and 48.0 us).
 constexpr int kFoldSteps = 2;
 __host__ __device__ constexpr bool folded(int MT, int R) { return R * MT <= (R <= 3 ? 18 : 16); }
 __host__ __device__ constexpr bool grouped(int MT, int R) { return R == 1 && (MT == 1 || MT == 2 || MT == 4); }
@@ -109,11 +109,17 @@ __host__ __device__ constexpr int stretches_parts(int MT, int R) { return folded
 //     16   7B-shaped layer   89.9     87.0
 // Above 64 rows x takes more of the way into a compute unit than weights do, the wavefronts drift apart
 // over it, and a barrier in every turn of the ring keeps them together (it waits for no load):
-//     96   [32000, 4096]     59.5     59.3, with the barrier 55.9
-//    128   [22016, 4096]     51.7     51.3                   47.5
-//    128   [4096, 11008]     32.8     32.9                   31.7
-// Not with 8 tiles by 128 rows, whose ring holds one k-step: [32000, 4096] 67.5, with the barrier 75.7; up to 64
-// rows it costs 0 to 1%.
+//     96   [32000, 4096]     60.3     61.0, with the barrier 58.8
+//     96   [20480, 4096]     40.5     40.0                   39.1
+//     96   [16384, 4096]     36.3     35.0                   33.5
+//    128   [27648, 4096]     64.6     65.2                   62.7
+//    128   [22016, 4096]     52.2     52.5                   48.1
+//    128   [16384, 4096]     40.2     39.5                   36.5
+//    128   [4096, 11008]     34.6     34.7                   33.7
+//    128   [32000, 4096]     68.1     68.3                   74.9
+// The last, 8 tiles by 128 rows, is the one that is slower with it, so it has none.  (Its ring holds one k-step, but so do
+// those of 7 tiles by 128 rows and of 4, 5 and 8 by 96; it adds 22 fragments up step by step, 7 tiles 6, the others none: see
+// NSTEP.)  Up to 64 rows it costs 0 to 1%.
 __host__ __device__ constexpr bool keeps_step(int MT, int R) { return MT > 4 && R * MT <= 56; }
 
 // A workgroup of one whole tile takes a single KiB out of every four of a block and, where x is read as it lies, 64 bytes of a
